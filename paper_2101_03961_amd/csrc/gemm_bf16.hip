@@ -206,9 +206,9 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // waits do not count it.  The compiler does not look into asm for hazards: the leading s_nop
 // keeps five states between a descriptor word it may just have reloaded from a spill lane
 // (v_readlane) and the store that reads it, the trailing one keeps a write of the data
-// registers one state away.
+// registers two states away (a 16-byte store without a scalar offset reads them that late on gfx950).
 __device__ __forceinline__ void store16(i32x4 rsrc, uint32_t voff, u32x4 data) {
-    asm volatile("s_nop 4\n\tbuffer_store_dwordx4 %0, %1, %2, 0 offen\n\ts_nop 0"
+    asm volatile("s_nop 4\n\tbuffer_store_dwordx4 %0, %1, %2, 0 offen\n\ts_nop 1"
                  :
                  : "v"(data), "v"(voff), "s"(rsrc)
                  : "memory");
