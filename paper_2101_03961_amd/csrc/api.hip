@@ -122,7 +122,21 @@ Workspace layout_workspace(const switch_config *cfg) {
     if (w.tps_m < 64) w.tps_m = 64;   // empty batch
     w.nsplit_m = ceil_div(w.T, w.tps_m);
     w.dWr_part_m = take((size_t)w.etiles * w.nsplit_m * (jit_mfma ? 2 * (size_t)w.dpad : d) * 256 * 4);
-    w.relu_bits = take(E * ceil_div(f, kGemmTile) * ceil_div(C, kGemmTile) * kReluBitsPerTile);
+    size_t bits = 0;
+    for (int &t : w.gemm_tile) t = ROWS_NONE;
+    if (cfg->act_dtype == SW_BF16) {
+        bits = E * ceil_div(f, kGemmTile) * ceil_div(C, kGemmTile) * kReluBitsPerTile;
+        if (!w.fused) {   // (the first GEMM and the masked gradient agree: same rows, columns and depth)
+            w.gemm_tile[GEMM_FWD1] = rows_tile_for(w, f1, d);
+            w.gemm_tile[GEMM_FWD2] = rows_tile_for(w, d, f);
+            w.gemm_tile[GEMM_DGRAD2] = rows_tile_for(w, f, d);
+            w.gemm_tile[GEMM_DGRAD1] = rows_tile_for(w, d, f1);
+            w.gemm_tile[GEMM_WGRAD1] = rows_wgrad_tile(w, d, f1);
+            w.gemm_tile[GEMM_WGRAD2] = rows_wgrad_tile(w, f, d);
+            bits = w.geglu ? 0 : rows_bits_bytes(w.gemm_tile[GEMM_FWD1], E, C, f);
+        }
+    }
+    w.relu_bits = take(bits);
     w.ntlb_rounds = cfg->ntlb_rounds;
     if (w.ntlb_rounds > 0) {
         const size_t nE = (size_t)w.n * E * 4;

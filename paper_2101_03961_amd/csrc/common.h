@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "switchffn.h"
 
@@ -120,6 +121,7 @@ struct Workspace {
     size_t kept;                // i32 [E]      kept tokens per expert: sum over groups of min(count, Cg)
     int fused;                  // bf16: dispatch and combine run inside the GEMMs (x, dy gathered by
                                 //   the slot -> token table, y written by the second GEMM)
+    int gemm_tile[6];           // RowsTile of each GemmKind; ROWS_NONE: the persistent kernel (bf16)
     size_t slot_token;          // i32 [E][C] + 128  token held by each slot (valid for slot < kept[e])
     size_t slot_gate;           // f32 [E][C]   gate of that token (the probability that scales its output)
     size_t slot_off;            // u32 [E][C] + 128  byte offset of that token's row in x / dy / y:
@@ -150,8 +152,8 @@ struct Workspace {
     size_t dWr_part_m;          // f32 [etiles][nsplit_m][d][256]  partial sums of x^T [dl_hi | dl_lo]
                                 //     (with jitter: [nsplit_m][2 dpad][256], hi and mid plane of x * m)
     int64_t tps_m, nsplit_m;    // tokens per split (multiple of 32), number of splits
-    size_t relu_bits;           // u8  [E][f tiles][slot tiles][kReluBitsPerTile]  one bit per element of A:
-                                //     A > 0, in the order the bf16 GEMM epilogue visits a tile
+    size_t relu_bits;           // u8  one bit per element of A, A > 0, in the order the epilogue of the
+                                //     first forward GEMM (and of the masked gradient) visits its tiles
     int64_t nsplit;
     // No-Token-Left-Behind (only laid out when ntlb_rounds > 0)
     int ntlb_rounds;
@@ -262,6 +264,24 @@ struct TokenMajor {
 hipError_t launch_gemm_bf16(GemmKind kind, const Workspace &w, char *ws, const void *W_in,
                             const void *W_out, void *dW_in, void *dW_out, const TokenMajor &tm,
                             hipStream_t s);
+// One-tile-per-block variants of launch_gemm_bf16 (gemm_rows.hip), rows x columns of a tile.
+enum RowsTile {
+    ROWS_NONE = 0,   // the persistent 256 x 256 kernel of gemm_bf16.hip
+    ROWS_32x128,
+    ROWS_64x256,
+    ROWS_96x128,
+    ROWS_128x128,
+    ROWS_256x128,
+    ROWS_256x256,
+    ROWS_320x256,
+    ROWS_256x384
+};
+// the tile that fits the layer (row-limited products, weight gradients), and the bytes of ReLU bits it takes
+int rows_tile_for(const Workspace &w, int64_t Pdim, int64_t Kdim);
+int rows_wgrad_tile(const Workspace &w, int64_t Qdim, int64_t Pdim);
+int64_t rows_bits_bytes(int tile, int64_t E, int64_t C, int64_t f);
+hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const void *W_in, const void *W_out,
+                            void *dW_in, void *dW_out, int tile, hipStream_t s);
 hipError_t launch_gemm_f32(GemmKind kind, const Workspace &w, char *ws, const void *W_in,
                            const void *W_out, void *dW_in, void *dW_out, const TokenMajor &tm,
                            hipStream_t s);

@@ -214,25 +214,6 @@ __device__ __forceinline__ void store16(i32x4 rsrc, uint32_t voff, u32x4 data) {
                  : "memory");
 }
 
-// two floats rounded to bf16 (nearest even), first in the low half
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
-}
-// per 16-bit half: signed maximum, unsigned minimum (written as asm: the compiler turns the
-// generic forms of these into compares and selects, several instructions per half)
-__device__ __forceinline__ uint32_t pk_max_i16(uint32_t x, uint32_t y) {
-    uint32_t d;
-    asm("v_pk_max_i16 %0, %1, %2" : "=v"(d) : "v"(x), "v"(y));
-    return d;
-}
-__device__ __forceinline__ uint32_t pk_min_u16(uint32_t x, uint32_t y) {
-    uint32_t d;
-    asm("v_pk_min_u16 %0, %1, %2" : "=v"(d) : "v"(x), "v"(y));
-    return d;
-}
-
 // Per-tile values of the epilogue, one set per lane (see tile_values in the kernel).
 struct TileVals {
     uint32_t ep_lo, ep_hi;   // SCALE / SCATTER: gate / row offset of rows lane, lane + 64 of the wave's q rows
@@ -913,6 +894,7 @@ hipError_t launch_gemm_bf16(GemmKind kind, const Workspace &w, char *ws, const v
                             const void *W_out, void *dW_in, void *dW_out, const TokenMajor &tm,
                             hipStream_t s) {
     const int d = (int)w.d, f = (int)w.f, f1 = (int)w.f1, C = (int)w.C, E = (int)w.E;
+    if (const int tile = w.gemm_tile[kind]) return launch_gemm_rows(kind, w, ws, W_in, W_out, dW_in, dW_out, tile, s);
     GemmArgs a{};
     a.kept = (const int32_t *)(ws + w.kept);
     const bf16 *Xd = (const bf16 *)(ws + w.Xd);
@@ -927,9 +909,9 @@ hipError_t launch_gemm_bf16(GemmKind kind, const Workspace &w, char *ws, const v
         a.tiles_p = (int)ceil_div(Pdim, kBP);
         a.total_tiles = a.tiles_q * a.tiles_p * E;
     };
-    // With w.fused the token-major tensors take the place of the dispatched copies: x for Xd,
-    // dy for dO (the gate moves into A and into the row scales), y is written by the second
-    // GEMM (see the head of this file).
+    // What is left to this kernel: everything with w.fused, where the token-major tensors take the
+    // place of the dispatched copies (x for Xd, dy for dO; the gate moves into A and into the row
+    // scales, y is written by the second GEMM, see the head of this file), and weight gradients.
     const bool fused = w.fused;
     a.slot_token = (const int32_t *)(ws + w.slot_token);
     a.slots = C;
@@ -942,7 +924,7 @@ hipError_t launch_gemm_bf16(GemmKind kind, const Workspace &w, char *ws, const v
     a.reverse = kind == GEMM_FWD2 || kind == GEMM_DGRAD1;
     switch (kind) {
     case GEMM_FWD1: {
-        a.Q = fused ? (const bf16 *)tm.x : Xd; a.q_batch = fused ? 0 : (size_t)C * d; a.ldq = d;
+        a.Q = (const bf16 *)tm.x; a.q_batch = 0; a.ldq = d;
         a.P = (const bf16 *)W_in; a.p_batch = (size_t)d * f1; a.ldp = f1;
         a.Cout = w.geglu ? (bf16 *)(ws + w.H) : A; a.c_batch = (size_t)C * f1; a.ldc = f1;
         a.relu_bits = (uint8_t *)(ws + w.relu_bits);
@@ -950,22 +932,14 @@ hipError_t launch_gemm_bf16(GemmKind kind, const Workspace &w, char *ws, const v
         if (a.total_tiles == 0) return hipSuccess;
         if (w.geglu) {   // the plain product; activation, dropout and gate follow in geglu_fwd
             ProfScope ps("gemm1_fwd", s);
-            if (fused)
-                return gemm_launch<false, true, EPI_NONE, true, false, MODE_EXPERTS, GATHER_Q>(a, s);
-            return gemm_launch<false, true, EPI_NONE, true, false>(a, s);
+            return gemm_launch<false, true, EPI_NONE, true, false, MODE_EXPERTS, GATHER_Q>(a, s);
         }
         ProfScope ps("gemm1_fwd_relu", s);
         a.nz = w.noise;
-        if (fused) {
-            if (w.noise.dropout)
-                return gemm_launch<false, true, EPI_RELU | EPI_DROP | EPI_SCALE, true, false,
-                                   MODE_EXPERTS, GATHER_Q>(a, s);
-            return gemm_launch<false, true, EPI_RELU | EPI_SCALE, true, false, MODE_EXPERTS,
-                               GATHER_Q>(a, s);
-        }
         if (w.noise.dropout)
-            return gemm_launch<false, true, EPI_RELU | EPI_DROP, true, false>(a, s);
-        return gemm_launch<false, true, EPI_RELU, true, false>(a, s);
+            return gemm_launch<false, true, EPI_RELU | EPI_DROP | EPI_SCALE, true, false, MODE_EXPERTS,
+                               GATHER_Q>(a, s);
+        return gemm_launch<false, true, EPI_RELU | EPI_SCALE, true, false, MODE_EXPERTS, GATHER_Q>(a, s);
     }
     case GEMM_FWD2: {
         a.Q = A; a.q_batch = (size_t)C * f; a.ldq = f;
@@ -978,12 +952,10 @@ hipError_t launch_gemm_bf16(GemmKind kind, const Workspace &w, char *ws, const v
         // (both operands come from HBM here, k is long: with the activations in the deep ring the
         // CUs that share an operand tile stay close enough for the L2 -- 1.03 GB fetched instead
         // of 1.38 GB at Switch-Base -- and the kernel is 3 % faster there, 5 % at the XXL shape)
-        if (fused)
-            return gemm_launch<false, true, EPI_SCATTER, true, false, MODE_EXPERTS, GATHER_NONE, true>(a, s);
-        return gemm_launch<false, true, EPI_NONE, true, false, MODE_EXPERTS, GATHER_NONE, true>(a, s);
+        return gemm_launch<false, true, EPI_SCATTER, true, false, MODE_EXPERTS, GATHER_NONE, true>(a, s);
     }
     case GEMM_DGRAD2: {
-        a.Q = fused ? (const bf16 *)tm.dy : dO; a.q_batch = fused ? 0 : (size_t)C * d; a.ldq = d;
+        a.Q = (const bf16 *)tm.dy; a.q_batch = 0; a.ldq = d;
         a.P = (const bf16 *)W_out; a.p_batch = (size_t)f * d; a.ldp = d;   // [p = f][k = d]
         a.Cout = w.geglu ? (bf16 *)(ws + w.dA) : dH; a.c_batch = (size_t)C * f; a.ldc = f;
         a.relu_bits = (uint8_t *)(ws + w.relu_bits);
@@ -992,21 +964,13 @@ hipError_t launch_gemm_bf16(GemmKind kind, const Workspace &w, char *ws, const v
         a.nz = w.noise;
         if (w.geglu) {
             ProfScope ps("gemm2_dgrad", s);
-            if (fused)
-                return gemm_launch<false, false, EPI_SCALE, true, false, MODE_EXPERTS, GATHER_Q>(a, s);
-            return gemm_launch<false, false, EPI_NONE, true, false>(a, s);
+            return gemm_launch<false, false, EPI_SCALE, true, false, MODE_EXPERTS, GATHER_Q>(a, s);
         }
         ProfScope ps("gemm2_dgrad_relumask", s);
-        if (fused) {
-            if (w.noise.dropout)
-                return gemm_launch<false, false, EPI_MASK | EPI_DROP | EPI_SCALE, true, false,
-                                   MODE_EXPERTS, GATHER_Q>(a, s);
-            return gemm_launch<false, false, EPI_MASK | EPI_SCALE, true, false, MODE_EXPERTS,
-                               GATHER_Q>(a, s);
-        }
         if (w.noise.dropout)
-            return gemm_launch<false, false, EPI_MASK | EPI_DROP, true, false>(a, s);
-        return gemm_launch<false, false, EPI_MASK, true, false>(a, s);
+            return gemm_launch<false, false, EPI_MASK | EPI_DROP | EPI_SCALE, true, false, MODE_EXPERTS,
+                               GATHER_Q>(a, s);
+        return gemm_launch<false, false, EPI_MASK | EPI_SCALE, true, false, MODE_EXPERTS, GATHER_Q>(a, s);
     }
     case GEMM_DGRAD1: {
         a.Q = dH; a.q_batch = (size_t)C * f1; a.ldq = f1;

@@ -1,0 +1,402 @@
+// Grouped expert GEMMs with one tile per block (bf16 MFMA, fp32 accumulation).
+//
+// The same products as gemm_bf16.hip's,
+//     C_e[q][p] = sum_k Q_e(q, k) P_e(p, k),
+// with tile shapes for every number of rows an expert may hold, and a plain structure: a block
+// computes one tile and ends, so the hardware deals the tiles to the CUs as they become free.
+// (Persistent blocks with the next tile's loads under way during the epilogue, fragments read
+// one sub-step ahead, or half of the waves loading and the other half storing, measured the same or
+// slower with these tiles: experts hold different numbers of rows, and the deal evens that out.)
+//
+// What bounds it.  With few rows per expert: streaming the weights from HBM.  So a tile is as tall
+// as the capacity asks for, every weight line is read once, and rows that do not exist cost no
+// traffic (the buffer descriptors end at the kept rows).  With many rows: the L2 -> LDS requests,
+// each of which waits for HBM or L2 (the loads of the 256 x 256 tile alone, without products and
+// LDS reads, take 85-90 % of the kernel's time).  So the tall tiles are as large as the registers
+// allow: eight waves with 3 x 4 or 2 x 5 MFMA tiles of 32 x 32 each hold 256 x 384 or 320 x 256
+// accumulators, 20 % fewer operand bytes per product than 256 x 256.
+//
+// A block has WP x WQ waves, each with IP x IQ MFMA 32x32x16 tiles (P is the MFMA "A" side).  k
+// advances BK at a time through STAGES LDS stages filled by direct loads; one barrier per step.
+#include <math.h>
+
+#include "common.h"
+#include "lds_operands.h"
+#include "rows_operands.h"
+
+namespace sw {
+
+struct RowsArgs {
+    const bf16 *Q;             // per expert q_batch elements: [rows][ldq], weight gradients [slot][ldq]
+    const bf16 *P;             // per expert p_batch elements
+    bf16 *Cout;                // per expert c_batch elements, [rows][ldc]
+    uint8_t *bits;             // ReLU bits: ROWS_RELU writes, ROWS_MASK reads
+    size_t q_batch, p_batch, c_batch;
+    int ldq, ldp, ldc;
+    int Qdim, Pdim, Kdim;
+    const int32_t *kept;
+    int tiles_q, tiles_p, total;
+    int by_xcd;                // an expert's tiles run on one XCD
+    const int32_t *slot_token; // dropout: token of each slot, [expert][slots]
+    int slots;
+    Noise nz;
+};
+
+enum { ROWS_PLAIN = 0, ROWS_RELU = 1, ROWS_MASK = 2 };
+
+// Mask bits: one byte per 16-byte piece of the output (bits 0..3: low halves of its four words, 4..7:
+// high halves), [tile][wave][32-row round][pass][lane] in the order the epilogue handles them.
+template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, int BK, bool P_TRANS, int EPI, bool DROP,
+          bool WGRAD>
+__global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a) {
+    constexpr int NW = WP * WQ, PB = 32 * IP * WP, QB = 32 * IQ * WQ;
+    constexpr int kPBytes = PB * BK * 2, kStage = (PB + QB) * BK * 2;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    int L = blockIdx.x;
+    if (a.by_xcd) {   // block b runs on XCD b mod 8: give each XCD a range of experts
+        const int per = (a.total + 7) >> 3;
+        L = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+        if ((int)(blockIdx.x >> 3) >= per || L >= a.total) return;
+    }
+    const int per_e = a.tiles_p * a.tiles_q;
+    const int e = L / per_e, rem = L - e * per_e;
+    int pt, qt;   // the dimension with fewer tiles runs fastest: sharers of the larger operand are neighbours
+    if (a.tiles_q <= a.tiles_p) {
+        pt = rem / a.tiles_q;
+        qt = rem - pt * a.tiles_q;
+    } else {
+        qt = rem / a.tiles_p;
+        pt = rem - qt * a.tiles_p;
+    }
+    const int used = a.kept[e];   // slots with a token
+    const int qlim = WGRAD ? a.Qdim : min(used, a.Qdim), klim = WGRAD ? min(used, a.Kdim) : a.Kdim;
+    const int q0 = qt * QB, p0 = pt * PB;
+    if (q0 >= qlim) return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wp = wave % WP, wq = wave / WP;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
+
+    typename std::conditional<P_TRANS, RowsTrans<PB, NW, BK>, RowsDirect<PB, NW, BK>>::type op;
+    typename std::conditional<WGRAD, RowsTrans<QB, NW, BK>, RowsDirect<QB, NW, BK>>::type oq;
+    op.init_frag(lane, wp * 32 * IP);
+    oq.init_frag(lane, wq * 32 * IQ);
+    op.init(a.P + (size_t)e * a.p_batch, a.ldp, p0, a.Pdim, klim, lane, wave);
+    oq.init(a.Q + (size_t)e * a.q_batch, a.ldq, q0, qlim, klim, lane, wave);
+    constexpr int kLoads = decltype(op)::kLoads + decltype(oq)::kLoads;
+    const int nk = (klim + BK - 1) / BK;
+
+    // the wave's bits of 32-row round j
+    constexpr int kBitBytes = 2 * IP;   // per lane
+    auto bits_of = [&](int j) { return a.bits + (((size_t)L * NW + wave) * IQ + j) * (64 * kBitBytes); };
+    uint32_t mb[IQ][2];
+    if (EPI == ROWS_MASK) {
+#pragma unroll
+        for (int j = 0; j < IQ; ++j) {
+            const uint8_t *b = bits_of(j);
+            mb[j][0] = IP == 1 ? ((const uint16_t *)b)[lane] : ((const uint32_t *)b)[lane];
+            mb[j][1] = IP == 3 ? ((const uint16_t *)(b + 256))[lane] : 0u;
+        }
+    }
+
+    f32x16 acc[IP][IQ];
+#pragma unroll
+    for (int i = 0; i < IP; ++i)
+#pragma unroll
+        for (int j = 0; j < IQ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    auto issue = [&](int kt, int st) {   // k past the end: zeros
+        const uint32_t at = lds0 + (uint32_t)(st * kStage);
+#pragma unroll
+        for (int i = 0; i < decltype(op)::kLoads; ++i) op.issue_one(at, kt * BK, wave, i);
+#pragma unroll
+        for (int i = 0; i < decltype(oq)::kLoads; ++i) oq.issue_one(at + kPBytes, kt * BK, wave, i);
+    };
+#pragma unroll
+    for (int s = 0; s < STAGES - 1; ++s) issue(s, s);
+    int st = 0, fill = STAGES - 1;
+    for (int kt = 0; kt < nk; ++kt) {
+        if (STAGES == 1) {   // a single stage: other blocks of the CU cover the wait
+            if (kt) __syncthreads();
+            issue(kt, 0);
+        }
+        rows_wait_vmcnt<(STAGES > 2 ? STAGES - 2 : 0) * kLoads>();   // step kt has landed
+        __syncthreads();                                             // ... for all waves; step kt - 1 is read
+        if (STAGES > 1) issue(kt + STAGES - 1, fill);
+        const char *sp = lds + st * kStage, *sq = sp + kPBytes;
+#pragma unroll
+        for (int ks = 0; ks < BK / 16; ++ks) {
+            bf16x8 fp[IP], fq[IQ];
+#pragma unroll
+            for (int i = 0; i < IP; ++i) fp[i] = op.frag(sp, i, ks);
+#pragma unroll
+            for (int j = 0; j < IQ; ++j) fq[j] = oq.frag(sq, j, ks);
+#pragma unroll
+            for (int i = 0; i < IP; ++i)
+#pragma unroll
+                for (int j = 0; j < IQ; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fp[i], fq[j], acc[i][j], 0, 0, 0);
+        }
+        st = st == STAGES - 1 ? 0 : st + 1;
+        fill = fill == STAGES - 1 ? 0 : fill + 1;
+    }
+    rows_wait_vmcnt<0>();   // the trailing (zero) loads
+    __syncthreads();
+
+    // Epilogue: 32 rows at a time through LDS of the wave's own, so that rows leave in segments
+    // of 32 IP columns, 16 bytes per lane.
+    constexpr int kPitch = rows_turn_pitch(IP), kChunks = 4 * IP, kPasses = 2 * IP;
+    char *ep = lds + wave * 32 * kPitch;
+    bf16 *Cout = a.Cout + (size_t)e * a.c_batch;
+    const int pw = p0 + wp * 32 * IP;
+    const int wrow = lane & 31;
+    auto swz = [](int row) { return IP == 1 ? (row >> 2) & 3 : IP == 2 ? (row >> 1) & 7 : row & 3; };
+#pragma unroll
+    for (int j = 0; j < IQ; ++j) {
+        const int qw = q0 + (wq * IQ + j) * 32;
+        if (qw >= qlim) break;
+        // expert dropout: the draw of hidden unit p of token t is element t * d_ff + p
+        uint32_t drop_row = 0;
+        if (DROP && EPI == ROWS_RELU) {
+            const int q = qw + wrow;
+            const int tok = q < qlim ? a.slot_token[(size_t)e * a.slots + q] : 0;
+            drop_row = (uint32_t)tok * (uint32_t)a.Pdim + (uint32_t)(pw + ((lane >> 5) << 2));
+        }
+#pragma unroll
+        for (int i = 0; i < IP; ++i)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                float v[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = acc[i][j][4 * g + r];
+                if (DROP && EPI == ROWS_RELU) {
+                    const uint32_t first = drop_row + (uint32_t)(i * 32 + g * 8);
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const uint32_t z = dropout_pair_bits(a.nz, (first >> 1) + (uint32_t)h);
+                        v[2 * h] = dropout_keeps_even(a.nz, z) ? v[2 * h] * a.nz.drop_scale : 0.f;
+                        v[2 * h + 1] = dropout_keeps_odd(a.nz, z) ? v[2 * h + 1] * a.nz.drop_scale : 0.f;
+                    }
+                }
+                if (DROP && EPI == ROWS_MASK)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[r] *= a.nz.drop_scale;
+                uint2 o = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+                if (EPI == ROWS_RELU) {   // on the bf16 values: negative ones (and -0) are < 0 as integers
+                    o.x = pk_max_i16(o.x, 0u);
+                    o.y = pk_max_i16(o.y, 0u);
+                }
+                const int ch = i * 4 + g;
+                *(uint2 *)(ep + wrow * kPitch + ((ch ^ swz(wrow)) << 4) + ((lane >> 5) << 3)) = o;
+            }
+        uint32_t nb[2] = {0u, 0u};
+#pragma unroll
+        for (int x = 0; x < kPasses; ++x) {
+            const int at = x * 64 + lane;
+            const int row = at / kChunks, c = at - row * kChunks;
+            const int q = qw + row, p = pw + c * 8;
+            u32x4 val = *(const u32x4 *)(ep + row * kPitch + ((c ^ swz(row)) << 4));
+            if (EPI == ROWS_RELU) {   // after ReLU a half word is > 0 exactly when min(., 1) is 1
+                uint32_t u = 0;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) u |= pk_min_u16(val[w], 0x00010001u) << w;
+                nb[x >> 2] |= ((u & 0xfu) | ((u >> 12) & 0xf0u)) << (8 * (x & 3));
+            }
+            if (EPI == ROWS_MASK) {
+                uint32_t byte = (mb[j][x >> 2] >> (8 * (x & 3))) & 0xffu;
+                byte |= byte << 12;   // bit w -> bit w, bit 4 + w -> bit 16 + w
+#pragma unroll
+                for (int w = 0; w < 4; ++w) val[w] &= ((byte >> w) & 0x10001u) * 0xffffu;
+            }
+            if (q < qlim && p < a.Pdim) *(u32x4 *)(Cout + (size_t)q * a.ldc + p) = val;
+        }
+        if (EPI == ROWS_RELU) {
+            uint8_t *b = bits_of(j);
+            if (IP == 1) ((uint16_t *)b)[lane] = (uint16_t)nb[0];
+            else ((uint32_t *)b)[lane] = nb[0];
+            if (IP == 3) ((uint16_t *)(b + 256))[lane] = (uint16_t)nb[1];
+        }
+    }
+}
+
+template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, int BK, bool P_TRANS, int EPI, bool DROP,
+          bool WGRAD>
+static hipError_t rows_launch(RowsArgs a, int E, hipStream_t s) {
+    auto kern = gemm_rows_kernel<IP, WP, IQ, WQ, STAGES, WPE, BK, P_TRANS, EPI, DROP, WGRAD>;
+    constexpr int PB = 32 * IP * WP, QB = 32 * IQ * WQ;
+    constexpr int ring = STAGES * (PB + QB) * BK * 2, turn = WP * WQ * 32 * rows_turn_pitch(IP);
+    constexpr int lds = ring > turn ? ring : turn;
+    static PerDeviceOnce once;
+    hipError_t err = once_per_device(once, [&] {
+        return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    });
+    if (err != hipSuccess) return err;
+    a.tiles_q = (int)ceil_div(a.Qdim, QB);
+    a.tiles_p = (int)ceil_div(a.Pdim, PB);
+    a.total = a.tiles_q * a.tiles_p * E;
+    // Up to 64 rows the shared operand is small next to the weights: the tiles are dealt over all XCDs
+    // in order, which stays even when only some experts hold tokens.
+    a.by_xcd = WGRAD || QB > 64;
+    const unsigned blocks = (unsigned)(a.by_xcd ? ceil_div(a.total, 8) * 8 : a.total);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * WP * WQ), lds, s, a);
+    return hipGetLastError();
+}
+
+// ---- which tile ---------------------------------------------------------------------
+// Per tile shape: CU time of one 64-k step and of a tile's start and epilogue (microseconds, all
+// CUs busy), and the rate at which the shape streams weights when they are what it waits for
+// (GB/s).  Measured on 128 experts of 768 x 3072 with 16 .. 512 rows each; the estimate made from
+// them picks the fastest or one within 5 % of it over that range and at 64 experts of 4096 x 10240.
+struct RowsModel {
+    int tile, qb, pb;
+    double step, once, gbs;
+};
+static const RowsModel kRowsModels[] = {
+    {ROWS_32x128, 32, 128, 0.52, 1.4, 5300.},  {ROWS_64x256, 64, 256, 1.30, 2.2, 5300.},
+    {ROWS_96x128, 96, 128, 0.66, 1.4, 4100.},  {ROWS_128x128, 128, 128, 0.65, 1.4, 4000.},
+    {ROWS_256x256, 256, 256, 2.10, 2.5, 3800.}, {ROWS_320x256, 320, 256, 2.20, 3.5, 3800.},
+    {ROWS_256x384, 256, 384, 2.86, 5.0, 4850.},
+};
+
+// Tiles of qb rows an expert takes on average: counts scatter around the mean by the routing's own
+// spread (about an eighth of it, from the router's initialisation) and by chance.
+static double rows_tiles(double mean, double cap, int qb) {
+    const double sd = sqrt(mean + 0.0169 * mean * mean);
+    static const double at[5] = {-1.3, -0.5, 0.0, 0.5, 1.3};
+    double sum = 0.;
+    for (double x : at) {
+        double c = mean + sd * x;
+        c = c < 1. ? 1. : (c > cap ? cap : c);
+        sum += ceil(c / qb);
+    }
+    return sum / 5.;
+}
+
+// Tile of a row-limited product of Pdim columns over Kdim.
+int rows_tile_for(const Workspace &w, int64_t Pdim, int64_t Kdim) {
+    if (w.C == 0) return ROWS_256x256;   // nothing will be launched
+    const double cap = (double)w.C, mean = fmin((double)w.T / (double)w.E, cap);
+    const double steps = ceil(Kdim / 64.);
+    // experts that get a token at all
+    const double hit = (double)w.E * (1. - pow(1. - 1. / (double)w.E, (double)w.T));
+    int best = ROWS_256x256;
+    double best_us = 1e30;
+    for (const RowsModel &m : kRowsModels) {
+        const double tq = rows_tiles(mean, cap, m.qb);
+        const double tiles = hit * tq * ceil((double)Pdim / m.pb);
+        // an expert's second tile finds the weights in L2 if it runs on the same XCD
+        const double reads = m.qb > 64 ? 1. : tq;
+        const double bytes = hit * (reads * Pdim * Kdim + mean * (Pdim + Kdim)) * 2.;
+        // rows that do not exist are not loaded; the widest tile, which waits for its loads most, gains by it
+        const double fill = mean / (tq * m.qb);
+        const double step = m.step * (m.tile == ROWS_256x384 ? fmin(0.36 + 0.75 * fill, 1.) : 1.);
+        // (fewer tiles than CUs: the longest block is the time)
+        const double us = fmax((steps * step + m.once) * fmax(tiles / 256., 1.), bytes / m.gbs * 1e-3);
+        if (us < best_us * 0.97) {   // later, larger tiles have to be clearly better
+            best = m.tile;
+            best_us = us;
+        }
+    }
+    return best;
+}
+
+// Tile of a weight gradient of Qdim x Pdim; ROWS_NONE: the persistent kernel.
+int rows_wgrad_tile(const Workspace &w, int64_t Qdim, int64_t Pdim) {
+    // too few large tiles for the CUs
+    if (w.E * ceil_div(Qdim, 256) * ceil_div(Pdim, 256) < 256) return ROWS_128x128;
+    // Few slots: little but the store of the gradient; two blocks per CU store and load in turns.
+    if (w.C <= 96) return ROWS_256x128;
+    // Up to about five k steps the large tile's shorter start wins over the persistent kernel's
+    // pipeline (193 against 205 us at 160 slots, equal at 256, 128 experts of 768 x 3072).  With
+    // more it is equal at full experts and stores the zeros of experts without tokens faster, if
+    // its columns fit (at 4096 columns, a third of a tile unused, it takes 6 % longer).
+    if (w.C <= 320 || ceil_div(Pdim, 384) * 384 * 50 <= Pdim * 51) return ROWS_256x384;
+    return ROWS_NONE;
+}
+
+int64_t rows_bits_bytes(int tile, int64_t E, int64_t C, int64_t f) {
+    for (const RowsModel &m : kRowsModels)
+        if (m.tile == tile) return E * ceil_div(C, m.qb) * ceil_div(f, m.pb) * (m.qb * m.pb / 8);
+    return 0;
+}
+
+template <bool P_TRANS, int EPI, bool DROP>
+static hipError_t rows_by_tile(const RowsArgs &a, int E, int tile, hipStream_t s) {
+    switch (tile) {
+    case ROWS_32x128: return rows_launch<1, 4, 1, 1, 3, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
+    case ROWS_64x256: return rows_launch<2, 4, 2, 1, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
+    case ROWS_96x128: return rows_launch<1, 4, 3, 1, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
+    case ROWS_128x128: return rows_launch<2, 2, 2, 2, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
+    case ROWS_256x256: return rows_launch<2, 4, 4, 2, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
+    case ROWS_320x256: return rows_launch<2, 4, 5, 2, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
+    case ROWS_256x384: return rows_launch<3, 4, 4, 2, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const void *W_in, const void *W_out,
+                            void *dW_in, void *dW_out, int tile, hipStream_t s) {
+    const int d = (int)w.d, f = (int)w.f, f1 = (int)w.f1, C = (int)w.C, E = (int)w.E;
+    RowsArgs a{};
+    a.kept = (const int32_t *)(ws + w.kept);
+    a.slot_token = (const int32_t *)(ws + w.slot_token);
+    a.slots = C;
+    a.nz = w.noise;
+    a.bits = (uint8_t *)(ws + w.relu_bits);
+    auto set = [&](size_t q, int ldq, const void *P, size_t p_batch, int ldp, size_t c, int ldc) {
+        a.Q = (const bf16 *)(ws + q); a.q_batch = (size_t)C * ldq; a.ldq = ldq;
+        a.P = (const bf16 *)P; a.p_batch = p_batch; a.ldp = ldp;
+        a.Cout = (bf16 *)(ws + c); a.c_batch = (size_t)C * ldc; a.ldc = ldc;
+        a.Qdim = C; a.Pdim = ldc; a.Kdim = ldq;
+    };
+    const bool drop = w.noise.dropout;
+    if (C == 0 && kind != GEMM_WGRAD1 && kind != GEMM_WGRAD2) return hipSuccess;
+    switch (kind) {
+    case GEMM_FWD1: {
+        ProfScope ps(w.geglu ? "gemm1_fwd" : "gemm1_fwd_relu", s);
+        set(w.Xd, d, W_in, (size_t)d * f1, f1, w.geglu ? w.H : w.A, f1);
+        if (w.geglu) return rows_by_tile<true, ROWS_PLAIN, false>(a, E, tile, s);
+        if (drop) return rows_by_tile<true, ROWS_RELU, true>(a, E, tile, s);
+        return rows_by_tile<true, ROWS_RELU, false>(a, E, tile, s);
+    }
+    case GEMM_FWD2: {
+        ProfScope ps("gemm2_fwd", s);
+        set(w.A, f, W_out, (size_t)f * d, d, w.O, d);
+        return rows_by_tile<true, ROWS_PLAIN, false>(a, E, tile, s);
+    }
+    case GEMM_DGRAD2: {
+        ProfScope ps(w.geglu ? "gemm2_dgrad" : "gemm2_dgrad_relumask", s);
+        set(w.dO, d, W_out, (size_t)f * d, d, w.geglu ? w.dA : w.dH, f);
+        if (w.geglu) return rows_by_tile<false, ROWS_PLAIN, false>(a, E, tile, s);
+        if (drop) return rows_by_tile<false, ROWS_MASK, true>(a, E, tile, s);
+        return rows_by_tile<false, ROWS_MASK, false>(a, E, tile, s);
+    }
+    case GEMM_DGRAD1: {
+        ProfScope ps("gemm1_dgrad", s);
+        set(w.dH, f1, W_in, (size_t)d * f1, f1, w.dXd, d);
+        return rows_by_tile<false, ROWS_PLAIN, false>(a, E, tile, s);
+    }
+    case GEMM_WGRAD2:
+    case GEMM_WGRAD1: {
+        const bool two = kind == GEMM_WGRAD2;
+        ProfScope ps(two ? "gemm2_wgrad" : "gemm1_wgrad", s);
+        a.Q = (const bf16 *)(ws + (two ? w.A : w.Xd)); a.ldq = two ? f : d; a.q_batch = (size_t)C * a.ldq;
+        a.P = (const bf16 *)(ws + (two ? w.dO : w.dH)); a.ldp = two ? d : f1; a.p_batch = (size_t)C * a.ldp;
+        a.Cout = (bf16 *)(two ? dW_out : dW_in); a.ldc = a.ldp; a.c_batch = (size_t)a.ldq * a.ldp;
+        a.Qdim = a.ldq; a.Pdim = a.ldp; a.Kdim = C;
+        switch (tile) {
+        case ROWS_128x128: return rows_launch<2, 2, 2, 2, 2, 2, 64, true, ROWS_PLAIN, false, true>(a, E, s);
+        case ROWS_256x128: return rows_launch<2, 2, 4, 2, 1, 2, 64, true, ROWS_PLAIN, false, true>(a, E, s);
+        case ROWS_256x384:   // few k steps: a shorter start
+            if (C <= 320) return rows_launch<3, 4, 4, 2, 4, 2, 32, true, ROWS_PLAIN, false, true>(a, E, s);
+            return rows_launch<3, 4, 4, 2, 2, 2, 64, true, ROWS_PLAIN, false, true>(a, E, s);
+        }
+        return hipErrorInvalidValue;
+    }
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace sw

@@ -45,6 +45,26 @@ __device__ __forceinline__ void dma16(i32x4 rsrc, uint32_t voff, uint32_t soff, 
                  : "memory");
 }
 
+// ---- epilogue arithmetic on pairs of bf16 ------------------------------------------
+// two floats rounded to bf16 (nearest even), first in the low half
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
+}
+// per 16-bit half: signed maximum, unsigned minimum (written as asm: the compiler turns the
+// generic forms of these into compares and selects, several instructions per half)
+__device__ __forceinline__ uint32_t pk_max_i16(uint32_t x, uint32_t y) {
+    uint32_t d;
+    asm("v_pk_max_i16 %0, %1, %2" : "=v"(d) : "v"(x), "v"(y));
+    return d;
+}
+__device__ __forceinline__ uint32_t pk_min_u16(uint32_t x, uint32_t y) {
+    uint32_t d;
+    asm("v_pk_min_u16 %0, %1, %2" : "=v"(d) : "v"(x), "v"(y));
+    return d;
+}
+
 // ---- operand stored [row][k], k contiguous ---------------------------------------
 // LDS stage layout: [256 rows][32 k] = 64 bytes per row, four 16-byte chunks,
 // chunk c of row r kept at position c ^ dswz(r).  dswz uses row bits 1..3, so

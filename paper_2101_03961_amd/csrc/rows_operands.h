@@ -1,0 +1,102 @@
+// Operand tiles of gemm_rows.hip: R rows by BK k, filled by NW waves with direct global -> LDS loads.
+#pragma once
+#include "lds_operands.h"
+
+namespace sw {
+
+// [row][k] operand of R rows, BK (64 or 32) k per step: LDS [R][BK k]; the 16-byte chunks of a
+// row are permuted as in DirectOperand64 / DirectOperand.
+template <int R, int NW, int BK = 64> struct RowsDirect {
+    static constexpr int kRowsPerLoad = 512 / BK;            // rows of one wave-wide load
+    static constexpr int kLoads = R / (kRowsPerLoad * NW);   // per wave and step
+    static constexpr int kPitch = BK * 2;                    // bytes of an LDS row
+    static_assert(kLoads * kRowsPerLoad * NW == R, "rows divide over the waves");
+    static __device__ __forceinline__ int perm(int r) { return BK == 64 ? (r >> 1) & 7 : dswz(r); }
+    i32x4 rsrc;
+    uint32_t voff, row_step;
+    int c8, klim;
+    uint32_t frag0;
+    __device__ __forceinline__ void init(const bf16 *base, int ld, int row0, int rowlim, int klim_,
+                                         int lane, int wave) {
+        rsrc = make_rsrc(base, (uint32_t)rowlim * (uint32_t)ld * 2u);
+        const int r = wave * kRowsPerLoad + lane / (BK / 8);
+        const int c = (lane % (BK / 8)) ^ perm(r);
+        c8 = c << 3;
+        voff = ((uint32_t)(row0 + r) * (uint32_t)ld + (uint32_t)c8) * 2u;
+        row_step = (uint32_t)(kRowsPerLoad * NW) * (uint32_t)ld * 2u;
+        klim = klim_;
+    }
+    __device__ __forceinline__ void disable_load() { klim = 0; }
+    __device__ __forceinline__ void init_frag(int lane, int frag_row) {
+        const int fr = frag_row + (lane & 31);
+        frag0 = (uint32_t)(fr * kPitch + (((lane >> 5) ^ perm(fr)) << 4));
+    }
+    __device__ __forceinline__ void issue_one(uint32_t st, int k0, int wave, int i) const {
+        const uint32_t vo = (k0 + c8 < klim) ? voff : kOobOffset;
+        dma16(rsrc, vo, (uint32_t)i * row_step + (uint32_t)k0 * 2u,
+              st + (uint32_t)((i * NW + wave) * 1024));
+    }
+    __device__ __forceinline__ bf16x8 frag(const char *st, int x, int ks) const {
+        return *(const bf16x8 *)(st + ((frag0 ^ (uint32_t)(ks << 5)) + (uint32_t)(x * 32 * kPitch)));
+    }
+};
+
+// [k][row] operand of R rows: LDS [BK k][R], see TransOperand64
+template <int R, int NW, int BK = 64> struct RowsTrans {
+    static constexpr int kLoads = R * BK / (512 * NW);
+    static constexpr int kChunks = R / 8;          // 16-byte chunks of a k-row
+    static constexpr int kPeriod = R == 384 ? 3 : R == 256 ? 2 : 1;   // loads until (k-row mod 4, chunk) repeat
+    static constexpr int kPeriodRows = kPeriod * 64 / kChunks;        // k-rows they cover
+    static_assert(kLoads * 512 * NW == R * BK && kLoads % kPeriod == 0, "rows divide over the waves");
+    static __device__ __forceinline__ int perm(int kr) { return R == 64 ? (kr & 2) << 1 : (kr & 3) << 2; }
+    i32x4 rsrc;
+    uint32_t voff[kPeriod];
+    uint32_t k_step;
+    uint32_t frag_base, frag_perm;
+    __device__ __forceinline__ void init(const bf16 *base, int ld, int row0, int rowlim, int klim,
+                                         int lane, int wave) {
+        rsrc = make_rsrc(base, (uint32_t)klim * (uint32_t)ld * 2u);
+        k_step = (uint32_t)ld * 2u;
+#pragma unroll
+        for (int i = 0; i < kPeriod; ++i) {
+            const int at = (wave * kLoads + i) * 64 + lane;   // chunk of the stage the lane fills
+            const int kr = at / kChunks;
+            const int c = (at - kr * kChunks) ^ perm(kr);
+            const int row = row0 + (c << 3);
+            voff[i] = row < rowlim ? ((uint32_t)kr * (uint32_t)ld + (uint32_t)row) * 2u : kOobOffset;
+        }
+    }
+    __device__ __forceinline__ void disable_load() {
+#pragma unroll
+        for (int i = 0; i < kPeriod; ++i) voff[i] = kOobOffset;
+    }
+    __device__ __forceinline__ void init_frag(int lane, int frag_row) {
+        const int g = lane >> 4, j = lane & 15;
+        const int kq = j >> 2;
+        const int n = frag_row + (g & 1) * 16 + (j & 3) * 4;
+        frag_base = (uint32_t)((((g >> 1) * 8 + kq) * (R * 2)) + ((n >> 3) << 4) + ((n & 4) << 1));
+        frag_perm = (uint32_t)perm(kq) << 4;
+    }
+    __device__ __forceinline__ void issue_one(uint32_t st, int k0, int wave, int i) const {
+        dma16(rsrc, voff[i % kPeriod], (uint32_t)(k0 + i / kPeriod * kPeriodRows) * k_step,
+              st + (uint32_t)((wave * kLoads + i) * 1024));
+    }
+    __device__ __forceinline__ bf16x8 frag(const char *st, int x, int ks) const {
+        typedef __attribute__((address_space(3))) s16x4 *lds_s16x4_ptr;
+        const char *p0 = st + ((frag_base + (uint32_t)(x << 6)) ^ frag_perm) + ks * (16 * R * 2);
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p0));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p0 + 4 * R * 2));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+};
+
+// bytes per row of the epilogue's turn-around buffer of a wave with 32 IP columns
+constexpr int rows_turn_pitch(int IP) { return IP == 1 ? 64 : IP == 2 ? 128 : 256; }
+
+// wait until at most N of this wave's direct loads are still in flight
+template <int N> __device__ __forceinline__ void rows_wait_vmcnt() {
+    static_assert(N >= 0 && N < 64, "the counter has six bits");
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+
+}  // namespace sw

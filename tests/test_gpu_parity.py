@@ -675,3 +675,24 @@ def test_xxl_sampled_parity():
     inp = make_inputs(s, _dev())
     errs = compare_sampled(s, inp, n_experts=4, n_tokens=16)
     _report("xxl", errs)
+
+
+# Tile shapes of the one-tile-per-block GEMMs, each at ragged rows, columns and depth; the comments
+# name the tiles of the first- and second-layer products (rows x columns).
+@pytest.mark.parametrize("T,d,f,E,cf,rate,ffn", [
+    (200, 264, 520, 12, 1.5, 0.0, "relu"),      # 32 x 128 both; weight gradients: few large tiles
+    (33, 72, 136, 4, 1.0, 0.3, "relu"),         # ... a handful of rows, one k step
+    (1900, 264, 776, 40, 1.25, 0.0, "relu"),    # 96 x 128 and 32 x 128
+    (2000, 264, 1032, 40, 2.0, 0.2, "relu"),    # dropout in both masked epilogues
+    (5003, 392, 1000, 10, 1.25, 0.0, "relu"),   # 128 x 128 and 96 x 128
+    (6000, 200, 2312, 16, 1.0, 0.1, "relu"),    # 256-row tiles; two per expert, the second short
+    (9000, 72, 2312, 16, 1.25, 0.0, "relu"),    # 256 x 384, three row tiles, one and a bit k steps
+    (2500, 136, 520, 40, 1.0, 0.0, "geglu"),    # plain products, first layer twice as wide
+])
+def test_row_tiles_full_parity(T, d, f, E, cf, rate, ffn):
+    from parity import compare_full
+    s = SwitchShape("t", T, d, f, E, cf, dtype="bf16", seed_index=45, expert_dropout=rate, noise_seed=9,
+                    ffn=ffn)
+    inp = make_inputs(s, _dev())
+    errs, gpu, fwd, _ = compare_full(s, inp, d_aux=1.0)
+    _report("row tiles %s" % ((T, d, f, E, cf, rate, ffn),), errs)
