@@ -1,7 +1,11 @@
-// Grouped expert GEMMs for the all-fp32 configuration (act_dtype = SW_F32).
-// A plain LDS-tiled FMA kernel with generic strides: this path exists for the
-// fp32 parity configuration, not for throughput.
+// Grouped expert GEMMs for the all-fp32 configuration (act_dtype = SW_F32): fp32 products and
+// sums on the matrix cores (v_mfma_f32_32x32x2_f32, 157 TFLOP/s), and a plain FMA kernel with 64-bit
+// addresses for layers whose per-expert matrices reach 2 GB.
+#include <math.h>
+
 #include "common.h"
+#include "lds_operands.h"
+#include "rows_operands.h"
 
 namespace sw {
 
@@ -114,6 +118,213 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
     }
 }
 
+// ---- fp32 on the matrix cores -----------------------------------------------------------
+// One tile per block, QB x PB, WP x WQ waves of IP x IQ MFMA 32x32x2 tiles; k advances 32 at a time
+// through two LDS stages filled by direct loads.  Bound by the MFMA rate (64 cycles for 4096
+// FLOP per SIMD): a 64 x 64 step takes 1024 cycles and needs 16 KB, so operand traffic is no issue
+// and the tile is chosen small enough to fill the chip; waves whose rows do not exist skip their
+// MFMAs.  Measured (32 experts x 256 tokens x 768 x 3072, us per launch): 345-392 = 98-111 TFLOP/s,
+// the FMA kernel 827-1269.
+// Two-level sums as in the FMA kernel: chains of kF32Flush products are folded into a total.
+//
+// MFMA k-pairs: in a group of eight k the half wave h holds k = 4 h .. 4 h + 3 of its row, so that a
+// fragment of a [row][k] operand is one 16-byte LDS read; MFMA m of the group multiplies the
+// pair (m, 4 + m).  Both operands use the same assignment.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// [row][k] operand: 32 k = 128 bytes per row, exactly the bf16 layout of 64 k (sizes in half words)
+template <int R, int NW> struct F32Direct : RowsDirect<R, NW, 64> {
+    __device__ __forceinline__ void init(const float *base, int ld, int row0, int rowlim, int klim,
+                                         int lane, int wave) {
+        RowsDirect<R, NW, 64>::init((const bf16 *)base, 2 * ld, row0, rowlim, 2 * klim, lane, wave);
+    }
+    __device__ __forceinline__ void issue_one(uint32_t st, int k0, int wave, int i) const {
+        RowsDirect<R, NW, 64>::issue_one(st, 2 * k0, wave, i);
+    }
+    __device__ __forceinline__ f32x4 frag4(const char *st, int x, int ks) const {
+        return __builtin_bit_cast(f32x4, RowsDirect<R, NW, 64>::frag(st, x, ks));
+    }
+};
+
+// [k][row] operand: LDS [32 k][R]; rows 32 apart trade places where k mod 8 >= 4, so that the two half
+// waves of a read (four k apart) use different banks.
+template <int R, int NW> struct F32Trans {
+    static constexpr int kLoads = R * 32 * 4 / (1024 * NW);
+    static constexpr int kChunks = R / 4;              // 16-byte chunks of a k-row
+    static constexpr int kRowsPerLoad = 64 / kChunks;  // k-rows of one wave-wide load
+    static_assert(kLoads * NW * kRowsPerLoad == 32 && (kLoads * kRowsPerLoad) % 4 == 0, "k-rows divide over the waves");
+    i32x4 rsrc;
+    uint32_t voff[2];   // k-rows whose rows are in place / traded
+    uint32_t k_step, frag0;
+    __device__ __forceinline__ void init(const float *base, int ld, int row0, int rowlim, int klim,
+                                         int lane, int wave) {
+        rsrc = make_rsrc(base, (uint32_t)klim * (uint32_t)ld * 4u);
+        k_step = (uint32_t)ld * 4u;
+        const int kk = lane / kChunks;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int c = (lane % kChunks) ^ (t << 3);
+            const int row = row0 + c * 4;
+            voff[t] = row < rowlim
+                          ? ((uint32_t)(wave * kLoads * kRowsPerLoad + kk) * (uint32_t)ld + (uint32_t)row) * 4u
+                          : kOobOffset;
+        }
+    }
+    __device__ __forceinline__ void init_frag(int lane, int frag_row) {
+        const int h = lane >> 5;
+        frag0 = (uint32_t)(((4 * h) * R + ((frag_row + (lane & 31)) ^ (h << 5))) * 4);
+    }
+    __device__ __forceinline__ void issue_one(uint32_t st, int k0, int wave, int i) const {
+        const int k = (wave * kLoads + i) * kRowsPerLoad;   // first k-row of the load (of the step)
+        dma16(rsrc, voff[(k >> 2) & 1], (uint32_t)(k0 + i * kRowsPerLoad) * k_step,
+              st + (uint32_t)((wave * kLoads + i) * 1024));
+    }
+    __device__ __forceinline__ f32x4 frag4(const char *st, int x, int ks) const {
+        const char *p = st + (frag0 ^ (uint32_t)(x << 7)) + ks * (8 * R * 4);
+        f32x4 v;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) v[m] = *(const float *)(p + m * (R * 4));
+        return v;
+    }
+};
+
+enum { F32_PLAIN = 0, F32_RELU = 1, F32_MASK = 2 };
+
+template <int IP, int WP, int IQ, int WQ, bool Q_TRANS, bool P_TRANS, int EPI>
+__global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32Args a, int tiles_q, int tiles_p) {
+    constexpr int NW = WP * WQ, PB = 32 * IP * WP, QB = 32 * IQ * WQ;
+    constexpr int kPBytes = PB * 128, kStage = (PB + QB) * 128;
+    __shared__ __attribute__((aligned(16))) char lds[2 * kStage];
+    const int per_e = tiles_q * tiles_p;
+    const int e = blockIdx.x / per_e, rem = blockIdx.x - e * per_e;
+    const int pt = rem / tiles_q, qt = rem - pt * tiles_q;
+    const int lim = a.kept[e];
+    const int qlim = a.q_limited ? min(lim, a.Qdim) : a.Qdim;
+    const int klim = a.k_limited ? min(lim, a.Kdim) : a.Kdim;
+    const int q0 = qt * QB, p0 = pt * PB;
+    if (q0 >= qlim) return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wp = wave % WP, wq = wave / WP;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
+    const bool live = q0 + wq * 32 * IQ < qlim && p0 + wp * 32 * IP < a.Pdim;
+
+    typename std::conditional<P_TRANS, F32Trans<PB, NW>, F32Direct<PB, NW>>::type op;
+    typename std::conditional<Q_TRANS, F32Trans<QB, NW>, F32Direct<QB, NW>>::type oq;
+    op.init_frag(lane, wp * 32 * IP);
+    oq.init_frag(lane, wq * 32 * IQ);
+    op.init(a.P + (size_t)e * a.p_batch, P_TRANS ? (int)a.p_ks : (int)a.p_rs, p0, a.Pdim, klim, lane, wave);
+    oq.init(a.Q + (size_t)e * a.q_batch, Q_TRANS ? (int)a.q_ks : (int)a.q_rs, q0, qlim, klim, lane, wave);
+    const int nk = (klim + 31) / 32;
+
+    f32x16 acc[IP][IQ], total[IP][IQ];
+#pragma unroll
+    for (int i = 0; i < IP; ++i)
+#pragma unroll
+        for (int j = 0; j < IQ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = total[i][j][r] = 0.f;
+
+    auto issue = [&](int kt) {   // k past the end: zeros
+        const uint32_t at = lds0 + (uint32_t)((kt & 1) * kStage);
+#pragma unroll
+        for (int i = 0; i < decltype(op)::kLoads; ++i) op.issue_one(at, kt * 32, wave, i);
+#pragma unroll
+        for (int i = 0; i < decltype(oq)::kLoads; ++i) oq.issue_one(at + kPBytes, kt * 32, wave, i);
+    };
+    if (nk > 0) issue(0);
+    for (int kt = 0; kt < nk; ++kt) {
+        rows_wait_vmcnt<0>();
+        __syncthreads();   // step kt has landed, step kt - 1 is read
+        if (kt + 1 < nk) issue(kt + 1);
+        if (!live) continue;
+        const char *sp = lds + (kt & 1) * kStage, *sq = sp + kPBytes;
+        if (kt != 0 && kt % (kF32Flush / 32) == 0) {
+#pragma unroll
+            for (int i = 0; i < IP; ++i)
+#pragma unroll
+                for (int j = 0; j < IQ; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        total[i][j][r] += acc[i][j][r];
+                        acc[i][j][r] = 0.f;
+                    }
+        }
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            f32x4 fp[IP], fq[IQ];
+#pragma unroll
+            for (int i = 0; i < IP; ++i) fp[i] = op.frag4(sp, i, ks);
+#pragma unroll
+            for (int j = 0; j < IQ; ++j) fq[j] = oq.frag4(sq, j, ks);
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int i = 0; i < IP; ++i)
+#pragma unroll
+                    for (int j = 0; j < IQ; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fp[i][m], fq[j][m], acc[i][j], 0, 0, 0);
+        }
+    }
+    if (!live) return;
+    // a lane holds, for row q = lane % 32 of each tile, columns 8 g + 4 (lane / 32) .. + 3
+    float *Cout = a.Cout + (size_t)e * a.c_batch;
+    const float *mask = EPI == F32_MASK ? a.mask + (size_t)e * a.c_batch : nullptr;
+#pragma unroll
+    for (int j = 0; j < IQ; ++j) {
+        const int q = q0 + (wq * IQ + j) * 32 + (lane & 31);
+        if (q >= qlim) continue;
+        uint32_t row_idx = 0;   // index of the token's first hidden unit in the dropout stream
+        if (EPI == F32_RELU && a.nz.dropout)
+            row_idx = (uint32_t)a.slot_token[(size_t)e * a.slots + q] * (uint32_t)a.Pdim;
+#pragma unroll
+        for (int i = 0; i < IP; ++i)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int p = p0 + (wp * IP + i) * 32 + 8 * g + ((lane >> 5) << 2);
+                if (p >= a.Pdim) continue;   // Pdim is a multiple of 4: four columns are in or out
+                float v[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = total[i][j][4 * g + r] + acc[i][j][4 * g + r];
+                const size_t at = (size_t)q * a.ldc + p;
+                if (EPI == F32_RELU) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[r] = v[r] > 0.f ? v[r] : 0.f;
+                    if (a.nz.dropout) {   // Sec. 2.4: expert dropout on the hidden activation
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            v[r] = dropout_keeps(a.nz, row_idx + (uint32_t)(p + r)) ? v[r] * a.nz.drop_scale : 0.f;
+                    }
+                }
+                if (EPI == F32_MASK) {   // a unit passes the gradient iff it was active and survived dropout
+                    const float4 m = *(const float4 *)(mask + at);
+                    v[0] = m.x > 0.f ? v[0] * a.nz.drop_scale : 0.f;
+                    v[1] = m.y > 0.f ? v[1] * a.nz.drop_scale : 0.f;
+                    v[2] = m.z > 0.f ? v[2] * a.nz.drop_scale : 0.f;
+                    v[3] = m.w > 0.f ? v[3] * a.nz.drop_scale : 0.f;
+                }
+                *(float4 *)(Cout + at) = make_float4(v[0], v[1], v[2], v[3]);
+            }
+    }
+}
+
+template <int IP, int WP, int IQ, int WQ, bool Q_TRANS, bool P_TRANS, int EPI>
+static hipError_t f32_launch(const GemmF32Args &a, int E, hipStream_t s) {
+    const int tq = (int)ceil_div(a.Qdim, 32 * IQ * WQ), tp = (int)ceil_div(a.Pdim, 32 * IP * WP);
+    hipLaunchKernelGGL((gemm_f32_mfma_kernel<IP, WP, IQ, WQ, Q_TRANS, P_TRANS, EPI>),
+                       dim3((unsigned)(tq * tp * E)), dim3(64 * WP * WQ), 0, s, a, tq, tp);
+    return hipGetLastError();
+}
+
+template <bool Q_TRANS, bool P_TRANS, int EPI>
+static hipError_t f32_mfma(const GemmF32Args &a, int E, hipStream_t s) {
+    // 64 x 64 keeps the chip even (a 128 x 128 tile takes 573 instead of 364 us in the second GEMM of
+    // 32 experts x 256 tokens x 768 x 3072); twice as wide is 2-8 % faster where there are many tiles.
+    if (E * ceil_div(a.Qdim, 64) * ceil_div(a.Pdim, 128) >= 1024)
+        return f32_launch<2, 2, 1, 2, Q_TRANS, P_TRANS, EPI>(a, E, s);
+    return f32_launch<1, 2, 1, 2, Q_TRANS, P_TRANS, EPI>(a, E, s);
+}
+
 hipError_t launch_gemm_f32(GemmKind kind, const Workspace &w, char *ws, const void *W_in,
                            const void *W_out, void *dW_in, void *dW_out, const TokenMajor &,
                            hipStream_t s) {
@@ -176,6 +387,21 @@ hipError_t launch_gemm_f32(GemmKind kind, const Workspace &w, char *ws, const vo
     }
     if (a.Qdim == 0) return hipSuccess;   // capacity 0 and a slot-indexed output: nothing to do
     ProfScope ps(name, s);
+    // the matrix-core kernel addresses one expert's matrices through 32-bit buffer descriptors
+    const double most = fmax(fmax((double)d * f1, (double)C * d), (double)C * f1) * 4.;
+    if (most < 2147483647.) {
+        const int E = (int)w.E;
+        switch (kind) {
+        case GEMM_FWD1:
+            return w.geglu ? f32_mfma<false, true, F32_PLAIN>(a, E, s) : f32_mfma<false, true, F32_RELU>(a, E, s);
+        case GEMM_FWD2: return f32_mfma<false, true, F32_PLAIN>(a, E, s);
+        case GEMM_DGRAD2:
+            return w.geglu ? f32_mfma<false, false, F32_PLAIN>(a, E, s) : f32_mfma<false, false, F32_MASK>(a, E, s);
+        case GEMM_DGRAD1: return f32_mfma<false, false, F32_PLAIN>(a, E, s);
+        case GEMM_WGRAD2:
+        case GEMM_WGRAD1: return f32_mfma<true, true, F32_PLAIN>(a, E, s);
+        }
+    }
     dim3 grid((unsigned)ceil_div(a.Pdim, kF32Tile), (unsigned)ceil_div(a.Qdim, kF32Tile),
               (unsigned)w.E);
     hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, s, a);

@@ -696,3 +696,18 @@ def test_row_tiles_full_parity(T, d, f, E, cf, rate, ffn):
     inp = make_inputs(s, _dev())
     errs, gpu, fwd, _ = compare_full(s, inp, d_aux=1.0)
     _report("row tiles %s" % ((T, d, f, E, cf, rate, ffn),), errs)
+
+
+# fp32 GEMMs on the matrix cores: edges of 64-row / 64- and 128-column tiles, k tails, two-level sums
+@pytest.mark.parametrize("T,d,f,E,cf,rate,ffn", [
+    (900, 20, 1028, 128, 2.0, 0.0, "relu"),    # wide tiles (many of them), k = 20 and a k tail of 4
+    (700, 68, 132, 5, 1.0, 0.25, "relu"),      # one column group past a tile, third row tile short
+    (600, 516, 36, 2, 1.25, 0.0, "geglu"),     # k past two flushes of the running sum
+])
+def test_fp32_matrix_core_tiles(T, d, f, E, cf, rate, ffn):
+    from parity import compare_full
+    s = SwitchShape("t", T, d, f, E, cf, dtype="f32", seed_index=46, expert_dropout=rate, noise_seed=3,
+                    ffn=ffn)
+    inp = make_inputs(s, _dev())
+    errs, gpu, fwd, _ = compare_full(s, inp, d_aux=0.8)
+    _report("fp32 tiles %s" % ((T, d, f, E, cf, rate, ffn),), errs)
