@@ -56,17 +56,21 @@ Workspace layout_workspace(const switch_config *cfg) {
     w.Tg = w.T / w.n;
     w.Cg = capacity_of(cfg);
     w.C = w.n * w.Cg;
-    w.nbg = ceil_div(w.Tg, kRouteTB);
+    w.router_block = router_block_supported(cfg);
+    w.tb = w.router_block ? router_block_tokens(cfg) : kRouteTB;
+    w.nbg = ceil_div(w.Tg, w.tb);
     w.nb = w.n * w.nbg;
+    w.nbg_r = ceil_div(w.Tg, kRouteTB);
+    w.nb_r = w.n * w.nbg_r;
     w.elt = cfg->act_dtype == SW_BF16 ? 2 : 4;
-    w.nsplit = w.nb < 64 ? w.nb : 64;
+    w.nsplit = w.nb_r < 64 ? w.nb_r : 64;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     const size_t T = w.T, E = w.E, C = w.C, d = w.d, f = w.f, f1 = w.f1, nb = w.nb;
     w.probs = take(T * E * 4);
     w.idx = take(T * 4);
     w.gate = take(T * 4);
-    w.local_rank = take(nb * kRouteTB * 4);
+    w.local_rank = take((size_t)w.nb_r * kRouteTB * 4);
     w.block_counts = take(nb * E * 4);
     w.block_psum = take(nb * E * 4);
     w.block_off = take(nb * E * 4);
@@ -85,6 +89,7 @@ Workspace layout_workspace(const switch_config *cfg) {
     // descriptor with 32-bit byte offsets
     w.fused = cfg->act_dtype == SW_BF16 && (cfg->flags & SW_FLAG_FUSED_DISPATCH) &&
               (double)T * (double)d * 2.0 < 2147483647.0;
+    w.inline_scan = !w.fused && w.nb <= kInlineBlocks && w.n <= 8;
     w.tok_slot = take(T * 4);
     w.Xd = take(E * C * d * w.elt);
     w.H = take(w.geglu ? E * C * f1 * w.elt : 0);
@@ -278,7 +283,9 @@ static int forward_on(const switch_config *cfg, const Workspace &w, const void *
     // the re-routing stages rank the experts by logit: keep the logits if the caller does not
     if (w.ntlb_rounds > 0 && !router_logits) router_logits = (float *)(ws + w.ntlb_logits);
 
-    if (router_fwd_mfma_supported(w, dt))
+    if (w.router_block)
+        st = status_of(launch_router_block(w, dt, x, W_r, b_r, ws, expert_index, gate, router_logits, s));
+    else if (router_fwd_mfma_supported(w, dt))
         st = status_of(launch_router_fwd_mfma(w, x, W_r, b_r, ws, expert_index, gate,
                                               router_logits, s));
     else
@@ -286,7 +293,7 @@ static int forward_on(const switch_config *cfg, const Workspace &w, const void *
                                          router_logits, s));
     if (st) return st;
     if ((st = status_of(launch_route_scan(w, ws, expert_counts, s)))) return st;
-    if ((st = status_of(launch_dispatch(w, dt, cfg->alpha, x, ws, position_in_expert, dropped,
+    if ((st = status_of(launch_dispatch(w, dt, cfg->alpha, x, ws, position_in_expert, dropped, expert_counts,
                                         aux_loss, router_logits, expert_index, gate, y, s))))
         return st;
     const TokenMajor tm{x, nullptr, y};

@@ -27,9 +27,12 @@ constexpr int kWave = 64;
 // beyond every descriptor (all are kept below 2 GB), so loads through it read zeros.
 constexpr uint32_t kNoRow = 0x80000000u;
 
-// Token block of the router / position kernels: one block of kRouteTB threads
-// owns kRouteTB consecutive tokens.
+// Tokens per block of the two-kernel router paths and of the re-routing stages ...
 constexpr int kRouteTB = 256;
+// (the one-kernel router has its own, see router_block_tokens; Workspace::tb is the one in use)
+// Up to this many token blocks the assign kernel sums the block histograms before its own itself;
+// beyond, a scan kernel leaves the prefix sums in a table.
+constexpr int kInlineBlocks = 128;
 
 // Output tile of the bf16 grouped GEMM (square), and the bytes of ReLU-mask bits per tile.
 constexpr int kGemmTile = 256;
@@ -37,13 +40,13 @@ constexpr int kReluBitsPerTile = kGemmTile * kGemmTile / 8;
 
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Token blocks of the router kernels: group g's Tg tokens are cut into nbg blocks of kRouteTB
+// Token blocks of the router kernels: group g's Tg tokens are cut into nbg blocks of tb
 // (the last one short), so that a block never holds tokens of two routing groups.
-__device__ __forceinline__ void block_token_range(int b, int nbg, int Tg, int &t0, int &tend) {
+__device__ __forceinline__ void block_token_range(int b, int nbg, int Tg, int tb, int &t0, int &tend) {
     const int g = b / nbg;
-    t0 = g * Tg + (b - g * nbg) * kRouteTB;
+    t0 = g * Tg + (b - g * nbg) * tb;
     const int gend = (g + 1) * Tg;
-    tend = t0 + kRouteTB < gend ? t0 + kRouteTB : gend;
+    tend = t0 + tb < gend ? t0 + tb : gend;
 }
 __device__ __forceinline__ int block_of_token(int t, int nbg, int Tg) {
     const int g = t / Tg;
@@ -103,7 +106,11 @@ struct Workspace {
     int64_t Tg;                 // tokens per group (T / n)
     int64_t Cg;                 // capacity: slots per expert and group (Eq. 3 on Tg tokens)
     int64_t C;                  // slots per expert in the expert-major buffers: n * Cg
+    int router_block;           // the one-kernel router runs (router_block.hip)
+    int tb;                     // tokens per block of the routing tables
     int64_t nbg, nb;            // token blocks per group (blocks never straddle groups), in all
+    int64_t nbg_r, nb_r;        // ... of kRouteTB tokens: the re-routing stages
+    int inline_scan;            // no scan kernel: the assign kernel sums the block histograms
     size_t elt;                 // bytes per activation element
     size_t probs;               // f32 [T][E]   router probabilities (saved for backward)
     size_t idx;                 // i32 [T]
@@ -213,17 +220,23 @@ hipError_t launch_router_softmax(const Workspace &w, char *ws, int32_t *expert_i
 hipError_t launch_router_fwd_mfma(const Workspace &w, const void *x, const float *W_r,
                                   const float *b_r, char *ws, int32_t *expert_index, float *gate,
                                   float *router_logits, hipStream_t s);
-// Per-expert scan over token blocks, counts, kept, aux loss.
+// The whole router forward in one kernel (router_block.hip).
+bool router_block_supported(const switch_config *cfg);
+int router_block_tokens(const switch_config *cfg);
+hipError_t launch_router_block(const Workspace &w, int dtype, const void *x, const float *W_r,
+                               const float *b_r, char *ws, int32_t *expert_index, float *gate,
+                               float *router_logits, hipStream_t s);
+// Per-expert scan over token blocks, counts, kept, aux loss parts (nothing with w.inline_scan).
 hipError_t launch_route_scan(const Workspace &w, char *ws, int32_t *expert_counts, hipStream_t s);
-// number of blocks of that launch = parts of the loss that positions_kernel adds up
-int route_scan_blocks(const Workspace &w);
-// Positions, dropped mask, the loss from its parts, gather of kept tokens into expert-major slots.
-// With No-Token-Left-Behind stages (logits != nullptr) between the two, which also update
-// expert_index and gate of the tokens they place.
+// number of loss parts it leaves for the assign kernel
+int route_scan_parts(const Workspace &w);
+// Positions, dropped mask, slot tables, the loss, and the gather of kept tokens into expert-major
+// slots.  With No-Token-Left-Behind stages (logits != nullptr) the gather follows them; they also
+// update expert_index and gate of the tokens they place.
 hipError_t launch_dispatch(const Workspace &w, int dtype, float alpha, const void *x, char *ws,
-                           int32_t *position_in_expert, uint8_t *dropped, float *aux_loss,
-                           const float *logits, int32_t *expert_index, float *gate, void *y,
-                           hipStream_t s);
+                           int32_t *position_in_expert, uint8_t *dropped, int32_t *expert_counts,
+                           float *aux_loss, const float *logits, int32_t *expert_index, float *gate,
+                           void *y, hipStream_t s);
 hipError_t launch_ntlb(const Workspace &w, char *ws, const float *logits, int32_t *expert_index,
                        float *gate, int32_t *position_in_expert, uint8_t *dropped,
                        hipStream_t s);
@@ -237,6 +250,7 @@ hipError_t launch_router_bwd(const Workspace &w, int dtype, float alpha, float d
                              const void *x, const float *W_r, char *ws, void *dx, float *dW_r,
                              float *db_r, hipStream_t s);
 // MFMA pieces of the router backward (bf16, E <= 128), in gemm_bf16.hip
+hipError_t launch_router_split_bwd(const Workspace &w, const float *W_r, char *ws, hipStream_t s);
 hipError_t launch_router_dx_mfma(const Workspace &w, char *ws, void *dx, hipStream_t s);
 hipError_t launch_router_dWr_mfma(const Workspace &w, const void *x, char *ws, hipStream_t s);
 

@@ -47,52 +47,191 @@ template <> __device__ __forceinline__ Chunk16 pack<bf16>(const float *v) {
 }
 
 // -----------------------------------------------------------------------------
+// Assign, 16 tokens per block (a token block of the routing tables is shared by several):
 // position_in_expert[t] = block_off[block(t)][e_t] + local_rank[t] (rank inside the token's
 // routing group); dropped mask (position >= Cg); slot of each kept token,
-// e * C + grp_off[g][e] + position, the slot -> token table and the gate of each slot's token.
-// Thread 0 also finishes the auxiliary loss.
+// e * C + grp_off[g][e] + position, the slot -> token table and the gate of each slot's token;
+// then (COPY) the dispatch gather Xd[slot] = x[t] of the block's kept tokens.
+// INLINE: the prefix sums of the block histograms are taken here instead of being read from the
+// scan kernel's tables, and one more block does what is left of that kernel: counts, kept, the
+// loss.  With few token blocks that costs less than a launch (T = 2048: 10 us; scan, positions and
+// gather as three launches took 27).  16 tokens per block: with 64, a gather of 16384 rows of
+// 8 KB took 97 us on its 256 blocks, with 16 it takes 53, as the row-per-wave pass it replaces.
 // -----------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void positions_kernel(
-    const int32_t *__restrict__ idx, const int32_t *__restrict__ local_rank,
-    const int32_t *__restrict__ block_off, const int32_t *__restrict__ grp_off,
-    const float *__restrict__ gate, int32_t *__restrict__ pos_out, uint8_t *__restrict__ dropped_out,
-    int32_t *__restrict__ slot_token, float *__restrict__ slot_gate, uint32_t *__restrict__ slot_off,
-    uint32_t row_bytes, int32_t *__restrict__ tok_slot, const double *__restrict__ loss_part,
-    int loss_parts,
-    double loss_scale /* alpha E / n */, float *__restrict__ aux_out, int T, int Tg, int nbg, int E,
-    int C, int Cg, Chunk16 *__restrict__ y_zero /* or null */, int cpr) {
-    __shared__ int32_t dropped_tokens[256];
-    __shared__ int n_dropped;
-    const int t = blockIdx.x * 256 + threadIdx.x;
-    if (threadIdx.x == 0) n_dropped = 0;
-    if (t == 0) {   // Eqs. 4-6 from the scan kernel's parts, in block order
-        double sum = 0.0;
-        for (int i = 0; i < loss_parts; ++i) sum += loss_part[i];
-        aux_out[0] = (float)(loss_scale * sum);
-    }
-    __syncthreads();
-    if (t < T) {
-        const int e = idx[t];
-        const int p = block_off[(size_t)block_of_token(t, nbg, Tg) * E + e] + local_rank[t];
-        const uint8_t dr = p >= Cg;
-        pos_out[t] = p;
-        dropped_out[t] = dr;
-        const int slot = e * C + grp_off[(size_t)(t / Tg) * E + e] + p;
-        if (!dr) {
-            slot_token[slot] = t;
-            slot_gate[slot] = gate[t];
-            slot_off[slot] = (uint32_t)t * row_bytes;   // used only where it cannot overflow
+struct AssignArgs {
+    const int32_t *idx, *local_rank, *block_counts, *block_off;
+    const float *block_psum, *gate;
+    int32_t *grp_off, *counts, *kept, *counts_g;
+    int32_t *pos_out, *counts_out;
+    uint8_t *dropped_out;
+    int32_t *slot_token;
+    float *slot_gate;
+    uint32_t *slot_off;          // only with dispatch inside the GEMMs
+    uint32_t row_bytes;
+    int32_t *tok_slot;
+    const double *loss_part;
+    int loss_parts;
+    double loss_scale;           // alpha E / n
+    float *aux_out;
+    int tb, nbg, nb, n, Tg, E, C, Cg;
+    const Chunk16 *x;            // COPY
+    Chunk16 *Xd;
+    Chunk16 *y_zero;             // rows of tokens without a slot become +0, or null
+    int cpr;                     // 16-byte chunks per row
+};
+
+// sums over rows [lo, hi) of a [..][E] table, columns e0 .. e0 + 255, into out[] (LDS); whole block.
+// The threads that are not needed side by side split the rows; W columns per thread.
+template <typename V, int W>
+__device__ __forceinline__ void column_sums_w(const V *__restrict__ table, int lo, int hi, int E, int e0,
+                                              V *part /* [256 W] */, V *out) {
+    int ew = 256 / W;
+    while (ew > 1 && ew / 2 * W >= E - e0) ew >>= 1;
+    const int P = 256 / ew < 16 ? 256 / ew : 16;   // (the parts are added up one after the other)
+    const int col = threadIdx.x % ew, p = threadIdx.x / ew;
+    const int per = (hi - lo + P - 1) / P;
+    const int a = lo + p * per, z = a + per < hi ? a + per : hi;
+    V s[W];
+#pragma unroll
+    for (int m = 0; m < W; ++m) s[m] = 0;
+    if (p < P && e0 + col * W < E)
+#pragma unroll 8
+        for (int b = a; b < z; ++b) {
+            V v[W];
+            __builtin_memcpy(v, __builtin_assume_aligned(table + (size_t)b * E + e0 + col * W, W * 4), W * 4);
+#pragma unroll
+            for (int m = 0; m < W; ++m) s[m] += v[m];
         }
-        tok_slot[t] = dr ? -1 : slot;
-        if (dr && y_zero) dropped_tokens[atomicAdd(&n_dropped, 1)] = t;   // any order
-    }
-    if (!y_zero) return;
-    // the block's tokens without a slot get their rows of y: +0, written by all 256 threads
+#pragma unroll
+    for (int m = 0; m < W; ++m) part[threadIdx.x * W + m] = s[m];
     __syncthreads();
-    const Chunk16 zero = {{0u, 0u, 0u, 0u}};
-    for (int i = threadIdx.x; i < n_dropped * cpr; i += 256) {
-        const int k = i / cpr;
-        y_zero[(size_t)dropped_tokens[k] * cpr + (i - k * cpr)] = zero;
+    if ((int)threadIdx.x < ew * W) {
+        V t = part[threadIdx.x];
+        for (int q = 1; q < P; ++q) t += part[q * ew * W + threadIdx.x];
+        out[threadIdx.x] = t;
+    }
+    __syncthreads();
+}
+template <typename V>
+__device__ __forceinline__ void column_sums(const V *__restrict__ table, int lo, int hi, int E, int e0, V *part,
+                                            V *out) {
+    if ((E & 3) == 0) column_sums_w<V, 4>(table, lo, hi, E, e0, part, out);
+    else column_sums_w<V, 1>(table, lo, hi, E, e0, part, out);
+}
+
+constexpr int kAssignTok = 16;   // tokens per block
+
+template <bool INLINE, bool COPY>
+__global__ __launch_bounds__(256) void assign_kernel(AssignArgs a) {
+    __shared__ int32_t slot_s[kAssignTok];
+    __shared__ int32_t part[INLINE ? 1024 : kAssignTok], sums[INLINE ? 256 : 1];
+    __shared__ float fpart[INLINE ? 1024 : 1], fsums[INLINE ? 256 : 1];
+    __shared__ double red[INLINE ? 256 : 1];
+    __shared__ int n_dropped;
+    extern __shared__ int32_t dyn[];   // INLINE: off[E], goff[E] of the block's group
+    const int tid = threadIdx.x;
+    const int per_b = a.tb / kAssignTok, b = blockIdx.x / per_b;
+    const int E = a.E;
+    if (INLINE && b == a.nb) {   // the extra block: totals over all token blocks
+        double loss = 0.0;
+        for (int e0 = 0; e0 < E; e0 += 256) {
+            int total = 0, kept = 0;
+            for (int g = 0; g < a.n; ++g) {
+                column_sums<int32_t>(a.block_counts, g * a.nbg, (g + 1) * a.nbg, E, e0, part, sums);
+                column_sums<float>(a.block_psum, g * a.nbg, (g + 1) * a.nbg, E, e0, fpart, fsums);
+                if (e0 + tid < E) {
+                    const int c = sums[tid];
+                    a.counts_g[(size_t)g * E + e0 + tid] = c;
+                    total += c;
+                    kept += c < a.Cg ? c : a.Cg;
+                    loss += ((double)c / (double)a.Tg) * ((double)fsums[tid] / (double)a.Tg);   // Eqs. 4-6
+                }
+                __syncthreads();
+            }
+            if (e0 + tid < E) {
+                a.counts[e0 + tid] = total;
+                a.counts_out[e0 + tid] = total;
+                a.kept[e0 + tid] = kept;
+            }
+        }
+        red[tid] = loss;
+        __syncthreads();
+        for (int s = 128; s >= 1; s >>= 1) {
+            if (tid < s) red[tid] += red[tid + s];
+            __syncthreads();
+        }
+        if (tid == 0) a.aux_out[0] = (float)(a.loss_scale * red[0]);
+        return;
+    }
+    const int g = b / a.nbg;
+    int t0, tend;
+    block_token_range(b, a.nbg, a.Tg, a.tb, t0, tend);
+    t0 += (blockIdx.x - b * per_b) * kAssignTok;   // this block's share
+    tend = t0 + kAssignTok < tend ? t0 + kAssignTok : tend;
+    if (t0 >= tend && blockIdx.x != 0) return;
+    if (tid == 0) n_dropped = 0;
+    if (INLINE) {
+        for (int e0 = 0; e0 < E; e0 += 256) {
+            int goff = 0;   // slots of the earlier groups
+            for (int q = 0; q < g; ++q) {
+                column_sums<int32_t>(a.block_counts, q * a.nbg, (q + 1) * a.nbg, E, e0, part, sums);
+                if (e0 + tid < E) goff += sums[tid] < a.Cg ? sums[tid] : a.Cg;
+                __syncthreads();
+            }
+            column_sums<int32_t>(a.block_counts, g * a.nbg, b, E, e0, part, sums);
+            if (e0 + tid < E) {
+                dyn[e0 + tid] = sums[tid];
+                dyn[E + e0 + tid] = goff;
+                if (t0 == g * a.Tg) a.grp_off[(size_t)g * E + e0 + tid] = goff;
+            }
+            __syncthreads();
+        }
+    } else {
+        if (blockIdx.x == 0 && tid == 0) {   // Eqs. 4-6 from the scan's parts, in order
+            double sum = 0.0;
+            for (int i = 0; i < a.loss_parts; ++i) sum += a.loss_part[i];
+            a.aux_out[0] = (float)(a.loss_scale * sum);
+        }
+        __syncthreads();
+    }
+    if (tid < kAssignTok) {
+        const int t = t0 + tid;
+        int slot_or_none = -1;
+        if (t < tend) {
+            const int e = a.idx[t];
+            const int p = (INLINE ? dyn[e] : a.block_off[(size_t)b * E + e]) + a.local_rank[t];
+            const uint8_t dr = p >= a.Cg;
+            a.pos_out[t] = p;
+            a.dropped_out[t] = dr;
+            if (!dr) {
+                const int slot = e * a.C + (INLINE ? dyn[E + e] : a.grp_off[(size_t)g * E + e]) + p;
+                slot_or_none = slot;
+                a.slot_token[slot] = t;
+                a.slot_gate[slot] = a.gate[t];
+                if (a.slot_off) a.slot_off[slot] = (uint32_t)t * a.row_bytes;
+            }
+            a.tok_slot[t] = slot_or_none;
+        }
+        slot_s[tid] = slot_or_none;
+        if (a.y_zero && t < tend && slot_or_none < 0) part[atomicAdd(&n_dropped, 1)] = t;   // any order
+    }
+    if (!COPY && !a.y_zero) return;
+    __syncthreads();
+    if (COPY) {
+        const int total = (tend - t0) * a.cpr;
+#pragma unroll 4
+        for (int i = tid; i < total; i += 256) {
+            const int tl = i / a.cpr, c = i - tl * a.cpr;
+            const int slot = slot_s[tl];
+            if (slot >= 0) a.Xd[(size_t)slot * a.cpr + c] = a.x[(size_t)(t0 + tl) * a.cpr + c];
+        }
+    }
+    if (a.y_zero) {   // the block's tokens without a slot get their rows of y: +0
+        const Chunk16 zero = {{0u, 0u, 0u, 0u}};
+        for (int i = tid; i < n_dropped * a.cpr; i += 256) {
+            const int k = i / a.cpr;
+            a.y_zero[(size_t)part[k] * a.cpr + (i - k * a.cpr)] = zero;
+        }
     }
 }
 
@@ -254,23 +393,51 @@ hipError_t launch_gate_grad(const Workspace &w, const void *dy, char *ws, hipStr
 }
 
 hipError_t launch_dispatch(const Workspace &w, int dtype, float alpha, const void *x, char *ws,
-                           int32_t *position_in_expert, uint8_t *dropped, float *aux_loss,
-                           const float *logits, int32_t *expert_index, float *gate, void *y,
-                           hipStream_t s) {
+                           int32_t *position_in_expert, uint8_t *dropped, int32_t *expert_counts,
+                           float *aux_loss, const float *logits, int32_t *expert_index, float *gate,
+                           void *y, hipStream_t s) {
     hipError_t err;
+    const int cpr = (int)(w.d * w.elt / 16);
+    // the gather of the kept tokens: here, unless re-routing stages place more of them first or the
+    // GEMMs read x through the slot -> token table
+    const bool gather = w.C > 0 && !w.fused, copy = gather && w.ntlb_rounds == 0;
     {
-        ProfScope ps("positions", s);
-        hipLaunchKernelGGL(positions_kernel, dim3((unsigned)ceil_div(w.T, 256)), dim3(256), 0, s,
-                           (const int32_t *)(ws + w.idx), (const int32_t *)(ws + w.local_rank),
-                           (const int32_t *)(ws + w.block_off), (const int32_t *)(ws + w.grp_off),
-                           (const float *)(ws + w.gate), position_in_expert, dropped,
-                           (int32_t *)(ws + w.slot_token), (float *)(ws + w.slot_gate),
-                           (uint32_t *)(ws + w.slot_off), (uint32_t)(w.d * w.elt),
-                           (int32_t *)(ws + w.tok_slot), (const double *)(ws + w.loss_part),
-                           route_scan_blocks(w), (double)alpha * (double)w.E / (double)w.n,
-                           aux_loss, (int)w.T, (int)w.Tg, (int)w.nbg, (int)w.E, (int)w.C,
-                           (int)w.Cg, (Chunk16 *)(zero_rows_with_positions(w) ? y : nullptr),
-                           (int)(w.d * w.elt / 16));
+        AssignArgs a{};
+        a.idx = (const int32_t *)(ws + w.idx);
+        a.local_rank = (const int32_t *)(ws + w.local_rank);
+        a.block_counts = (const int32_t *)(ws + w.block_counts);
+        a.block_psum = (const float *)(ws + w.block_psum);
+        a.block_off = (const int32_t *)(ws + w.block_off);
+        a.gate = (const float *)(ws + w.gate);
+        a.grp_off = (int32_t *)(ws + w.grp_off);
+        a.counts = (int32_t *)(ws + w.counts);
+        a.kept = (int32_t *)(ws + w.kept);
+        a.counts_g = (int32_t *)(ws + w.counts_g);
+        a.pos_out = position_in_expert;
+        a.counts_out = expert_counts;
+        a.dropped_out = dropped;
+        a.slot_token = (int32_t *)(ws + w.slot_token);
+        a.slot_gate = (float *)(ws + w.slot_gate);
+        a.slot_off = w.fused ? (uint32_t *)(ws + w.slot_off) : nullptr;
+        a.row_bytes = (uint32_t)(w.d * w.elt);
+        a.tok_slot = (int32_t *)(ws + w.tok_slot);
+        a.loss_part = (const double *)(ws + w.loss_part);
+        a.loss_parts = route_scan_parts(w);
+        a.loss_scale = (double)alpha * (double)w.E / (double)w.n;
+        a.aux_out = aux_loss;
+        a.tb = w.tb; a.nbg = (int)w.nbg; a.nb = (int)w.nb; a.n = (int)w.n; a.Tg = (int)w.Tg;
+        a.E = (int)w.E; a.C = (int)w.C; a.Cg = (int)w.Cg;
+        a.x = (const Chunk16 *)x;
+        a.Xd = (Chunk16 *)(ws + w.Xd);
+        a.y_zero = zero_rows_with_positions(w) ? (Chunk16 *)y : nullptr;
+        a.cpr = cpr;
+        ProfScope ps("assign_gather", s);
+        const dim3 grid((unsigned)(w.nb * (w.tb / kAssignTok) + (w.inline_scan ? 1 : 0)));
+        const size_t dyn = w.inline_scan ? 2 * sizeof(int32_t) * (size_t)w.E : 0;
+        if (w.inline_scan && copy) hipLaunchKernelGGL((assign_kernel<true, true>), grid, dim3(256), dyn, s, a);
+        else if (w.inline_scan) hipLaunchKernelGGL((assign_kernel<true, false>), grid, dim3(256), dyn, s, a);
+        else if (copy) hipLaunchKernelGGL((assign_kernel<false, true>), grid, dim3(256), dyn, s, a);
+        else hipLaunchKernelGGL((assign_kernel<false, false>), grid, dim3(256), dyn, s, a);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
     if (w.C == 0) return hipSuccess;
@@ -278,17 +445,12 @@ hipError_t launch_dispatch(const Workspace &w, int dtype, float alpha, const voi
         (err = launch_ntlb(w, ws, logits, expert_index, gate, position_in_expert, dropped, s)) !=
             hipSuccess)
         return err;
-    if (w.fused) return hipSuccess;   // the GEMMs read x through the slot -> token table
-    {
-        ProfScope ps("dispatch_gather", s);
-        const int vec = dtype == SW_BF16 ? 8 : 4;
-        const int cpr = (int)(w.d / vec);
-        hipLaunchKernelGGL(dispatch_kernel, dim3((unsigned)ceil_div(w.T, 256 / kWave)), dim3(256),
-                           0, s, (const Chunk16 *)x, (Chunk16 *)(ws + w.Xd),
-                           (const int32_t *)(ws + w.tok_slot), (int)w.T, cpr);
-        err = hipGetLastError();
-    }
-    return err;
+    if (!gather || copy) return hipSuccess;
+    ProfScope ps("dispatch_gather", s);
+    hipLaunchKernelGGL(dispatch_kernel, dim3((unsigned)ceil_div(w.T, 256 / kWave)), dim3(256), 0, s,
+                       (const Chunk16 *)x, (Chunk16 *)(ws + w.Xd), (const int32_t *)(ws + w.tok_slot),
+                       (int)w.T, cpr);
+    return hipGetLastError();
 }
 
 hipError_t launch_combine(const Workspace &w, int dtype, char *ws, void *y, hipStream_t s) {

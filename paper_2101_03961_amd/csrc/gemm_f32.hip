@@ -127,63 +127,40 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
 // the FMA kernel 827-1269.
 // Two-level sums as in the FMA kernel: chains of kF32Flush products are folded into a total.
 //
-// MFMA k-pairs: in a group of eight k the half wave h holds k = 4 h .. 4 h + 3 of its row, so that a
-// fragment of a [row][k] operand is one 16-byte LDS read; MFMA m of the group multiplies the
-// pair (m, 4 + m).  Both operands use the same assignment.
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-// [row][k] operand: 32 k = 128 bytes per row, exactly the bf16 layout of 64 k (sizes in half words)
-template <int R, int NW> struct F32Direct : RowsDirect<R, NW, 64> {
-    __device__ __forceinline__ void init(const float *base, int ld, int row0, int rowlim, int klim,
-                                         int lane, int wave) {
-        RowsDirect<R, NW, 64>::init((const bf16 *)base, 2 * ld, row0, rowlim, 2 * klim, lane, wave);
-    }
-    __device__ __forceinline__ void issue_one(uint32_t st, int k0, int wave, int i) const {
-        RowsDirect<R, NW, 64>::issue_one(st, 2 * k0, wave, i);
-    }
-    __device__ __forceinline__ f32x4 frag4(const char *st, int x, int ks) const {
-        return __builtin_bit_cast(f32x4, RowsDirect<R, NW, 64>::frag(st, x, ks));
-    }
-};
-
-// [k][row] operand: LDS [32 k][R]; rows 32 apart trade places where k mod 8 >= 4, so that the two half
-// waves of a read (four k apart) use different banks.
+// k runs in order: MFMA m of a group of eight multiplies the pair (2 m, 2 m + 1), so that every
+// sum is the same chain of fused multiply-adds as the FMA kernel's, bit for bit.
+// [k][row] operand: LDS [32 k][R]; rows 32 apart trade places in odd k-rows, so that the two half
+// waves of a read (neighbouring k) use different banks.
 template <int R, int NW> struct F32Trans {
     static constexpr int kLoads = R * 32 * 4 / (1024 * NW);
     static constexpr int kChunks = R / 4;              // 16-byte chunks of a k-row
     static constexpr int kRowsPerLoad = 64 / kChunks;  // k-rows of one wave-wide load
-    static_assert(kLoads * NW * kRowsPerLoad == 32 && (kLoads * kRowsPerLoad) % 4 == 0, "k-rows divide over the waves");
+    static_assert(kLoads * NW * kRowsPerLoad == 32 && kRowsPerLoad % 2 == 0, "k-rows divide over the waves");
     i32x4 rsrc;
-    uint32_t voff[2];   // k-rows whose rows are in place / traded
-    uint32_t k_step, frag0;
+    uint32_t voff, k_step, frag0;
     __device__ __forceinline__ void init(const float *base, int ld, int row0, int rowlim, int klim,
                                          int lane, int wave) {
         rsrc = make_rsrc(base, (uint32_t)klim * (uint32_t)ld * 4u);
         k_step = (uint32_t)ld * 4u;
         const int kk = lane / kChunks;
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int c = (lane % kChunks) ^ (t << 3);
-            const int row = row0 + c * 4;
-            voff[t] = row < rowlim
-                          ? ((uint32_t)(wave * kLoads * kRowsPerLoad + kk) * (uint32_t)ld + (uint32_t)row) * 4u
-                          : kOobOffset;
-        }
+        const int row = row0 + ((lane % kChunks) ^ ((kk & 1) << 3)) * 4;
+        voff = row < rowlim ? ((uint32_t)(wave * kLoads * kRowsPerLoad + kk) * (uint32_t)ld + (uint32_t)row) * 4u
+                            : kOobOffset;
     }
     __device__ __forceinline__ void init_frag(int lane, int frag_row) {
         const int h = lane >> 5;
-        frag0 = (uint32_t)(((4 * h) * R + ((frag_row + (lane & 31)) ^ (h << 5))) * 4);
+        frag0 = (uint32_t)((h * R + ((frag_row + (lane & 31)) ^ (h << 5))) * 4);
     }
     __device__ __forceinline__ void issue_one(uint32_t st, int k0, int wave, int i) const {
-        const int k = (wave * kLoads + i) * kRowsPerLoad;   // first k-row of the load (of the step)
-        dma16(rsrc, voff[(k >> 2) & 1], (uint32_t)(k0 + i * kRowsPerLoad) * k_step,
+        dma16(rsrc, voff, (uint32_t)(k0 + i * kRowsPerLoad) * k_step,
               st + (uint32_t)((wave * kLoads + i) * 1024));
     }
+    // element m: k = 8 ks + 2 m + lane / 32
     __device__ __forceinline__ f32x4 frag4(const char *st, int x, int ks) const {
         const char *p = st + (frag0 ^ (uint32_t)(x << 7)) + ks * (8 * R * 4);
         f32x4 v;
 #pragma unroll
-        for (int m = 0; m < 4; ++m) v[m] = *(const float *)(p + m * (R * 4));
+        for (int m = 0; m < 4; ++m) v[m] = *(const float *)(p + m * (2 * R * 4));
         return v;
     }
 };

@@ -98,7 +98,7 @@ __global__ __launch_bounds__(kRouteTB) void ntlb_rank_kernel(
     const int lane = tid & 63, wave = tid >> 6;
     const int b = blockIdx.x;
     int t0, tend;
-    block_token_range(b, nbg, Tg, t0, tend);
+    block_token_range(b, nbg, Tg, kRouteTB, t0, tend);
     for (int i = tid; i < E; i += kRouteTB) hist[i] = 0;
     const int tw = t0 + tid;
     const int next = (tw < tend && tok_slot[tw] < 0) ? asked[tw] : -1;
@@ -220,14 +220,14 @@ hipError_t launch_ntlb(const Workspace &w, char *ws, const float *logits, int32_
         hipLaunchKernelGGL(ntlb_choice_kernel, dim3((unsigned)ceil_div(W, 4)), dim3(256), 0, s, logits,
                            (const int32_t *)(ws + w.tok_slot), (const int32_t *)(ws + w.idx),
                            (int32_t *)(ws + w.ntlb_asked), (int)w.T, (int)w.E, W, round);
-        hipLaunchKernelGGL(ntlb_rank_kernel, dim3((unsigned)w.nb), dim3(kRouteTB), smem, s,
+        hipLaunchKernelGGL(ntlb_rank_kernel, dim3((unsigned)w.nb_r), dim3(kRouteTB), smem, s,
                            (const int32_t *)(ws + w.tok_slot), (const int32_t *)(ws + w.ntlb_asked),
                            (int32_t *)(ws + w.local_rank), (int32_t *)(ws + w.block_counts),
-                           (int)w.nbg, (int)w.Tg, (int)w.E);
+                           (int)w.nbg_r, (int)w.Tg, (int)w.E);
         hipLaunchKernelGGL(ntlb_block_scan_kernel, dim3((unsigned)ceil_div(w.n * w.E, 4)), dim3(256),
                            0, s, (const int32_t *)(ws + w.block_counts),
                            (int32_t *)(ws + w.block_off), (int32_t *)(ws + w.ntlb_cnt), (int)w.n,
-                           (int)w.nbg, (int)w.E);
+                           (int)w.nbg_r, (int)w.E);
         hipLaunchKernelGGL(ntlb_expert_scan_kernel, dim3((unsigned)ceil_div(w.E, 256)), dim3(256), 0,
                            s, (const int32_t *)(ws + w.ntlb_cnt), (const int32_t *)(ws + w.counts_g),
                            (int32_t *)(ws + w.ntlb_used), (int32_t *)(ws + w.kept),
@@ -241,7 +241,7 @@ hipError_t launch_ntlb(const Workspace &w, char *ws, const float *logits, int32_
                            (float *)(ws + w.slot_gate), (uint32_t *)(ws + w.slot_off),
                            (uint32_t)(w.d * w.elt), (int32_t *)(ws + w.idx),
                            (float *)(ws + w.gate), expert_index, gate,
-                           position_in_expert, dropped, (int)w.T, (int)w.Tg, (int)w.nbg, (int)w.E,
+                           position_in_expert, dropped, (int)w.T, (int)w.Tg, (int)w.nbg_r, (int)w.E,
                            (int)w.Cg);
         hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;

@@ -116,7 +116,7 @@ __global__ __launch_bounds__(WAVES * kWave) void router_softmax_kernel(
     const int wave = tid / kWave;
     const int b = blockIdx.x;
     int t0, tend;
-    block_token_range(b, nbg, Tg, t0, tend);
+    block_token_range(b, nbg, Tg, kRouteTB, t0, tend);
     constexpr int kThreads = WAVES * kWave;
     constexpr int kTokPerWave = kRouteTB / WAVES;
     for (int e = tid; e < E; e += kThreads) hist[e] = 0;
@@ -234,28 +234,34 @@ __global__ __launch_bounds__(WAVES * kWave) void router_softmax_kernel(
 }
 
 // -----------------------------------------------------------------------------
-// Per-expert scan over token blocks: each block of 1024 threads takes a slice of the experts
-// and leaves its part of sum_e (counts / T) (psum / T) in loss_part; positions_kernel adds
-// the parts up in block order.
-//   block_off[b][e] = sum_{b' < b} block_counts[b'][e]
-//   counts[e], kept[e] = min(counts[e], C),  P-sum[e] in fixed order
-//   aux = alpha * E * sum_e (counts[e] / T) * (psum[e] / T)             (Eqs. 4-6)
+// Per-expert scan over the token blocks of group blockIdx.y: each block of 1024 threads takes a slice
+// of the experts.
+//   block_off[b][e] = sum of block_counts[b'][e] over the group's earlier blocks
+//   counts_g[g][e], psum_g[g][e] in fixed order
+// With one group also counts[e], kept[e] = min(counts[e], C) and the block's part of
+// sum_e (counts / T) (psum / T)  (Eqs. 4-6); the assign kernel adds the parts up in order.
 // -----------------------------------------------------------------------------
 constexpr int kScanThreads = 1024;
 
 __global__ __launch_bounds__(kScanThreads) void route_scan_kernel(
     const int32_t *__restrict__ block_counts, const float *__restrict__ block_psum,
     int32_t *__restrict__ block_off, int32_t *__restrict__ counts_ws, int32_t *__restrict__ kept_ws,
-    int32_t *__restrict__ counts_g, int32_t *__restrict__ grp_off, int32_t *__restrict__ counts_out,
-    double *__restrict__ loss_part, uint32_t *__restrict__ slot_off, int slot_off_n, int nb, int E,
-    int C, int T) {
-    // every slot starts without a token (the position kernel, which runs next, fills in the rest)
-    for (int i = blockIdx.x * kScanThreads + threadIdx.x; i < slot_off_n; i += gridDim.x * kScanThreads)
+    int32_t *__restrict__ counts_g, float *__restrict__ psum_g, int32_t *__restrict__ grp_off,
+    int32_t *__restrict__ counts_out, double *__restrict__ loss_part, uint32_t *__restrict__ slot_off,
+    int slot_off_n, int nbg, int E, int C, int Tg) {
+    // dispatch inside the GEMMs: every slot starts without a token (the assign kernel fills in the rest)
+    for (int i = (blockIdx.y * gridDim.x + blockIdx.x) * kScanThreads + threadIdx.x; i < slot_off_n;
+         i += gridDim.x * gridDim.y * kScanThreads)
         slot_off[i] = kNoRow;
     __shared__ int32_t part_cnt[kScanThreads];
     __shared__ float part_ps[kScanThreads];
     __shared__ double red[kScanThreads];
     const int tid = threadIdx.x;
+    const int g = blockIdx.y;
+    const bool one_group = gridDim.y == 1;
+    block_counts += (size_t)g * nbg * E;
+    block_psum += (size_t)g * nbg * E;
+    block_off += (size_t)g * nbg * E;
     // this block's experts: [e_lo, e_hi)
     const int slice = (E + (int)gridDim.x - 1) / (int)gridDim.x;
     const int e_lo = blockIdx.x * slice;
@@ -264,9 +270,9 @@ __global__ __launch_bounds__(kScanThreads) void route_scan_kernel(
     const int P = kScanThreads / Ew;                              // block-range parts per expert
     const int el = tid % Ew;
     const int part = tid / Ew;
-    const int per = (nb + P - 1) / P;
+    const int per = (nbg + P - 1) / P;
     const int b_lo = part * per;
-    const int b_hi = (b_lo + per < nb) ? b_lo + per : nb;
+    const int b_hi = (b_lo + per < nbg) ? b_lo + per : nbg;
     double loss_acc = 0.0;
     for (int ebase = e_lo; ebase < e_hi; ebase += Ew) {
         const int e = ebase + el;
@@ -274,6 +280,7 @@ __global__ __launch_bounds__(kScanThreads) void route_scan_kernel(
         int csum = 0;
         float psum = 0.f;
         if (active)
+#pragma unroll 8
             for (int b = b_lo; b < b_hi; ++b) {
                 csum += block_counts[(size_t)b * E + e];
                 psum += block_psum[(size_t)b * E + e];
@@ -281,13 +288,14 @@ __global__ __launch_bounds__(kScanThreads) void route_scan_kernel(
         part_cnt[tid] = csum;
         part_ps[tid] = psum;
         __syncthreads();
-        int start = 0;
         if (active) {
-            for (int q = 0; q < part; ++q) start += part_cnt[q * Ew + el];
-            int run = start;
+            int run = 0;
+            for (int q = 0; q < part; ++q) run += part_cnt[q * Ew + el];
+#pragma unroll 8
             for (int b = b_lo; b < b_hi; ++b) {
+                const int c = block_counts[(size_t)b * E + e];
                 block_off[(size_t)b * E + e] = run;
-                run += block_counts[(size_t)b * E + e];
+                run += c;
             }
         }
         if (part == 0 && e < e_hi) {
@@ -297,15 +305,19 @@ __global__ __launch_bounds__(kScanThreads) void route_scan_kernel(
                 total += part_cnt[q * Ew + el];
                 ptot += part_ps[q * Ew + el];
             }
-            counts_ws[e] = total;
-            counts_g[e] = total;   // one group
-            grp_off[e] = 0;
-            counts_out[e] = total;
-            kept_ws[e] = total < C ? total : C;
-            loss_acc += ((double)total / (double)T) * ((double)ptot / (double)T);
+            counts_g[(size_t)g * E + e] = total;
+            psum_g[(size_t)g * E + e] = ptot;
+            if (one_group) {
+                grp_off[e] = 0;
+                counts_ws[e] = total;
+                counts_out[e] = total;
+                kept_ws[e] = total < C ? total : C;
+                loss_acc += ((double)total / (double)Tg) * ((double)ptot / (double)Tg);
+            }
         }
         __syncthreads();
     }
+    if (!one_group) return;
     red[tid] = loss_acc;
     __syncthreads();
     for (int s = kScanThreads / 2; s >= 1; s >>= 1) {
@@ -315,43 +327,24 @@ __global__ __launch_bounds__(kScanThreads) void route_scan_kernel(
     if (tid == 0) loss_part[blockIdx.x] = red[0];
 }
 
-// -----------------------------------------------------------------------------
-// The same for several routing groups (single block).  Phase 1, one thread per (group,
-// expert) pair: exclusive scan of the group's blocks, counts_g and P-sums.  Phase 2, one
-// thread per expert: slots of the groups inside the expert's buffer (grp_off), totals, and the
-// expert's share of   aux = (1/n) sum_g alpha E sum_e (counts_g / Tg) (psum_g / Tg).
-// -----------------------------------------------------------------------------
-__global__ __launch_bounds__(kScanThreads) void route_scan_groups_kernel(
-    const int32_t *__restrict__ block_counts, const float *__restrict__ block_psum,
-    int32_t *__restrict__ block_off, int32_t *__restrict__ counts_ws, int32_t *__restrict__ kept_ws,
-    int32_t *__restrict__ counts_g, float *__restrict__ psum_g, int32_t *__restrict__ grp_off,
-    int32_t *__restrict__ counts_out, double *__restrict__ loss_part,
-    uint32_t *__restrict__ slot_off, int slot_off_n, int n, int nbg, int E, int Cg, int Tg) {
-    __shared__ double red[kScanThreads];
+// Several routing groups: per expert, the slots of the groups inside the expert's buffer (grp_off),
+// totals, and the block's share of   sum_g sum_e (counts_g / Tg) (psum_g / Tg).
+__global__ __launch_bounds__(256) void route_groups_kernel(
+    const int32_t *__restrict__ counts_g, const float *__restrict__ psum_g, int32_t *__restrict__ grp_off,
+    int32_t *__restrict__ counts_ws, int32_t *__restrict__ kept_ws, int32_t *__restrict__ counts_out,
+    double *__restrict__ loss_part, int n, int E, int Cg, int Tg) {
+    __shared__ double red[256];
     const int tid = threadIdx.x;
-    for (int i = tid; i < slot_off_n; i += kScanThreads) slot_off[i] = kNoRow;
-    for (int pair = tid; pair < n * E; pair += kScanThreads) {
-        const int g = pair / E, e = pair - g * E;
-        int run = 0;
-        float ps = 0.f;
-        for (int b = g * nbg; b < (g + 1) * nbg; ++b) {
-            block_off[(size_t)b * E + e] = run;
-            run += block_counts[(size_t)b * E + e];
-            ps += block_psum[(size_t)b * E + e];
-        }
-        counts_g[pair] = run;
-        psum_g[pair] = ps;
-    }
-    __syncthreads();   // the block's own global writes are visible to it after the barrier
     double loss_acc = 0.0;
-    for (int e = tid; e < E; e += kScanThreads) {
+    for (int e = blockIdx.x * 256 + tid; e < E; e += gridDim.x * 256) {
         int total = 0, kept = 0;
+#pragma unroll 8
         for (int g = 0; g < n; ++g) {
-            const int c = counts_g[g * E + e];
-            grp_off[g * E + e] = kept;
+            const int c = counts_g[(size_t)g * E + e];
+            grp_off[(size_t)g * E + e] = kept;
             kept += c < Cg ? c : Cg;
             total += c;
-            loss_acc += ((double)c / (double)Tg) * ((double)psum_g[g * E + e] / (double)Tg);
+            loss_acc += ((double)c / (double)Tg) * ((double)psum_g[(size_t)g * E + e] / (double)Tg);
         }
         counts_ws[e] = total;
         counts_out[e] = total;
@@ -359,11 +352,11 @@ __global__ __launch_bounds__(kScanThreads) void route_scan_groups_kernel(
     }
     red[tid] = loss_acc;
     __syncthreads();
-    for (int s = kScanThreads / 2; s >= 1; s >>= 1) {
+    for (int s = 128; s >= 1; s >>= 1) {
         if (tid < s) red[tid] += red[tid + s];
         __syncthreads();
     }
-    if (tid == 0) loss_part[0] = red[0];
+    if (tid == 0) loss_part[blockIdx.x] = red[0];
 }
 
 // -----------------------------------------------------------------------------
@@ -787,32 +780,26 @@ hipError_t launch_router_softmax(const Workspace &w, char *ws, int32_t *expert_i
     return err;
 }
 
-int route_scan_blocks(const Workspace &w) {
-    if (w.n > 1) return 1;
-    return w.E >= 64 ? 8 : 1;
-}
+// blocks of the scan kernel per group, and of the group kernel: at most 8 loss parts
+static int scan_blocks(const Workspace &w) { return w.E >= 64 ? 8 : 1; }
+static int group_blocks(const Workspace &w) { return (int)(w.E >= 2048 ? 8 : ceil_div(w.E, 256)); }
+int route_scan_parts(const Workspace &w) { return w.n == 1 ? scan_blocks(w) : group_blocks(w); }
 
 hipError_t launch_route_scan(const Workspace &w, char *ws, int32_t *expert_counts, hipStream_t s) {
+    if (w.inline_scan) return hipSuccess;
     ProfScope ps("route_scan_aux", s);
-    if (w.n == 1)
-        hipLaunchKernelGGL(route_scan_kernel, dim3((unsigned)route_scan_blocks(w)),
-                           dim3(kScanThreads), 0, s, (const int32_t *)(ws + w.block_counts),
-                           (const float *)(ws + w.block_psum), (int32_t *)(ws + w.block_off),
-                           (int32_t *)(ws + w.counts), (int32_t *)(ws + w.kept),
-                           (int32_t *)(ws + w.counts_g), (int32_t *)(ws + w.grp_off),
-                           expert_counts, (double *)(ws + w.loss_part),
-                           (uint32_t *)(ws + w.slot_off), (int)(w.E * w.C + 128), (int)w.nb,
-                           (int)w.E, (int)w.C, (int)w.T);
-    else
-        hipLaunchKernelGGL(route_scan_groups_kernel, dim3(1), dim3(kScanThreads), 0, s,
-                           (const int32_t *)(ws + w.block_counts),
-                           (const float *)(ws + w.block_psum), (int32_t *)(ws + w.block_off),
-                           (int32_t *)(ws + w.counts), (int32_t *)(ws + w.kept),
-                           (int32_t *)(ws + w.counts_g), (float *)(ws + w.psum_g),
-                           (int32_t *)(ws + w.grp_off), expert_counts,
-                           (double *)(ws + w.loss_part), (uint32_t *)(ws + w.slot_off),
-                           (int)(w.E * w.C + 128), (int)w.n, (int)w.nbg, (int)w.E, (int)w.Cg,
-                           (int)w.Tg);
+    hipLaunchKernelGGL(route_scan_kernel, dim3((unsigned)scan_blocks(w), (unsigned)w.n), dim3(kScanThreads), 0,
+                       s, (const int32_t *)(ws + w.block_counts), (const float *)(ws + w.block_psum),
+                       (int32_t *)(ws + w.block_off), (int32_t *)(ws + w.counts), (int32_t *)(ws + w.kept),
+                       (int32_t *)(ws + w.counts_g), (float *)(ws + w.psum_g), (int32_t *)(ws + w.grp_off),
+                       expert_counts, (double *)(ws + w.loss_part), (uint32_t *)(ws + w.slot_off),
+                       w.fused ? (int)(w.E * w.C + 128) : 0, (int)w.nbg, (int)w.E, (int)w.C, (int)w.Tg);
+    hipError_t err = hipGetLastError();
+    if (err != hipSuccess || w.n == 1) return err;
+    hipLaunchKernelGGL(route_groups_kernel, dim3((unsigned)group_blocks(w)), dim3(256), 0, s,
+                       (const int32_t *)(ws + w.counts_g), (const float *)(ws + w.psum_g),
+                       (int32_t *)(ws + w.grp_off), (int32_t *)(ws + w.counts), (int32_t *)(ws + w.kept),
+                       expert_counts, (double *)(ws + w.loss_part), (int)w.n, (int)w.E, (int)w.Cg, (int)w.Tg);
     return hipGetLastError();
 }
 
@@ -839,7 +826,7 @@ static hipError_t router_bwd_typed(const Workspace &w, float alpha, float d_aux,
                        s, (const float *)(ws + w.probs), (const int32_t *)(ws + w.idx),          \
                        (const float *)(ws + w.dgate), (const int32_t *)(ws + w.counts_g),        \
                        dlogits_out, dl_split, (int)w.T, (int)w.Tg, (int)w.E, aux_scale)
-        if (mfma && w.etiles == 1)
+        if (mfma && w.etiles == 1 && w.E % 2 == 0)
             hipLaunchKernelGGL(router_dlogits_pair_kernel, dim3((unsigned)ceil_div(w.T, 16)), dim3(256),
                                0, s, (const float *)(ws + w.probs), (const int32_t *)(ws + w.idx),
                                (const float *)(ws + w.dgate), (const int32_t *)(ws + w.counts_g),
@@ -851,6 +838,7 @@ static hipError_t router_bwd_typed(const Workspace &w, float alpha, float d_aux,
     }
     if (mfma) {
         const bool jitter = w.noise.jitter;
+        if (w.router_block && (err = launch_router_split_bwd(w, W_r, ws, s)) != hipSuccess) return err;
         if (jitter) {   // the matrix-core kernel writes the bare product: no token has an addend
             hipLaunchKernelGGL(fill_minus_one_kernel, dim3((unsigned)ceil_div(w.T, 256)), dim3(256),
                                0, s, (int32_t *)(ws + w.no_slot), (int)w.T);

@@ -123,7 +123,7 @@ __global__ __launch_bounds__(256) void router_fwd_mfma_kernel(
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
     const int b = blockIdx.x;
     int t0, tend;   // the block's tokens: [t0, tend), inside one routing group
-    block_token_range(b, nbg, Tg, t0, tend);
+    block_token_range(b, nbg, Tg, kRouteTB, t0, tend);
 
     const int e_base = FUSED ? 0 : (int)blockIdx.y * kRmExperts;   // first expert of the tile
     DirectOperand ox, ow;
@@ -333,10 +333,32 @@ __global__ __launch_bounds__(256) void router_fwd_mfma_kernel(
 }
 #undef SW_WAIT_VMCNT
 
+// The backward operand alone (the one-kernel router reads W_r itself): wsplit_b as above.
+__global__ __launch_bounds__(256) void router_split_bwd_kernel(const float *__restrict__ W_r,
+                                                               bf16 *__restrict__ wsplit_b, int d, int E,
+                                                               int total /* tiles * d * 128 */) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= total) return;
+    const int el = i & 127, row = i >> 7;   // row of the [tiles][d] planes
+    const int tile = row / d, k = row - tile * d, e = tile * 128 + el;
+    const float w = e < E ? W_r[(size_t)k * E + e] : 0.f;
+    const bf16 hi = (bf16)w;
+    wsplit_b[(size_t)row * 256 + el] = hi;
+    wsplit_b[(size_t)row * 256 + 128 + el] = (bf16)(w - (float)hi);
+}
+
+hipError_t launch_router_split_bwd(const Workspace &w, const float *W_r, char *ws, hipStream_t s) {
+    ProfScope ps("router_split_weights", s);
+    const int total = (int)(w.etiles * w.d * 128);
+    hipLaunchKernelGGL(router_split_bwd_kernel, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, s, W_r,
+                       (bf16 *)(ws + w.wsplit_b), (int)w.d, (int)w.E, total);
+    return hipGetLastError();
+}
+
 // The backward contractions address all expert tiles' planes of dl and of W_r through one
-// buffer descriptor each.
+// buffer descriptor each; with input jitter they read the planes of x * m that the forward pass left.
 bool router_bwd_mfma_supported(const Workspace &w, int dtype) {
-    return router_fwd_mfma_supported(w, dtype) &&
+    return dtype == SW_BF16 && (w.router_block || router_fwd_mfma_supported(w, dtype)) &&
            (uint64_t)w.etiles * (uint64_t)w.T * 512u < 0x7fffffffu &&
            (uint64_t)w.etiles * (uint64_t)w.d * 512u < 0x7fffffffu;
 }

@@ -711,3 +711,22 @@ def test_fp32_matrix_core_tiles(T, d, f, E, cf, rate, ffn):
     inp = make_inputs(s, _dev())
     errs, gpu, fwd, _ = compare_full(s, inp, d_aux=0.8)
     _report("fp32 tiles %s" % ((T, d, f, E, cf, rate, ffn),), errs)
+
+
+# Router forward in one kernel and the assign kernel: expert tiles of 32 with and without 16-byte
+# weight loads, token blocks of 64 (and 128 from 32768 tokens on) with remainders, block prefix sums
+# inside the assign kernel (up to 128 token blocks) and by the scan kernel, groups that end inside a block
+@pytest.mark.parametrize("dtype,T,d,E,cf,n", [
+    ("bf16", 63, 72, 3, 1.0, 1), ("bf16", 65, 40, 30, 2.0, 1), ("bf16", 129, 136, 33, 1.0, 3),
+    ("bf16", 1000, 776, 60, 1.25, 1), ("bf16", 8192, 64, 126, 1.0, 1), ("bf16", 8193, 64, 128, 1.0, 1),
+    ("bf16", 2085, 72, 132, 1.0, 5), ("bf16", 700, 200, 256, 1.5, 1), ("bf16", 32768, 16, 31, 1.0, 8),
+    ("bf16", 32779, 40, 64, 1.0, 1), ("bf16", 33001, 16, 100, 0.8, 1), ("bf16", 34000, 8, 250, 1.0, 2),
+    ("f32", 66, 20, 5, 1.0, 1), ("f32", 1030, 132, 36, 1.25, 2), ("f32", 9000, 12, 128, 1.0, 1),
+    ("f32", 500, 68, 201, 2.0, 1),
+])
+def test_router_forward_blocks(dtype, T, d, E, cf, n):
+    from parity import compare_full
+    s = SwitchShape("t", T, d, 24, E, cf, dtype=dtype, seed_index=47, n_groups=n)
+    inp = make_inputs(s, _dev())
+    errs, gpu, fwd, _ = compare_full(s, inp, d_aux=1.2)
+    _report("router blocks %s" % ((dtype, T, d, E, cf, n),), errs)
