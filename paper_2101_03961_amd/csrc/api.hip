@@ -63,7 +63,6 @@ Workspace layout_workspace(const switch_config *cfg) {
     w.nbg_r = ceil_div(w.Tg, kRouteTB);
     w.nb_r = w.n * w.nbg_r;
     w.elt = cfg->act_dtype == SW_BF16 ? 2 : 4;
-    w.nsplit = w.nb_r < 64 ? w.nb_r : 64;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     const size_t T = w.T, E = w.E, C = w.C, d = w.d, f = w.f, f1 = w.f1, nb = w.nb;
@@ -100,9 +99,6 @@ Workspace layout_workspace(const switch_config *cfg) {
     w.dH = take(E * C * f1 * w.elt);
     w.dXd = take(E * C * d * w.elt);
     w.dgate = take(T * 4);
-    w.dlogits = take(T * E * 4);
-    w.dWr_part = take((size_t)w.nsplit * d * E * 4);
-    w.dbr_part = take((size_t)ceil_div(w.T, kRouteTB) * E * 4);
     w.dpad = ceil_div(w.d, 32) * 32;
     // noise parameters first: the router's layout depends on the jitter
     Noise &nz = w.noise;
@@ -118,11 +114,25 @@ Workspace layout_workspace(const switch_config *cfg) {
     const bool jit_mfma = nz.jitter && cfg->act_dtype == SW_BF16;
     w.dpad_r = jit_mfma ? 3 * w.dpad : w.dpad;
     w.etiles = ceil_div(w.E, 128);
-    w.wsplit = take((size_t)w.etiles * 3 * 128 * w.dpad_r * 2);
-    w.wsplit_b = take((size_t)w.etiles * d * 256 * 2);
-    w.dl_split = take((size_t)w.etiles * T * 256 * 2);
+    const bool mfma = router_bwd_mfma_supported(w, cfg->act_dtype);
+    // (bf16 beyond 128 experts: the one kernel holds too much in registers for two blocks per CU,
+    // 222 us against 46 + 145 for the two it replaces; 65536 x 768, 256 experts)
+    w.router_bwd_block = cfg->act_dtype == SW_F32 ? w.E <= 256 : mfma && w.E <= 128;
+    w.wsplit = take(w.router_block ? 0 : (size_t)w.etiles * 3 * 128 * w.dpad_r * 2);
+    w.wsplit_b = take(mfma && !w.router_bwd_block ? (size_t)w.etiles * d * 256 * 2 : 0);
+    w.dl_split = take(mfma ? (size_t)w.etiles * T * 256 * 2 : 0);
+    w.dlogits = take(w.router_bwd_block && mfma ? 0 : T * E * 4);
+    // Vector-ALU dW_r: a split of 64 tokens is two short chains of loads; the parts lie in the
+    // gradient of the expert outputs, which the second weight gradient has read by then.
+    w.nsplit = w.T < 64 * 64 ? ceil_div(w.T, 64) : 64;
+    w.dWr_part = w.dO;
+    if ((size_t)w.nsplit * 4 > C * w.elt) {
+        if (w.nsplit > w.nb_r) w.nsplit = w.nb_r;
+        w.dWr_part = take(mfma ? 0 : (size_t)w.nsplit * d * E * 4);
+    }
+    w.dbr_part = take((size_t)ceil_div(w.T, 128) * E * 4);
     w.xj = take(jit_mfma ? T * (size_t)w.dpad_r * 2 : 0);
-    w.no_slot = take(jit_mfma ? T * 4 : 0);
+    w.no_slot = take(jit_mfma && !w.router_bwd_block ? T * 4 : 0);
     w.tps_m = ceil_div(ceil_div(w.T, 85), 64) * 64;
     if (w.tps_m < 64) w.tps_m = 64;   // empty batch
     w.nsplit_m = ceil_div(w.T, w.tps_m);

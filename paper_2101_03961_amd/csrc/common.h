@@ -144,9 +144,10 @@ struct Workspace {
     size_t dH;                  // act [E][C][f1]  gradient of Xd W_in
     size_t dXd;                 // act [E][C][d]
     size_t dgate;               // f32 [T]
-    size_t dlogits;             // f32 [T][E]
+    bool router_bwd_block;      // router_bwd.hip computes dlogits and dx
+    size_t dlogits;             // f32 [T][E]   (only where a kernel reads them)
     size_t dWr_part;            // f32 [nsplit][d][E]  split-T partial sums of dW_r
-    size_t dbr_part;            // f32 [ceil(T / 256)][E]  per-256-token sums of dlogits
+    size_t dbr_part;            // f32 [ceil(T / 128)][E]  per-block sums of dlogits
     int64_t etiles;             // tiles of 128 experts: ceil(E / 128)
     size_t wsplit;              // bf16 [etiles][3][128][dpad_r]  W_r^T as three bf16 terms (MFMA router)
     int64_t dpad;               // d rounded up to a multiple of 32
@@ -249,7 +250,10 @@ hipError_t launch_combine_bwd(const Workspace &w, int dtype, const void *dy, cha
 hipError_t launch_router_bwd(const Workspace &w, int dtype, float alpha, float d_aux,
                              const void *x, const float *W_r, char *ws, void *dx, float *dW_r,
                              float *db_r, hipStream_t s);
-// MFMA pieces of the router backward (bf16, E <= 128), in gemm_bf16.hip
+// dlogits and dx in one kernel (router_bwd.hip); bias: also the per-block sums for db_r
+hipError_t launch_router_dx_block(const Workspace &w, int dtype, float aux_scale, const float *W_r, char *ws,
+                                  void *dx, bool bias, hipStream_t s);
+// MFMA pieces of the router backward (bf16), in gemm_bf16.hip
 hipError_t launch_router_split_bwd(const Workspace &w, const float *W_r, char *ws, hipStream_t s);
 hipError_t launch_router_dx_mfma(const Workspace &w, char *ws, void *dx, hipStream_t s);
 hipError_t launch_router_dWr_mfma(const Workspace &w, const void *x, char *ws, hipStream_t s);

@@ -429,53 +429,28 @@ __global__ __launch_bounds__(256) void router_dlogits_kernel(
     }
 }
 
-// The same for the matrix-core backward (E <= 128, E % 4 == 0): a lane owns the two adjacent
-// experts 2 lane and 2 lane + 1, so a wave reads a probability row with one 8-byte load per
-// lane and writes the bf16 hi | lo halves as 4-byte pairs; four tokens per wave at once.
-__global__ __launch_bounds__(256) void router_dlogits_pair_kernel(
-    const float *__restrict__ probs, const int32_t *__restrict__ idx,
-    const float *__restrict__ dgate, const int32_t *__restrict__ counts_g /* [n][E] */,
-    float *__restrict__ dlogits /* [T][E] or nullptr */, bf16 *__restrict__ dl_split /* [T][256] */,
-    int T, int Tg, int E, float aux_scale) {
-    typedef bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    constexpr int kTok = 4;
-    const float mean_count = (float)Tg / (float)E;
-    const int lane = threadIdx.x % kWave;
-    const int t_first = (blockIdx.x * (256 / kWave) + threadIdx.x / kWave) * kTok;
-    const int e0 = 2 * lane;
-    const bool live = e0 < E;   // E is even: both experts of the lane or neither
-    float2 p[kTok], dp[kTok];
-    float s[kTok];
-#pragma unroll
-    for (int u = 0; u < kTok; ++u) {
-        const int t = t_first + u;
-        s[u] = 0.f;
-        p[u] = dp[u] = make_float2(0.f, 0.f);
-        if (t >= T || !live) continue;
-        const int me = idx[t];
-        const float dg = dgate[t];
-        const int2 c = *(const int2 *)(counts_g + (size_t)(t / Tg) * E + e0);
-        p[u] = *(const float2 *)(probs + (size_t)t * E + e0);
-        dp[u].x = aux_scale * ((float)c.x - mean_count) + (me == e0 ? dg : 0.f);
-        dp[u].y = aux_scale * ((float)c.y - mean_count) + (me == e0 + 1 ? dg : 0.f);
-        s[u] = p[u].x * dp[u].x + p[u].y * dp[u].y;
+// db_r[e] = sum over parts of part[q][e], in blocks behind those of a dW_r reduction: kDbrExperts
+// experts per block, eight interleaved chains per expert, added in order.
+constexpr int kDbrExperts = 32;
+struct DbrArgs {
+    const float *part;   // [nparts][E]
+    float *out;          // nullptr: no bias
+    int E, nparts;
+};
+__device__ static void reduce_dbr(const DbrArgs &a, int block) {
+    __shared__ float sums[8][kDbrExperts];
+    const int j = threadIdx.x % kDbrExperts, chain = threadIdx.x / kDbrExperts;
+    const int e = block * kDbrExperts + j;
+    float s = 0.f;
+    if (e < a.E) {
+#pragma unroll 8
+        for (int q = chain; q < a.nparts; q += 8) s += a.part[(size_t)q * a.E + e];
     }
-#pragma unroll
-    for (int u = 0; u < kTok; ++u) s[u] = wave_sum(s[u]);
-#pragma unroll
-    for (int u = 0; u < kTok; ++u) {
-        const int t = t_first + u;
-        if (t >= T) continue;
-        const float2 dl = make_float2(p[u].x * (dp[u].x - s[u]), p[u].y * (dp[u].y - s[u]));   // 0 past E
-        if (dlogits && live) *(float2 *)(dlogits + (size_t)t * E + e0) = dl;
-        bf16x2 hi, lo;
-        hi[0] = (bf16)dl.x;
-        hi[1] = (bf16)dl.y;
-        lo[0] = (bf16)(dl.x - (float)hi[0]);
-        lo[1] = (bf16)(dl.y - (float)hi[1]);
-        *(bf16x2 *)(dl_split + (size_t)t * 256 + e0) = hi;        // all 128 columns of each half
-        *(bf16x2 *)(dl_split + (size_t)t * 256 + 128 + e0) = lo;
-    }
+    sums[chain][j] = s;
+    __syncthreads();
+    if (chain != 0 || e >= a.E) return;
+    for (int c = 1; c < 8; ++c) s += sums[c][j];
+    a.out[e] = s;
 }
 
 // dW_r[k][j] = sum over splits of (part[s][k][j] + part[s][k][128 + j]), fixed order.
@@ -484,7 +459,9 @@ __global__ __launch_bounds__(256) void router_dlogits_pair_kernel(
 __global__ __launch_bounds__(256) void reduce_dWr_split_kernel(const float *__restrict__ part,
                                                                float *__restrict__ dW_r, int d,
                                                                int E, int nsplit, int rows,
-                                                               int second) {
+                                                               int second, DbrArgs db) {
+    const int blocks = (d * E + 255) / 256;
+    if ((int)blockIdx.x >= blocks) return reduce_dbr(db, (int)blockIdx.x - blocks);
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= d * E) return;
     const int k = i / E, j = i - k * E;
@@ -714,7 +691,9 @@ __global__ __launch_bounds__(256) void router_dbr_kernel(const float *__restrict
 
 __global__ __launch_bounds__(256) void reduce_partials_kernel(const float *__restrict__ part,
                                                               float *__restrict__ out, size_t n,
-                                                              int nsplit) {
+                                                              int nsplit, DbrArgs db) {
+    const size_t blocks = (n + 255) / 256;
+    if (blockIdx.x >= blocks) return reduce_dbr(db, (int)(blockIdx.x - blocks));
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     float s = 0.f;
@@ -809,35 +788,34 @@ static hipError_t router_bwd_typed(const Workspace &w, float alpha, float d_aux,
                                    hipStream_t s) {
     hipError_t err = hipSuccess;
     float *dlogits = (float *)(ws + w.dlogits);
-    // bf16 tokens and up to 128 experts: the two contractions run on the matrix cores
+    // bf16 tokens: the two contractions run on the matrix cores
     // (dl and W_r as two bf16 terms each; x is bf16 already)
     // (the forward pass took the same path and left W_r's bf16 terms in the workspace)
     const bool mfma = router_bwd_mfma_supported(w, sizeof(XT) == 2 ? SW_BF16 : SW_F32);
     bf16 *dl_split = mfma ? (bf16 *)(ws + w.dl_split) : nullptr;
     // the fp32 copy is read only by the vector-ALU contractions and by the bias gradient
     float *dlogits_out = (mfma && !db_r) ? nullptr : dlogits;
-    {
+    const float aux_scale =
+        (float)((double)d_aux * (double)alpha * (double)w.E / ((double)w.n * (double)w.Tg * (double)w.Tg));
+    if (w.router_bwd_block) {
+        err = launch_router_dx_block(w, sizeof(XT) == 2 ? SW_BF16 : SW_F32, aux_scale, W_r, ws, dx, db_r != nullptr, s);
+        if (err != hipSuccess) return err;
+    } else {
         ProfScope ps("router_dlogits", s);
-        const float aux_scale = (float)((double)d_aux * (double)alpha * (double)w.E /
-                                        ((double)w.n * (double)w.Tg * (double)w.Tg));
 #define CALL(N)                                                                                  \
     hipLaunchKernelGGL(router_dlogits_kernel<N>,                                                  \
                        dim3((unsigned)ceil_div(w.T, 4 * dl_tokens(N))), dim3(256), 0,             \
                        s, (const float *)(ws + w.probs), (const int32_t *)(ws + w.idx),          \
                        (const float *)(ws + w.dgate), (const int32_t *)(ws + w.counts_g),        \
                        dlogits_out, dl_split, (int)w.T, (int)w.Tg, (int)w.E, aux_scale)
-        if (mfma && w.etiles == 1 && w.E % 2 == 0)
-            hipLaunchKernelGGL(router_dlogits_pair_kernel, dim3((unsigned)ceil_div(w.T, 16)), dim3(256),
-                               0, s, (const float *)(ws + w.probs), (const int32_t *)(ws + w.idx),
-                               (const float *)(ws + w.dgate), (const int32_t *)(ws + w.counts_g),
-                               dlogits_out, dl_split, (int)w.T, (int)w.Tg, (int)w.E, aux_scale);
-        else
-            SW_DISPATCH_EPL(w.E, CALL);
+        SW_DISPATCH_EPL(w.E, CALL);
 #undef CALL
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
-    if (mfma) {
-        const bool jitter = w.noise.jitter;
+    const bool jitter = w.noise.jitter;
+    if (w.router_bwd_block) {
+        // dx is there
+    } else if (mfma) {
         if (w.router_block && (err = launch_router_split_bwd(w, W_r, ws, s)) != hipSuccess) return err;
         if (jitter) {   // the matrix-core kernel writes the bare product: no token has an addend
             hipLaunchKernelGGL(fill_minus_one_kernel, dim3((unsigned)ceil_div(w.T, 256)), dim3(256),
@@ -853,13 +831,6 @@ static hipError_t router_bwd_typed(const Workspace &w, float alpha, float d_aux,
                                (const int32_t *)(ws + w.tok_slot), (int)w.T, (int)w.d, w.noise);
             if ((err = hipGetLastError()) != hipSuccess) return err;
         }
-        if ((err = launch_router_dWr_mfma(w, x, ws, s)) != hipSuccess) return err;
-        ProfScope ps("router_dWr_reduce", s);
-        hipLaunchKernelGGL(reduce_dWr_split_kernel, dim3((unsigned)ceil_div(w.d * w.E, 256)),
-                           dim3(256), 0, s, (const float *)(ws + w.dWr_part_m), dW_r, (int)w.d,
-                           (int)w.E, (int)w.nsplit_m, jitter ? 2 * (int)w.dpad : (int)w.d,
-                           jitter ? (int)w.dpad : 0);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
     } else {
         ProfScope ps("router_dx", s);
         dim3 grid((unsigned)ceil_div(w.T, kLogTB), (unsigned)ceil_div(w.d, kLogEB));
@@ -868,31 +839,34 @@ static hipError_t router_bwd_typed(const Workspace &w, float alpha, float d_aux,
                            (int)w.T, (int)w.d, (int)w.E, w.noise);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }
-    const int tokens_per_split = (int)ceil_div(w.T, w.nsplit);
-    if (!mfma) {
-        ProfScope ps("router_dWr", s);
-        dim3 grid((unsigned)ceil_div(w.d, kWrTile), (unsigned)ceil_div(w.E, kWrTile),
-                  (unsigned)w.nsplit);
-        hipLaunchKernelGGL(router_dWr_kernel<XT>, grid, dim3(256), 0, s, x, dlogits,
-                           (float *)(ws + w.dWr_part), (int)w.T, (int)w.d, (int)w.E,
-                           tokens_per_split, w.noise);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
-        const size_t n = (size_t)w.d * w.E;
-        hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0,
-                           s, (const float *)(ws + w.dWr_part), dW_r, n, (int)w.nsplit);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
-    }
-    if (db_r) {
+    // the reductions of dW_r's parts also add up db_r's, in blocks of their own
+    const DbrArgs db{(const float *)(ws + w.dbr_part), db_r, (int)w.E, (int)ceil_div(w.T, w.router_bwd_block ? 128 : 256)};
+    const unsigned db_blocks = db_r ? (unsigned)ceil_div(w.E, kDbrExperts) : 0;
+    if (db_r && !w.router_bwd_block) {
         ProfScope ps("router_dbr", s);
-        const int nblk = (int)ceil_div(w.T, 256);
-        hipLaunchKernelGGL(router_dbr_kernel, dim3((unsigned)nblk), dim3(256), 0, s, dlogits,
+        hipLaunchKernelGGL(router_dbr_kernel, dim3((unsigned)db.nparts), dim3(256), 0, s, dlogits,
                            (float *)(ws + w.dbr_part), (int)w.T, (int)w.E);
         if ((err = hipGetLastError()) != hipSuccess) return err;
-        hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)ceil_div(w.E, 256)), dim3(256),
-                           0, s, (const float *)(ws + w.dbr_part), db_r, (size_t)w.E, nblk);
-        if ((err = hipGetLastError()) != hipSuccess) return err;
     }
-    return err;
+    if (mfma) {
+        if ((err = launch_router_dWr_mfma(w, x, ws, s)) != hipSuccess) return err;
+        ProfScope ps("router_dWr_reduce", s);
+        hipLaunchKernelGGL(reduce_dWr_split_kernel, dim3((unsigned)ceil_div(w.d * w.E, 256) + db_blocks),
+                           dim3(256), 0, s, (const float *)(ws + w.dWr_part_m), dW_r, (int)w.d,
+                           (int)w.E, (int)w.nsplit_m, jitter ? 2 * (int)w.dpad : (int)w.d,
+                           jitter ? (int)w.dpad : 0, db);
+        return hipGetLastError();
+    }
+    ProfScope ps("router_dWr", s);
+    const int tokens_per_split = (int)ceil_div(w.T, w.nsplit);
+    dim3 grid((unsigned)ceil_div(w.d, kWrTile), (unsigned)ceil_div(w.E, kWrTile), (unsigned)w.nsplit);
+    hipLaunchKernelGGL(router_dWr_kernel<XT>, grid, dim3(256), 0, s, x, dlogits, (float *)(ws + w.dWr_part),
+                       (int)w.T, (int)w.d, (int)w.E, tokens_per_split, w.noise);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+    const size_t n = (size_t)w.d * w.E;
+    hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)ceil_div(n, 256) + db_blocks), dim3(256), 0, s,
+                       (const float *)(ws + w.dWr_part), dW_r, n, (int)w.nsplit, db);
+    return hipGetLastError();
 }
 
 hipError_t launch_router_bwd(const Workspace &w, int dtype, float alpha, float d_aux,

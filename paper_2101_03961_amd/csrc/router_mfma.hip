@@ -40,7 +40,7 @@ constexpr int kRmLds = kRmTileBytes + kRmTokens * 4 + 4 * kRmExperts * 4;
 // with p + s <= 2, whose omitted rest is below 2^-24 of the leading one.
 __global__ __launch_bounds__(256) void router_split_kernel(const float *__restrict__ W_r,
                                                            bf16 *__restrict__ wsplit,
-                                                           bf16 *__restrict__ wsplit_b, int d,
+                                                           bf16 *__restrict__ wsplit_b /* or nullptr */, int d,
                                                            int dpad, int E, int planes) {
     const int k = blockIdx.x * 256 + threadIdx.x;
     const int e = blockIdx.y;                 // 0 .. 128 * expert tiles
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256) void router_split_kernel(const float *__restri
         wt[term + at] = p <= 1 ? mid : zero;
         wt[2 * term + at] = p == 0 ? lo : zero;
     }
-    if (k < d) {   // the backward operand: one [d][hi 128 | lo 128] plane per expert tile
+    if (wsplit_b && k < d) {   // the backward operand: one [d][hi 128 | lo 128] plane per expert tile
         bf16 *row = wsplit_b + ((size_t)tile * d + k) * 256 + el;
         row[0] = hi;
         row[128] = mid;
@@ -387,7 +387,7 @@ hipError_t launch_router_fwd_mfma(const Workspace &w, const void *x, const float
         ProfScope ps("router_split_weights", s);
         dim3 grid((unsigned)ceil_div(w.dpad, 256), (unsigned)(kRmExperts * w.etiles));
         hipLaunchKernelGGL(router_split_kernel, grid, dim3(256), 0, s, W_r, (bf16 *)(ws + w.wsplit),
-                           (bf16 *)(ws + w.wsplit_b), (int)w.d, (int)w.dpad, (int)w.E,
+                           w.router_bwd_block ? nullptr : (bf16 *)(ws + w.wsplit_b), (int)w.d, (int)w.dpad, (int)w.E,
                            jitter ? 3 : 1);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }

@@ -730,3 +730,23 @@ def test_router_forward_blocks(dtype, T, d, E, cf, n):
     inp = make_inputs(s, _dev())
     errs, gpu, fwd, _ = compare_full(s, inp, d_aux=1.2)
     _report("router blocks %s" % ((dtype, T, d, E, cf, n),), errs)
+
+
+# Router backward in one kernel: expert counts with and without 16-byte rows at each fragment count
+# (32, 64, 128; fp32 also 256), token remainders of the 128-token blocks, column groups of 64 with
+# remainders in one or several blocks, groups that end inside a block, bias sums, jitter on bf16 tokens
+@pytest.mark.parametrize("dtype,T,d,E,cf,n,jit,bias", [
+    ("bf16", 31, 8, 2, 1.0, 1, 0.0, True), ("bf16", 129, 72, 32, 1.0, 1, 0.0, True),
+    ("bf16", 390, 136, 33, 1.0, 3, 0.0, True), ("bf16", 3000, 1032, 63, 1.25, 1, 0.0, False),
+    ("bf16", 1025, 200, 128, 1.5, 1, 0.0, True), ("bf16", 2050, 328, 100, 1.0, 2, 0.05, True),
+    ("f32", 1, 4, 3, 3.0, 1, 0.0, True), ("f32", 257, 132, 32, 1.0, 1, 0.1, True),
+    ("f32", 640, 68, 62, 1.0, 5, 0.0, False), ("f32", 1000, 36, 256, 1.0, 1, 0.0, True),
+    ("f32", 129, 100, 131, 2.0, 1, 0.0, True),
+])
+def test_router_backward_blocks(dtype, T, d, E, cf, n, jit, bias):
+    from parity import compare_full
+    s = SwitchShape("t", T, d, 24, E, cf, dtype=dtype, seed_index=48, n_groups=n, jitter_eps=jit, noise_seed=4,
+                    zipf_bias=bias)
+    inp = make_inputs(s, _dev())
+    errs, gpu, fwd, _ = compare_full(s, inp, d_aux=1.3)
+    _report("router backward %s" % ((dtype, T, d, E, cf, n, jit, bias),), errs)
