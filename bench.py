@@ -57,20 +57,28 @@ def kernel_work(shape, kept, elt):
     jit = shape.jitter_eps > 0
     zero_with_positions = (shape.dtype == "bf16" and shape.fused_dispatch and
                            shape.ntlb_rounds == 0)
+    gathers = not (shape.dtype == "bf16" and shape.fused_dispatch) and shape.ntlb_rounds == 0
+    # one kernel for dl and dx (bf16: up to 128 experts), which leaves dl for dW_r
+    bf16_block = shape.dtype == "bf16" and E <= 128
     dpad = -(-d // 32) * 32
     x_router = T * 3 * dpad * 2 if jit else T * d * elt     # bytes of the router's input operand
     return {**{
         "router_jitter_split": (0.0, T * d * elt + T * 3 * dpad * 2, "hbm"),
         "router_dx_jitter": (0.0, 2.0 * T * d * elt + kept * d * elt + T * 4, "hbm"),
         "router_split_weights": (0.0, d * E * 4 + 3 * 128 * d * 2 + d * 512, "hbm"),
+        # one kernel up to 256 experts (bf16: three bf16 terms per weight)
+        "router_fwd": ((6.0 if elt == 2 else 2.0) * T * d * E,
+                       T * d * elt + d * E * 4 + T * E * 4 + T * 12, "hbm"),
         "router_fwd_mfma": (6.0 * T * d * E, x_router + T * E * 4 + T * 12, "hbm"),
         "router_logits": (2.0 * T * d * E, T * d * elt + T * E * 4 + d * E * 4, "hbm"),
         "router_softmax_top1": (0.0, 2.0 * T * E * 4 + T * 8, "hbm"),
         "route_scan_aux": (0.0, 3.0 * (T / 256.0) * E * 4, "hbm"),
-        # (with dispatch / combine inside the GEMMs and no re-routing stages it also clears the
-        # rows of y of the tokens without a slot)
-        "positions": (0.0, T * (4 + 4 + 4 + 4 + 1 + 4 + 1) +
-                      ((T - kept) * d * elt if zero_with_positions else 0), "hbm"),
+        # positions, slot tables and, unless re-routing stages come first or the GEMMs gather, the
+        # dispatch (with dispatch / combine inside the GEMMs and no re-routing stages it also
+        # clears the rows of y of the tokens without a slot)
+        "assign_gather": (0.0, T * (4 + 4 + 4 + 4 + 1 + 4 + 1) +
+                          ((T - kept) * d * elt if zero_with_positions else 0) +
+                          (2.0 * kept * d * elt if gathers else 0), "hbm"),
         "dispatch_gather": (0.0, 2.0 * kept * d * elt, "hbm"),
         # dispatch / combine inside the GEMMs: what is left of the two passes
         "zero_dropped": (0.0, T * 4.0 + (T - kept) * d * elt, "hbm"),
@@ -87,7 +95,9 @@ def kernel_work(shape, kept, elt):
         "router_dx_mfma": (6.0 * T * d * E, T * 512 + kept * d * elt + T * d * elt, "hbm"),
         "router_dWr_mfma": (4.0 * T * d * E, (T * 2 * dpad * 2 if jit else T * d * elt) + T * 512, "hbm"),
         "router_dWr_reduce": (0.0, -(-T // (-(-(-(-T // 85)) // 64) * 64)) * d * 256 * 4.0 + d * E * 4.0, "hbm"),
-        "router_dx": (2.0 * T * d * E, T * E * 4 + kept * d * elt + T * d * elt, "hbm"),
+        "router_dx": ((6.0 if bf16_block else 2.0) * T * d * E,
+                      T * E * 4 + T * (512 if bf16_block else 4 * E) + kept * d * elt + T * d * elt,
+                      "hbm"),
         "router_dWr": (2.0 * T * d * E, T * d * elt + T * E * 4, "hbm"),
         "router_dbr": (0.0, T * E * 4.0, "hbm"),
         # per stage: the logits rows of the waiting tokens are not known in advance; priced
