@@ -98,6 +98,18 @@ Workspace layout_workspace(const switch_config *cfg) {
     w.dA = take(w.geglu ? E * C * f * w.elt : 0);
     w.dH = take(E * C * f1 * w.elt);
     w.dXd = take(E * C * d * w.elt);
+    // What only the router's backward pass writes, after the last kernel that reads dH: in dH's
+    // memory while it fits.  (Tiles other than 256 x 256 may pad the ReLU bits further; this more
+    // than makes up for it, so the static scratch takes every configuration that it took with
+    // 256 x 256 tiles alone.)
+    size_t dead = 0;
+    const size_t dead_room = E * C * f1 * w.elt;
+    auto take_dead = [&](size_t bytes) {
+        if (dead + bytes > dead_room) return take(bytes);
+        const size_t o = w.dH + dead;
+        dead = align_up(dead + bytes, 256);
+        return o;
+    };
     w.dgate = take(T * 4);
     w.dpad = ceil_div(w.d, 32) * 32;
     // noise parameters first: the router's layout depends on the jitter
@@ -120,8 +132,8 @@ Workspace layout_workspace(const switch_config *cfg) {
     w.router_bwd_block = cfg->act_dtype == SW_F32 ? w.E <= 256 : mfma && w.E <= 128;
     w.wsplit = take(w.router_block ? 0 : (size_t)w.etiles * 3 * 128 * w.dpad_r * 2);
     w.wsplit_b = take(mfma && !w.router_bwd_block ? (size_t)w.etiles * d * 256 * 2 : 0);
-    w.dl_split = take(mfma ? (size_t)w.etiles * T * 256 * 2 : 0);
-    w.dlogits = take(w.router_bwd_block && mfma ? 0 : T * E * 4);
+    w.dl_split = take_dead(mfma ? (size_t)w.etiles * T * 256 * 2 : 0);
+    w.dlogits = take_dead(w.router_bwd_block && mfma ? 0 : T * E * 4);
     // Vector-ALU dW_r: a split of 64 tokens is two short chains of loads; the parts lie in the
     // gradient of the expert outputs, which the second weight gradient has read by then.
     w.nsplit = w.T < 64 * 64 ? ceil_div(w.T, 64) : 64;
@@ -130,13 +142,13 @@ Workspace layout_workspace(const switch_config *cfg) {
         if (w.nsplit > w.nb_r) w.nsplit = w.nb_r;
         w.dWr_part = take(mfma ? 0 : (size_t)w.nsplit * d * E * 4);
     }
-    w.dbr_part = take((size_t)ceil_div(w.T, 128) * E * 4);
+    w.dbr_part = take_dead((size_t)ceil_div(w.T, 128) * E * 4);
     w.xj = take(jit_mfma ? T * (size_t)w.dpad_r * 2 : 0);
     w.no_slot = take(jit_mfma && !w.router_bwd_block ? T * 4 : 0);
     w.tps_m = ceil_div(ceil_div(w.T, 85), 64) * 64;
     if (w.tps_m < 64) w.tps_m = 64;   // empty batch
     w.nsplit_m = ceil_div(w.T, w.tps_m);
-    w.dWr_part_m = take((size_t)w.etiles * w.nsplit_m * (jit_mfma ? 2 * (size_t)w.dpad : d) * 256 * 4);
+    w.dWr_part_m = take_dead((size_t)w.etiles * w.nsplit_m * (jit_mfma ? 2 * (size_t)w.dpad : d) * 256 * 4);
     size_t bits = 0;
     for (int &t : w.gemm_tile) t = ROWS_NONE;
     if (cfg->act_dtype == SW_BF16) {

@@ -134,6 +134,16 @@ def test_static_scratch_variant_refuses_what_does_not_fit():
     assert "static scratch" in sw.switch_status_string(-9)
 
 
+# Just below the static limit with the ReLU bits laid out for 256 x 256 tiles; a taller or wider tile
+# pads the bits further, which the workspace makes up for elsewhere.
+@pytest.mark.parametrize("T,d,f,E,cf,jitter", [
+    (335, 200, 9712, 57, 1.0, 0.01), (414, 264, 8168, 54, 1.0, 0.01), (327, 152, 10480, 55, 1.0, 0.01),
+    (236, 168, 7792, 64, 2.0, 0.01), (419, 176, 7384, 60, 1.25, 0.01)])
+def test_static_scratch_variant_keeps_what_fits(T, d, f, E, cf, jitter):
+    cfg = sw.SwitchConfig(T, d, f, E, cf, 0.01, sw.SW_BF16, 0, 1, 0.0, jitter, 1, 0, 0)
+    assert sw.switch_workspace_size(cfg) <= sw.SW_STATIC_SCRATCH_BYTES
+
+
 def test_status_strings():
     assert sw.switch_status_string(0) == "ok"
     seen = {sw.switch_status_string(s) for s in range(-9, 1)}
