@@ -131,7 +131,8 @@ Workspace layout_workspace(const switch_config *cfg) {
     // 222 us against 46 + 145 for the two it replaces; 65536 x 768, 256 experts)
     w.router_bwd_block = cfg->act_dtype == SW_F32 ? w.E <= 256 : mfma && w.E <= 128;
     w.wsplit = take(w.router_block ? 0 : (size_t)w.etiles * 3 * 128 * w.dpad_r * 2);
-    w.wsplit_b = take(mfma && !w.router_bwd_block ? (size_t)w.etiles * d * 256 * 2 : 0);
+    w.has_wsplit_b = mfma && !w.router_bwd_block;
+    w.wsplit_b = take(w.has_wsplit_b ? (size_t)w.etiles * d * 256 * 2 : 0);
     w.dl_split = take_dead(mfma ? (size_t)w.etiles * T * 256 * 2 : 0);
     w.dlogits = take_dead(w.router_bwd_block && mfma ? 0 : T * E * 4);
     // Vector-ALU dW_r: a split of 64 tokens is two short chains of loads; the parts lie in the

@@ -156,6 +156,7 @@ struct Workspace {
     size_t xj;                  // bf16 [T][3 dpad]  x * m as hi | mid | lo planes (jitter + MFMA router)
     size_t no_slot;             // i32 [T]  all -1 (jitter + MFMA router backward)
     size_t wsplit_b;            // bf16 [etiles][d][256]   W_r rows as hi | lo halves (MFMA router backward)
+    bool has_wsplit_b;          // it is laid out: only where the backward pass reads it
     size_t dl_split;            // bf16 [etiles][T][256]   dlogits rows as hi | lo halves
     size_t dWr_part_m;          // f32 [etiles][nsplit_m][d][256]  partial sums of x^T [dl_hi | dl_lo]
                                 //     (with jitter: [nsplit_m][2 dpad][256], hi and mid plane of x * m)

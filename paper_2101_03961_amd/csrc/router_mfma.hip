@@ -387,7 +387,7 @@ hipError_t launch_router_fwd_mfma(const Workspace &w, const void *x, const float
         ProfScope ps("router_split_weights", s);
         dim3 grid((unsigned)ceil_div(w.dpad, 256), (unsigned)(kRmExperts * w.etiles));
         hipLaunchKernelGGL(router_split_kernel, grid, dim3(256), 0, s, W_r, (bf16 *)(ws + w.wsplit),
-                           w.router_bwd_block ? nullptr : (bf16 *)(ws + w.wsplit_b), (int)w.d, (int)w.dpad, (int)w.E,
+                           w.has_wsplit_b ? (bf16 *)(ws + w.wsplit_b) : nullptr, (int)w.d, (int)w.dpad, (int)w.E,
                            jitter ? 3 : 1);
         if ((err = hipGetLastError()) != hipSuccess) return err;
     }

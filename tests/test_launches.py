@@ -1,0 +1,61 @@
+"""What the library launches, recorded without a GPU (launch_recorder.c stands in for the HIP
+runtime): routes, grids and buffers of layers that are too large or too odd to run in a test."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+import paper_2101_03961_amd as sw
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+pytestmark = pytest.mark.skipif(shutil.which("gcc") is None, reason="needs gcc")
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("launches") / "launch_recorder")
+    subprocess.run(["gcc", "-O1", "-Wall", "-Werror", "-rdynamic", "-I", os.path.join(ROOT, "include"), "-o", exe,
+                    os.path.join(ROOT, "tests", "launch_recorder.c"), "-ldl"], check=True)
+
+    def record(*calls):
+        """[(status, workspace address, bytes, [(kernel, grid, block, lds, args)])] of the calls."""
+        lines = "".join(" ".join(str(v) for v in c) + "\n" for c in calls)
+        run = subprocess.run([exe, sw.library_path()], input=lines, capture_output=True, text=True, check=True)
+        out, launches = [], []
+        for line in run.stdout.splitlines():
+            word = line.split()
+            if word[0] == "launch":
+                v = [int(t) for t in word[2:]]
+                launches.append((word[1], tuple(v[:3]), tuple(v[3:6]), v[6], v[7:]))
+            elif word[0] == "call":
+                out.append((int(word[1]), int(word[2]), int(word[3]), launches))
+                launches = []
+        assert len(out) == len(calls)
+        return out
+    return record
+
+
+def call(what, T, d, f, E, cf, dtype="bf16", ffn="relu", n=1, dropout=0.0, jitter=0.0, ntlb=0, fused=False, bias=False):
+    return (what, T, d, f, E, cf, 1 if dtype == "bf16" else 0, 1 if ffn == "geglu" else 0, n, dropout, jitter, ntlb,
+            int(fused), int(bias))
+
+
+# The router's weights are split for the forward pass and, where its backward pass reads them, for that:
+# the second buffer is written only if it is there, and lies inside the workspace then.
+@pytest.mark.parametrize("kw,backward_reads", [
+    (dict(T=262144, d=768, f=3072, E=2048, cf=1.0, ffn="geglu"), False),   # more logits than a descriptor spans
+    (dict(T=524288, d=512, f=1536, E=1024, cf=1.0, ffn="geglu"), False),
+    (dict(T=1 << 22, d=64, f=64, E=128, cf=1.0, jitter=0.01), False),
+    (dict(T=8192, d=768, f=3072, E=2048, cf=1.0, ffn="geglu"), True),
+    (dict(T=8192, d=768, f=3072, E=128, cf=1.0, jitter=0.01), False),      # the one-kernel backward reads W_r
+])
+def test_split_router_weights_stay_in_the_workspace(recorder, kw, backward_reads):
+    (status, base, size, launches), = recorder(call("forward", **kw))
+    assert status == 0
+    (_, _, _, _, (_, wsplit, wsplit_b)), = [k for k in launches if "router_split_kernel" in k[0]]
+    assert base <= wsplit < base + size
+    assert (wsplit_b != 0) == backward_reads
+    if wsplit_b:
+        tiles = -(-kw["E"] // 128)
+        assert base <= wsplit_b and wsplit_b + tiles * kw["d"] * 512 <= base + size
