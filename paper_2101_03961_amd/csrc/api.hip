@@ -127,9 +127,11 @@ Workspace layout_workspace(const switch_config *cfg) {
     w.dpad_r = jit_mfma ? 3 * w.dpad : w.dpad;
     w.etiles = ceil_div(w.E, 128);
     const bool mfma = router_bwd_mfma_supported(w, cfg->act_dtype);
-    // (bf16 beyond 128 experts: the one kernel holds too much in registers for two blocks per CU,
-    // 222 us against 46 + 145 for the two it replaces; 65536 x 768, 256 experts)
-    w.router_bwd_block = cfg->act_dtype == SW_F32 ? w.E <= 256 : mfma && w.E <= 128;
+    // With fp32 products (fp32 tokens, or an expert count that is no multiple of 4) the one kernel serves
+    // all that the one-kernel forward does.  With bf16 terms it holds too much in registers for two blocks
+    // per CU beyond 128 experts: 222 us against 46 + 145 for the two it replaces; 65536 x 768, 256 experts.
+    const bool f32_products = cfg->act_dtype == SW_F32 || (w.router_block && w.E % 4 != 0);
+    w.router_bwd_block = f32_products ? w.E <= 256 : mfma && w.E <= 128;
     w.wsplit = take(w.router_block ? 0 : (size_t)w.etiles * 3 * 128 * w.dpad_r * 2);
     w.has_wsplit_b = mfma && !w.router_bwd_block;
     w.wsplit_b = take(w.has_wsplit_b ? (size_t)w.etiles * d * 256 * 2 : 0);

@@ -788,9 +788,9 @@ static hipError_t router_bwd_typed(const Workspace &w, float alpha, float d_aux,
                                    hipStream_t s) {
     hipError_t err = hipSuccess;
     float *dlogits = (float *)(ws + w.dlogits);
-    // bf16 tokens: the two contractions run on the matrix cores
-    // (dl and W_r as two bf16 terms each; x is bf16 already)
-    // (the forward pass took the same path and left W_r's bf16 terms in the workspace)
+    // bf16 tokens and a multiple of 4 experts: the two contractions run on the bf16 matrix cores (dl
+    // and W_r as two bf16 terms each; x is bf16 already).  The two-kernel dx reads W_r's terms from the
+    // workspace: the MFMA forward pass left them there, after the one-kernel router they are made here.
     const bool mfma = router_bwd_mfma_supported(w, sizeof(XT) == 2 ? SW_BF16 : SW_F32);
     bf16 *dl_split = mfma ? (bf16 *)(ws + w.dl_split) : nullptr;
     // the fp32 copy is read only by the vector-ALU contractions and by the bias gradient

@@ -1,12 +1,13 @@
-// Router backward for up to 128 experts (fp32 tokens: 256): the logits' gradient and the gradient of
+// Router backward for up to 128 experts (with fp32 products: 256): the logits' gradient and the gradient of
 // the layer's input in one kernel, from the saved probabilities and the fp32 router weights.
 //
 //   dl[t][e] = p[t][e] (dp[t][e] - sum_i p[t][i] dp[t][i])       (see router_dlogits_kernel)
 //   dx[t][k] = m[t][k] sum_e dl[t][e] W_r[k][e] + kept_t dXd[slot_t][k]     (m: input jitter, else 1)
 //
 // A wave owns 32 tokens and keeps their dl as MFMA fragments in registers: bf16 tokens as two bf16
-// terms hi + lo (16 mantissa bits, three products per pair of terms, as the weights), fp32 tokens
-// as fp32 on the fp32 MFMA.  The block's four waves walk groups of 64 columns (32 beyond 128
+// terms hi + lo (16 mantissa bits, three products per pair of terms, as the weights), fp32 tokens,
+// and bf16 tokens where the expert count is no multiple of 4, as fp32 on the fp32 MFMA (dW_r then
+// comes from the fp32 dl too).  The block's four waves walk groups of 64 columns (32 beyond 128
 // experts): the group's weights come through registers, one group ahead, are split and laid out
 // in LDS in fragment order; the product is turned through LDS so that a wave adds and stores whole
 // 128-byte row segments.  Few tokens: several blocks take a column range each and the
@@ -28,8 +29,8 @@ struct RouterBwdArgs {
     const int32_t *idx, *counts_g, *tok_slot;
     const void *dXd;
     void *dx;
-    float *dlogits;    // fp32 tokens: [T][E]
-    bf16 *dl_split;    // bf16 tokens: [T][hi 128 | lo 128]
+    float *dlogits;    // fp32 products: [T][E]
+    bf16 *dl_split;    // bf16 terms: [T][hi 128 | lo 128]
     float *dbr_part;   // [ceil(T / 128)][E] sums of dl, or nullptr
     int T, Tg, d, E, groups_per_block;
     float aux_scale;
@@ -39,7 +40,7 @@ struct RouterBwdArgs {
 // EK: 16 experts each.  WIDE: E is a multiple of 4 (rows of E floats are read 16 bytes at a time).
 template <typename XT, int EK, bool WIDE>
 __global__ __launch_bounds__(256, EK > 8 ? 1 : 2) void router_dx_block_kernel(RouterBwdArgs a) {
-    constexpr bool kBf16 = sizeof(XT) == 2;
+    constexpr bool kSplit = sizeof(XT) == 2 && WIDE;            // products of bf16 terms, else fp32
     constexpr int NT = EK > 8 ? 1 : 2, COLS = 32 * NT;          // column tiles and columns of a group
     constexpr int kQuads = COLS * EK * 4 / 256;                 // 4-expert pieces per thread and group
     constexpr int kCPL = 16 / (int)sizeof(XT);                  // columns of a lane's 16-byte piece
@@ -160,7 +161,7 @@ __global__ __launch_bounds__(256, EK > 8 ? 1 : 2) void router_dx_block_kernel(Ro
             a.dbr_part[(size_t)blockIdx.x * E + e] = (dbs[0][e] + dbs[1][e]) + (dbs[2][e] + dbs[3][e]);
     }
     bf16x8 hi[EK], lo[EK];
-    if (kBf16) {
+    if (kSplit) {
 #pragma unroll
         for (int ks = 0; ks < EK; ++ks)
 #pragma unroll
@@ -170,7 +171,7 @@ __global__ __launch_bounds__(256, EK > 8 ? 1 : 2) void router_dx_block_kernel(Ro
             }
     }
     if (writer && live) {
-        if (kBf16) {
+        if (kSplit) {
 #pragma unroll
             for (int ks = 0; ks < 8; ++ks) {   // all 128 columns of each half
                 bf16 *row = a.dl_split + (size_t)t * 256 + ks * 16 + half * 8;
@@ -215,7 +216,7 @@ __global__ __launch_bounds__(256, EK > 8 ? 1 : 2) void router_dx_block_kernel(Ro
             const int e4 = at % (EK * 4), c = at / (EK * 4);
             const int ks = e4 >> 2, h = (e4 >> 1) & 1, sub = e4 & 1;
             char *frag = wlds + (((c >> 5) * EK + ks) * 2) * 1024 + (h * 32 + ((c & 31) ^ ((ks * 2 + h) & 15))) * 16;
-            if (kBf16) {
+            if (kSplit) {
                 bf16x4 whi, wlo;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
@@ -245,7 +246,7 @@ __global__ __launch_bounds__(256, EK > 8 ? 1 : 2) void router_dx_block_kernel(Ro
 #pragma unroll
             for (int n = 0; n < NT; ++n) {
                 const char *frag = wlds + ((n * EK + ks) * 2) * 1024 + (frag0 ^ (uint32_t)(((ks * 2) & 15) << 4));
-                if (kBf16) {
+                if (kSplit) {
                     const bf16x8 whi = *(const bf16x8 *)frag, wlo = *(const bf16x8 *)(frag + 1024);
                     acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(whi, hi[ks], acc[n], 0, 0, 0);
                     acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(whi, lo[ks], acc[n], 0, 0, 0);
@@ -301,12 +302,13 @@ template <typename XT, int EK> static void dx_block_wide(const RouterBwdArgs &a,
     else dx_block_launch<XT, EK, false>(a, s);
 }
 
-// (bf16: at most 128 experts come here)
+// (bf16 terms: at most 128 experts come here)
 template <typename XT> static void dx_block_typed(const RouterBwdArgs &a, hipStream_t s) {
     if (a.E <= 32) dx_block_wide<XT, 2>(a, s);
     else if (a.E <= 64) dx_block_wide<XT, 4>(a, s);
-    else if (sizeof(XT) == 2 || a.E <= 128) dx_block_wide<XT, 8>(a, s);
-    else dx_block_wide<float, 16>(a, s);
+    else if (a.E <= 128) dx_block_wide<XT, 8>(a, s);
+    else if (sizeof(XT) == 4 && a.E % 4 == 0) dx_block_launch<float, 16, true>(a, s);
+    else dx_block_launch<XT, 16, false>(a, s);
 }
 
 hipError_t launch_router_dx_block(const Workspace &w, int dtype, float aux_scale, const float *W_r, char *ws,

@@ -355,10 +355,12 @@ hipError_t launch_router_split_bwd(const Workspace &w, const float *W_r, char *w
     return hipGetLastError();
 }
 
-// The backward contractions address all expert tiles' planes of dl and of W_r through one
+// The backward contractions take dl, and for dx the weights, as two bf16 terms: 16 mantissa bits.  They are
+// for expert counts that are a multiple of 4; the others keep fp32 operands (router_bwd.hip, router.hip).
+// They address all expert tiles' planes of dl and of W_r through one
 // buffer descriptor each; with input jitter they read the planes of x * m that the forward pass left.
 bool router_bwd_mfma_supported(const Workspace &w, int dtype) {
-    return dtype == SW_BF16 && (w.router_block || router_fwd_mfma_supported(w, dtype)) &&
+    return dtype == SW_BF16 && w.E % 4 == 0 && (w.router_block || router_fwd_mfma_supported(w, dtype)) &&
            (uint64_t)w.etiles * (uint64_t)w.T * 512u < 0x7fffffffu &&
            (uint64_t)w.etiles * (uint64_t)w.d * 512u < 0x7fffffffu;
 }

@@ -741,7 +741,7 @@ def test_router_forward_blocks(dtype, T, d, E, cf, n):
     ("bf16", 1025, 200, 128, 1.5, 1, 0.0, True), ("bf16", 2050, 328, 100, 1.0, 2, 0.05, True),
     ("f32", 1, 4, 3, 3.0, 1, 0.0, True), ("f32", 257, 132, 32, 1.0, 1, 0.1, True),
     ("f32", 640, 68, 62, 1.0, 5, 0.0, False), ("f32", 1000, 36, 256, 1.0, 1, 0.0, True),
-    ("f32", 129, 100, 131, 2.0, 1, 0.0, True),
+    ("f32", 129, 100, 131, 2.0, 1, 0.0, True), ("bf16", 700, 104, 253, 1.0, 2, 0.0, True),
 ])
 def test_router_backward_blocks(dtype, T, d, E, cf, n, jit, bias):
     from parity import compare_full
@@ -750,3 +750,32 @@ def test_router_backward_blocks(dtype, T, d, E, cf, n, jit, bias):
     inp = make_inputs(s, _dev())
     errs, gpu, fwd, _ = compare_full(s, inp, d_aux=1.3)
     _report("router backward %s" % ((dtype, T, d, E, cf, n, jit, bias),), errs)
+
+
+# Router gradients from fp32 operands: fp32 tokens, and bf16 tokens where the expert count is no multiple
+# of 4.  At capacity 0 they are the loss's alone and exact up to fp32 arithmetic: each of their terms sees
+# a few roundings of 2^-24 (logit, exponential, quotient, product, sums of 64 in a chain), 2 .. 3e-7 of the
+# norm together.  Operands of two bf16 terms, 2^-18 off, would show 1.6e-6.
+@pytest.mark.parametrize("dtype,E", [("bf16", 3), ("bf16", 10), ("bf16", 33), ("bf16", 126), ("bf16", 130),
+                                     ("bf16", 250), ("f32", 64), ("f32", 201)])
+def test_router_gradients_keep_fp32_operands(dtype, E):
+    from paper_2101_03961_amd.layer import SwitchLayer
+    T, d = 1500, 200
+    inp = make_inputs(SwitchShape("t", T, d, 24, E, 1e-4, dtype=dtype, seed_index=49), _dev())
+    layer = SwitchLayer(T, d, 24, E, 1e-4, 0.01, dtype, _dev())
+    args = (inp["x"], inp["W_r"], inp["W_in"], inp["W_out"])
+    counts = layer.forward(*args)["expert_counts"].cpu().double()
+    grads = layer.backward(inp["dy"], *args, d_aux=2.0)
+    x, W = inp["x"].cpu().double(), inp["W_r"].cpu().double()
+    p = torch.softmax(x @ W, 1)
+    dp = 2.0 * 0.01 * E / T ** 2 * counts
+    dl = p * (dp - (p * dp).sum(1, keepdim=True))
+    for name, want in (("dW_r", x.T @ dl), ("db_r", dl.sum(0))):
+        err = float((grads[name].cpu().double() - want).norm() / want.norm())
+        _report("fp32 router operands %s %s" % ((dtype, E), name), {"err": err})
+        if name == "dW_r":
+            assert err < 2.0 ** -20
+    want = dl @ W.T
+    err = float((grads["dx"].cpu().double() - want).norm() / want.norm())
+    # one rounding to the tokens' type: at most half a unit, 2^-9 of the value in bf16
+    assert err < (2.0 ** -9 if dtype == "bf16" else 2.0 ** -20)
