@@ -88,7 +88,7 @@ Workspace layout_workspace(const switch_config *cfg) {
     // descriptor with 32-bit byte offsets
     w.fused = cfg->act_dtype == SW_BF16 && (cfg->flags & SW_FLAG_FUSED_DISPATCH) &&
               (double)T * (double)d * 2.0 < 2147483647.0;
-    w.inline_scan = !w.fused && w.nb <= kInlineBlocks && w.n <= 8;
+    w.inline_scan = !w.fused && scan_inline(w.E, w.n, w.nb);
     w.tok_slot = take(T * 4);
     w.Xd = take(E * C * d * w.elt);
     w.H = take(w.geglu ? E * C * f1 * w.elt : 0);

@@ -30,9 +30,15 @@ constexpr uint32_t kNoRow = 0x80000000u;
 // Tokens per block of the two-kernel router paths and of the re-routing stages ...
 constexpr int kRouteTB = 256;
 // (the one-kernel router has its own, see router_block_tokens; Workspace::tb is the one in use)
-// Up to this many token blocks the assign kernel sums the block histograms before its own itself;
-// beyond, a scan kernel leaves the prefix sums in a table.
-constexpr int kInlineBlocks = 128;
+// No scan kernel where that saves more than it costs: every block of the assign kernel then sums the block
+// histograms before its own itself, all experts 256 at a time and all earlier groups one by one.  Forward of
+// 64 x 64 wide layers (us, without / with the scan kernel): one group, 256 experts: 512 tokens 24 / 27,
+// 8192: 29.8 / 30.3; 512 experts, 2048 tokens: 62.4 / 61.9, 32768: 112 / 95; 4096 experts, 64 tokens:
+// 491 / 472, 32768: 1011 / 802.  128 experts, 2048 tokens in 4 groups: 27 / 30, 8192 in 4: 38 / 32,
+// 8192 in 2: 28 / 31, 2048 in 8: 33 / 31.
+inline bool scan_inline(int64_t E, int64_t groups, int64_t blocks) {
+    return E <= 256 && blocks <= 128 && groups <= 4 && groups * blocks <= 256;
+}
 
 // Output tile of the bf16 grouped GEMM (square), and the bytes of ReLU-mask bits per tile.
 constexpr int kGemmTile = 256;

@@ -54,8 +54,8 @@ template <> __device__ __forceinline__ Chunk16 pack<bf16>(const float *v) {
 // then (COPY) the dispatch gather Xd[slot] = x[t] of the block's kept tokens.
 // INLINE: the prefix sums of the block histograms are taken here instead of being read from the
 // scan kernel's tables, and one more block does what is left of that kernel: counts, kept, the
-// loss.  With few token blocks that costs less than a launch (T = 2048: 10 us; scan, positions and
-// gather as three launches took 27).  16 tokens per block: with 64, a gather of 16384 rows of
+// loss.  With few token blocks and experts that costs less than a launch (T = 2048: 10 us; scan, positions
+// and gather as three launches took 27); see scan_inline for where it does not.  16 tokens per block: with 64, a gather of 16384 rows of
 // 8 KB took 97 us on its 256 blocks, with 16 it takes 53, as the row-per-wave pass it replaces.
 // -----------------------------------------------------------------------------
 struct AssignArgs {

@@ -59,3 +59,17 @@ def test_split_router_weights_stay_in_the_workspace(recorder, kw, backward_reads
     if wsplit_b:
         tiles = -(-kw["E"] // 128)
         assert base <= wsplit_b and wsplit_b + tiles * kw["d"] * 512 <= base + size
+
+
+# Prefix sums of the block histograms: by the assign kernel itself with few experts, groups and token blocks
+# (it sums all of them in every block), by the scan kernel otherwise.
+@pytest.mark.parametrize("T,E,n,fused,scan", [
+    (64, 128, 1, False, False), (8192, 256, 1, False, False), (8193, 256, 1, False, True),
+    (64, 260, 1, False, True), (32768, 4096, 1, False, True), (64, 4096, 1, False, True),
+    (8192, 128, 2, False, False), (4096, 128, 4, False, False), (8192, 128, 4, False, True),
+    (2048, 64, 8, False, True), (64, 128, 1, True, True)])
+def test_scan_kernel_beside_many_experts_groups_or_blocks(recorder, T, E, n, fused, scan):
+    (status, _, _, launches), = recorder(call("forward", T, 64, 64, E, 1.25 * max(1.0, n * E / T), n=n, fused=fused))
+    assert status == 0
+    assert any("route_scan_kernel" in k[0] for k in launches) == scan
+    assert sum("assign_kernelILb%d" % (not scan) in k[0] for k in launches) == 1
