@@ -289,9 +289,12 @@ int rows_tile_for(const Workspace &w, int64_t Pdim, int64_t Kdim) {
         // an expert's second tile finds the weights in L2 if it runs on the same XCD
         const double reads = m.qb > 64 ? 1. : tq;
         const double bytes = hit * (reads * Pdim * Kdim + mean * (Pdim + Kdim)) * 2.;
-        // rows that do not exist are not loaded; the widest tile, which waits for its loads most, gains by it
+        // rows that do not exist are not loaded; the widest tile, which waits for its loads most, gains by it,
+        // down to the time of its products (1.5 us at the sustained MFMA rate: rows that do not exist are
+        // multiplied all the same).  Without that limit it was taken for a handful of rows of a shallow
+        // layer: 8 rows, 256 experts of 264 x 2704, masked gradient 123 us, with 32 x 128 tiles 83.
         const double fill = mean / (tq * m.qb);
-        const double step = m.step * (m.tile == ROWS_256x384 ? fmin(0.36 + 0.75 * fill, 1.) : 1.);
+        const double step = m.tile == ROWS_256x384 ? fmax(m.step * fmin(0.36 + 0.75 * fill, 1.), 1.5) : m.step;
         // (fewer tiles than CUs: the longest block is the time)
         const double us = fmax((steps * step + m.once) * fmax(tiles / 256., 1.), bytes / m.gbs * 1e-3);
         if (us < best_us * 0.97) {   // later, larger tiles have to be clearly better

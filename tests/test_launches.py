@@ -1,6 +1,7 @@
 """What the library launches, recorded without a GPU (launch_recorder.c stands in for the HIP
 runtime): routes, grids and buffers of layers that are too large or too odd to run in a test."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -73,3 +74,18 @@ def test_scan_kernel_beside_many_experts_groups_or_blocks(recorder, T, E, n, fus
     assert status == 0
     assert any("route_scan_kernel" in k[0] for k in launches) == scan
     assert sum("assign_kernelILb%d" % (not scan) in k[0] for k in launches) == 1
+
+
+# Tile of the products whose rows are tokens, by rows per expert (the first four template arguments of the
+# kernel: 32-column tiles per wave, waves, 32-row tiles per wave, waves): no tall tile for a handful of rows.
+@pytest.mark.parametrize("T,d,f,E,cf,first,second", [
+    (240, 184, 664, 232, 1.0, "1,4,1,1", "1,4,1,1"), (2048, 264, 2704, 256, 1.0, "1,4,1,1", "1,4,1,1"),
+    (503, 264, 2000, 308, 1.0, "1,4,1,1", "1,4,1,1"), (64, 768, 3072, 128, 8.0, "1,4,1,1", "1,4,1,1"),
+    (4096, 768, 3072, 128, 1.25, "2,4,2,1", "2,4,2,1"), (8192, 768, 3072, 128, 1.25, "3,4,4,2", "3,4,4,2"),
+    (65536, 768, 3072, 128, 1.0, "3,4,4,2", "3,4,4,2"), (16384, 4096, 10240, 64, 1.25, "2,4,5,2", "2,4,5,2"),
+])
+def test_tile_follows_the_rows_of_an_expert(recorder, T, d, f, E, cf, first, second):
+    (status, _, _, launches), = recorder(call("forward", T, d, f, E, cf))
+    assert status == 0
+    tiles = [",".join(re.findall(r"Li(\d+)E", k[0])[:4]) for k in launches if "gemm_rows_kernel" in k[0]]
+    assert tiles == [first, second]
