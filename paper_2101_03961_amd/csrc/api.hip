@@ -70,9 +70,6 @@ Workspace layout_workspace(const switch_config *cfg) {
     w.idx = take(T * 4);
     w.gate = take(T * 4);
     w.local_rank = take((size_t)w.nb_r * kRouteTB * 4);
-    w.block_counts = take(nb * E * 4);
-    w.block_psum = take(nb * E * 4);
-    w.block_off = take(nb * E * 4);
     w.counts = take(E * 4);
     w.counts_g = take((size_t)w.n * E * 4);
     w.psum_g = take((size_t)w.n * E * 4);
@@ -99,9 +96,7 @@ Workspace layout_workspace(const switch_config *cfg) {
     w.dH = take(E * C * f1 * w.elt);
     w.dXd = take(E * C * d * w.elt);
     // What only the router's backward pass writes, after the last kernel that reads dH: in dH's
-    // memory while it fits.  (Tiles other than 256 x 256 may pad the ReLU bits further; this more
-    // than makes up for it, so the static scratch takes every configuration that it took with
-    // 256 x 256 tiles alone.)
+    // memory while it fits.
     size_t dead = 0;
     const size_t dead_room = E * C * f1 * w.elt;
     auto take_dead = [&](size_t bytes) {
@@ -136,7 +131,15 @@ Workspace layout_workspace(const switch_config *cfg) {
     w.has_wsplit_b = mfma && !w.router_bwd_block;
     w.wsplit_b = take(w.has_wsplit_b ? (size_t)w.etiles * d * 256 * 2 : 0);
     w.dl_split = take_dead(mfma ? (size_t)w.etiles * T * 256 * 2 : 0);
-    w.dlogits = take_dead(w.router_bwd_block && mfma ? 0 : T * E * 4);
+    const size_t dlogits_bytes = w.router_bwd_block && mfma ? 0 : T * E * 4;
+    const bool dlogits_own = dead + dlogits_bytes > dead_room;   // ... in memory of its own
+    w.dlogits = take_dead(dlogits_bytes);
+    // The routing tables of the token blocks: nothing reads them once the forward pass has assigned the
+    // slots, so they share the memory of dlogits if that has its own.
+    const size_t table = align_up(nb * E * 4, 256);
+    w.block_counts = dlogits_own && 3 * table <= dlogits_bytes ? w.dlogits : take(3 * table);
+    w.block_psum = w.block_counts + table;
+    w.block_off = w.block_psum + table;
     // Vector-ALU dW_r: a split of 64 tokens is two short chains of loads; the parts lie in the
     // gradient of the expert outputs, which the second weight gradient has read by then.
     w.nsplit = w.T < 64 * 64 ? ceil_div(w.T, 64) : 64;
@@ -157,10 +160,15 @@ Workspace layout_workspace(const switch_config *cfg) {
     if (cfg->act_dtype == SW_BF16) {
         bits = E * ceil_div(f, kGemmTile) * ceil_div(C, kGemmTile) * kReluBitsPerTile;
         if (!w.fused) {   // (the first GEMM and the masked gradient agree: same rows, columns and depth)
-            w.gemm_tile[GEMM_FWD1] = rows_tile_for(w, f1, d);
-            w.gemm_tile[GEMM_FWD2] = rows_tile_for(w, d, f);
-            w.gemm_tile[GEMM_DGRAD2] = rows_tile_for(w, f, d);
-            w.gemm_tile[GEMM_DGRAD1] = rows_tile_for(w, d, f1);
+            // The static scratch goes on taking what it took with 256 x 256 tiles alone: a layer that may fit
+            // it gets no tile that pads the ReLU bits further.  (dlogits and the weights' terms, which the
+            // one-kernel router keeps no memory for, outweigh the tables of its smaller token blocks.)
+            const bool may_fit = E * C * f * 2 <= SW_STATIC_SCRATCH_BYTES;
+            const int64_t bits_limit = w.geglu || !may_fit ? INT64_MAX : (int64_t)bits;
+            w.gemm_tile[GEMM_FWD1] = rows_tile_for(w, f1, d, bits_limit);
+            w.gemm_tile[GEMM_FWD2] = rows_tile_for(w, d, f, INT64_MAX);
+            w.gemm_tile[GEMM_DGRAD2] = rows_tile_for(w, f, d, bits_limit);
+            w.gemm_tile[GEMM_DGRAD1] = rows_tile_for(w, d, f1, INT64_MAX);
             w.gemm_tile[GEMM_WGRAD1] = rows_wgrad_tile(w, d, f1);
             w.gemm_tile[GEMM_WGRAD2] = rows_wgrad_tile(w, f, d);
             bits = w.geglu ? 0 : rows_bits_bytes(w.gemm_tile[GEMM_FWD1], E, C, f);

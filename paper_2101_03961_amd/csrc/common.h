@@ -301,8 +301,9 @@ enum RowsTile {
     ROWS_320x256,
     ROWS_256x384
 };
-// the tile that fits the layer (row-limited products, weight gradients), and the bytes of ReLU bits it takes
-int rows_tile_for(const Workspace &w, int64_t Pdim, int64_t Kdim);
+// the tile that fits the layer (row-limited products, none with more ReLU bits than the limit; weight
+// gradients), and the bytes of ReLU bits it takes
+int rows_tile_for(const Workspace &w, int64_t Pdim, int64_t Kdim, int64_t bits_limit);
 int rows_wgrad_tile(const Workspace &w, int64_t Qdim, int64_t Pdim);
 int64_t rows_bits_bytes(int tile, int64_t E, int64_t C, int64_t f);
 hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const void *W_in, const void *W_out,

@@ -274,8 +274,14 @@ static double rows_tiles(double mean, double cap, int qb) {
     return sum / 5.;
 }
 
+int64_t rows_bits_bytes(int tile, int64_t E, int64_t C, int64_t f) {
+    for (const RowsModel &m : kRowsModels)
+        if (m.tile == tile) return E * ceil_div(C, m.qb) * ceil_div(f, m.pb) * (m.qb * m.pb / 8);
+    return 0;
+}
+
 // Tile of a row-limited product of Pdim columns over Kdim.
-int rows_tile_for(const Workspace &w, int64_t Pdim, int64_t Kdim) {
+int rows_tile_for(const Workspace &w, int64_t Pdim, int64_t Kdim, int64_t bits_limit) {
     if (w.C == 0) return ROWS_256x256;   // nothing will be launched
     const double cap = (double)w.C, mean = fmin((double)w.T / (double)w.E, cap);
     const double steps = ceil(Kdim / 64.);
@@ -284,6 +290,7 @@ int rows_tile_for(const Workspace &w, int64_t Pdim, int64_t Kdim) {
     int best = ROWS_256x256;
     double best_us = 1e30;
     for (const RowsModel &m : kRowsModels) {
+        if (rows_bits_bytes(m.tile, w.E, w.C, Pdim) > bits_limit) continue;   // (never 256 x 256)
         const double tq = rows_tiles(mean, cap, m.qb);
         const double tiles = hit * tq * ceil((double)Pdim / m.pb);
         // an expert's second tile finds the weights in L2 if it runs on the same XCD
@@ -317,12 +324,6 @@ int rows_wgrad_tile(const Workspace &w, int64_t Qdim, int64_t Pdim) {
     // its columns fit (at 4096 columns, a third of a tile unused, it takes 6 % longer).
     if (w.C <= 320 || ceil_div(Pdim, 384) * 384 * 50 <= Pdim * 51) return ROWS_256x384;
     return ROWS_NONE;
-}
-
-int64_t rows_bits_bytes(int tile, int64_t E, int64_t C, int64_t f) {
-    for (const RowsModel &m : kRowsModels)
-        if (m.tile == tile) return E * ceil_div(C, m.qb) * ceil_div(f, m.pb) * (m.qb * m.pb / 8);
-    return 0;
 }
 
 template <bool P_TRANS, int EPI, bool DROP>
