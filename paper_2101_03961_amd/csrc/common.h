@@ -44,6 +44,10 @@ inline bool scan_inline(int64_t E, int64_t groups, int64_t blocks) {
 constexpr int kGemmTile = 256;
 constexpr int kReluBitsPerTile = kGemmTile * kGemmTile / 8;
 
+// Threads that one dimension of a grid may hold: 32 bits hold them, and 2^32 and more launch what is left
+// modulo 2^32 without an error.
+constexpr int64_t kMaxGridThreads = 0xffffffffll;
+
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Token blocks of the router kernels: group g's Tg tokens are cut into nbg blocks of tb

@@ -1,6 +1,6 @@
 // Grouped expert GEMMs for the all-fp32 configuration (act_dtype = SW_F32): fp32 products and
 // sums on the matrix cores (v_mfma_f32_32x32x2_f32, 157 TFLOP/s), and a plain FMA kernel with 64-bit
-// addresses for layers whose per-expert matrices reach 2 GB.
+// addresses for layers whose per-expert matrices reach 2 GB or whose tiles fill more than one grid dimension.
 #include <math.h>
 
 #include "common.h"
@@ -364,9 +364,11 @@ hipError_t launch_gemm_f32(GemmKind kind, const Workspace &w, char *ws, const vo
     }
     if (a.Qdim == 0) return hipSuccess;   // capacity 0 and a slot-indexed output: nothing to do
     ProfScope ps(name, s);
-    // the matrix-core kernel addresses one expert's matrices through 32-bit buffer descriptors
+    // the matrix-core kernel addresses one expert's matrices through 32-bit buffer descriptors, and all its
+    // tiles (64 x 128, 256 threads, or half of that) lie in one dimension of the grid
     const double most = fmax(fmax((double)d * f1, (double)C * d), (double)C * f1) * 4.;
-    if (most < 2147483647.) {
+    const int64_t tiles = w.E * ceil_div(a.Qdim, 64) * ceil_div(a.Pdim, 128);
+    if (most < 2147483647. && tiles * 256 <= kMaxGridThreads) {
         const int E = (int)w.E;
         switch (kind) {
         case GEMM_FWD1:

@@ -36,6 +36,7 @@ struct RowsArgs {
     int Qdim, Pdim, Kdim;
     const int32_t *kept;
     int tiles_q, tiles_p, total;
+    int grid_x;
     int by_xcd;                // an expert's tiles run on one XCD
     const int32_t *slot_token; // dropout: token of each slot, [expert][slots]
     int slots;
@@ -52,12 +53,13 @@ __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a
     constexpr int NW = WP * WQ, PB = 32 * IP * WP, QB = 32 * IQ * WQ;
     constexpr int kPBytes = PB * BK * 2, kStage = (PB + QB) * BK * 2;
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    int L = blockIdx.x;
+    int L = blockIdx.y * a.grid_x + blockIdx.x;
     if (a.by_xcd) {   // block b runs on XCD b mod 8: give each XCD a range of experts
-        const int per = (a.total + 7) >> 3;
-        L = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-        if ((int)(blockIdx.x >> 3) >= per || L >= a.total) return;
+        const int per = (a.total + 7) >> 3, at = L >> 3;
+        L = (L & 7) * per + at;
+        if (at >= per) return;
     }
+    if (L >= a.total) return;
     const int per_e = a.tiles_p * a.tiles_q;
     const int e = L / per_e, rem = L - e * per_e;
     int pt, qt;   // the dimension with fewer tiles runs fastest: sharers of the larger operand are neighbours
@@ -239,8 +241,11 @@ static hipError_t rows_launch(RowsArgs a, int E, hipStream_t s) {
     // Up to 64 rows the shared operand is small next to the weights: the tiles are dealt over all XCDs
     // in order, which stays even when only some experts hold tokens.
     a.by_xcd = WGRAD || QB > 64;
-    const unsigned blocks = (unsigned)(a.by_xcd ? ceil_div(a.total, 8) * 8 : a.total);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * WP * WQ), lds, s, a);
+    const int64_t blocks = a.by_xcd ? ceil_div(a.total, 8) * 8 : a.total;
+    const int64_t most = kMaxGridThreads / (64 * WP * WQ) / 8 * 8;   // (whole rounds of XCDs)
+    a.grid_x = (int)(blocks < most ? blocks : most);
+    hipLaunchKernelGGL(kern, dim3((unsigned)a.grid_x, (unsigned)ceil_div(blocks, a.grid_x)), dim3(64 * WP * WQ), lds,
+                       s, a);
     return hipGetLastError();
 }
 

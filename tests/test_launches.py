@@ -89,3 +89,20 @@ def test_tile_follows_the_rows_of_an_expert(recorder, T, d, f, E, cf, first, sec
     assert status == 0
     tiles = [",".join(re.findall(r"Li(\d+)E", k[0])[:4]) for k in launches if "gemm_rows_kernel" in k[0]]
     assert tiles == [first, second]
+
+
+# Layers whose expert GEMMs have more tiles than one grid dimension takes (2^32 threads): many experts of
+# extreme widths.  Every launch stays inside the limit, and the tiles are all there.
+@pytest.mark.parametrize("what", ["forward", "backward"])
+@pytest.mark.parametrize("dtype,d,f,cf", [("bf16", 8, 1 << 20, 1.0), ("bf16", 8, (1 << 19) + 136, 1.0), ("f32", 4, 1 << 20, 1.0)])
+def test_grids_stay_inside_the_launch_limits(recorder, what, dtype, d, f, cf):
+    E = 4096
+    (status, _, _, launches), = recorder(call(what, E, d, f, E, cf, dtype=dtype))
+    assert status == 0
+    for name, grid, block, lds, _ in launches:
+        assert all(g * b < 1 << 32 and g > 0 for g, b in zip(grid, block)), name
+        assert max(grid[1:]) <= 65536 and lds <= 160 * 1024, name
+    # the first one: f columns of one row tile per expert
+    name, grid = [k[:2] for k in launches if "gemm_" in k[0]][0]
+    ip, wp = (int(v) for v in re.findall(r"Li(\d+)E", name)[:2]) if dtype == "bf16" else (1, 2)   # FMA kernel: 64 columns
+    assert grid[0] * grid[1] * grid[2] >= E * -(-f // (32 * ip * wp))
