@@ -713,6 +713,17 @@ def test_fp32_matrix_core_tiles(T, d, f, E, cf, rate, ffn):
     _report("fp32 tiles %s" % ((T, d, f, E, cf, rate, ffn),), errs)
 
 
+# The FMA kernel with 64-bit addresses: slots x hidden units of an expert reach 2 GB (room for a million slots,
+# 50 tokens in them), all six products, the dropout epilogue
+def test_fp32_beyond_one_buffer_descriptor():
+    from parity import compare_full
+    s = SwitchShape("t", 101, 12, 516, 2, 20800.0, dtype="f32", seed_index=50, expert_dropout=0.25, noise_seed=3)
+    inp = make_inputs(s, _dev())
+    errs, gpu, fwd, _ = compare_full(s, inp, d_aux=0.8)
+    _report("fp32 2 GB", errs)
+    assert fwd["capacity"] * 516 * 4 >= 1 << 31
+
+
 # Router forward in one kernel and the assign kernel: expert tiles of 32 with and without 16-byte
 # weight loads, token blocks of 64 (and 128 from 32768 tokens on) with remainders, block prefix sums
 # inside the assign kernel (up to 128 token blocks) and by the scan kernel, groups that end inside a block

@@ -91,6 +91,17 @@ def test_tile_follows_the_rows_of_an_expert(recorder, T, d, f, E, cf, first, sec
     assert tiles == [first, second]
 
 
+# fp32 products: matrix cores while an expert's matrices fit a buffer descriptor, else the FMA kernel
+@pytest.mark.parametrize("T,d,f,E,cf,kernel", [(256, 64, 256, 4, 1.25, "gemm_f32_mfma_kernel"),
+                                               (101, 12, 516, 2, 20800.0, "gemm_f32_kernel"),
+                                               (8, 4096, 131072, 1, 1.0, "gemm_f32_kernel")])
+def test_fp32_products_by_size(recorder, T, d, f, E, cf, kernel):
+    for what, n in (("forward", 2), ("backward", 4)):
+        (status, _, _, launches), = recorder(call(what, T, d, f, E, cf, dtype="f32"))
+        assert status == 0
+        assert [kernel in k[0] for k in launches if "gemm_f32" in k[0]] == [True] * n
+
+
 # Layers whose expert GEMMs have more tiles than one grid dimension takes (2^32 threads): many experts of
 # extreme widths.  Every launch stays inside the limit, and the tiles are all there.
 @pytest.mark.parametrize("what", ["forward", "backward"])
