@@ -46,6 +46,17 @@ template <> __device__ __forceinline__ Chunk16 pack<bf16>(const float *v) {
     return c;
 }
 
+// Passes with one wave per token: blocks of four tokens, 2^23 of them (2^31 threads) in the grid's first
+// dimension, more than 2^25 tokens in the second.
+constexpr int kRowBlocks = 1 << 23;
+static dim3 row_grid(int64_t T) {
+    const int64_t blocks = ceil_div(T, 256 / kWave);
+    return dim3((unsigned)(blocks < kRowBlocks ? blocks : kRowBlocks), (unsigned)ceil_div(blocks, kRowBlocks));
+}
+__device__ __forceinline__ uint32_t wave_token() {
+    return (blockIdx.y * kRowBlocks + blockIdx.x) * (256 / kWave) + threadIdx.x / kWave;
+}
+
 // -----------------------------------------------------------------------------
 // Assign, 16 tokens per block (a token block of the routing tables is shared by several):
 // position_in_expert[t] = block_off[block(t)][e_t] + local_rank[t] (rank inside the token's
@@ -245,8 +256,8 @@ __global__ __launch_bounds__(256) void dispatch_kernel(const Chunk16 *__restrict
                                                        const int32_t *__restrict__ tok_slot,
                                                        int T, int cpr) {
     const int lane = threadIdx.x % kWave;
-    const int t = blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
-    if (t >= T) return;
+    const uint32_t t = wave_token();
+    if (t >= (uint32_t)T) return;
     const int slot_or_none = tok_slot[t];
     if (slot_or_none < 0) return;
     const size_t slot = (size_t)slot_or_none;
@@ -264,8 +275,8 @@ __global__ __launch_bounds__(256) void combine_kernel(const Chunk16 *__restrict_
                                                       const float *__restrict__ gate,
                                                       int T, int cpr) {
     const int lane = threadIdx.x % kWave;
-    const int t = blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
-    if (t >= T) return;
+    const uint32_t t = wave_token();
+    if (t >= (uint32_t)T) return;
     const int slot_or_none = tok_slot[t];
     if (slot_or_none < 0) {
         const Chunk16 zero = {{0u, 0u, 0u, 0u}};
@@ -294,8 +305,8 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(
     const int32_t *__restrict__ tok_slot, const float *__restrict__ gate,
     float *__restrict__ dgate, int T, int cpr) {
     const int lane = threadIdx.x % kWave;
-    const int t = blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
-    if (t >= T) return;
+    const uint32_t t = wave_token();
+    if (t >= (uint32_t)T) return;
     const int slot_or_none = tok_slot[t];
     if (slot_or_none < 0) {
         if (lane == 0) dgate[t] = 0.f;
@@ -335,8 +346,8 @@ __global__ __launch_bounds__(256) void zero_dropped_kernel(Chunk16 *__restrict__
                                                            const int32_t *__restrict__ tok_slot,
                                                            int T, int cpr) {
     const int lane = threadIdx.x % kWave;
-    const int t = blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
-    if (t >= T || tok_slot[t] >= 0) return;
+    const uint32_t t = wave_token();
+    if (t >= (uint32_t)T || tok_slot[t] >= 0) return;
     const Chunk16 zero = {{0u, 0u, 0u, 0u}};
     for (int col = lane; col < cpr; col += kWave) y[(size_t)t * cpr + col] = zero;
 }
@@ -348,8 +359,8 @@ __global__ __launch_bounds__(256) void gate_grad_kernel(const Chunk16 *__restric
                                                         const float *__restrict__ gate,
                                                         float *__restrict__ dgate, int T, int cpr) {
     const int lane = threadIdx.x % kWave;
-    const int t = blockIdx.x * (256 / kWave) + threadIdx.x / kWave;
-    if (t >= T) return;
+    const uint32_t t = wave_token();
+    if (t >= (uint32_t)T) return;
     const int slot_or_none = tok_slot[t];
     if (slot_or_none < 0) {
         if (lane == 0) dgate[t] = 0.f;
@@ -377,7 +388,7 @@ __global__ __launch_bounds__(256) void gate_grad_kernel(const Chunk16 *__restric
 // -----------------------------------------------------------------------------
 hipError_t launch_zero_dropped(const Workspace &w, char *ws, void *y, hipStream_t s) {
     ProfScope ps("zero_dropped", s);
-    hipLaunchKernelGGL(zero_dropped_kernel, dim3((unsigned)ceil_div(w.T, 256 / kWave)), dim3(256), 0,
+    hipLaunchKernelGGL(zero_dropped_kernel, row_grid(w.T), dim3(256), 0,
                        s, (Chunk16 *)y, (const int32_t *)(ws + w.tok_slot), (int)w.T,
                        (int)(w.d / 8));
     return hipGetLastError();
@@ -385,7 +396,7 @@ hipError_t launch_zero_dropped(const Workspace &w, char *ws, void *y, hipStream_
 
 hipError_t launch_gate_grad(const Workspace &w, const void *dy, char *ws, hipStream_t s) {
     ProfScope ps("gate_grad", s);
-    hipLaunchKernelGGL(gate_grad_kernel<bf16>, dim3((unsigned)ceil_div(w.T, 256 / kWave)), dim3(256),
+    hipLaunchKernelGGL(gate_grad_kernel<bf16>, row_grid(w.T), dim3(256),
                        0, s, (const Chunk16 *)dy, (const Chunk16 *)(ws + w.O),
                        (const int32_t *)(ws + w.tok_slot), (const float *)(ws + w.gate),
                        (float *)(ws + w.dgate), (int)w.T, (int)(w.d / 8));
@@ -447,7 +458,7 @@ hipError_t launch_dispatch(const Workspace &w, int dtype, float alpha, const voi
         return err;
     if (!gather || copy) return hipSuccess;
     ProfScope ps("dispatch_gather", s);
-    hipLaunchKernelGGL(dispatch_kernel, dim3((unsigned)ceil_div(w.T, 256 / kWave)), dim3(256), 0, s,
+    hipLaunchKernelGGL(dispatch_kernel, row_grid(w.T), dim3(256), 0, s,
                        (const Chunk16 *)x, (Chunk16 *)(ws + w.Xd), (const int32_t *)(ws + w.tok_slot),
                        (int)w.T, cpr);
     return hipGetLastError();
@@ -457,7 +468,7 @@ hipError_t launch_combine(const Workspace &w, int dtype, char *ws, void *y, hipS
     ProfScope ps("combine_scatter", s);
     const int vec = dtype == SW_BF16 ? 8 : 4;
     const int cpr = (int)(w.d / vec);
-    const dim3 grid((unsigned)ceil_div(w.T, 256 / kWave));
+    const dim3 grid = row_grid(w.T);
     if (dtype == SW_BF16)
         hipLaunchKernelGGL(combine_kernel<bf16>, grid, dim3(256), 0, s,
                            (const Chunk16 *)(ws + w.O), (Chunk16 *)y,
@@ -476,7 +487,7 @@ hipError_t launch_combine_bwd(const Workspace &w, int dtype, const void *dy, cha
     ProfScope ps("combine_bwd", s);
     const int vec = dtype == SW_BF16 ? 8 : 4;
     const int cpr = (int)(w.d / vec);
-    dim3 grid((unsigned)ceil_div(w.T, 256 / kWave));
+    const dim3 grid = row_grid(w.T);
     if (dtype == SW_BF16)
         hipLaunchKernelGGL(combine_bwd_kernel<bf16>, grid, dim3(256), 0, s, (const Chunk16 *)dy,
                            (const Chunk16 *)(ws + w.O), (Chunk16 *)(ws + w.dO),

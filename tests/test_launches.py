@@ -102,6 +102,19 @@ def test_fp32_products_by_size(recorder, T, d, f, E, cf, kernel):
         assert [kernel in k[0] for k in launches if "gemm_f32" in k[0]] == [True] * n
 
 
+# Passes with one wave per token, beyond 2^26 tokens: the same limit
+@pytest.mark.parametrize("kw", [dict(), dict(fused=True), dict(ntlb=2), dict(fused=True, ntlb=1), dict(dtype="f32", jitter=0.1)])
+def test_grids_of_very_many_tokens(recorder, kw):
+    T = (1 << 26) + 12
+    for what in ("forward", "backward"):
+        (status, _, _, launches), = recorder(call(what, T, 8, 8, 4, 1.0, bias=True, **kw))
+        assert status == 0
+        for name, grid, block, _, _ in launches:
+            assert all(g * b < 1 << 32 for g, b in zip(grid, block)) and grid[1] <= 65536, name
+            if "combine" in name or "dispatch_kernel" in name or "dropped" in name or "gate_grad" in name:
+                assert grid[0] * grid[1] * 4 >= T, name
+
+
 # Layers whose expert GEMMs have more tiles than one grid dimension takes (2^32 threads): many experts of
 # extreme widths.  Every launch stays inside the limit, and the tiles are all there.
 @pytest.mark.parametrize("what", ["forward", "backward"])
