@@ -776,7 +776,8 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_bf16_kernel(GemmArgs a) {
                     } else if (q < cur.qlim && p < a.Pdim) {
                         const size_t off = (size_t)q * a.ldc + p;
                         if (MODE == MODE_ROUTER_DX && has_addend[i8]) {
-                            // add the token's row of the expert-side gradient (fp32 add, one rounding)
+                            // add the token's row of the expert-side gradient (to the product, which is
+                            // rounded already: fp32 add, a second rounding)
                             const bf16x8 va = __builtin_bit_cast(bf16x8, val);
                             const bf16x8 vb = __builtin_bit_cast(bf16x8, addend[i8]);
                             bf16x8 vo;

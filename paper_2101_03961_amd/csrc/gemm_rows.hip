@@ -325,8 +325,10 @@ int rows_wgrad_tile(const Workspace &w, int64_t Qdim, int64_t Pdim) {
     if (w.C <= 96) return ROWS_256x128;
     // Up to about five k steps the large tile's shorter start wins over the persistent kernel's
     // pipeline (193 against 205 us at 160 slots, equal at 256, 128 experts of 768 x 3072).  With
-    // more it is equal at full experts and stores the zeros of experts without tokens faster, if
-    // its columns fit (at 4096 columns, a third of a tile unused, it takes 6 % longer).
+    // more it is within 2 % at full experts (512 slots, first / second layer, persistent: 326 / 334 us,
+    // here 332 / 334) and stores the zeros of experts without tokens faster (nearly all of them empty:
+    // 165 / 188, here 124 / 151), if its columns fit (at 4096 columns, a third of a tile unused, it
+    // takes 6 % longer).
     if (w.C <= 320 || ceil_div(Pdim, 384) * 384 * 50 <= Pdim * 51) return ROWS_256x384;
     return ROWS_NONE;
 }

@@ -26,7 +26,6 @@ template <int R, int NW, int BK = 64> struct RowsDirect {
         row_step = (uint32_t)(kRowsPerLoad * NW) * (uint32_t)ld * 2u;
         klim = klim_;
     }
-    __device__ __forceinline__ void disable_load() { klim = 0; }
     __device__ __forceinline__ void init_frag(int lane, int frag_row) {
         const int fr = frag_row + (lane & 31);
         frag0 = (uint32_t)(fr * kPitch + (((lane >> 5) ^ perm(fr)) << 4));
@@ -73,7 +72,8 @@ template <int R, int NW, int BK = 64> struct RowsTrans {
     static constexpr int kPeriod = R == 384 ? 3 : R == 256 ? 2 : 1;   // loads until (k-row mod 4, chunk) repeat
     static constexpr int kPeriodRows = kPeriod * 64 / kChunks;        // k-rows they cover
     static_assert(kLoads * 512 * NW == R * BK && kLoads % kPeriod == 0, "rows divide over the waves");
-    static __device__ __forceinline__ int perm(int kr) { return R == 64 ? (kr & 2) << 1 : (kr & 3) << 2; }
+    static_assert(R >= 128, "the permutation moves a chunk by up to 12");
+    static __device__ __forceinline__ int perm(int kr) { return (kr & 3) << 2; }
     i32x4 rsrc;
     uint32_t voff[kPeriod];
     uint32_t k_step;
@@ -90,10 +90,6 @@ template <int R, int NW, int BK = 64> struct RowsTrans {
             const int row = row0 + (c << 3);
             voff[i] = row < rowlim ? ((uint32_t)kr * (uint32_t)ld + (uint32_t)row) * 2u : kOobOffset;
         }
-    }
-    __device__ __forceinline__ void disable_load() {
-#pragma unroll
-        for (int i = 0; i < kPeriod; ++i) voff[i] = kOobOffset;
     }
     __device__ __forceinline__ void init_frag(int lane, int frag_row) {
         const int g = lane >> 4, j = lane & 15;
