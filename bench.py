@@ -58,8 +58,13 @@ def kernel_work(shape, kept, elt):
     zero_with_positions = (shape.dtype == "bf16" and shape.fused_dispatch and
                            shape.ntlb_rounds == 0)
     gathers = not (shape.dtype == "bf16" and shape.fused_dispatch) and shape.ntlb_rounds == 0
-    # one kernel for dl and dx (bf16: up to 128 experts), which leaves dl for dW_r
-    bf16_block = shape.dtype == "bf16" and E <= 128
+    # one kernel for dl and dx (bf16 terms: up to 128 experts, a multiple of 4), which leaves dl for dW_r
+    bf16_block = shape.dtype == "bf16" and E <= 128 and E % 4 == 0
+    # tokens per block of the routing tables
+    if E > 256 or (shape.dtype == "bf16" and jit):
+        block = 256
+    else:
+        block = 128 if shape.dtype == "bf16" and E <= 128 and T >= 32768 else 64
     dpad = -(-d // 32) * 32
     x_router = T * 3 * dpad * 2 if jit else T * d * elt     # bytes of the router's input operand
     return {**{
@@ -72,7 +77,7 @@ def kernel_work(shape, kept, elt):
         "router_fwd_mfma": (6.0 * T * d * E, x_router + T * E * 4 + T * 12, "hbm"),
         "router_logits": (2.0 * T * d * E, T * d * elt + T * E * 4 + d * E * 4, "hbm"),
         "router_softmax_top1": (0.0, 2.0 * T * E * 4 + T * 8, "hbm"),
-        "route_scan_aux": (0.0, 3.0 * (T / 256.0) * E * 4, "hbm"),
+        "route_scan_aux": (0.0, 3.0 * (T / block) * E * 4, "hbm"),
         # positions, slot tables and, unless re-routing stages come first or the GEMMs gather, the
         # dispatch (with dispatch / combine inside the GEMMs and no re-routing stages it also
         # clears the rows of y of the tokens without a slot)

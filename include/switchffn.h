@@ -119,8 +119,8 @@ typedef struct {
  * the tokens.  With this flag a bf16 layer (whose x is below 2 GB; otherwise the flag has no
  * effect) runs them inside the expert GEMMs instead: token rows are gathered by the operand
  * loads, output rows are written to their tokens by the second GEMM's epilogue.  That needs
- * about 4 % less memory traffic and no expert-major copies of x and dy, and takes 1-2 % longer
- * at the Switch-Base shape.  Same results up to rounding (the gate is applied at a different
+ * no expert-major copies of x and dy; memory traffic and time are about 2 % more at the
+ * Switch-Base shape.  Same results up to rounding (the gate is applied at a different
  * place). */
 #define SW_FLAG_FUSED_DISPATCH 1
 

@@ -16,7 +16,7 @@
 // What bounds it: HBM (probabilities, dXd and dx once each: about 50 us at 65536 tokens x 768, 128
 // experts) and what two blocks per CU, the most that LDS and registers leave room for, do not
 // overlap of products and loads.  Measured (us, before: dlogits + weight split + product kernels):
-// 65536 x 768, E 128: 97 (138); 8192: 30 (49); 5003 x 392, E 10 with the bias sums: 10 (56);
+// 65536 x 768, E 128: 97 (138); 8192: 30 (49); 5003 x 392, E 10 (fp32 products) with the bias sums: 11 (56);
 // 65536 with jitter: 110 (160); fp32 256 x 64, E 4: 6 (25), 8192 x 768, E 32: 17 (54).
 #include "common.h"
 #include "lds_operands.h"

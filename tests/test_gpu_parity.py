@@ -744,7 +744,7 @@ def test_router_forward_blocks(dtype, T, d, E, cf, n):
 
 
 # Router backward in one kernel: expert counts with and without 16-byte rows at each fragment count
-# (32, 64, 128; fp32 also 256), token remainders of the 128-token blocks, column groups of 64 with
+# (32, 64, 128; with fp32 operands 256), token remainders of the 128-token blocks, column groups of 64 with
 # remainders in one or several blocks, groups that end inside a block, bias sums, jitter on bf16 tokens
 @pytest.mark.parametrize("dtype,T,d,E,cf,n,jit,bias", [
     ("bf16", 31, 8, 2, 1.0, 1, 0.0, True), ("bf16", 129, 72, 32, 1.0, 1, 0.0, True),
