@@ -109,13 +109,20 @@ __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    auto issue = [&](int kt, int st) {   // k past the end: zeros
-        const uint32_t at = lds0 + (uint32_t)(st * kStage);
-#pragma unroll
-        for (int i = 0; i < decltype(op)::kLoads; ++i) op.issue_one(at, kt * BK, wave, i);
-#pragma unroll
-        for (int i = 0; i < decltype(oq)::kLoads; ++i) oq.issue_one(at + kPBytes, kt * BK, wave, i);
+    auto issue_load = [&](uint32_t at, int kt, int i) {   // load i of a step; k past the end: zeros
+        if (i < decltype(op)::kLoads) op.issue_one(at, kt * BK, wave, i);
+        else oq.issue_one(at + kPBytes, kt * BK, wave, i - decltype(op)::kLoads);
     };
+    auto issue = [&](int kt, int st) {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) issue_load(lds0 + (uint32_t)(st * kStage), kt, i);
+    };
+    // Eight waves issue a step's loads in parts behind the fragment reads of its first sub-steps: in one
+    // burst ahead of them, the address unit's queue held up the reads and with them the products (start
+    // of a step 1300 cycles without an MFMA; over 3 of the 4 sub-steps / before the reads: masked gradient of
+    // 128 experts x 512 x 768 x 3072 310 / 332 us, 64 x 256 x 4096 x 10240 1360-1530 / 1380-1580).  Four waves
+    // issue few, and their steps are short: first.
+    constexpr int kSpread = NW < 8 ? 0 : BK == 64 ? 3 : 1;
 #pragma unroll
     for (int s = 0; s < STAGES - 1; ++s) issue(s, s);
     int st = 0, fill = STAGES - 1;
@@ -126,7 +133,8 @@ __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a
         }
         rows_wait_vmcnt<(STAGES > 2 ? STAGES - 2 : 0) * kLoads>();   // step kt has landed
         __syncthreads();                                             // ... for all waves; step kt - 1 is read
-        if (STAGES > 1) issue(kt + STAGES - 1, fill);
+        const uint32_t fill_at = lds0 + (uint32_t)(fill * kStage);
+        if (STAGES > 1 && kSpread == 0) issue(kt + STAGES - 1, fill);
         const char *sp = lds + st * kStage, *sq = sp + kPBytes;
 #pragma unroll
         for (int ks = 0; ks < BK / 16; ++ks) {
@@ -135,6 +143,10 @@ __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a
             for (int i = 0; i < IP; ++i) fp[i] = op.frag(sp, i, ks);
 #pragma unroll
             for (int j = 0; j < IQ; ++j) fq[j] = oq.frag(sq, j, ks);
+            if (STAGES > 1 && kSpread > 0)
+#pragma unroll
+                for (int i = 0; i < kLoads; ++i)
+                    if (i * kSpread / kLoads == ks) issue_load(fill_at, kt + STAGES - 1, i);
 #pragma unroll
             for (int i = 0; i < IP; ++i)
 #pragma unroll
@@ -151,10 +163,20 @@ __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a
     // of 32 IP columns, 16 bytes per lane.
     constexpr int kPitch = rows_turn_pitch(IP), kChunks = 4 * IP, kPasses = 2 * IP;
     char *ep = lds + wave * 32 * kPitch;
-    bf16 *Cout = a.Cout + (size_t)e * a.c_batch;
     const int pw = p0 + wp * 32 * IP;
     const int wrow = lane & 31;
-    auto swz = [](int row) { return IP == 1 ? (row >> 2) & 3 : IP == 2 ? (row >> 1) & 7 : row & 3; };
+    auto swz = [](int row) { return IP == 1 ? (row >> 2) & 3 : IP == 2 ? (row >> 1) & 7 : 0; };
+    // Stores against a descriptor of the existing rows: rows past them, and columns past the matrix (whose
+    // offsets are set beyond it), store nothing, without a branch per store.
+    const auto crsrc = __builtin_amdgcn_make_buffer_rsrc(a.Cout + (size_t)e * a.c_batch, 0,
+                                                         (int)((uint32_t)qlim * (uint32_t)a.ldc * 2u), 0x00020000);
+    const uint32_t c_step = 64u * (uint32_t)a.ldc;   // bytes of 32 rows
+    uint32_t cvoff[kPasses];   // of the lane's piece in pass x, first 32 rows of the wave
+#pragma unroll
+    for (int x = 0; x < kPasses; ++x) {
+        const int at = x * 64 + lane, row = at / kChunks, p = pw + (at - row * kChunks) * 8;
+        cvoff[x] = p < a.Pdim ? ((uint32_t)(q0 + wq * IQ * 32 + row) * (uint32_t)a.ldc + (uint32_t)p) * 2u : kOobOffset;
+    }
 #pragma unroll
     for (int j = 0; j < IQ; ++j) {
         const int qw = q0 + (wq * IQ + j) * 32;
@@ -198,7 +220,6 @@ __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a
         for (int x = 0; x < kPasses; ++x) {
             const int at = x * 64 + lane;
             const int row = at / kChunks, c = at - row * kChunks;
-            const int q = qw + row, p = pw + c * 8;
             u32x4 val = *(const u32x4 *)(ep + row * kPitch + ((c ^ swz(row)) << 4));
             if (EPI == ROWS_RELU) {   // after ReLU a half word is > 0 exactly when min(., 1) is 1
                 uint32_t u = 0;
@@ -212,7 +233,7 @@ __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a
 #pragma unroll
                 for (int w = 0; w < 4; ++w) val[w] &= ((byte >> w) & 0x10001u) * 0xffffu;
             }
-            if (q < qlim && p < a.Pdim) *(u32x4 *)(Cout + (size_t)q * a.ldc + p) = val;
+            __builtin_amdgcn_raw_buffer_store_b128(val, crsrc, (int)(cvoff[x] + (uint32_t)j * c_step), 0, 0);
         }
         if (EPI == ROWS_RELU) {
             uint8_t *b = bits_of(j);

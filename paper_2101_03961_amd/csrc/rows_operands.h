@@ -111,8 +111,9 @@ template <int R, int NW, int BK = 64> struct RowsTrans {
     }
 };
 
-// bytes per row of the epilogue's turn-around buffer of a wave with 32 IP columns
-constexpr int rows_turn_pitch(int IP) { return IP == 1 ? 64 : IP == 2 ? 128 : 256; }
+// bytes per row of the epilogue's turn-around buffer of a wave with 32 IP columns (96 columns: 13 chunks, an
+// odd number, so that 16 consecutive rows begin in 16 different places of the 256-byte bank window)
+constexpr int rows_turn_pitch(int IP) { return IP == 1 ? 64 : IP == 2 ? 128 : 208; }
 
 // wait until at most N of this wave's direct loads are still in flight
 template <int N> __device__ __forceinline__ void rows_wait_vmcnt() {
