@@ -303,7 +303,8 @@ enum RowsTile {
     ROWS_256x128,
     ROWS_256x256,
     ROWS_320x256,
-    ROWS_256x384
+    ROWS_256x384,
+    ROWS_384x256
 };
 // the tile that fits the layer (row-limited products, none with more ReLU bits than the limit; weight
 // gradients), and the bytes of ReLU bits it takes
@@ -312,6 +313,9 @@ int rows_wgrad_tile(const Workspace &w, int64_t Qdim, int64_t Pdim);
 int64_t rows_bits_bytes(int tile, int64_t E, int64_t C, int64_t f);
 hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const void *W_in, const void *W_out,
                             void *dW_in, void *dW_out, int tile, hipStream_t s);
+// Weight gradients with persistent blocks (gemm_wgrad.hip), tile ROWS_256x384 or ROWS_384x256.
+hipError_t launch_gemm_wgrad(GemmKind kind, const Workspace &w, char *ws, void *dW_in, void *dW_out, int tile,
+                             hipStream_t s);
 hipError_t launch_gemm_f32(GemmKind kind, const Workspace &w, char *ws, const void *W_in,
                            const void *W_out, void *dW_in, void *dW_out, const TokenMajor &tm,
                            hipStream_t s);

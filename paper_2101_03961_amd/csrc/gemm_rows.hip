@@ -166,16 +166,18 @@ __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a
     const int pw = p0 + wp * 32 * IP;
     const int wrow = lane & 31;
     auto swz = [](int row) { return IP == 1 ? (row >> 2) & 3 : IP == 2 ? (row >> 1) & 7 : 0; };
-    // Stores against a descriptor of the existing rows: rows past them, and columns past the matrix (whose
-    // offsets are set beyond it), store nothing, without a branch per store.
+    // Stores through a descriptor: rows past the last one and columns past the matrix get an offset outside it
+    // and store nothing, without a branch per store.
     const auto crsrc = __builtin_amdgcn_make_buffer_rsrc(a.Cout + (size_t)e * a.c_batch, 0,
                                                          (int)((uint32_t)qlim * (uint32_t)a.ldc * 2u), 0x00020000);
     const uint32_t c_step = 64u * (uint32_t)a.ldc;   // bytes of 32 rows
-    uint32_t cvoff[kPasses];   // of the lane's piece in pass x, first 32 rows of the wave
+    uint32_t cvoff[kPasses];   // of the lane's piece in pass x, first 32 rows of the wave,
+    int left[kPasses];         // and the rows from there to the last one (offsets of rows past it may wrap)
 #pragma unroll
     for (int x = 0; x < kPasses; ++x) {
         const int at = x * 64 + lane, row = at / kChunks, p = pw + (at - row * kChunks) * 8;
-        cvoff[x] = p < a.Pdim ? ((uint32_t)(q0 + wq * IQ * 32 + row) * (uint32_t)a.ldc + (uint32_t)p) * 2u : kOobOffset;
+        cvoff[x] = ((uint32_t)(q0 + wq * IQ * 32 + row) * (uint32_t)a.ldc + (uint32_t)p) * 2u;
+        left[x] = p < a.Pdim ? qlim - (q0 + wq * IQ * 32 + row) : 0;
     }
 #pragma unroll
     for (int j = 0; j < IQ; ++j) {
@@ -233,7 +235,8 @@ __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a
 #pragma unroll
                 for (int w = 0; w < 4; ++w) val[w] &= ((byte >> w) & 0x10001u) * 0xffffu;
             }
-            __builtin_amdgcn_raw_buffer_store_b128(val, crsrc, (int)(cvoff[x] + (uint32_t)j * c_step), 0, 0);
+            const uint32_t off = 32 * j < left[x] ? cvoff[x] + (uint32_t)j * c_step : kOobOffset;
+            __builtin_amdgcn_raw_buffer_store_b128(val, crsrc, (int)off, 0, 0);
         }
         if (EPI == ROWS_RELU) {
             uint8_t *b = bits_of(j);
@@ -338,20 +341,42 @@ int rows_tile_for(const Workspace &w, int64_t Pdim, int64_t Kdim, int64_t bits_l
     return best;
 }
 
-// Tile of a weight gradient of Qdim x Pdim; ROWS_NONE: the persistent kernel.
+// Weight gradients: CU time of a 64-k step and of a tile's epilogue (and start) per shape; persistent blocks
+// take whole rounds.  Fitted to 22 shapes of 4 .. 256 experts, 64 .. 4096 wide, 4 .. 7500 slots; us of the first
+// gradient measured, estimated best first (256 x 384 or 384 x 256: gemm_wgrad.hip; 256 x 256: gemm_bf16.hip):
+//   128 experts of 768 x 3072, 512 slots   384x256 299, 256x128 326, 256x256 334
+//   32 of 512 x 1024, 1024 slots           256x256 37, 256x384 41, 256x128 41, 128x128 51
+//   32 of 512 x 1024, 256 slots            256x128 16, 128x128 17, 256x384 18, 256x256 18
+//   16 of 128 x 512, 3750 slots            128x128 38, 256x256 73, 256x128 76, 256x384 97
+struct WgradModel {
+    int tile, qb, pb;
+    double step, once;
+    bool rounds;
+};
+static const WgradModel kWgradModels[] = {
+    {ROWS_128x128, 128, 128, 0.65, 1.4, false}, {ROWS_256x128, 256, 128, 0.95, 2.2, false},
+    {ROWS_NONE, 256, 256, 1.5, 6.0, true},      {ROWS_256x384, 256, 384, 2.05, 6.0, true},
+    {ROWS_384x256, 384, 256, 2.05, 6.0, true},
+};
+
+// Tile of a weight gradient of Qdim x Pdim; ROWS_NONE: the persistent kernel of gemm_bf16.hip.
 int rows_wgrad_tile(const Workspace &w, int64_t Qdim, int64_t Pdim) {
-    // too few large tiles for the CUs
-    if (w.E * ceil_div(Qdim, 256) * ceil_div(Pdim, 256) < 256) return ROWS_128x128;
-    // Few slots: little but the store of the gradient; two blocks per CU store and load in turns.
-    if (w.C <= 96) return ROWS_256x128;
-    // Up to about five k steps the large tile's shorter start wins over the persistent kernel's
-    // pipeline (193 against 205 us at 160 slots, equal at 256, 128 experts of 768 x 3072).  With
-    // more it is within 2 % at full experts (512 slots, first / second layer, persistent: 326 / 334 us,
-    // here 332 / 334) and stores the zeros of experts without tokens faster (nearly all of them empty:
-    // 165 / 188, here 124 / 151), if its columns fit (at 4096 columns, a third of a tile unused, it
-    // takes 6 % longer).
-    if (w.C <= 320 || ceil_div(Pdim, 384) * 384 * 50 <= Pdim * 51) return ROWS_256x384;
-    return ROWS_NONE;
+    const double cap = (double)w.C, mean = fmin((double)w.T / (double)w.E, cap);
+    const double steps = rows_tiles(mean, cap, 64);
+    int best = ROWS_128x128;
+    double best_us = 1e30;
+    for (const WgradModel &m : kWgradModels) {
+        const double per_cu = (double)(w.E * ceil_div(Qdim, m.qb) * ceil_div(Pdim, m.pb)) / 256.;
+        double us = (m.rounds ? ceil(per_cu) : fmax(per_cu, 1.)) * (steps * m.step + m.once);
+        // of the two large shapes the one with the long side along the smaller dimension: 64 experts of
+        // 4096 x 10240, 256 slots: first gradient 1990 us, second 1980; the other way 2140 and 2080
+        if ((m.tile == ROWS_256x384 && Qdim < Pdim) || (m.tile == ROWS_384x256 && Pdim < Qdim)) us *= 1.03;
+        if (us < best_us) {
+            best = m.tile;
+            best_us = us;
+        }
+    }
+    return best;
 }
 
 template <bool P_TRANS, int EPI, bool DROP>
@@ -412,6 +437,7 @@ hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const v
     }
     case GEMM_WGRAD2:
     case GEMM_WGRAD1: {
+        if (tile == ROWS_256x384 || tile == ROWS_384x256) return launch_gemm_wgrad(kind, w, ws, dW_in, dW_out, tile, s);
         const bool two = kind == GEMM_WGRAD2;
         ProfScope ps(two ? "gemm2_wgrad" : "gemm1_wgrad", s);
         a.Q = (const bf16 *)(ws + (two ? w.A : w.Xd)); a.ldq = two ? f : d; a.q_batch = (size_t)C * a.ldq;
@@ -421,9 +447,6 @@ hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const v
         switch (tile) {
         case ROWS_128x128: return rows_launch<2, 2, 2, 2, 2, 2, 64, true, ROWS_PLAIN, false, true>(a, E, s);
         case ROWS_256x128: return rows_launch<2, 2, 4, 2, 1, 2, 64, true, ROWS_PLAIN, false, true>(a, E, s);
-        case ROWS_256x384:   // few k steps: a shorter start
-            if (C <= 320) return rows_launch<3, 4, 4, 2, 4, 2, 32, true, ROWS_PLAIN, false, true>(a, E, s);
-            return rows_launch<3, 4, 4, 2, 2, 2, 64, true, ROWS_PLAIN, false, true>(a, E, s);
         }
         return hipErrorInvalidValue;
     }

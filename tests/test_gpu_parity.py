@@ -66,6 +66,20 @@ def test_bf16_shapes_full_parity(T, d, f, E, cf, bias, in_gemm):
         assert fwd["dropped"].sum() > 0 and (fwd["expert_counts"] == 0).any()
 
 
+@pytest.mark.parametrize("T,d,f,E,cf,bias", [
+    (2400, 264, 904, 120, 1.25, False),   # two rounds of tiles, one k step, ragged in both dimensions
+    (9000, 264, 760, 80, 1.25, False),    # two or three k steps
+    (2400, 264, 904, 120, 4.0, True),     # experts of 80 tokens beside many without any
+    (9000, 264, 760, 80, 0.007, False),   # no slots at all
+])
+def test_weight_gradients_of_persistent_blocks(T, d, f, E, cf, bias):
+    """Sizes that take the 384 x 256 and 256 x 384 tiles of gemm_wgrad.hip (tests/test_launches.py)."""
+    from parity import compare_full
+    s = SwitchShape("t", T, d, f, E, cf, dtype="bf16", zipf_bias=bias, seed_index=47)
+    errs, gpu, fwd, _ = compare_full(s, make_inputs(s, _dev()), d_aux=1.0)
+    _report("persistent weight gradients %s" % ((T, d, f, E, cf, bias),), errs)
+
+
 @pytest.mark.parametrize("T,d,f,E,cf,n,bias,ffn,rate,rounds", [
     (2000, 264, 520, 5, 1.5, 1, False, "relu", 0.0, 0),    # ragged tiles everywhere
     (4096, 128, 256, 16, 1.0, 2, True, "relu", 0.1, 1),    # groups, skew, dropout, re-routing

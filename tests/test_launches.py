@@ -91,6 +91,29 @@ def test_tile_follows_the_rows_of_an_expert(recorder, T, d, f, E, cf, first, sec
     assert tiles == [first, second]
 
 
+# Kernel of the weight gradients (first layer, second layer) by size: persistent blocks with the long side along
+# the smaller dimension unless that pads more, smaller tiles for few experts, 256 x 256 where that fills the rounds.
+@pytest.mark.parametrize("T,d,f,E,cf,first,second", [
+    (65536, 768, 3072, 128, 1.0, "wgrad 4,2,3,4", "wgrad 3,4,4,2"),
+    (16384, 4096, 10240, 64, 1.25, "wgrad 4,2,3,4", "wgrad 3,4,4,2"),
+    (65536, 1024, 2816, 128, 1.25, "wgrad 3,4,4,2", "wgrad 4,2,3,4"),   # the other way: 32 tiles instead of 33
+    (2400, 264, 904, 120, 1.25, "wgrad 4,2,3,4", "wgrad 3,4,4,2"),
+    (9000, 264, 760, 80, 1.25, "wgrad 4,2,3,4", "wgrad 3,4,4,2"),
+    (32768, 512, 1024, 32, 1.0, "bf16", "bf16"),
+    (60000, 128, 512, 16, 1.0, "rows 2,2,2,2", "rows 2,2,2,2"),
+    (4096, 256, 1024, 64, 1.0, "rows 2,2,4,2", "rows 2,2,4,2"),
+])
+def test_kernel_of_the_weight_gradients(recorder, T, d, f, E, cf, first, second):
+    (status, _, _, launches), = recorder(call("backward", T, d, f, E, cf))
+    assert status == 0
+    got = []
+    for name, *_ in launches:
+        m = re.search(r"gemm_(rows|wgrad|bf16)_kernelI((?:L[ib]\d+E)*)", name)
+        if m and (m[1] == "wgrad" or m[1] == "rows" and m[2].endswith("Lb1E") or m[1] == "bf16" and m[2].startswith("Lb1ELb1E")):
+            got.append(m[1] + ("" if m[1] == "bf16" else " " + ",".join(re.findall(r"Li(\d+)E", m[2])[:4])))
+    assert got[:2] == [first, second]
+
+
 # fp32 products: matrix cores while an expert's matrices fit a buffer descriptor, else the FMA kernel
 @pytest.mark.parametrize("T,d,f,E,cf,kernel", [(256, 64, 256, 4, 1.25, "gemm_f32_mfma_kernel"),
                                                (101, 12, 516, 2, 20800.0, "gemm_f32_kernel"),
