@@ -45,37 +45,15 @@ struct RowsArgs {
 
 enum { ROWS_PLAIN = 0, ROWS_RELU = 1, ROWS_MASK = 2 };
 
+// The tile's products and epilogue, with IQ row blocks of 32 per wave (IQ_MAX of them fit the tile).
 // Mask bits: one byte per 16-byte piece of the output (bits 0..3: low halves of its four words, 4..7:
 // high halves), [tile][wave][32-row round][pass][lane] in the order the epilogue handles them.
-template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, int BK, bool P_TRANS, int EPI, bool DROP,
+template <int IP, int WP, int IQ, int IQ_MAX, int WQ, int STAGES, int BK, bool P_TRANS, int EPI, bool DROP,
           bool WGRAD>
-__global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a) {
-    constexpr int NW = WP * WQ, PB = 32 * IP * WP, QB = 32 * IQ * WQ;
+__device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, int e, int q0, int p0, int qlim,
+                                          int klim, int lane, int wave) {
+    constexpr int NW = WP * WQ, PB = 32 * IP * WP, QB = 32 * IQ_MAX * WQ;
     constexpr int kPBytes = PB * BK * 2, kStage = (PB + QB) * BK * 2;
-    extern __shared__ __attribute__((aligned(16))) char lds[];
-    int L = blockIdx.y * a.grid_x + blockIdx.x;
-    if (a.by_xcd) {   // block b runs on XCD b mod 8: give each XCD a range of experts
-        const int per = (a.total + 7) >> 3, at = L >> 3;
-        L = (L & 7) * per + at;
-        if (at >= per) return;
-    }
-    if (L >= a.total) return;
-    const int per_e = a.tiles_p * a.tiles_q;
-    const int e = L / per_e, rem = L - e * per_e;
-    int pt, qt;   // the dimension with fewer tiles runs fastest: sharers of the larger operand are neighbours
-    if (a.tiles_q <= a.tiles_p) {
-        pt = rem / a.tiles_q;
-        qt = rem - pt * a.tiles_q;
-    } else {
-        qt = rem / a.tiles_p;
-        pt = rem - qt * a.tiles_p;
-    }
-    const int used = a.kept[e];   // slots with a token
-    const int qlim = WGRAD ? a.Qdim : min(used, a.Qdim), klim = WGRAD ? min(used, a.Kdim) : a.Kdim;
-    const int q0 = qt * QB, p0 = pt * PB;
-    if (q0 >= qlim) return;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int wp = wave % WP, wq = wave / WP;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
 
@@ -85,12 +63,14 @@ __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a
     oq.init_frag(lane, wq * 32 * IQ);
     op.init(a.P + (size_t)e * a.p_batch, a.ldp, p0, a.Pdim, klim, lane, wave);
     oq.init(a.Q + (size_t)e * a.q_batch, a.ldq, q0, qlim, klim, lane, wave);
-    constexpr int kLoads = decltype(op)::kLoads + decltype(oq)::kLoads;
+    constexpr int kLoadsP = decltype(op)::kLoads;
+    constexpr int kLoads = kLoadsP + decltype(oq)::kLoads * IQ / IQ_MAX;   // (load i: rows of block row i and up)
+    static_assert(IQ == IQ_MAX || (!WGRAD && decltype(oq)::kLoads == IQ_MAX), "a load per block row");
     const int nk = (klim + BK - 1) / BK;
 
     // the wave's bits of 32-row round j
     constexpr int kBitBytes = 2 * IP;   // per lane
-    auto bits_of = [&](int j) { return a.bits + (((size_t)L * NW + wave) * IQ + j) * (64 * kBitBytes); };
+    auto bits_of = [&](int j) { return a.bits + (((size_t)L * NW + wave) * IQ_MAX + j) * (64 * kBitBytes); };
     uint32_t mb[IQ][2];
     if (EPI == ROWS_MASK) {
 #pragma unroll
@@ -110,8 +90,8 @@ __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
     auto issue_load = [&](uint32_t at, int kt, int i) {   // load i of a step; k past the end: zeros
-        if (i < decltype(op)::kLoads) op.issue_one(at, kt * BK, wave, i);
-        else oq.issue_one(at + kPBytes, kt * BK, wave, i - decltype(op)::kLoads);
+        if (i < kLoadsP) op.issue_one(at, kt * BK, wave, i);
+        else oq.issue_one(at + kPBytes, kt * BK, wave, i - kLoadsP);
     };
     auto issue = [&](int kt, int st) {
 #pragma unroll
@@ -247,6 +227,54 @@ __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a
     }
 }
 
+// The wave's share of the tile's rows comes in IQ blocks of 32.  Tiles of eight waves that hold fewer rows run
+// with as few blocks as hold them, so with fewer products, fragment reads and loads (128 experts of 768 x 3072, 64
+// rows in tiles of 256: masked gradient 152 -> 140 us, first forward 186 -> 176; 64 of 4096 x 10240, 256 rows in
+// tiles of 320: 1530 -> 1480).
+template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, int BK, bool P_TRANS, int EPI, bool DROP,
+          bool WGRAD>
+__global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a) {
+    constexpr int PB = 32 * IP * WP, QB = 32 * IQ * WQ;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    int L = blockIdx.y * a.grid_x + blockIdx.x;
+    if (a.by_xcd) {   // block b runs on XCD b mod 8: give each XCD a range of experts
+        const int per = (a.total + 7) >> 3, at = L >> 3;
+        L = (L & 7) * per + at;
+        if (at >= per) return;
+    }
+    if (L >= a.total) return;
+    const int per_e = a.tiles_p * a.tiles_q;
+    const int e = L / per_e, rem = L - e * per_e;
+    int pt, qt;   // the dimension with fewer tiles runs fastest: sharers of the larger operand are neighbours
+    if (a.tiles_q <= a.tiles_p) {
+        pt = rem / a.tiles_q;
+        qt = rem - pt * a.tiles_q;
+    } else {
+        qt = rem / a.tiles_p;
+        pt = rem - qt * a.tiles_p;
+    }
+    const int used = a.kept[e];   // slots with a token
+    const int qlim = WGRAD ? a.Qdim : min(used, a.Qdim), klim = WGRAD ? min(used, a.Kdim) : a.Kdim;
+    const int q0 = qt * QB, p0 = pt * PB;
+    if (q0 >= qlim) return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+#define SW_ROWS(N) \
+    rows_tile<IP, WP, (N) < IQ ? (N) : IQ, IQ, WQ, STAGES, BK, P_TRANS, EPI, DROP, WGRAD>(a, lds, L, e, q0, p0, qlim, \
+                                                                                          klim, lane, wave)
+    if constexpr (WP * WQ == 8 && !WGRAD) {
+        const int blocks = (qlim - q0 + 32 * WQ - 1) / (32 * WQ);
+        if (blocks <= 1) SW_ROWS(1);
+        else if (blocks == 2) SW_ROWS(2);
+        else if (blocks == 3) SW_ROWS(3);
+        else if (blocks == 4 || IQ == 4) SW_ROWS(4);
+        else if constexpr (IQ > 4) SW_ROWS(5);
+    } else {
+        SW_ROWS(IQ);
+    }
+#undef SW_ROWS
+}
+
 template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, int BK, bool P_TRANS, int EPI, bool DROP,
           bool WGRAD>
 static hipError_t rows_launch(RowsArgs a, int E, hipStream_t s) {
@@ -326,8 +354,7 @@ int rows_tile_for(const Workspace &w, int64_t Pdim, int64_t Kdim, int64_t bits_l
         const double reads = m.qb > 64 ? 1. : tq;
         const double bytes = hit * (reads * Pdim * Kdim + mean * (Pdim + Kdim)) * 2.;
         // rows that do not exist are not loaded; the widest tile, which waits for its loads most, gains by it,
-        // down to the time of its products (1.5 us at the sustained MFMA rate: rows that do not exist are
-        // multiplied all the same).  Without that limit it was taken for a handful of rows of a shallow
+        // down to the time of its products at the sustained MFMA rate (1.5 us for all of its rows).  Without that limit it was taken for a handful of rows of a shallow
         // layer: 8 rows, 256 experts of 264 x 2704, masked gradient 123 us, with 32 x 128 tiles 83.
         const double fill = mean / (tq * m.qb);
         const double step = m.tile == ROWS_256x384 ? fmax(m.step * fmin(0.36 + 0.75 * fill, 1.), 1.5) : m.step;
