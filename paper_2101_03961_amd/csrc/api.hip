@@ -74,7 +74,8 @@ Workspace layout_workspace(const switch_config *cfg) {
     w.counts_g = take((size_t)w.n * E * 4);
     w.psum_g = take((size_t)w.n * E * 4);
     w.grp_off = take((size_t)w.n * E * 4);
-    w.loss_part = take(8 * 8);
+    w.loss_part = take(8 * 8 + 4);
+    w.hit = w.loss_part + 8 * 8;
     w.kept = take(E * 4);
     // 128 entries of padding: the GEMMs that gather k-rows read the table a step past an
     // expert's last slot (and mask what they read)

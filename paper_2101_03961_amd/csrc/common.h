@@ -133,6 +133,7 @@ struct Workspace {
     size_t counts_g;            // i32 [n][E]   ... per group
     size_t psum_g;              // f32 [n][E]   sum of router probabilities per group and expert
     size_t loss_part;           // f64 [8]      parts of sum (counts / Tg) (psum / Tg), one per scan block
+    size_t hit;                 // i32          experts with a kept token, before re-routing stages
     size_t grp_off;             // i32 [n][E]   first slot of group g inside expert e's slots:
                                 //              sum of min(counts_g, Cg) over earlier groups
     size_t kept;                // i32 [E]      kept tokens per expert: sum over groups of min(count, Cg)

@@ -34,14 +34,21 @@ struct RowsArgs {
     size_t q_batch, p_batch, c_batch;
     int ldq, ldp, ldc;
     int Qdim, Pdim, Kdim;
-    const int32_t *kept;
+    const int32_t *kept, *hit;
     int tiles_q, tiles_p, total;
+    int E;
     int grid_x;
     int by_xcd;                // an expert's tiles run on one XCD
     const int32_t *slot_token; // dropout: token of each slot, [expert][slots]
     int slots;
     Noise nz;
 };
+
+// A skewed router leaves a layer of many experts a handful of tiles, each a CU's work for all of k: up to
+// kFewTiles tiles are cut into pieces of 64 x 128, one per block (two experts of 512 tokens, 768 x 3072: forward
+// 62 + 97 us -> 36 + 35, data gradients 65 + 107 -> 32 + 31).  Decided by the blocks from the counts, which only the
+// device knows; up to 64 kFewExperts experts.
+constexpr int kFewExperts = 4, kFewTiles = 64;
 
 enum { ROWS_PLAIN = 0, ROWS_RELU = 1, ROWS_MASK = 2 };
 
@@ -236,7 +243,44 @@ template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, int BK, bool P_TR
 __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a) {
     constexpr int PB = 32 * IP * WP, QB = 32 * IQ * WQ;
     extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     int L = blockIdx.y * a.grid_x + blockIdx.x;
+    if constexpr (WP * WQ == 8 && !WGRAD) {
+        if (a.E <= 64 * kFewExperts && *a.hit * a.tiles_p <= kFewTiles) {
+            constexpr int kSubRows = QB / 64, kSubs = kSubRows * (PB / 128);
+            int rows[kFewExperts], tiles = 0;   // row tiles of experts lane, lane + 64, ..
+#pragma unroll
+            for (int m = 0; m < kFewExperts; ++m) {
+                rows[m] = lane + 64 * m < a.E ? (min(a.kept[lane + 64 * m], a.Qdim) + QB - 1) / QB : 0;
+#pragma unroll
+                for (int b = 0; b < 6; ++b)   // (a digit at a time; 64 and more tiles: anything above the limit)
+                    tiles += __popcll(__ballot(rows[m] > 63 || (rows[m] >> b & 1))) << b;
+            }
+            tiles *= a.tiles_p;
+            if (tiles > 0 && tiles <= kFewTiles && tiles * kSubs <= a.total) {
+                int at = L / kSubs, sub = L - at * kSubs, e = 0;
+                if (at >= tiles) return;
+#pragma unroll
+                for (int m = 0; m < kFewExperts; ++m)
+                    for (int i = 0; i < 64; ++i) {
+                        const int n = __builtin_amdgcn_readlane(rows[m], i) * a.tiles_p;
+                        if (at < n) {
+                            e = 64 * m + i;
+                            const int tq = n / a.tiles_p, pt = at / tq;
+                            const int qlim = min(a.kept[e], a.Qdim);
+                            const int q0 = (at - pt * tq) * QB + sub % kSubRows * 64, p0 = pt * PB + sub / kSubRows * 128;
+                            if (q0 < qlim && p0 < a.Pdim)
+                                rows_tile<1, 4, 1, 1, 2, (STAGES * (PB + QB)) / 192, BK, P_TRANS, EPI, DROP, false>(
+                                    a, lds, L, e, q0, p0, qlim, a.Kdim, lane, wave);
+                            return;
+                        }
+                        at -= n;
+                    }
+                return;
+            }
+        }
+    }
     if (a.by_xcd) {   // block b runs on XCD b mod 8: give each XCD a range of experts
         const int per = (a.total + 7) >> 3, at = L >> 3;
         L = (L & 7) * per + at;
@@ -257,8 +301,6 @@ __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a
     const int qlim = WGRAD ? a.Qdim : min(used, a.Qdim), klim = WGRAD ? min(used, a.Kdim) : a.Kdim;
     const int q0 = qt * QB, p0 = pt * PB;
     if (q0 >= qlim) return;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
 #define SW_ROWS(N) \
     rows_tile<IP, WP, (N) < IQ ? (N) : IQ, IQ, WQ, STAGES, BK, P_TRANS, EPI, DROP, WGRAD>(a, lds, L, e, q0, p0, qlim, \
                                                                                           klim, lane, wave)
@@ -290,6 +332,7 @@ static hipError_t rows_launch(RowsArgs a, int E, hipStream_t s) {
     a.tiles_q = (int)ceil_div(a.Qdim, QB);
     a.tiles_p = (int)ceil_div(a.Pdim, PB);
     a.total = a.tiles_q * a.tiles_p * E;
+    a.E = E;
     // Up to 64 rows the shared operand is small next to the weights: the tiles are dealt over all XCDs
     // in order, which stays even when only some experts hold tokens.
     a.by_xcd = WGRAD || QB > 64;
@@ -425,6 +468,7 @@ hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const v
     const int d = (int)w.d, f = (int)w.f, f1 = (int)w.f1, C = (int)w.C, E = (int)w.E;
     RowsArgs a{};
     a.kept = (const int32_t *)(ws + w.kept);
+    a.hit = (const int32_t *)(ws + w.hit);
     a.slot_token = (const int32_t *)(ws + w.slot_token);
     a.slots = C;
     a.nz = w.noise;

@@ -80,6 +80,22 @@ def test_weight_gradients_of_persistent_blocks(T, d, f, E, cf, bias):
     _report("persistent weight gradients %s" % ((T, d, f, E, cf, bias),), errs)
 
 
+@pytest.mark.parametrize("T,d,f,E,cf,n,rate,ffn,rounds", [
+    (12000, 264, 1544, 64, 1.0, 1, 0.0, "relu", 0),     # 256 x 384, one row tile per expert, ragged both ways
+    (16000, 264, 1544, 60, 1.25, 2, 0.1, "relu", 0),    # 320 x 256, two row tiles, groups, dropout
+    (20000, 520, 1544, 40, 1.25, 1, 0.0, "geglu", 0),   # every product
+    (20000, 520, 1544, 40, 1.0, 1, 0.0, "relu", 2),     # re-routing fills more experts than the router asked for
+])
+def test_few_large_tiles_in_pieces(T, d, f, E, cf, n, rate, ffn, rounds):
+    """A collapsed router leaves one or two of many experts with tokens: their large tiles run in pieces."""
+    from parity import compare_full
+    s = SwitchShape("t", T, d, f, E, cf, dtype="bf16", zipf_bias=True, seed_index=53, n_groups=n, expert_dropout=rate,
+                    ffn=ffn, ntlb_rounds=rounds, noise_seed=3)
+    errs, gpu, fwd, _ = compare_full(s, make_inputs(s, _dev()), d_aux=1.0)
+    _report("few tiles %s" % ((T, d, f, E, cf, n, rate, ffn, rounds),), errs)
+    assert rounds or (fwd["expert_counts"] > 0).sum() <= 8
+
+
 @pytest.mark.parametrize("T,d,f,E,cf,n,bias,ffn,rate,rounds", [
     (2000, 264, 520, 5, 1.5, 1, False, "relu", 0.0, 0),    # ragged tiles everywhere
     (4096, 128, 256, 16, 1.0, 2, True, "relu", 0.1, 1),    # groups, skew, dropout, re-routing
