@@ -314,6 +314,10 @@ int rows_wgrad_tile(const Workspace &w, int64_t Qdim, int64_t Pdim);
 int64_t rows_bits_bytes(int tile, int64_t E, int64_t C, int64_t f);
 hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const void *W_in, const void *W_out,
                             void *dW_in, void *dW_out, int tile, hipStream_t s);
+// First layer's data gradient and both weight gradients in one launch, where that pays.
+bool rows_backward_supported(const Workspace &w);
+hipError_t launch_rows_backward(const Workspace &w, char *ws, const void *W_in, const void *W_out, void *dW_in,
+                                void *dW_out, hipStream_t s);
 // Weight gradients with persistent blocks (gemm_wgrad.hip), tile ROWS_256x384 or ROWS_384x256.
 hipError_t launch_gemm_wgrad(GemmKind kind, const Workspace &w, char *ws, void *dW_in, void *dW_out, int tile,
                              hipStream_t s);

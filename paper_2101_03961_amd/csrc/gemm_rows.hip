@@ -238,14 +238,11 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
 // with as few blocks as hold them, so with fewer products, fragment reads and loads (128 experts of 768 x 3072, 64
 // rows in tiles of 256: masked gradient 152 -> 140 us, first forward 186 -> 176; 64 of 4096 x 10240, 256 rows in
 // tiles of 320: 1530 -> 1480).
-template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, int BK, bool P_TRANS, int EPI, bool DROP,
-          bool WGRAD>
-__global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a) {
+template <int IP, int WP, int IQ, int WQ, int STAGES, int BK, bool P_TRANS, int EPI, bool DROP, bool WGRAD>
+__device__ __forceinline__ void rows_block(const RowsArgs &a, char *lds, int L) {
     constexpr int PB = 32 * IP * WP, QB = 32 * IQ * WQ;
-    extern __shared__ __attribute__((aligned(16))) char lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    int L = blockIdx.y * a.grid_x + blockIdx.x;
     if constexpr (WP * WQ == 8 && !WGRAD) {
         if (a.E <= 64 * kFewExperts && *a.hit * a.tiles_p <= kFewTiles) {
             constexpr int kSubRows = QB / 64, kSubs = kSubRows * (PB / 128);
@@ -319,24 +316,56 @@ __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a
 
 template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, int BK, bool P_TRANS, int EPI, bool DROP,
           bool WGRAD>
-static hipError_t rows_launch(RowsArgs a, int E, hipStream_t s) {
-    auto kern = gemm_rows_kernel<IP, WP, IQ, WQ, STAGES, WPE, BK, P_TRANS, EPI, DROP, WGRAD>;
-    constexpr int PB = 32 * IP * WP, QB = 32 * IQ * WQ;
-    constexpr int ring = STAGES * (PB + QB) * BK * 2, turn = WP * WQ * 32 * rows_turn_pitch(IP);
-    constexpr int lds = ring > turn ? ring : turn;
-    static PerDeviceOnce once;
-    hipError_t err = once_per_device(once, [&] {
-        return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    });
-    if (err != hipSuccess) return err;
+__global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    rows_block<IP, WP, IQ, WQ, STAGES, BK, P_TRANS, EPI, DROP, WGRAD>(a, lds, blockIdx.y * a.grid_x + blockIdx.x);
+}
+
+// Three products in one launch: the first layer's data gradient and both weight gradients, which do not depend on
+// each other.  Tiles of four waves.
+struct RowsArgs3 {
+    RowsArgs data, first, second;
+    int end[2];   // blocks of the data gradient, and of it and the first weight gradient (multiples of eight)
+};
+template <int IP, int WP, int IQ, int WQ, int STAGES, int GP, int GWP, int GQ, int GWQ, int GSTAGES>
+__global__ __launch_bounds__(256, 2) void gemm_rows_backward_kernel(RowsArgs3 a) {
+    static_assert(WP * WQ == 4 && GWP * GWQ == 4, "256 threads");
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int L = blockIdx.x;
+    if (L < a.end[0]) rows_block<IP, WP, IQ, WQ, STAGES, 64, false, ROWS_PLAIN, false, false>(a.data, lds, L);
+    else if (L < a.end[1]) rows_block<GP, GWP, GQ, GWQ, GSTAGES, 64, true, ROWS_PLAIN, false, true>(a.first, lds, L - a.end[0]);
+    else rows_block<GP, GWP, GQ, GWQ, GSTAGES, 64, true, ROWS_PLAIN, false, true>(a.second, lds, L - a.end[1]);
+}
+
+constexpr int rows_lds(int IP, int WP, int IQ, int WQ, int STAGES, int BK) {
+    const int ring = STAGES * 32 * (IP * WP + IQ * WQ) * BK * 2, turn = WP * WQ * 32 * rows_turn_pitch(IP);
+    return ring > turn ? ring : turn;
+}
+
+// sets the tile counts; returns the blocks to launch
+static int64_t rows_plan(RowsArgs &a, int E, int QB, int PB, bool wgrad) {
     a.tiles_q = (int)ceil_div(a.Qdim, QB);
     a.tiles_p = (int)ceil_div(a.Pdim, PB);
     a.total = a.tiles_q * a.tiles_p * E;
     a.E = E;
     // Up to 64 rows the shared operand is small next to the weights: the tiles are dealt over all XCDs
     // in order, which stays even when only some experts hold tokens.
-    a.by_xcd = WGRAD || QB > 64;
-    const int64_t blocks = a.by_xcd ? ceil_div(a.total, 8) * 8 : a.total;
+    a.by_xcd = wgrad || QB > 64;
+    return a.by_xcd ? ceil_div(a.total, 8) * 8 : a.total;
+}
+
+template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, int BK, bool P_TRANS, int EPI, bool DROP,
+          bool WGRAD>
+static hipError_t rows_launch(RowsArgs a, int E, hipStream_t s) {
+    auto kern = gemm_rows_kernel<IP, WP, IQ, WQ, STAGES, WPE, BK, P_TRANS, EPI, DROP, WGRAD>;
+    constexpr int PB = 32 * IP * WP, QB = 32 * IQ * WQ;
+    constexpr int lds = rows_lds(IP, WP, IQ, WQ, STAGES, BK);
+    static PerDeviceOnce once;
+    hipError_t err = once_per_device(once, [&] {
+        return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    });
+    if (err != hipSuccess) return err;
+    const int64_t blocks = rows_plan(a, E, QB, PB, WGRAD);
     const int64_t most = kMaxGridThreads / (64 * WP * WQ) / 8 * 8;   // (whole rounds of XCDs)
     a.grid_x = (int)(blocks < most ? blocks : most);
     hipLaunchKernelGGL(kern, dim3((unsigned)a.grid_x, (unsigned)ceil_div(blocks, a.grid_x)), dim3(64 * WP * WQ), lds,
@@ -432,6 +461,10 @@ static const WgradModel kWgradModels[] = {
 // Tile of a weight gradient of Qdim x Pdim; ROWS_NONE: the persistent kernel of gemm_bf16.hip.
 int rows_wgrad_tile(const Workspace &w, int64_t Qdim, int64_t Pdim) {
     const double cap = (double)w.C, mean = fmin((double)w.T / (double)w.E, cap);
+    // Fewer than eight tokens per expert: little but the store, where two small blocks per CU do as well or better
+    // (169 experts of 272 x 2064, 186 tokens: 31 us, 384 x 256 36; 236 of 2000 x 856, 205 tokens: 191, 256 x 384 200;
+    // 147 of 296 x 2464, 96 tokens: 43, 128 x 128 48).
+    if (mean < 8.) return w.E * ceil_div(Qdim, 256) * ceil_div(Pdim, 256) < 256 ? ROWS_128x128 : ROWS_256x128;
     const double steps = rows_tiles(mean, cap, 64);
     int best = ROWS_128x128;
     double best_us = 1e30;
@@ -463,9 +496,10 @@ static hipError_t rows_by_tile(const RowsArgs &a, int E, int tile, hipStream_t s
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const void *W_in, const void *W_out,
-                            void *dW_in, void *dW_out, int tile, hipStream_t s) {
-    const int d = (int)w.d, f = (int)w.f, f1 = (int)w.f1, C = (int)w.C, E = (int)w.E;
+// Operands and output of a product.
+static RowsArgs rows_args(GemmKind kind, const Workspace &w, char *ws, const void *W_in, const void *W_out,
+                          void *dW_in, void *dW_out) {
+    const int d = (int)w.d, f = (int)w.f, f1 = (int)w.f1, C = (int)w.C;
     RowsArgs a{};
     a.kept = (const int32_t *)(ws + w.kept);
     a.hit = (const int32_t *)(ws + w.hit);
@@ -479,31 +513,48 @@ hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const v
         a.Cout = (bf16 *)(ws + c); a.c_batch = (size_t)C * ldc; a.ldc = ldc;
         a.Qdim = C; a.Pdim = ldc; a.Kdim = ldq;
     };
+    auto set_wgrad = [&](size_t q, int ldq, size_t p, int ldp, void *out) {
+        a.Q = (const bf16 *)(ws + q); a.q_batch = (size_t)C * ldq; a.ldq = ldq;
+        a.P = (const bf16 *)(ws + p); a.p_batch = (size_t)C * ldp; a.ldp = ldp;
+        a.Cout = (bf16 *)out; a.c_batch = (size_t)ldq * ldp; a.ldc = ldp;
+        a.Qdim = ldq; a.Pdim = ldp; a.Kdim = C;
+    };
+    switch (kind) {
+    case GEMM_FWD1: set(w.Xd, d, W_in, (size_t)d * f1, f1, w.geglu ? w.H : w.A, f1); break;
+    case GEMM_FWD2: set(w.A, f, W_out, (size_t)f * d, d, w.O, d); break;
+    case GEMM_DGRAD2: set(w.dO, d, W_out, (size_t)f * d, d, w.geglu ? w.dA : w.dH, f); break;
+    case GEMM_DGRAD1: set(w.dH, f1, W_in, (size_t)d * f1, f1, w.dXd, d); break;
+    case GEMM_WGRAD2: set_wgrad(w.A, f, w.dO, d, dW_out); break;
+    case GEMM_WGRAD1: set_wgrad(w.Xd, d, w.dH, f1, dW_in); break;
+    }
+    return a;
+}
+
+hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const void *W_in, const void *W_out,
+                            void *dW_in, void *dW_out, int tile, hipStream_t s) {
+    const int C = (int)w.C, E = (int)w.E;
+    const RowsArgs a = rows_args(kind, w, ws, W_in, W_out, dW_in, dW_out);
     const bool drop = w.noise.dropout;
     if (C == 0 && kind != GEMM_WGRAD1 && kind != GEMM_WGRAD2) return hipSuccess;
     switch (kind) {
     case GEMM_FWD1: {
         ProfScope ps(w.geglu ? "gemm1_fwd" : "gemm1_fwd_relu", s);
-        set(w.Xd, d, W_in, (size_t)d * f1, f1, w.geglu ? w.H : w.A, f1);
         if (w.geglu) return rows_by_tile<true, ROWS_PLAIN, false>(a, E, tile, s);
         if (drop) return rows_by_tile<true, ROWS_RELU, true>(a, E, tile, s);
         return rows_by_tile<true, ROWS_RELU, false>(a, E, tile, s);
     }
     case GEMM_FWD2: {
         ProfScope ps("gemm2_fwd", s);
-        set(w.A, f, W_out, (size_t)f * d, d, w.O, d);
         return rows_by_tile<true, ROWS_PLAIN, false>(a, E, tile, s);
     }
     case GEMM_DGRAD2: {
         ProfScope ps(w.geglu ? "gemm2_dgrad" : "gemm2_dgrad_relumask", s);
-        set(w.dO, d, W_out, (size_t)f * d, d, w.geglu ? w.dA : w.dH, f);
         if (w.geglu) return rows_by_tile<false, ROWS_PLAIN, false>(a, E, tile, s);
         if (drop) return rows_by_tile<false, ROWS_MASK, true>(a, E, tile, s);
         return rows_by_tile<false, ROWS_MASK, false>(a, E, tile, s);
     }
     case GEMM_DGRAD1: {
         ProfScope ps("gemm1_dgrad", s);
-        set(w.dH, f1, W_in, (size_t)d * f1, f1, w.dXd, d);
         return rows_by_tile<false, ROWS_PLAIN, false>(a, E, tile, s);
     }
     case GEMM_WGRAD2:
@@ -511,16 +562,65 @@ hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const v
         if (tile == ROWS_256x384 || tile == ROWS_384x256) return launch_gemm_wgrad(kind, w, ws, dW_in, dW_out, tile, s);
         const bool two = kind == GEMM_WGRAD2;
         ProfScope ps(two ? "gemm2_wgrad" : "gemm1_wgrad", s);
-        a.Q = (const bf16 *)(ws + (two ? w.A : w.Xd)); a.ldq = two ? f : d; a.q_batch = (size_t)C * a.ldq;
-        a.P = (const bf16 *)(ws + (two ? w.dO : w.dH)); a.ldp = two ? d : f1; a.p_batch = (size_t)C * a.ldp;
-        a.Cout = (bf16 *)(two ? dW_out : dW_in); a.ldc = a.ldp; a.c_batch = (size_t)a.ldq * a.ldp;
-        a.Qdim = a.ldq; a.Pdim = a.ldp; a.Kdim = C;
         switch (tile) {
         case ROWS_128x128: return rows_launch<2, 2, 2, 2, 2, 2, 64, true, ROWS_PLAIN, false, true>(a, E, s);
         case ROWS_256x128: return rows_launch<2, 2, 4, 2, 1, 2, 64, true, ROWS_PLAIN, false, true>(a, E, s);
         }
         return hipErrorInvalidValue;
     }
+    }
+    return hipErrorInvalidValue;
+}
+
+template <int IP, int WP, int IQ, int WQ, int STAGES, int GP, int GWP, int GQ, int GWQ, int GSTAGES>
+static hipError_t rows_backward_launch(RowsArgs3 a, int E, hipStream_t s) {
+    auto kern = gemm_rows_backward_kernel<IP, WP, IQ, WQ, STAGES, GP, GWP, GQ, GWQ, GSTAGES>;
+    constexpr int l0 = rows_lds(IP, WP, IQ, WQ, STAGES, 64), l1 = rows_lds(GP, GWP, GQ, GWQ, GSTAGES, 64);
+    constexpr int lds = l0 > l1 ? l0 : l1;
+    static PerDeviceOnce once;
+    hipError_t err = once_per_device(once, [&] {
+        return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    });
+    if (err != hipSuccess) return err;
+    const int64_t n0 = ceil_div(rows_plan(a.data, E, 32 * IQ * WQ, 32 * IP * WP, false), 8) * 8;
+    const int64_t n1 = rows_plan(a.first, E, 32 * GQ * GWQ, 32 * GP * GWP, true);
+    const int64_t n2 = rows_plan(a.second, E, 32 * GQ * GWQ, 32 * GP * GWP, true);
+    a.end[0] = (int)n0;
+    a.end[1] = (int)(n0 + n1);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(n0 + n1 + n2)), dim3(256), lds, s, a);
+    return hipGetLastError();
+}
+
+// Where the tiles of all three have four waves and the weights are small enough for the memory-side cache: there a
+// launch is a good part of a product, and few tiles leave CUs idle at the end of each (us per forward + backward
+// pass, three launches / one: 5003 x 392 x 1000, 10 experts 119 / 109; 256 x 64 x 256, 4 experts 53 / 47; 4096 x 256 x 1024,
+// 64 experts 120 / 108).  Beyond it the streams of the three disturb each other (512 x 768 x 3072, 128 experts:
+// 764 / 778).
+bool rows_backward_supported(const Workspace &w) {
+    const int t = w.gemm_tile[GEMM_DGRAD1], g = w.gemm_tile[GEMM_WGRAD1];
+    return w.C > 0 && !w.fused && t >= ROWS_32x128 && t <= ROWS_128x128 && (g == ROWS_128x128 || g == ROWS_256x128) &&
+           w.gemm_tile[GEMM_WGRAD2] == g && (double)w.E * (double)w.d * (double)(w.f1 + w.f) * 2. <= 256e6 &&
+           w.E * (ceil_div(w.C, 32) * ceil_div(w.d, 128) + 2 * ceil_div(w.d, 128) * ceil_div(w.f1, 128)) < 1 << 22;
+}
+
+hipError_t launch_rows_backward(const Workspace &w, char *ws, const void *W_in, const void *W_out, void *dW_in,
+                                void *dW_out, hipStream_t s) {
+    ProfScope ps("gemm_backward", s);
+    RowsArgs3 a{};
+    a.data = rows_args(GEMM_DGRAD1, w, ws, W_in, W_out, dW_in, dW_out);
+    a.first = rows_args(GEMM_WGRAD1, w, ws, W_in, W_out, dW_in, dW_out);
+    a.second = rows_args(GEMM_WGRAD2, w, ws, W_in, W_out, dW_in, dW_out);
+    const int E = (int)w.E;
+    const bool small = w.gemm_tile[GEMM_WGRAD1] == ROWS_128x128;
+    switch (w.gemm_tile[GEMM_DGRAD1]) {
+#define SW_THREE(...)                                                             \
+    return small ? rows_backward_launch<__VA_ARGS__, 2, 2, 2, 2, 2>(a, E, s)      \
+                 : rows_backward_launch<__VA_ARGS__, 2, 2, 4, 2, 1>(a, E, s)
+    case ROWS_32x128: SW_THREE(1, 4, 1, 1, 3);
+    case ROWS_64x256: SW_THREE(2, 4, 2, 1, 2);
+    case ROWS_96x128: SW_THREE(1, 4, 3, 1, 2);
+    case ROWS_128x128: SW_THREE(2, 2, 2, 2, 2);
+#undef SW_THREE
     }
     return hipErrorInvalidValue;
 }

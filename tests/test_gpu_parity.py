@@ -80,6 +80,18 @@ def test_weight_gradients_of_persistent_blocks(T, d, f, E, cf, bias):
     _report("persistent weight gradients %s" % ((T, d, f, E, cf, bias),), errs)
 
 
+@pytest.mark.parametrize("T,d,f,E,cf,ffn,bias", [
+    (5000, 520, 776, 24, 1.25, "relu", False),   # tiles of 128 x 128, gradients of 256 x 128, ragged in all of them
+    (3100, 264, 776, 11, 1.25, "geglu", True),   # 96 x 128 and 128 x 128, experts without tokens
+    (500, 136, 520, 13, 2.0, "relu", False),     # 32 x 128 and 128 x 128
+])
+def test_three_backward_products_in_one_launch(T, d, f, E, cf, ffn, bias):
+    from parity import compare_full
+    s = SwitchShape("t", T, d, f, E, cf, dtype="bf16", zipf_bias=bias, seed_index=59, ffn=ffn)
+    errs, _, _, _ = compare_full(s, make_inputs(s, _dev()), d_aux=1.0)
+    _report("three products %s" % ((T, d, f, E, cf, ffn, bias),), errs)
+
+
 @pytest.mark.parametrize("T,d,f,E,cf,n,rate,ffn,rounds", [
     (12000, 264, 1544, 64, 1.0, 1, 0.0, "relu", 0),     # 256 x 384, one row tile per expert, ragged both ways
     (16000, 264, 1544, 60, 1.25, 2, 0.1, "relu", 0),    # 320 x 256, two row tiles, groups, dropout

@@ -100,8 +100,7 @@ def test_tile_follows_the_rows_of_an_expert(recorder, T, d, f, E, cf, first, sec
     (2400, 264, 904, 120, 1.25, "wgrad 4,2,3,4", "wgrad 3,4,4,2"),
     (9000, 264, 760, 80, 1.25, "wgrad 4,2,3,4", "wgrad 3,4,4,2"),
     (32768, 512, 1024, 32, 1.0, "bf16", "bf16"),
-    (60000, 128, 512, 16, 1.0, "rows 2,2,2,2", "rows 2,2,2,2"),
-    (4096, 256, 1024, 64, 1.0, "rows 2,2,4,2", "rows 2,2,4,2"),
+    (512, 768, 3072, 128, 4.0, "rows 2,2,4,2", "rows 2,2,4,2"),
 ])
 def test_kernel_of_the_weight_gradients(recorder, T, d, f, E, cf, first, second):
     (status, _, _, launches), = recorder(call("backward", T, d, f, E, cf))
@@ -112,6 +111,21 @@ def test_kernel_of_the_weight_gradients(recorder, T, d, f, E, cf, first, second)
         if m and (m[1] == "wgrad" or m[1] == "rows" and m[2].endswith("Lb1E") or m[1] == "bf16" and m[2].startswith("Lb1ELb1E")):
             got.append(m[1] + ("" if m[1] == "bf16" else " " + ",".join(re.findall(r"Li(\d+)E", m[2])[:4])))
     assert got[:2] == [first, second]
+
+
+# Small layers: the first layer's data gradient and both weight gradients in one launch (tiles of four waves and
+# weights that fit the memory-side cache), else one launch each.
+@pytest.mark.parametrize("T,d,f,E,cf,data,weights", [
+    (5003, 392, 1000, 10, 1.25, "1,4,3,1,2", "2,2,2,2,2"), (60000, 128, 512, 16, 1.0, "1,4,3,1,2", "2,2,2,2,2"),
+    (4096, 256, 1024, 64, 1.0, "1,4,3,1,2", "2,2,4,2,1"), (300, 512, 2048, 16, 2.0, "1,4,1,1,3", "2,2,4,2,1"),
+    (512, 768, 3072, 128, 4.0, None, None), (65536, 768, 3072, 128, 1.0, None, None),
+])
+def test_small_layers_take_three_products_in_one_launch(recorder, T, d, f, E, cf, data, weights):
+    (status, _, _, launches), = recorder(call("backward", T, d, f, E, cf))
+    assert status == 0
+    got = [re.findall(r"Li(\d+)E", k[0]) for k in launches if "gemm_rows_backward" in k[0]]
+    assert [(",".join(g[:5]), ",".join(g[5:])) for g in got] == ([(data, weights)] if data else [])
+    assert sum("gemm_" in k[0] and "router" not in k[0] for k in launches) >= (2 if data else 4)
 
 
 # fp32 products: matrix cores while an expert's matrices fit a buffer descriptor, else the FMA kernel
