@@ -139,6 +139,8 @@ struct Workspace {
     size_t kept;                // i32 [E]      kept tokens per expert: sum over groups of min(count, Cg)
     int fused;                  // bf16: dispatch and combine run inside the GEMMs (x, dy gathered by
                                 //   the slot -> token table, y written by the second GEMM)
+    bool combine_in_gemm;       // the second GEMM's epilogue writes y too (small tiles, fp32); rows without a slot are
+                                //   cleared where the slots are assigned
     int gemm_tile[6];           // RowsTile of each GemmKind; ROWS_NONE: the persistent kernel (bf16)
     size_t slot_token;          // i32 [E][C] + 128  token held by each slot (valid for slot < kept[e])
     size_t slot_gate;           // f32 [E][C]   gate of that token (the probability that scales its output)
@@ -313,7 +315,7 @@ int rows_tile_for(const Workspace &w, int64_t Pdim, int64_t Kdim, int64_t bits_l
 int rows_wgrad_tile(const Workspace &w, int64_t Qdim, int64_t Pdim);
 int64_t rows_bits_bytes(int tile, int64_t E, int64_t C, int64_t f);
 hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const void *W_in, const void *W_out,
-                            void *dW_in, void *dW_out, int tile, hipStream_t s);
+                            void *dW_in, void *dW_out, void *y, int tile, hipStream_t s);
 // First layer's data gradient and both weight gradients in one launch, where that pays.
 bool rows_backward_supported(const Workspace &w);
 hipError_t launch_rows_backward(const Workspace &w, char *ws, const void *W_in, const void *W_out, void *dW_in,
@@ -324,11 +326,15 @@ hipError_t launch_gemm_wgrad(GemmKind kind, const Workspace &w, char *ws, void *
 hipError_t launch_gemm_f32(GemmKind kind, const Workspace &w, char *ws, const void *W_in,
                            const void *W_out, void *dW_in, void *dW_out, const TokenMajor &tm,
                            hipStream_t s);
-// Dispatch and combine inside the GEMMs: the rows of y of tokens without a slot are cleared by
+// fp32: a product of Qdim x Pdim runs on the matrix cores
+bool gemm_f32_on_mfma(const Workspace &w, int64_t Qdim, int64_t Pdim);
+// Combine inside the second GEMM: the rows of y of tokens without a slot are cleared by
 // the kernel that assigns the slots (launch_dispatch) -- unless re-routing stages follow it and
 // hand some of those tokens a slot after all; then launch_zero_dropped runs behind them.
-inline bool zero_rows_with_positions(const Workspace &w) { return w.fused && w.ntlb_rounds == 0; }
-// fused path: +0 rows of y for the tokens without a slot; gate gradient from the saved outputs
+inline bool zero_rows_with_positions(const Workspace &w) {
+    return (w.fused || w.combine_in_gemm) && w.ntlb_rounds == 0;
+}
+// +0 rows of y for the tokens without a slot; fused path: gate gradient from the saved outputs
 hipError_t launch_zero_dropped(const Workspace &w, char *ws, void *y, hipStream_t s);
 hipError_t launch_gate_grad(const Workspace &w, const void *dy, char *ws, hipStream_t s);
 

@@ -398,7 +398,7 @@ hipError_t launch_zero_dropped(const Workspace &w, char *ws, void *y, hipStream_
     ProfScope ps("zero_dropped", s);
     hipLaunchKernelGGL(zero_dropped_kernel, row_grid(w.T), dim3(256), 0,
                        s, (Chunk16 *)y, (const int32_t *)(ws + w.tok_slot), (int)w.T,
-                       (int)(w.d / 8));
+                       (int)(w.d * w.elt / 16));
     return hipGetLastError();
 }
 

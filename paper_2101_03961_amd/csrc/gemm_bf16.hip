@@ -895,7 +895,7 @@ hipError_t launch_gemm_bf16(GemmKind kind, const Workspace &w, char *ws, const v
                             const void *W_out, void *dW_in, void *dW_out, const TokenMajor &tm,
                             hipStream_t s) {
     const int d = (int)w.d, f = (int)w.f, f1 = (int)w.f1, C = (int)w.C, E = (int)w.E;
-    if (const int tile = w.gemm_tile[kind]) return launch_gemm_rows(kind, w, ws, W_in, W_out, dW_in, dW_out, tile, s);
+    if (const int tile = w.gemm_tile[kind]) return launch_gemm_rows(kind, w, ws, W_in, W_out, dW_in, dW_out, tm.y, tile, s);
     GemmArgs a{};
     a.kept = (const int32_t *)(ws + w.kept);
     const bf16 *Xd = (const bf16 *)(ws + w.Xd);

@@ -22,7 +22,9 @@ struct GemmF32Args {
     int k_limited;       // reduction runs over k < kept[e]
     int epi;             // 0 none, 1 ReLU (+ expert dropout), 2 multiply by [mask > 0] (and by
                          // the dropout scale of the surviving units)
-    const int32_t *slot_token;   // epi 1 with dropout: token of slot e * slots + q
+    const int32_t *slot_token;   // epi 1 with dropout, F32_COMBINE: token of slot e * slots + q
+    const float *slot_gate;      // F32_COMBINE: its gate, and the output rows by token
+    float *y;
     long slots;
     Noise nz;
 };
@@ -165,7 +167,7 @@ template <int R, int NW> struct F32Trans {
     }
 };
 
-enum { F32_PLAIN = 0, F32_RELU = 1, F32_MASK = 2 };
+enum { F32_PLAIN = 0, F32_RELU = 1, F32_MASK = 2, F32_COMBINE = 3 };   // (see gemm_rows.hip)
 
 template <int IP, int WP, int IQ, int WQ, bool Q_TRANS, bool P_TRANS, int EPI>
 __global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32Args a, int tiles_q, int tiles_p) {
@@ -254,6 +256,12 @@ __global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32A
         uint32_t row_idx = 0;   // index of the token's first hidden unit in the dropout stream
         if (EPI == F32_RELU && a.nz.dropout)
             row_idx = (uint32_t)a.slot_token[(size_t)e * a.slots + q] * (uint32_t)a.Pdim;
+        int tok = 0;
+        float gate = 0.f;
+        if (EPI == F32_COMBINE) {
+            tok = a.slot_token[(size_t)e * a.slots + q];
+            gate = a.slot_gate[(size_t)e * a.slots + q];
+        }
 #pragma unroll
         for (int i = 0; i < IP; ++i)
 #pragma unroll
@@ -281,6 +289,8 @@ __global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32A
                     v[3] = m.w > 0.f ? v[3] * a.nz.drop_scale : 0.f;
                 }
                 *(float4 *)(Cout + at) = make_float4(v[0], v[1], v[2], v[3]);
+                if (EPI == F32_COMBINE)
+                    *(float4 *)(a.y + (size_t)tok * a.ldc + p) = make_float4(v[0] * gate, v[1] * gate, v[2] * gate, v[3] * gate);
             }
     }
 }
@@ -302,14 +312,23 @@ static hipError_t f32_mfma(const GemmF32Args &a, int E, hipStream_t s) {
     return f32_launch<1, 2, 1, 2, Q_TRANS, P_TRANS, EPI>(a, E, s);
 }
 
+// The matrix-core kernel addresses one expert's matrices through 32-bit buffer descriptors, and all of a
+// product's tiles (64 x 128, 256 threads, or half of that) lie in one dimension of the grid.
+bool gemm_f32_on_mfma(const Workspace &w, int64_t Qdim, int64_t Pdim) {
+    const double d = (double)w.d, f1 = (double)w.f1, C = (double)w.C, most = fmax(fmax(d * f1, C * d), C * f1) * 4.;
+    return most < 2147483647. && w.E * ceil_div(Qdim, 64) * ceil_div(Pdim, 128) * 256 <= kMaxGridThreads;
+}
+
 hipError_t launch_gemm_f32(GemmKind kind, const Workspace &w, char *ws, const void *W_in,
-                           const void *W_out, void *dW_in, void *dW_out, const TokenMajor &,
+                           const void *W_out, void *dW_in, void *dW_out, const TokenMajor &tm,
                            hipStream_t s) {
     const long d = w.d, f = w.f, f1 = w.f1, C = w.C;
     GemmF32Args a{};
     a.kept = (const int32_t *)(ws + w.kept);
     a.slot_token = (const int32_t *)(ws + w.slot_token);
     a.slots = C;
+    a.slot_gate = (const float *)(ws + w.slot_gate);
+    a.y = (float *)tm.y;
     a.nz = w.noise;
     const float *Xd = (const float *)(ws + w.Xd);
     float *A = (float *)(ws + w.A);
@@ -364,16 +383,13 @@ hipError_t launch_gemm_f32(GemmKind kind, const Workspace &w, char *ws, const vo
     }
     if (a.Qdim == 0) return hipSuccess;   // capacity 0 and a slot-indexed output: nothing to do
     ProfScope ps(name, s);
-    // the matrix-core kernel addresses one expert's matrices through 32-bit buffer descriptors, and all its
-    // tiles (64 x 128, 256 threads, or half of that) lie in one dimension of the grid
-    const double most = fmax(fmax((double)d * f1, (double)C * d), (double)C * f1) * 4.;
-    const int64_t tiles = w.E * ceil_div(a.Qdim, 64) * ceil_div(a.Pdim, 128);
-    if (most < 2147483647. && tiles * 256 <= kMaxGridThreads) {
+    if (gemm_f32_on_mfma(w, a.Qdim, a.Pdim)) {
         const int E = (int)w.E;
         switch (kind) {
         case GEMM_FWD1:
             return w.geglu ? f32_mfma<false, true, F32_PLAIN>(a, E, s) : f32_mfma<false, true, F32_RELU>(a, E, s);
-        case GEMM_FWD2: return f32_mfma<false, true, F32_PLAIN>(a, E, s);
+        case GEMM_FWD2:
+            return w.combine_in_gemm ? f32_mfma<false, true, F32_COMBINE>(a, E, s) : f32_mfma<false, true, F32_PLAIN>(a, E, s);
         case GEMM_DGRAD2:
             return w.geglu ? f32_mfma<false, false, F32_PLAIN>(a, E, s) : f32_mfma<false, false, F32_MASK>(a, E, s);
         case GEMM_DGRAD1: return f32_mfma<false, false, F32_PLAIN>(a, E, s);

@@ -39,7 +39,9 @@ struct RowsArgs {
     int E;
     int grid_x;
     int by_xcd;                // an expert's tiles run on one XCD
-    const int32_t *slot_token; // dropout: token of each slot, [expert][slots]
+    const int32_t *slot_token; // dropout, ROWS_COMBINE: token of each slot, [expert][slots]
+    const float *slot_gate;    // ROWS_COMBINE: and its gate
+    bf16 *y;                   // ROWS_COMBINE: [token][ldc]
     int slots;
     Noise nz;
 };
@@ -50,7 +52,8 @@ struct RowsArgs {
 // device knows; up to 64 kFewExperts experts.
 constexpr int kFewExperts = 4, kFewTiles = 64;
 
-enum { ROWS_PLAIN = 0, ROWS_RELU = 1, ROWS_MASK = 2 };
+// ROWS_COMBINE: the rows, times the gates of their tokens, also go to the tokens' rows of y.
+enum { ROWS_PLAIN = 0, ROWS_RELU = 1, ROWS_MASK = 2, ROWS_COMBINE = 3 };
 
 // The tile's products and epilogue, with IQ row blocks of 32 per wave (IQ_MAX of them fit the tile).
 // Mask bits: one byte per 16-byte piece of the output (bits 0..3: low halves of its four words, 4..7:
@@ -205,6 +208,16 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
                 *(uint2 *)(ep + wrow * kPitch + ((ch ^ swz(wrow)) << 4) + ((lane >> 5) << 3)) = o;
             }
         uint32_t nb[2] = {0u, 0u};
+        int tok[kPasses];
+        float gate[kPasses];
+        if (EPI == ROWS_COMBINE)
+#pragma unroll
+            for (int x = 0; x < kPasses; ++x) {
+                const bool in = 32 * j < left[x];
+                const size_t at = (size_t)e * a.slots + (in ? qw + (x * 64 + lane) / kChunks : 0);
+                tok[x] = in ? a.slot_token[at] : -1;
+                gate[x] = a.slot_gate[at];
+            }
 #pragma unroll
         for (int x = 0; x < kPasses; ++x) {
             const int at = x * 64 + lane;
@@ -224,6 +237,14 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
             }
             const uint32_t off = 32 * j < left[x] ? cvoff[x] + (uint32_t)j * c_step : kOobOffset;
             __builtin_amdgcn_raw_buffer_store_b128(val, crsrc, (int)off, 0, 0);
+            if (EPI == ROWS_COMBINE && tok[x] >= 0) {   // of the rounded values, as the combine pass
+                u32x4 out;
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+                    out[w] = pack_bf16(__uint_as_float(val[w] << 16) * gate[x],
+                                       __uint_as_float(val[w] & 0xffff0000u) * gate[x]);
+                *(u32x4 *)(a.y + (size_t)tok[x] * a.ldc + pw + c * 8) = out;
+            }
         }
         if (EPI == ROWS_RELU) {
             uint8_t *b = bits_of(j);
@@ -489,6 +510,8 @@ static hipError_t rows_by_tile(const RowsArgs &a, int E, int tile, hipStream_t s
     case ROWS_64x256: return rows_launch<2, 4, 2, 1, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
     case ROWS_96x128: return rows_launch<1, 4, 3, 1, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
     case ROWS_128x128: return rows_launch<2, 2, 2, 2, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
+    }
+    if constexpr (EPI != ROWS_COMBINE) switch (tile) {
     case ROWS_256x256: return rows_launch<2, 4, 4, 2, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
     case ROWS_320x256: return rows_launch<2, 4, 5, 2, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
     case ROWS_256x384: return rows_launch<3, 4, 4, 2, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
@@ -531,9 +554,11 @@ static RowsArgs rows_args(GemmKind kind, const Workspace &w, char *ws, const voi
 }
 
 hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const void *W_in, const void *W_out,
-                            void *dW_in, void *dW_out, int tile, hipStream_t s) {
+                            void *dW_in, void *dW_out, void *y, int tile, hipStream_t s) {
     const int C = (int)w.C, E = (int)w.E;
-    const RowsArgs a = rows_args(kind, w, ws, W_in, W_out, dW_in, dW_out);
+    RowsArgs a = rows_args(kind, w, ws, W_in, W_out, dW_in, dW_out);
+    a.slot_gate = (const float *)(ws + w.slot_gate);
+    a.y = (bf16 *)y;
     const bool drop = w.noise.dropout;
     if (C == 0 && kind != GEMM_WGRAD1 && kind != GEMM_WGRAD2) return hipSuccess;
     switch (kind) {
@@ -545,6 +570,7 @@ hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const v
     }
     case GEMM_FWD2: {
         ProfScope ps("gemm2_fwd", s);
+        if (w.combine_in_gemm) return rows_by_tile<true, ROWS_COMBINE, false>(a, E, tile, s);
         return rows_by_tile<true, ROWS_PLAIN, false>(a, E, tile, s);
     }
     case GEMM_DGRAD2: {
