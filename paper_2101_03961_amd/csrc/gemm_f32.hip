@@ -130,8 +130,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
 // Two-level sums as in the FMA kernel: chains of kF32Flush products are folded into a total.
 //
 // k runs in order: MFMA m of a group of eight multiplies the pair (2 m, 2 m + 1), so that every
-// sum is the same chain of fused multiply-adds as the FMA kernel's, bit for bit.
-// [k][row] operand: LDS [32 k][R]; rows 32 apart trade places in odd k-rows, so that the two half
+// sum is the same chain of fused multiply-adds as the FMA kernel's, bit for bit.  (KS = 4: wave w of a 32 x 32 tile
+// takes eight k of every 32, and the four sums are added up in order.)
+// [k][row] operand: LDS [32 k][R]; rows 32 apart (R > 32) trade places in odd k-rows, so that the two half
 // waves of a read (neighbouring k) use different banks.
 template <int R, int NW> struct F32Trans {
     static constexpr int kLoads = R * 32 * 4 / (1024 * NW);
@@ -145,13 +146,13 @@ template <int R, int NW> struct F32Trans {
         rsrc = make_rsrc(base, (uint32_t)klim * (uint32_t)ld * 4u);
         k_step = (uint32_t)ld * 4u;
         const int kk = lane / kChunks;
-        const int row = row0 + ((lane % kChunks) ^ ((kk & 1) << 3)) * 4;
+        const int row = row0 + ((lane % kChunks) ^ (R > 32 ? (kk & 1) << 3 : 0)) * 4;
         voff = row < rowlim ? ((uint32_t)(wave * kLoads * kRowsPerLoad + kk) * (uint32_t)ld + (uint32_t)row) * 4u
                             : kOobOffset;
     }
     __device__ __forceinline__ void init_frag(int lane, int frag_row) {
         const int h = lane >> 5;
-        frag0 = (uint32_t)((h * R + ((frag_row + (lane & 31)) ^ (h << 5))) * 4);
+        frag0 = (uint32_t)((h * R + ((frag_row + (lane & 31)) ^ (R > 32 ? h << 5 : 0))) * 4);
     }
     __device__ __forceinline__ void issue_one(uint32_t st, int k0, int wave, int i) const {
         dma16(rsrc, voff, (uint32_t)(k0 + i * kRowsPerLoad) * k_step,
@@ -169,11 +170,12 @@ template <int R, int NW> struct F32Trans {
 
 enum { F32_PLAIN = 0, F32_RELU = 1, F32_MASK = 2, F32_COMBINE = 3 };   // (see gemm_rows.hip)
 
-template <int IP, int WP, int IQ, int WQ, bool Q_TRANS, bool P_TRANS, int EPI>
-__global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32Args a, int tiles_q, int tiles_p) {
-    constexpr int NW = WP * WQ, PB = 32 * IP * WP, QB = 32 * IQ * WQ;
+template <int IP, int WP, int IQ, int WQ, int KS, int STAGES, bool Q_TRANS, bool P_TRANS, int EPI>
+__global__ __launch_bounds__(64 * WP * WQ * KS, 2) void gemm_f32_mfma_kernel(GemmF32Args a, int tiles_q, int tiles_p) {
+    constexpr int NW = WP * WQ * KS, PB = 32 * IP * WP, QB = 32 * IQ * WQ;
     constexpr int kPBytes = PB * 128, kStage = (PB + QB) * 128;
-    __shared__ __attribute__((aligned(16))) char lds[2 * kStage];
+    static_assert(KS == 1 || (KS == 4 && IP * IQ * WP * WQ == 1), "four waves share a tile's k, or one has all");
+    __shared__ __attribute__((aligned(16))) char lds[STAGES * kStage];
     const int per_e = tiles_q * tiles_p;
     const int e = blockIdx.x / per_e, rem = blockIdx.x - e * per_e;
     const int pt = rem / tiles_q, qt = rem - pt * tiles_q;
@@ -184,7 +186,7 @@ __global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32A
     if (q0 >= qlim) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int wp = wave % WP, wq = wave / WP;
+    const int wp = wave % WP, wq = wave / WP % WQ;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
     const bool live = q0 + wq * 32 * IQ < qlim && p0 + wp * 32 * IP < a.Pdim;
 
@@ -204,20 +206,22 @@ __global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32A
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = total[i][j][r] = 0.f;
 
+    constexpr int kLoads = decltype(op)::kLoads + decltype(oq)::kLoads;
     auto issue = [&](int kt) {   // k past the end: zeros
-        const uint32_t at = lds0 + (uint32_t)((kt & 1) * kStage);
+        const uint32_t at = lds0 + (uint32_t)(kt % STAGES * kStage);
 #pragma unroll
         for (int i = 0; i < decltype(op)::kLoads; ++i) op.issue_one(at, kt * 32, wave, i);
 #pragma unroll
         for (int i = 0; i < decltype(oq)::kLoads; ++i) oq.issue_one(at + kPBytes, kt * 32, wave, i);
     };
-    if (nk > 0) issue(0);
+#pragma unroll
+    for (int st = 0; st < STAGES - 1; ++st) issue(st);
     for (int kt = 0; kt < nk; ++kt) {
-        rows_wait_vmcnt<0>();
+        rows_wait_vmcnt<(STAGES - 2) * kLoads>();
         __syncthreads();   // step kt has landed, step kt - 1 is read
-        if (kt + 1 < nk) issue(kt + 1);
+        issue(kt + STAGES - 1);
         if (!live) continue;
-        const char *sp = lds + (kt & 1) * kStage, *sq = sp + kPBytes;
+        const char *sp = lds + kt % STAGES * kStage, *sq = sp + kPBytes;
         if (kt != 0 && kt % (kF32Flush / 32) == 0) {
 #pragma unroll
             for (int i = 0; i < IP; ++i)
@@ -230,7 +234,8 @@ __global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32A
                     }
         }
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
+        for (int kk = 0; kk < 4 / KS; ++kk) {
+            const int ks = KS == 1 ? kk : wave;
             f32x4 fp[IP], fq[IQ];
 #pragma unroll
             for (int i = 0; i < IP; ++i) fp[i] = op.frag4(sp, i, ks);
@@ -245,7 +250,28 @@ __global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32A
                         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fp[i][m], fq[j][m], acc[i][j], 0, 0, 0);
         }
     }
+    rows_wait_vmcnt<0>();   // the trailing (zero) loads
     if (!live) return;
+    if constexpr (KS == 4) {   // the four sums, in order; wave g goes on with columns 8 g ..
+        __syncthreads();
+        f32x4 *part = (f32x4 *)lds;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            f32x4 v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = total[0][0][4 * g + r] + acc[0][0][4 * g + r];
+            part[(wave * 4 + g) * 64 + lane] = v;
+        }
+        __syncthreads();
+        f32x4 v = part[wave * 64 + lane];
+#pragma unroll
+        for (int q = 1; q < 4; ++q) v += part[(q * 4 + wave) * 64 + lane];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            total[0][0][r] = v[r];
+            acc[0][0][r] = 0.f;
+        }
+    }
     // a lane holds, for row q = lane % 32 of each tile, columns 8 g + 4 (lane / 32) .. + 3
     float *Cout = a.Cout + (size_t)e * a.c_batch;
     const float *mask = EPI == F32_MASK ? a.mask + (size_t)e * a.c_batch : nullptr;
@@ -265,8 +291,8 @@ __global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32A
 #pragma unroll
         for (int i = 0; i < IP; ++i)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int p = p0 + (wp * IP + i) * 32 + 8 * g + ((lane >> 5) << 2);
+            for (int g = 0; g < (KS == 4 ? 1 : 4); ++g) {
+                const int p = p0 + (wp * IP + i) * 32 + 8 * (KS == 4 ? wave : g) + ((lane >> 5) << 2);
                 if (p >= a.Pdim) continue;   // Pdim is a multiple of 4: four columns are in or out
                 float v[4];
 #pragma unroll
@@ -295,11 +321,11 @@ __global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32A
     }
 }
 
-template <int IP, int WP, int IQ, int WQ, bool Q_TRANS, bool P_TRANS, int EPI>
+template <int IP, int WP, int IQ, int WQ, int KS, int STAGES, bool Q_TRANS, bool P_TRANS, int EPI>
 static hipError_t f32_launch(const GemmF32Args &a, int E, hipStream_t s) {
     const int tq = (int)ceil_div(a.Qdim, 32 * IQ * WQ), tp = (int)ceil_div(a.Pdim, 32 * IP * WP);
-    hipLaunchKernelGGL((gemm_f32_mfma_kernel<IP, WP, IQ, WQ, Q_TRANS, P_TRANS, EPI>),
-                       dim3((unsigned)(tq * tp * E)), dim3(64 * WP * WQ), 0, s, a, tq, tp);
+    hipLaunchKernelGGL((gemm_f32_mfma_kernel<IP, WP, IQ, WQ, KS, STAGES, Q_TRANS, P_TRANS, EPI>),
+                       dim3((unsigned)(tq * tp * E)), dim3(64 * WP * WQ * KS), 0, s, a, tq, tp);
     return hipGetLastError();
 }
 
@@ -308,8 +334,14 @@ static hipError_t f32_mfma(const GemmF32Args &a, int E, hipStream_t s) {
     // 64 x 64 keeps the chip even (a 128 x 128 tile takes 573 instead of 364 us in the second GEMM of
     // 32 experts x 256 tokens x 768 x 3072); twice as wide is 2-8 % faster where there are many tiles.
     if (E * ceil_div(a.Qdim, 64) * ceil_div(a.Pdim, 128) >= 1024)
-        return f32_launch<2, 2, 1, 2, Q_TRANS, P_TRANS, EPI>(a, E, s);
-    return f32_launch<1, 2, 1, 2, Q_TRANS, P_TRANS, EPI>(a, E, s);
+        return f32_launch<2, 2, 1, 2, 1, 2, Q_TRANS, P_TRANS, EPI>(a, E, s);
+    // Few tiles: a 64 x 64 tile keeps one CU's matrix cores busy for 1024 cycles per 32 k, whatever the others do.  Tiles
+    // of 32 x 32 whose four waves take a quarter of the k each spread over four times as many (us per forward +
+    // backward pass, 256 x 64 x 256, 4 experts 70 / 55; 1000 x 512 x 1536, 8 experts 222 / 174; at 512 tiles of 64 x 64
+    // they lose: 2000 x 256 x 1024, 8 experts, first GEMM 17 / 20).
+    if (E * ceil_div(a.Qdim, 64) * ceil_div(a.Pdim, 64) <= 384)
+        return f32_launch<1, 1, 1, 1, 4, 4, Q_TRANS, P_TRANS, EPI>(a, E, s);
+    return f32_launch<1, 2, 1, 2, 1, 2, Q_TRANS, P_TRANS, EPI>(a, E, s);
 }
 
 // The matrix-core kernel addresses one expert's matrices through 32-bit buffer descriptors, and all of a
