@@ -96,6 +96,9 @@ def kernel_work(shape, kept, elt):
         "gemm2_wgrad": (gemm, w_bytes + kept * (f + d) * elt, "mfma"),
         "gemm1_dgrad": (gemm, w_bytes + kept * (f + d) * elt, "mfma"),
         "gemm1_wgrad": (gemm, w_bytes + kept * (d + f) * elt, "mfma"),
+        # small layers: first layer's data gradient and both weight gradients in one launch
+        "gemm_backward": (2.0 * gemm_in + gemm, 2.0 * (w_in_bytes + kept * (f1 + d) * elt) + w_bytes +
+                          kept * (f + d) * elt, "mfma"),
         "router_dlogits": (0.0, T * E * 4 + T * 512 + T * 8, "hbm"),
         "router_dx_mfma": (6.0 * T * d * E, T * 512 + kept * d * elt + T * d * elt, "hbm"),
         "router_dWr_mfma": (4.0 * T * d * E, (T * 2 * dpad * 2 if jit else T * d * elt) + T * 512, "hbm"),
