@@ -354,8 +354,10 @@ __global__ __launch_bounds__(256, 2) void gemm_rows_backward_kernel(RowsArgs3 a)
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int L = blockIdx.x;
     if (L < a.end[0]) rows_block<IP, WP, IQ, WQ, STAGES, 64, false, ROWS_PLAIN, false, false>(a.data, lds, L);
-    else if (L < a.end[1]) rows_block<GP, GWP, GQ, GWQ, GSTAGES, 64, true, ROWS_PLAIN, false, true>(a.first, lds, L - a.end[0]);
-    else rows_block<GP, GWP, GQ, GWQ, GSTAGES, 64, true, ROWS_PLAIN, false, true>(a.second, lds, L - a.end[1]);
+    else if (L < a.end[1])
+        rows_block<GP, GWP, GQ, GWQ, GSTAGES, 64, true, ROWS_PLAIN, false, true>(a.first, lds, L - a.end[0]);
+    else
+        rows_block<GP, GWP, GQ, GWQ, GSTAGES, 64, true, ROWS_PLAIN, false, true>(a.second, lds, L - a.end[1]);
 }
 
 constexpr int rows_lds(int IP, int WP, int IQ, int WQ, int STAGES, int BK) {
@@ -447,8 +449,9 @@ int rows_tile_for(const Workspace &w, int64_t Pdim, int64_t Kdim, int64_t bits_l
         const double reads = m.qb > 64 ? 1. : tq;
         const double bytes = hit * (reads * Pdim * Kdim + mean * (Pdim + Kdim)) * 2.;
         // rows that do not exist are not loaded; the widest tile, which waits for its loads most, gains by it,
-        // down to the time of its products at the sustained MFMA rate (1.5 us for all of its rows).  Without that limit it was taken for a handful of rows of a shallow
-        // layer: 8 rows, 256 experts of 264 x 2704, masked gradient 123 us, with 32 x 128 tiles 83.
+        // down to the time of its products at the sustained MFMA rate (1.5 us for all of its rows).  Without that
+        // limit it was taken for a handful of rows of a shallow layer: 8 rows, 256 experts of 264 x 2704, masked
+        // gradient 123 us, with 32 x 128 tiles 83.
         const double fill = mean / (tq * m.qb);
         const double step = m.tile == ROWS_256x384 ? fmax(m.step * fmin(0.36 + 0.75 * fill, 1.), 1.5) : m.step;
         // (fewer tiles than CUs: the longest block is the time)

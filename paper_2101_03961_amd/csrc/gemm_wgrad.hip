@@ -12,10 +12,10 @@
 // read; the other stage holds the next tile's first step by then.
 //
 // us per launch, first / second gradient, a block per tile -> here: 128 experts of 768 x 3072, 512 slots
-// 344 / 340 -> 299 / 310, 64 slots 151 / 152 -> 119 / 125, two experts with tokens 123 / 151 -> 102 / 119; 64 experts of 4096 x 10240, 256 slots 2340 / 2170 ->
-// 1990 / 1980.  A step of 64 k takes 4500 .. 5800 cycles for 3072 of MFMA: both operands are read transposed
-// (8 bytes per lane), 1800 cycles of LDS reads and 640 of writes by the loads; the clock is 1.8 .. 2.0 GHz under
-// the products' power.  (256 x 256 here: 348 / 350.)
+// 344 / 340 -> 299 / 310, 64 slots 151 / 152 -> 119 / 125, two experts with tokens 123 / 151 -> 102 / 119; 64 experts
+// of 4096 x 10240, 256 slots 2340 / 2170 -> 1990 / 1980.  A step of 64 k takes 4500 .. 5800 cycles for 3072 of
+// MFMA: both operands are read transposed (8 bytes per lane), 1800 cycles of LDS reads and 640 of writes by the
+// loads; the clock is 1.8 .. 2.0 GHz under the products' power.  (256 x 256 here: 348 / 350.)
 #include "common.h"
 #include "lds_operands.h"
 #include "rows_operands.h"
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(512, 2) void gemm_wgrad_kernel(WgradArgs a) {
 #pragma unroll
                 for (int j = 0; j < IQ; ++j) {
                     if (decltype(first)::value && ks == 0) {
-                        const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                        const f32x16 zero = {};
                         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fp[i], fq[j], zero, 0, 0, 0);
                     } else {
                         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fp[i], fq[j], acc[i][j], 0, 0, 0);
@@ -139,7 +139,8 @@ __global__ __launch_bounds__(512, 2) void gemm_wgrad_kernel(WgradArgs a) {
 #pragma unroll
             for (int x = 0; x < kStores; ++x) {
                 const int at = (wave * kStores + x) * 64 + lane_e, row = q0 + at / (PB / 8), p = p0 + at % (PB / 8) * 8;
-                const uint32_t off = row < a.ldq && p < a.ldp ? ((uint32_t)row * (uint32_t)a.ldp + (uint32_t)p) * 2u : kOobOffset;
+                const bool in = row < a.ldq && p < a.ldp;
+                const uint32_t off = in ? ((uint32_t)row * (uint32_t)a.ldp + (uint32_t)p) * 2u : kOobOffset;
                 __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, crsrc, (int)off, 0, 0);
             }
             stores = true;
@@ -212,8 +213,8 @@ template <int IP, int WP, int IQ, int WQ> static hipError_t wgrad_launch(WgradAr
         int cus = 0;
         hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         cu_count[dev] = cus >= 8 ? cus / 8 * 8 : 8;
-        return e != hipSuccess ? e
-                               : hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+        return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     });
     if (err != hipSuccess) return err;
     a.tiles_q = (int)ceil_div(a.ldq, QB);
@@ -222,7 +223,8 @@ template <int IP, int WP, int IQ, int WQ> static hipError_t wgrad_launch(WgradAr
     // an expert's tiles on one XCD, whose L2 then holds its operands; neighbours, which a skewed router likes
     // alike, on different ones
     a.by_expert = E % 8 == 0 || E >= 64;
-    const int64_t blocks = a.by_expert ? ceil_div(E, 8) * a.tiles_q * a.tiles_p * 8 : ceil_div((int64_t)a.tiles_q * a.tiles_p * E, 8) * 8;
+    const int64_t per_e = (int64_t)a.tiles_q * a.tiles_p;
+    const int64_t blocks = a.by_expert ? ceil_div(E, 8) * per_e * 8 : ceil_div(per_e * E, 8) * 8;
     hipLaunchKernelGGL(kern, dim3((unsigned)(blocks < cu_count[dev] ? blocks : cu_count[dev])), dim3(512), lds, s, a);
     return hipGetLastError();
 }
