@@ -5,15 +5,15 @@
 // contraction runs on the bf16 matrix cores: a fp32 weight is split, where its fragment is read,
 // into three bf16 terms hi + mid + lo (8 + 8 + 8 mantissa bits, the split is exact), so every
 // product x * term is exact in fp32 and the MFMA accumulates in fp32.  With fp32 tokens it runs on
-// the fp32 MFMA (input jitter applied to the token fragments).  Every sum runs over its share of d in one
-// wave, in order, and the KS shares are added in order: a token's logits do not depend on the other tokens.
+// the fp32 MFMA (input jitter applied to the token fragments).  Every sum runs over all of d in one
+// wave, in order, so a token's logits, and its expert, do not depend on the batch it comes in.
 //
-// A wave owns one tile of 32 experts, TT / WT MFMA tiles of 32 tokens ("A" = weights, "B" =
-// tokens) and every KS-th fragment pair of a step; weights and tokens come through a ring of direct-load stages.
-// What bounds it: a call of few tokens takes one block's chain of loads, splits and MFMAs.  Blocks of 64 tokens,
-// one per CU at most up to 16384 tokens, have eight waves so that a SIMD splits for one beside the products of
-// the other (64 tokens, d = 768, E = 128: 15 us, with four waves 19; 5003 x 392, E = 10, eight / two: 7 / 11; fp32
-// 8192 x 768, E = 32, four / two: 14 / 21).  At 65536 tokens it is the
+// A wave owns one tile of 32 experts and TT / WT MFMA tiles of 32 tokens ("A" = weights, "B" =
+// tokens); weights and tokens come through a ring of direct-load stages.  What bounds it: a call of
+// few tokens takes one block's chain of loads, splits and MFMAs (64 tokens, d = 768, E = 128: 19 us; the
+// 256-token blocks before it and the weight split they needed took 52.  Eight waves that take shares of d
+// run in 15, but add up in another order than the blocks of large batches; eight over halves of the tokens
+// split every weight twice: 19).  At 65536 tokens it is the
 // splits (about 20 vector operations per pair of weights and block) and the token stream together:
 // two blocks per CU, one's softmax beside the other's products, 128 tokens per block to halve the
 // splits: 57 us (before: 68 plus 5), T = 16384, d = 4096, E = 64: 67 us (before: 210 plus 8).
@@ -75,11 +75,11 @@ template <int EP, int BK, int NW, int SH, bool WIDE> struct RouterWeights {
     }
 };
 
-// ET expert tiles times WT shares of the TT token tiles times KS shares of the k of a step.
-template <typename XT, int ET, int WT, int TT, int KS> struct RouterBlock {
+// ET expert tiles times WT shares of the TT token tiles.
+template <typename XT, int ET, int WT, int TT> struct RouterBlock {
     static constexpr int kTok = 32 * TT;
     static constexpr bool kBf16 = sizeof(XT) == 2;
-    static constexpr int NW = ET * WT * KS;
+    static constexpr int NW = ET * WT;
     static constexpr int EP = 32 * ET;
     static constexpr int BK = kBf16 && ET <= 2 ? 64 : 32;
     static constexpr int UNIT = kBf16 ? 16 : 8;                   // k of one fragment pair
@@ -87,26 +87,26 @@ template <typename XT, int ET, int WT, int TT, int KS> struct RouterBlock {
     static constexpr int kStage = kXBytes + BK * EP * 4;
     static constexpr int STAGES = 4 * kStage <= 80 * 1024 || (ET == 8 && kBf16) ? 4 : 3;   // two blocks per CU, but ET = 8
     static constexpr int kPitch = EP + 4;                         // floats per row of the logits tile
-    static constexpr int kTile = kTok * kPitch * 4;               // one share's logits
-    static constexpr int kLds = (STAGES * kStage > KS * kTile ? STAGES * kStage : KS * kTile) + kTok * 4;
+    static constexpr int kTile = kTok * kPitch * 4;
+    static constexpr int kLds = (STAGES * kStage > kTile ? STAGES * kStage : kTile) + kTok * 4;
     static_assert(kLds <= 160 * 1024, "the block fits a CU");
 };
 
-template <typename XT, int ET, int WT, int TT, int KS, bool WIDE>
-__global__ __launch_bounds__(64 * (RouterBlock<XT, ET, WT, TT, KS>::NW), 2) void router_block_kernel(
+template <typename XT, int ET, int WT, int TT, bool WIDE>
+__global__ __launch_bounds__(64 * (RouterBlock<XT, ET, WT, TT>::NW), 2) void router_block_kernel(
     const XT *__restrict__ x, const float *__restrict__ W_r, const float *__restrict__ b_r,
     float *__restrict__ probs, float *__restrict__ logits_out, int32_t *__restrict__ idx_out,
     float *__restrict__ gate_out, int32_t *__restrict__ idx_ws, float *__restrict__ gate_ws,
     int32_t *__restrict__ local_rank, int32_t *__restrict__ block_counts,
     float *__restrict__ block_psum, int nbg, int Tg, int d, int E, Noise nz) {
-    typedef RouterBlock<XT, ET, WT, TT, KS> R;
+    typedef RouterBlock<XT, ET, WT, TT> R;
     constexpr bool BF = R::kBf16;
     constexpr int NW = R::NW, EP = R::EP, BK = R::BK, STAGES = R::STAGES, TOK = R::kTok;
     constexpr int TW = TT / WT, NX = NW < 4 ? NW : 4;   // token tiles per wave, waves that load tokens
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int et = wave % ET, wt = wave / ET % WT, ks = wave / (ET * WT);
+    const int et = wave % ET, wt = wave / ET;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
     const int b = blockIdx.x;
     int t0, tend;   // the block's tokens, inside one routing group
@@ -141,8 +141,7 @@ __global__ __launch_bounds__(64 * (RouterBlock<XT, ET, WT, TT, KS>::NW), 2) void
         issue(kt + STAGES - 1);
         const char *sx = lds + (kt % STAGES) * R::kStage, *sw_ = sx + R::kXBytes;
 #pragma unroll
-        for (int uu = 0; uu < BK / R::UNIT / KS; ++uu) {
-            const int u = uu * KS + ks;
+        for (int u = 0; u < BK / R::UNIT; ++u) {
             if constexpr (BF) {
                 float w[8];
                 ow.template frag<8>(sw_, u, w);
@@ -200,7 +199,7 @@ __global__ __launch_bounds__(64 * (RouterBlock<XT, ET, WT, TT, KS>::NW), 2) void
     for (int tt = 0; tt < TW; ++tt)
 #pragma unroll
         for (int g = 0; g < 4; ++g)
-            *(float4 *)(tile + ks * (R::kTile / 4) + ((wt * TW + tt) * 32 + (lane & 31)) * R::kPitch + et * 32 + 8 * g + 4 * (lane >> 5)) =
+            *(float4 *)(tile + ((wt * TW + tt) * 32 + (lane & 31)) * R::kPitch + et * 32 + 8 * g + 4 * (lane >> 5)) =
                 make_float4(acc[tt][4 * g], acc[tt][4 * g + 1], acc[tt][4 * g + 2], acc[tt][4 * g + 3]);
     __syncthreads();
 
@@ -217,11 +216,6 @@ __global__ __launch_bounds__(64 * (RouterBlock<XT, ET, WT, TT, KS>::NW), 2) void
         const int e = 4 * (j * LT + l);
         float4 v = *(const float4 *)(tile + row * R::kPitch + e);
         float *hv = (float *)&v;
-#pragma unroll
-        for (int q = 1; q < KS; ++q) {   // the shares' sums, in order
-            const float4 o = *(const float4 *)(tile + q * (R::kTile / 4) + row * R::kPitch + e);
-            v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
-        }
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
             hv[m] = e + m < E ? hv[m] + (b_r ? b_r[e + m] : 0.f) : -INFINITY;
@@ -329,12 +323,12 @@ bool router_block_supported(const switch_config *cfg) {
            !(cfg->act_dtype == SW_BF16 && cfg->jitter_eps > 0.f);
 }
 
-template <typename XT, int ET, int WT, int TT, int KS, bool WIDE>
+template <typename XT, int ET, int WT, int TT, bool WIDE>
 static hipError_t router_block_launch(const Workspace &w, const void *x, const float *W_r, const float *b_r,
                                       char *ws, int32_t *expert_index, float *gate, float *router_logits,
                                       hipStream_t s) {
-    auto kern = router_block_kernel<XT, ET, WT, TT, KS, WIDE>;
-    typedef RouterBlock<XT, ET, WT, TT, KS> R;
+    auto kern = router_block_kernel<XT, ET, WT, TT, WIDE>;
+    typedef RouterBlock<XT, ET, WT, TT> R;
     static PerDeviceOnce once;
     hipError_t err = once_per_device(once, [&] {
         return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, R::kLds);
@@ -351,14 +345,14 @@ static hipError_t router_block_launch(const Workspace &w, const void *x, const f
 template <typename XT>
 static hipError_t router_block_typed(const Workspace &w, const void *x, const float *W_r, const float *b_r,
                                      char *ws, int32_t *expert_index, float *gate, float *logits, hipStream_t s) {
-#define SW_RB(ET, WT, TT, KS)                                                                                          \
-    (w.E % 4 == 0 ? router_block_launch<XT, ET, WT, TT, KS, true>(w, x, W_r, b_r, ws, expert_index, gate, logits, s)   \
-                  : router_block_launch<XT, ET, WT, TT, KS, false>(w, x, W_r, b_r, ws, expert_index, gate, logits, s))
+#define SW_RB(ET, WT, TT)                                                                                          \
+    (w.E % 4 == 0 ? router_block_launch<XT, ET, WT, TT, true>(w, x, W_r, b_r, ws, expert_index, gate, logits, s)   \
+                  : router_block_launch<XT, ET, WT, TT, false>(w, x, W_r, b_r, ws, expert_index, gate, logits, s))
     if constexpr (sizeof(XT) == 2)
-        if (w.tb == 128) return w.E <= 32 ? SW_RB(1, 4, 4, 1) : w.E <= 64 ? SW_RB(2, 2, 4, 1) : SW_RB(4, 1, 4, 1);
-    if (w.E <= 32) return SW_RB(1, 2, 2, (sizeof(XT) == 2 ? 4 : 2));   // (fp32: one load per wave fills a stage of 4 waves)
-    if (w.E <= 64) return SW_RB(2, 2, 2, 2);
-    return w.E <= 128 ? SW_RB(4, 1, 2, 2) : SW_RB(8, 1, 2, 1);
+        if (w.tb == 128) return w.E <= 32 ? SW_RB(1, 4, 4) : w.E <= 64 ? SW_RB(2, 2, 4) : SW_RB(4, 1, 4);
+    if (w.E <= 32) return SW_RB(1, 2, 2);
+    if (w.E <= 64) return SW_RB(2, 2, 2);
+    return w.E <= 128 ? SW_RB(4, 1, 2) : SW_RB(8, 1, 2);
 #undef SW_RB
 }
 
