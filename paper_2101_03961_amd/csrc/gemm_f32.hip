@@ -121,24 +121,25 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Args a) {
 }
 
 // ---- fp32 on the matrix cores -----------------------------------------------------------
-// One tile per block, QB x PB, WP x WQ waves of IP x IQ MFMA 32x32x2 tiles; k advances 32 at a time
-// through two LDS stages filled by direct loads.  Bound by the MFMA rate (64 cycles for 4096
-// FLOP per SIMD): a 64 x 64 step takes 1024 cycles and needs 16 KB, so operand traffic is no issue
+// One tile per block, QB x PB, WP x WQ waves of IP x IQ MFMA tiles of S x S (32x32x2 or 16x16x4); k advances
+// 32 at a time through STAGES LDS stages filled by direct loads.  Bound by the MFMA rate (64 cycles for
+// 4096 FLOP per SIMD, of either shape): a 64 x 64 step takes 1024 cycles and needs 16 KB, so operand traffic is no issue
 // and the tile is chosen small enough to fill the chip; waves whose rows do not exist skip their
 // MFMAs.  Measured (32 experts x 256 tokens x 768 x 3072, us per launch): 345-392 = 98-111 TFLOP/s,
 // the FMA kernel 827-1269.
 // Two-level sums as in the FMA kernel: chains of kF32Flush products are folded into a total.
 //
-// k runs in order: MFMA m of a group of eight multiplies the pair (2 m, 2 m + 1), so that every
-// sum is the same chain of fused multiply-adds as the FMA kernel's, bit for bit.  (KS = 4: wave w of a 32 x 32 tile
-// takes eight k of every 32, and the four sums are added up in order.)
-// [k][row] operand: LDS [32 k][R]; rows 32 apart (R > 32) trade places in odd k-rows, so that the two half
-// waves of a read (neighbouring k) use different banks.
-template <int R, int NW> struct F32Trans {
+// k runs in order: an MFMA of S x S multiplies the next 64 / S of them one after the other, so that every
+// sum is the same chain of fused multiply-adds as the FMA kernel's, bit for bit, with each tile.
+// [k][row] operand: LDS [32 k][R]; rows S apart trade places in odd k-rows (S = 16: in k-rows 4 n + 2 and
+// 4 n + 3), so that the k-rows of a read use different banks.
+template <int R, int NW, int S> struct F32Trans {
+    static_assert(S == 32 ? R > 32 : R == 32, "rows S apart, whose k-rows would meet in a bank");
+    static __device__ __forceinline__ int turn(int k) { return S == 32 ? (k & 1) << 5 : (k >> 1 & 1) << 4; }
     static constexpr int kLoads = R * 32 * 4 / (1024 * NW);
     static constexpr int kChunks = R / 4;              // 16-byte chunks of a k-row
     static constexpr int kRowsPerLoad = 64 / kChunks;  // k-rows of one wave-wide load
-    static_assert(kLoads * NW * kRowsPerLoad == 32 && kRowsPerLoad % 2 == 0, "k-rows divide over the waves");
+    static_assert(kLoads * NW * kRowsPerLoad == 32 && kRowsPerLoad % (64 / S) == 0, "k-rows divide over the waves");
     i32x4 rsrc;
     uint32_t voff, k_step, frag0;
     __device__ __forceinline__ void init(const float *base, int ld, int row0, int rowlim, int klim,
@@ -146,35 +147,45 @@ template <int R, int NW> struct F32Trans {
         rsrc = make_rsrc(base, (uint32_t)klim * (uint32_t)ld * 4u);
         k_step = (uint32_t)ld * 4u;
         const int kk = lane / kChunks;
-        const int row = row0 + ((lane % kChunks) ^ (R > 32 ? (kk & 1) << 3 : 0)) * 4;
+        const int row = row0 + ((lane % kChunks) ^ (turn(kk) >> 2)) * 4;
         voff = row < rowlim ? ((uint32_t)(wave * kLoads * kRowsPerLoad + kk) * (uint32_t)ld + (uint32_t)row) * 4u
                             : kOobOffset;
     }
     __device__ __forceinline__ void init_frag(int lane, int frag_row) {
-        const int h = lane >> 5;
-        frag0 = (uint32_t)((h * R + ((frag_row + (lane & 31)) ^ (R > 32 ? h << 5 : 0))) * 4);
+        const int h = lane / S;
+        frag0 = (uint32_t)((h * R + ((frag_row + lane % S) ^ turn(h))) * 4);
     }
     __device__ __forceinline__ void issue_one(uint32_t st, int k0, int wave, int i) const {
         dma16(rsrc, voff, (uint32_t)(k0 + i * kRowsPerLoad) * k_step,
               st + (uint32_t)((wave * kLoads + i) * 1024));
     }
-    // element m: k = 8 ks + 2 m + lane / 32
+    // element m: k = 8 ks + 64 / S m + lane / S
     __device__ __forceinline__ f32x4 frag4(const char *st, int x, int ks) const {
         const char *p = st + (frag0 ^ (uint32_t)(x << 7)) + ks * (8 * R * 4);
-        f32x4 v;
+        f32x4 v = {};
 #pragma unroll
-        for (int m = 0; m < 4; ++m) v[m] = *(const float *)(p + m * (2 * R * 4));
+        for (int m = 0; m < S / 8; ++m) v[m] = *(const float *)(p + m * (64 / S * R * 4));
         return v;
     }
 };
 
 enum { F32_PLAIN = 0, F32_RELU = 1, F32_MASK = 2, F32_COMBINE = 3 };   // (see gemm_rows.hip)
 
-template <int IP, int WP, int IQ, int WQ, int KS, int STAGES, bool Q_TRANS, bool P_TRANS, int EPI>
-__global__ __launch_bounds__(64 * WP * WQ * KS, 2) void gemm_f32_mfma_kernel(GemmF32Args a, int tiles_q, int tiles_p) {
-    constexpr int NW = WP * WQ * KS, PB = 32 * IP * WP, QB = 32 * IQ * WQ;
+// MFMA tiles of S x S, S 32 or 16
+__device__ __forceinline__ f32x16 mfma_f32(float p, float q, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(p, q, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 mfma_f32(float p, float q, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(p, q, c, 0, 0, 0);
+}
+
+template <int S, int IP, int WP, int IQ, int WQ, int STAGES, bool Q_TRANS, bool P_TRANS, int EPI>
+__global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32Args a, int tiles_q, int tiles_p) {
+    constexpr int NW = WP * WQ, PB = S * IP * WP, QB = S * IQ * WQ;
     constexpr int kPBytes = PB * 128, kStage = (PB + QB) * 128;
-    static_assert(KS == 1 || (KS == 4 && IP * IQ * WP * WQ == 1), "four waves share a tile's k, or one has all");
+    constexpr int kAcc = S * S / 64;   // accumulators per lane and MFMA tile
+    typedef typename std::conditional<S == 32, f32x16, f32x4>::type Acc;
+    static_assert(S == 32 || IP * IQ == 1, "fragments lie 32 rows apart");
     __shared__ __attribute__((aligned(16))) char lds[STAGES * kStage];
     const int per_e = tiles_q * tiles_p;
     const int e = blockIdx.x / per_e, rem = blockIdx.x - e * per_e;
@@ -186,25 +197,25 @@ __global__ __launch_bounds__(64 * WP * WQ * KS, 2) void gemm_f32_mfma_kernel(Gem
     if (q0 >= qlim) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int wp = wave % WP, wq = wave / WP % WQ;
+    const int wp = wave % WP, wq = wave / WP;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
-    const bool live = q0 + wq * 32 * IQ < qlim && p0 + wp * 32 * IP < a.Pdim;
+    const bool live = q0 + wq * S * IQ < qlim && p0 + wp * S * IP < a.Pdim;
 
-    typename std::conditional<P_TRANS, F32Trans<PB, NW>, F32Direct<PB, NW>>::type op;
-    typename std::conditional<Q_TRANS, F32Trans<QB, NW>, F32Direct<QB, NW>>::type oq;
-    op.init_frag(lane, wp * 32 * IP);
-    oq.init_frag(lane, wq * 32 * IQ);
+    typename std::conditional<P_TRANS, F32Trans<PB, NW, S>, F32Direct<PB, NW, S>>::type op;
+    typename std::conditional<Q_TRANS, F32Trans<QB, NW, S>, F32Direct<QB, NW, S>>::type oq;
+    op.init_frag(lane, wp * S * IP);
+    oq.init_frag(lane, wq * S * IQ);
     op.init(a.P + (size_t)e * a.p_batch, P_TRANS ? (int)a.p_ks : (int)a.p_rs, p0, a.Pdim, klim, lane, wave);
     oq.init(a.Q + (size_t)e * a.q_batch, Q_TRANS ? (int)a.q_ks : (int)a.q_rs, q0, qlim, klim, lane, wave);
     const int nk = (klim + 31) / 32;
 
-    f32x16 acc[IP][IQ], total[IP][IQ];
+    Acc acc[IP][IQ], total[IP][IQ];
 #pragma unroll
     for (int i = 0; i < IP; ++i)
 #pragma unroll
         for (int j = 0; j < IQ; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = total[i][j][r] = 0.f;
+            for (int r = 0; r < kAcc; ++r) acc[i][j][r] = total[i][j][r] = 0.f;
 
     constexpr int kLoads = decltype(op)::kLoads + decltype(oq)::kLoads;
     auto issue = [&](int kt) {   // k past the end: zeros
@@ -228,56 +239,34 @@ __global__ __launch_bounds__(64 * WP * WQ * KS, 2) void gemm_f32_mfma_kernel(Gem
 #pragma unroll
                 for (int j = 0; j < IQ; ++j)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
+                    for (int r = 0; r < kAcc; ++r) {
                         total[i][j][r] += acc[i][j][r];
                         acc[i][j][r] = 0.f;
                     }
         }
 #pragma unroll
-        for (int kk = 0; kk < 4 / KS; ++kk) {
-            const int ks = KS == 1 ? kk : wave;
+        for (int ks = 0; ks < 4; ++ks) {
             f32x4 fp[IP], fq[IQ];
 #pragma unroll
             for (int i = 0; i < IP; ++i) fp[i] = op.frag4(sp, i, ks);
 #pragma unroll
             for (int j = 0; j < IQ; ++j) fq[j] = oq.frag4(sq, j, ks);
 #pragma unroll
-            for (int m = 0; m < 4; ++m)
+            for (int m = 0; m < S / 8; ++m)
 #pragma unroll
                 for (int i = 0; i < IP; ++i)
 #pragma unroll
-                    for (int j = 0; j < IQ; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fp[i][m], fq[j][m], acc[i][j], 0, 0, 0);
+                    for (int j = 0; j < IQ; ++j) acc[i][j] = mfma_f32(fp[i][m], fq[j][m], acc[i][j]);
         }
     }
     rows_wait_vmcnt<0>();   // the trailing (zero) loads
     if (!live) return;
-    if constexpr (KS == 4) {   // the four sums, in order; wave g goes on with columns 8 g ..
-        __syncthreads();
-        f32x4 *part = (f32x4 *)lds;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            f32x4 v;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = total[0][0][4 * g + r] + acc[0][0][4 * g + r];
-            part[(wave * 4 + g) * 64 + lane] = v;
-        }
-        __syncthreads();
-        f32x4 v = part[wave * 64 + lane];
-#pragma unroll
-        for (int q = 1; q < 4; ++q) v += part[(q * 4 + wave) * 64 + lane];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            total[0][0][r] = v[r];
-            acc[0][0][r] = 0.f;
-        }
-    }
-    // a lane holds, for row q = lane % 32 of each tile, columns 8 g + 4 (lane / 32) .. + 3
+    // a lane holds, for row q = lane % S of each tile, columns 256 / S g + 4 (lane / S) .. + 3
     float *Cout = a.Cout + (size_t)e * a.c_batch;
     const float *mask = EPI == F32_MASK ? a.mask + (size_t)e * a.c_batch : nullptr;
 #pragma unroll
     for (int j = 0; j < IQ; ++j) {
-        const int q = q0 + (wq * IQ + j) * 32 + (lane & 31);
+        const int q = q0 + (wq * IQ + j) * S + lane % S;
         if (q >= qlim) continue;
         uint32_t row_idx = 0;   // index of the token's first hidden unit in the dropout stream
         if (EPI == F32_RELU && a.nz.dropout)
@@ -291,8 +280,8 @@ __global__ __launch_bounds__(64 * WP * WQ * KS, 2) void gemm_f32_mfma_kernel(Gem
 #pragma unroll
         for (int i = 0; i < IP; ++i)
 #pragma unroll
-            for (int g = 0; g < (KS == 4 ? 1 : 4); ++g) {
-                const int p = p0 + (wp * IP + i) * 32 + 8 * (KS == 4 ? wave : g) + ((lane >> 5) << 2);
+            for (int g = 0; g < kAcc / 4; ++g) {
+                const int p = p0 + (wp * IP + i) * S + 256 / S * g + lane / S * 4;
                 if (p >= a.Pdim) continue;   // Pdim is a multiple of 4: four columns are in or out
                 float v[4];
 #pragma unroll
@@ -321,11 +310,11 @@ __global__ __launch_bounds__(64 * WP * WQ * KS, 2) void gemm_f32_mfma_kernel(Gem
     }
 }
 
-template <int IP, int WP, int IQ, int WQ, int KS, int STAGES, bool Q_TRANS, bool P_TRANS, int EPI>
+template <int S, int IP, int WP, int IQ, int WQ, int STAGES, bool Q_TRANS, bool P_TRANS, int EPI>
 static hipError_t f32_launch(const GemmF32Args &a, int E, hipStream_t s) {
-    const int tq = (int)ceil_div(a.Qdim, 32 * IQ * WQ), tp = (int)ceil_div(a.Pdim, 32 * IP * WP);
-    hipLaunchKernelGGL((gemm_f32_mfma_kernel<IP, WP, IQ, WQ, KS, STAGES, Q_TRANS, P_TRANS, EPI>),
-                       dim3((unsigned)(tq * tp * E)), dim3(64 * WP * WQ * KS), 0, s, a, tq, tp);
+    const int tq = (int)ceil_div(a.Qdim, S * IQ * WQ), tp = (int)ceil_div(a.Pdim, S * IP * WP);
+    hipLaunchKernelGGL((gemm_f32_mfma_kernel<S, IP, WP, IQ, WQ, STAGES, Q_TRANS, P_TRANS, EPI>),
+                       dim3((unsigned)(tq * tp * E)), dim3(64 * WP * WQ), 0, s, a, tq, tp);
     return hipGetLastError();
 }
 
@@ -334,14 +323,18 @@ static hipError_t f32_mfma(const GemmF32Args &a, int E, hipStream_t s) {
     // 64 x 64 keeps the chip even (a 128 x 128 tile takes 573 instead of 364 us in the second GEMM of
     // 32 experts x 256 tokens x 768 x 3072); twice as wide is 2-8 % faster where there are many tiles.
     if (E * ceil_div(a.Qdim, 64) * ceil_div(a.Pdim, 128) >= 1024)
-        return f32_launch<2, 2, 1, 2, 1, 2, Q_TRANS, P_TRANS, EPI>(a, E, s);
-    // Few tiles: a 64 x 64 tile keeps one CU's matrix cores busy for 1024 cycles per 32 k, whatever the others do.  Tiles
-    // of 32 x 32 whose four waves take a quarter of the k each spread over four times as many (us per forward +
-    // backward pass, 256 x 64 x 256, 4 experts 70 / 55; 1000 x 512 x 1536, 8 experts 222 / 174; at 512 tiles of 64 x 64
-    // they lose: 2000 x 256 x 1024, 8 experts, first GEMM 17 / 20).
+        return f32_launch<32, 2, 2, 1, 2, 2, Q_TRANS, P_TRANS, EPI>(a, E, s);
+    // Few tiles: a 64 x 64 tile keeps one CU's matrix cores busy for 1024 cycles per 32 k, whatever the others do.
+    // Tiles of 32 x 32, a quarter of 16 x 16 per wave, spread over four times as many (us per forward + backward
+    // pass, 64 x 64 / 32 x 32: 256 x 64 x 256, 4 experts 71 / 56; 1000 x 512 x 1536, 8 experts 244 / 219; 512 x 768 x
+    // 3072, 4 experts 387 / 310; all products at 384 tiles or beside it, 3000 x 256 x 512, 8 experts: 132 / 135).  With
+    // 385 to 700 tiles either may win: the limit at 700 instead, 2000 x 256 x 1024, 8 experts 153 -> 156, 700 x 128 x 512,
+    // 32 experts 74 -> 76, 1000 x 512 x 1536 224 -> 212.
+    // (Four waves that take a quarter of the k each of one 32 x 32: 2-8 % less per pass, but other sums than the
+    // larger tiles'.)
     if (E * ceil_div(a.Qdim, 64) * ceil_div(a.Pdim, 64) <= 384)
-        return f32_launch<1, 1, 1, 1, 4, 4, Q_TRANS, P_TRANS, EPI>(a, E, s);
-    return f32_launch<1, 2, 1, 2, 1, 2, Q_TRANS, P_TRANS, EPI>(a, E, s);
+        return f32_launch<16, 1, 2, 1, 2, 4, Q_TRANS, P_TRANS, EPI>(a, E, s);
+    return f32_launch<32, 1, 2, 1, 2, 2, Q_TRANS, P_TRANS, EPI>(a, E, s);
 }
 
 // The matrix-core kernel addresses one expert's matrices through 32-bit buffer descriptors, and all of a

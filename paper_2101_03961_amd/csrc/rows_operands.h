@@ -42,8 +42,9 @@ template <int R, int NW, int BK = 64> struct RowsDirect {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// fp32 [row][k] operand: 32 k = 128 bytes per row, exactly the bf16 layout of 64 k (sizes in half words)
-template <int R, int NW> struct F32Direct : RowsDirect<R, NW, 64> {
+// fp32 [row][k] operand of MFMA tiles of S rows: 32 k = 128 bytes per row, exactly the bf16 layout of 64 k
+// (sizes in half words)
+template <int R, int NW, int S = 32> struct F32Direct : RowsDirect<R, NW, 64> {
     __device__ __forceinline__ void init(const float *base, int ld, int row0, int rowlim, int klim,
                                          int lane, int wave) {
         RowsDirect<R, NW, 64>::init((const bf16 *)base, 2 * ld, row0, rowlim, 2 * klim, lane, wave);
@@ -52,17 +53,19 @@ template <int R, int NW> struct F32Direct : RowsDirect<R, NW, 64> {
         RowsDirect<R, NW, 64>::issue_one(st, 2 * k0, wave, i);
     }
     __device__ __forceinline__ void init_frag(int lane, int frag_row) {
-        RowsDirect<R, NW, 64>::init_frag(lane & 31, frag_row);   // both half waves: chunk 2 ks ...
-        odd = lane >> 5;
+        RowsDirect<R, NW, 64>::init_frag(lane % S, frag_row);   // all parts of the wave: chunk 2 ks ...
+        part = lane / S;
     }
-    // element m: k = 8 ks + 2 m + lane / 32 (... and chunk 2 ks + 1)
+    // element m: k = 8 ks + 64 / S m + lane / S (... and chunk 2 ks + 1)
     __device__ __forceinline__ f32x4 frag4(const char *st, int x, int ks) const {
         const char *p = st + (uint32_t)(x * 32 * 128);
         const uint32_t at = this->frag0 ^ (uint32_t)(ks << 5);
+        if (S == 16)
+            return f32x4{*(const float *)(p + at + 4 * part), *(const float *)(p + (at ^ 16u) + 4 * part), 0.f, 0.f};
         const f32x4 a = *(const f32x4 *)(p + at), b = *(const f32x4 *)(p + (at ^ 16u));
-        return odd ? f32x4{a[1], a[3], b[1], b[3]} : f32x4{a[0], a[2], b[0], b[2]};
+        return part ? f32x4{a[1], a[3], b[1], b[3]} : f32x4{a[0], a[2], b[0], b[2]};
     }
-    int odd;
+    int part;
 };
 
 // [k][row] operand of R rows: LDS [BK k][R], see TransOperand64

@@ -69,18 +69,22 @@ def test_bf16_shapes_full_parity(T, d, f, E, cf, bias, in_gemm):
 @pytest.mark.parametrize("dtype,d,f,E", [
     ("bf16", 392, 72, 10), ("bf16", 136, 72, 60), ("bf16", 768, 136, 128), ("bf16", 264, 72, 200),
     ("f32", 132, 68, 10), ("f32", 392, 72, 60), ("f32", 392, 36, 128), ("f32", 64, 256, 4)])
-def test_a_tokens_logits_do_not_depend_on_the_batch(dtype, d, f, E):
-    """A logit is one chain of sums over d, whatever the number of tokens has chosen as blocks: the first
-    tokens of a large batch by themselves get the same bits, and with them the same expert."""
+def test_a_tokens_results_do_not_depend_on_the_batch(dtype, d, f, E):
+    """A logit is one chain of sums over d, whatever the number of tokens has chosen as blocks, and so is an
+    fp32 product, whatever tile: the first tokens of a large batch by themselves get the same bits."""
     from paper_2101_03961_amd.layer import SwitchLayer
     T, few = 40000, 150
     inp = make_inputs(SwitchShape("t", T, d, f, E, 4.0, dtype=dtype, seed_index=61), _dev())
     got = []
     for n, cf in ((T, 4.0), (few, float(E))):   # room for all tokens
         layer = SwitchLayer(n, d, f, E, cf, 0.01, dtype, _dev(), want_logits=True)
-        out = layer.forward(inp["x"][:n].contiguous(), inp["W_r"], inp["W_in"], inp["W_out"])
+        x, dy = inp["x"][:n].contiguous(), inp["dy"][:n].contiguous()
+        out = dict(layer.forward(x, inp["W_r"], inp["W_in"], inp["W_out"]))
         assert not out["dropped"].any()
-        got.append({k: out[k][:few].clone() for k in ("router_logits", "expert_index")})
+        if dtype == "f32":
+            out["dx"] = layer.backward(dy, x, inp["W_r"], inp["W_in"], inp["W_out"], d_aux=0.0)["dx"]
+        got.append({k: out[k][:few].clone() for k in
+                    ("router_logits", "expert_index") + (("gate", "y", "dx") if dtype == "f32" else ())})
     for k in got[0]:
         assert torch.equal(got[0][k], got[1][k]), k
 
