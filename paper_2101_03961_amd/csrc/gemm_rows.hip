@@ -267,13 +267,15 @@ __device__ __forceinline__ void rows_block(const RowsArgs &a, char *lds, int L) 
     if constexpr (WP * WQ == 8 && !WGRAD) {
         if (a.E <= 64 * kFewExperts && *a.hit * a.tiles_p <= kFewTiles) {
             constexpr int kSubRows = QB / 64, kSubs = kSubRows * (PB / 128);
-            int rows[kFewExperts], tiles = 0;   // row tiles of experts lane, lane + 64, ..
+            // row tiles of experts lane, lane + 64, .. (more than the limit: one more than it, so that their sum is
+            // right up to the limit and above it beyond)
+            int rows[kFewExperts], tiles = 0;
 #pragma unroll
             for (int m = 0; m < kFewExperts; ++m) {
-                rows[m] = lane + 64 * m < a.E ? (min(a.kept[lane + 64 * m], a.Qdim) + QB - 1) / QB : 0;
+                rows[m] = lane + 64 * m < a.E ? min((min(a.kept[lane + 64 * m], a.Qdim) + QB - 1) / QB, kFewTiles + 1) : 0;
 #pragma unroll
-                for (int b = 0; b < 6; ++b)   // (a digit at a time; 64 and more tiles: anything above the limit)
-                    tiles += __popcll(__ballot(rows[m] > 63 || (rows[m] >> b & 1))) << b;
+                for (int b = 0; (kFewTiles + 1) >> b; ++b)   // a digit at a time
+                    tiles += __popcll(__ballot(rows[m] >> b & 1)) << b;
             }
             tiles *= a.tiles_p;
             if (tiles > 0 && tiles <= kFewTiles && tiles * kSubs <= a.total) {

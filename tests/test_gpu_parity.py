@@ -131,6 +131,19 @@ def test_few_large_tiles_in_pieces(T, d, f, E, cf, n, rate, ffn, rounds):
     assert rounds or (fwd["expert_counts"] > 0).sum() <= 8
 
 
+@pytest.mark.parametrize("d,E,cf,tiles", [
+    (136, 8, 1.96875, 63), (136, 8, 2.0, 64), (200, 8, 2.0, 65), (136, 4, 2.0, 128)])   # (200: two experts)
+def test_many_row_tiles_of_one_expert(d, E, cf, tiles):
+    """Second forward GEMM and first data gradient with one column tile of 256 x 256, so that a collapsed router
+    leaves as many tiles as its favourite has rows of 256: up to 64 run in pieces, which all have to be counted."""
+    from parity import compare_full
+    s = SwitchShape("t", 65536, d, 264, E, cf, dtype="bf16", zipf_bias=True, seed_index=71)
+    errs, gpu, fwd, _ = compare_full(s, make_inputs(s, _dev()), d_aux=1.0)
+    _report("row tiles %s" % ((d, E, cf),), errs)
+    kept = np.minimum(fwd["expert_counts"], fwd["capacity"])
+    assert (-(-kept // 256)).sum() == tiles
+
+
 @pytest.mark.parametrize("T,d,f,E,cf,n,bias,ffn,rate,rounds", [
     (2000, 264, 520, 5, 1.5, 1, False, "relu", 0.0, 0),    # ragged tiles everywhere
     (4096, 128, 256, 16, 1.0, 2, True, "relu", 0.1, 1),    # groups, skew, dropout, re-routing

@@ -83,6 +83,9 @@ def test_scan_kernel_beside_many_experts_groups_or_blocks(recorder, T, E, n, fus
     (503, 264, 2000, 308, 1.0, "1,4,1,1", "1,4,1,1"), (64, 768, 3072, 128, 8.0, "1,4,1,1", "1,4,1,1"),
     (4096, 768, 3072, 128, 1.25, "2,4,2,1", "2,4,2,1"), (8192, 768, 3072, 128, 1.25, "3,4,4,2", "3,4,4,2"),
     (65536, 768, 3072, 128, 1.0, "3,4,4,2", "3,4,4,2"), (16384, 4096, 10240, 64, 1.25, "2,4,5,2", "2,4,5,2"),
+    # (experts of 64 row tiles and more, one column tile: cut into pieces if there are no more than 64)
+    (65536, 136, 264, 8, 1.96875, "3,4,4,2", "2,4,4,2"), (65536, 136, 264, 8, 2.0, "3,4,4,2", "2,4,4,2"),
+    (65536, 200, 264, 8, 2.0, "3,4,4,2", "2,4,4,2"), (65536, 136, 264, 4, 2.0, "3,4,4,2", "2,4,4,2"),
 ])
 def test_tile_follows_the_rows_of_an_expert(recorder, T, d, f, E, cf, first, second):
     (status, _, _, launches), = recorder(call("forward", T, d, f, E, cf))
