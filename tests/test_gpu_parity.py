@@ -89,18 +89,36 @@ def test_a_tokens_results_do_not_depend_on_the_batch(dtype, d, f, E):
         assert torch.equal(got[0][k], got[1][k]), k
 
 
-@pytest.mark.parametrize("T,d,f,E,cf,bias", [
-    (2400, 264, 904, 120, 1.25, False),   # two rounds of tiles, one k step, ragged in both dimensions
-    (9000, 264, 760, 80, 1.25, False),    # two or three k steps
-    (2400, 264, 904, 120, 4.0, True),     # experts of 80 tokens beside many without any
-    (9000, 264, 760, 80, 0.007, False),   # no slots at all
+@pytest.mark.parametrize("T,d,f,E,cf,likes", [
+    (2400, 264, 904, 120, 1.25, "all"),    # two rounds of tiles, one k step, ragged in both dimensions
+    (9000, 264, 760, 80, 1.25, "all"),     # two or three k steps
+    (2400, 264, 904, 120, 4.0, "first"),   # experts of 80 tokens beside many without any
+    (2500, 264, 904, 250, 4.0, "all"),     # E no multiple of the XCDs; four rounds of tiles:
+    (2500, 264, 904, 250, 4.0, "first"),   # ... with tokens, then without, several in a row
+    (2500, 264, 904, 250, 4.0, "last"),    # ... without tokens, then with
 ])
-def test_weight_gradients_of_persistent_blocks(T, d, f, E, cf, bias):
-    """Sizes that take the 384 x 256 and 256 x 384 tiles of gemm_wgrad.hip (tests/test_launches.py)."""
+def test_weight_gradients_of_persistent_blocks(T, d, f, E, cf, likes):
+    """Sizes that take the 384 x 256 and 256 x 384 tiles of gemm_wgrad.hip (listed in tests/test_launches.py)."""
     from parity import compare_full
-    s = SwitchShape("t", T, d, f, E, cf, dtype="bf16", zipf_bias=bias, seed_index=47)
+    s = SwitchShape("t", T, d, f, E, cf, dtype="bf16", zipf_bias=likes != "all", seed_index=47)
+    inp = make_inputs(s, _dev())
+    if likes == "last":
+        inp["b_r"] = inp["b_r"].flip(0).contiguous()
+    errs, gpu, fwd, _ = compare_full(s, inp, d_aux=1.0)
+    _report("persistent weight gradients %s" % ((T, d, f, E, cf, likes),), errs)
+    empty = fwd["expert_counts"] == 0
+    if E == 250 and likes != "all":   # a block's tiles lie about 64 experts apart
+        assert empty[64:][:64].all() if likes == "first" else empty[:192].all()
+        assert not empty[0 if likes == "first" else -1]
+
+
+def test_bf16_without_slots():
+    """Capacity 0 in a layer of many experts: zero outputs and zero weight gradients."""
+    from parity import compare_full
+    s = SwitchShape("t", 9000, 264, 760, 80, 0.007, dtype="bf16", seed_index=47)
     errs, gpu, fwd, _ = compare_full(s, make_inputs(s, _dev()), d_aux=1.0)
-    _report("persistent weight gradients %s" % ((T, d, f, E, cf, bias),), errs)
+    _report("no slots", errs)
+    assert fwd["capacity"] == 0 and fwd["dropped"].all()
 
 
 @pytest.mark.parametrize("T,d,f,E,cf,ffn,bias", [

@@ -102,6 +102,9 @@ def test_tile_follows_the_rows_of_an_expert(recorder, T, d, f, E, cf, first, sec
     (65536, 1024, 2816, 128, 1.25, "wgrad 3,4,4,2", "wgrad 4,2,3,4"),   # the other way: 32 tiles instead of 33
     (2400, 264, 904, 120, 1.25, "wgrad 4,2,3,4", "wgrad 3,4,4,2"),
     (9000, 264, 760, 80, 1.25, "wgrad 4,2,3,4", "wgrad 3,4,4,2"),
+    (2400, 264, 904, 120, 4.0, "wgrad 4,2,3,4", "wgrad 3,4,4,2"),
+    (2500, 264, 904, 250, 4.0, "wgrad 4,2,3,4", "wgrad 3,4,4,2"),
+    (9000, 264, 760, 80, 0.007, "rows 2,2,4,2", "rows 2,2,4,2"),        # no slots
     (32768, 512, 1024, 32, 1.0, "bf16", "bf16"),
     (512, 768, 3072, 128, 4.0, "rows 2,2,4,2", "rows 2,2,4,2"),
 ])
