@@ -17,7 +17,7 @@
 // accumulators, 20 % fewer operand bytes per product than 256 x 256.
 //
 // A block has WP x WQ waves, each with IP x IQ MFMA 32x32x16 tiles (P is the MFMA "A" side).  k
-// advances BK at a time through STAGES LDS stages filled by direct loads; one barrier per step.
+// advances 64 (BK) at a time through STAGES LDS stages filled by direct loads; one barrier per step.
 #include <math.h>
 
 #include "common.h"
@@ -25,6 +25,8 @@
 #include "rows_operands.h"
 
 namespace sw {
+
+constexpr int BK = 64;
 
 struct RowsArgs {
     const bf16 *Q;             // per expert q_batch elements: [rows][ldq], weight gradients [slot][ldq]
@@ -58,7 +60,7 @@ enum { ROWS_PLAIN = 0, ROWS_RELU = 1, ROWS_MASK = 2, ROWS_COMBINE = 3 };
 // The tile's products and epilogue, with IQ row blocks of 32 per wave (IQ_MAX of them fit the tile).
 // Mask bits: one byte per 16-byte piece of the output (bits 0..3: low halves of its four words, 4..7:
 // high halves), [tile][wave][32-row round][pass][lane] in the order the epilogue handles them.
-template <int IP, int WP, int IQ, int IQ_MAX, int WQ, int STAGES, int BK, bool P_TRANS, int EPI, bool DROP,
+template <int IP, int WP, int IQ, int IQ_MAX, int WQ, int STAGES, bool P_TRANS, int EPI, bool DROP,
           bool WGRAD>
 __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, int e, int q0, int p0, int qlim,
                                           int klim, int lane, int wave) {
@@ -67,8 +69,8 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
     const int wp = wave % WP, wq = wave / WP;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
 
-    typename std::conditional<P_TRANS, RowsTrans<PB, NW, BK>, RowsDirect<PB, NW, BK>>::type op;
-    typename std::conditional<WGRAD, RowsTrans<QB, NW, BK>, RowsDirect<QB, NW, BK>>::type oq;
+    typename std::conditional<P_TRANS, RowsTrans<PB, NW>, RowsDirect<PB, NW>>::type op;
+    typename std::conditional<WGRAD, RowsTrans<QB, NW>, RowsDirect<QB, NW>>::type oq;
     op.init_frag(lane, wp * 32 * IP);
     oq.init_frag(lane, wq * 32 * IQ);
     op.init(a.P + (size_t)e * a.p_batch, a.ldp, p0, a.Pdim, klim, lane, wave);
@@ -112,7 +114,7 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
     // of a step 1300 cycles without an MFMA; over 3 of the 4 sub-steps / before the reads: masked gradient of
     // 128 experts x 512 x 768 x 3072 310 / 332 us, 64 x 256 x 4096 x 10240 1360-1530 / 1380-1580).  Four waves
     // issue few, and their steps are short: first.
-    constexpr int kSpread = NW < 8 ? 0 : BK == 64 ? 3 : 1;
+    constexpr int kSpread = NW < 8 ? 0 : 3;
 #pragma unroll
     for (int s = 0; s < STAGES - 1; ++s) issue(s, s);
     int st = 0, fill = STAGES - 1;
@@ -259,7 +261,7 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
 // with as few blocks as hold them, so with fewer products, fragment reads and loads (128 experts of 768 x 3072, 64
 // rows in tiles of 256: masked gradient 152 -> 140 us, first forward 186 -> 176; 64 of 4096 x 10240, 256 rows in
 // tiles of 320: 1530 -> 1480).
-template <int IP, int WP, int IQ, int WQ, int STAGES, int BK, bool P_TRANS, int EPI, bool DROP, bool WGRAD>
+template <int IP, int WP, int IQ, int WQ, int STAGES, bool P_TRANS, int EPI, bool DROP, bool WGRAD>
 __device__ __forceinline__ void rows_block(const RowsArgs &a, char *lds, int L) {
     constexpr int PB = 32 * IP * WP, QB = 32 * IQ * WQ;
     const int lane = threadIdx.x & 63;
@@ -291,7 +293,7 @@ __device__ __forceinline__ void rows_block(const RowsArgs &a, char *lds, int L) 
                             const int qlim = min(a.kept[e], a.Qdim);
                             const int q0 = (at - pt * tq) * QB + sub % kSubRows * 64, p0 = pt * PB + sub / kSubRows * 128;
                             if (q0 < qlim && p0 < a.Pdim)
-                                rows_tile<1, 4, 1, 1, 2, (STAGES * (PB + QB)) / 192, BK, P_TRANS, EPI, DROP, false>(
+                                rows_tile<1, 4, 1, 1, 2, (STAGES * (PB + QB)) / 192, P_TRANS, EPI, DROP, false>(
                                     a, lds, L, e, q0, p0, qlim, a.Kdim, lane, wave);
                             return;
                         }
@@ -322,7 +324,7 @@ __device__ __forceinline__ void rows_block(const RowsArgs &a, char *lds, int L) 
     const int q0 = qt * QB, p0 = pt * PB;
     if (q0 >= qlim) return;
 #define SW_ROWS(N) \
-    rows_tile<IP, WP, (N) < IQ ? (N) : IQ, IQ, WQ, STAGES, BK, P_TRANS, EPI, DROP, WGRAD>(a, lds, L, e, q0, p0, qlim, \
+    rows_tile<IP, WP, (N) < IQ ? (N) : IQ, IQ, WQ, STAGES, P_TRANS, EPI, DROP, WGRAD>(a, lds, L, e, q0, p0, qlim, \
                                                                                           klim, lane, wave)
     if constexpr (WP * WQ == 8 && !WGRAD) {
         const int blocks = (qlim - q0 + 32 * WQ - 1) / (32 * WQ);
@@ -337,11 +339,11 @@ __device__ __forceinline__ void rows_block(const RowsArgs &a, char *lds, int L) 
 #undef SW_ROWS
 }
 
-template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, int BK, bool P_TRANS, int EPI, bool DROP,
+template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, bool P_TRANS, int EPI, bool DROP,
           bool WGRAD>
 __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    rows_block<IP, WP, IQ, WQ, STAGES, BK, P_TRANS, EPI, DROP, WGRAD>(a, lds, blockIdx.y * a.grid_x + blockIdx.x);
+    rows_block<IP, WP, IQ, WQ, STAGES, P_TRANS, EPI, DROP, WGRAD>(a, lds, blockIdx.y * a.grid_x + blockIdx.x);
 }
 
 // Three products in one launch: the first layer's data gradient and both weight gradients, which do not depend on
@@ -355,14 +357,14 @@ __global__ __launch_bounds__(256, 2) void gemm_rows_backward_kernel(RowsArgs3 a)
     static_assert(WP * WQ == 4 && GWP * GWQ == 4, "256 threads");
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int L = blockIdx.x;
-    if (L < a.end[0]) rows_block<IP, WP, IQ, WQ, STAGES, 64, false, ROWS_PLAIN, false, false>(a.data, lds, L);
+    if (L < a.end[0]) rows_block<IP, WP, IQ, WQ, STAGES, false, ROWS_PLAIN, false, false>(a.data, lds, L);
     else if (L < a.end[1])
-        rows_block<GP, GWP, GQ, GWQ, GSTAGES, 64, true, ROWS_PLAIN, false, true>(a.first, lds, L - a.end[0]);
+        rows_block<GP, GWP, GQ, GWQ, GSTAGES, true, ROWS_PLAIN, false, true>(a.first, lds, L - a.end[0]);
     else
-        rows_block<GP, GWP, GQ, GWQ, GSTAGES, 64, true, ROWS_PLAIN, false, true>(a.second, lds, L - a.end[1]);
+        rows_block<GP, GWP, GQ, GWQ, GSTAGES, true, ROWS_PLAIN, false, true>(a.second, lds, L - a.end[1]);
 }
 
-constexpr int rows_lds(int IP, int WP, int IQ, int WQ, int STAGES, int BK) {
+constexpr int rows_lds(int IP, int WP, int IQ, int WQ, int STAGES) {
     const int ring = STAGES * 32 * (IP * WP + IQ * WQ) * BK * 2, turn = WP * WQ * 32 * rows_turn_pitch(IP);
     return ring > turn ? ring : turn;
 }
@@ -379,12 +381,12 @@ static int64_t rows_plan(RowsArgs &a, int E, int QB, int PB, bool wgrad) {
     return a.by_xcd ? ceil_div(a.total, 8) * 8 : a.total;
 }
 
-template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, int BK, bool P_TRANS, int EPI, bool DROP,
+template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, bool P_TRANS, int EPI, bool DROP,
           bool WGRAD>
 static hipError_t rows_launch(RowsArgs a, int E, hipStream_t s) {
-    auto kern = gemm_rows_kernel<IP, WP, IQ, WQ, STAGES, WPE, BK, P_TRANS, EPI, DROP, WGRAD>;
+    auto kern = gemm_rows_kernel<IP, WP, IQ, WQ, STAGES, WPE, P_TRANS, EPI, DROP, WGRAD>;
     constexpr int PB = 32 * IP * WP, QB = 32 * IQ * WQ;
-    constexpr int lds = rows_lds(IP, WP, IQ, WQ, STAGES, BK);
+    constexpr int lds = rows_lds(IP, WP, IQ, WQ, STAGES);
     static PerDeviceOnce once;
     hipError_t err = once_per_device(once, [&] {
         return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -511,15 +513,15 @@ int rows_wgrad_tile(const Workspace &w, int64_t Qdim, int64_t Pdim) {
 template <bool P_TRANS, int EPI, bool DROP>
 static hipError_t rows_by_tile(const RowsArgs &a, int E, int tile, hipStream_t s) {
     switch (tile) {
-    case ROWS_32x128: return rows_launch<1, 4, 1, 1, 3, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
-    case ROWS_64x256: return rows_launch<2, 4, 2, 1, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
-    case ROWS_96x128: return rows_launch<1, 4, 3, 1, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
-    case ROWS_128x128: return rows_launch<2, 2, 2, 2, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
+    case ROWS_32x128: return rows_launch<1, 4, 1, 1, 3, 2, P_TRANS, EPI, DROP, false>(a, E, s);
+    case ROWS_64x256: return rows_launch<2, 4, 2, 1, 2, 2, P_TRANS, EPI, DROP, false>(a, E, s);
+    case ROWS_96x128: return rows_launch<1, 4, 3, 1, 2, 2, P_TRANS, EPI, DROP, false>(a, E, s);
+    case ROWS_128x128: return rows_launch<2, 2, 2, 2, 2, 2, P_TRANS, EPI, DROP, false>(a, E, s);
     }
     if constexpr (EPI != ROWS_COMBINE) switch (tile) {
-    case ROWS_256x256: return rows_launch<2, 4, 4, 2, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
-    case ROWS_320x256: return rows_launch<2, 4, 5, 2, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
-    case ROWS_256x384: return rows_launch<3, 4, 4, 2, 2, 2, 64, P_TRANS, EPI, DROP, false>(a, E, s);
+    case ROWS_256x256: return rows_launch<2, 4, 4, 2, 2, 2, P_TRANS, EPI, DROP, false>(a, E, s);
+    case ROWS_320x256: return rows_launch<2, 4, 5, 2, 2, 2, P_TRANS, EPI, DROP, false>(a, E, s);
+    case ROWS_256x384: return rows_launch<3, 4, 4, 2, 2, 2, P_TRANS, EPI, DROP, false>(a, E, s);
     }
     return hipErrorInvalidValue;
 }
@@ -594,8 +596,8 @@ hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const v
         const bool two = kind == GEMM_WGRAD2;
         ProfScope ps(two ? "gemm2_wgrad" : "gemm1_wgrad", s);
         switch (tile) {
-        case ROWS_128x128: return rows_launch<2, 2, 2, 2, 2, 2, 64, true, ROWS_PLAIN, false, true>(a, E, s);
-        case ROWS_256x128: return rows_launch<2, 2, 4, 2, 1, 2, 64, true, ROWS_PLAIN, false, true>(a, E, s);
+        case ROWS_128x128: return rows_launch<2, 2, 2, 2, 2, 2, true, ROWS_PLAIN, false, true>(a, E, s);
+        case ROWS_256x128: return rows_launch<2, 2, 4, 2, 1, 2, true, ROWS_PLAIN, false, true>(a, E, s);
         }
         return hipErrorInvalidValue;
     }
@@ -606,7 +608,7 @@ hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const v
 template <int IP, int WP, int IQ, int WQ, int STAGES, int GP, int GWP, int GQ, int GWQ, int GSTAGES>
 static hipError_t rows_backward_launch(RowsArgs3 a, int E, hipStream_t s) {
     auto kern = gemm_rows_backward_kernel<IP, WP, IQ, WQ, STAGES, GP, GWP, GQ, GWQ, GSTAGES>;
-    constexpr int l0 = rows_lds(IP, WP, IQ, WQ, STAGES, 64), l1 = rows_lds(GP, GWP, GQ, GWQ, GSTAGES, 64);
+    constexpr int l0 = rows_lds(IP, WP, IQ, WQ, STAGES), l1 = rows_lds(GP, GWP, GQ, GWQ, GSTAGES);
     constexpr int lds = l0 > l1 ? l0 : l1;
     static PerDeviceOnce once;
     hipError_t err = once_per_device(once, [&] {

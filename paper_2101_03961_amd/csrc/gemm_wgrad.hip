@@ -64,8 +64,8 @@ __global__ __launch_bounds__(512, 2) void gemm_wgrad_kernel(WgradArgs a) {
         q0 = qt * QB;
         p0 = pt * PB;
     };
-    RowsTrans<PB, NW, BK> op;
-    RowsTrans<QB, NW, BK> oq;
+    RowsTrans<PB, NW> op;
+    RowsTrans<QB, NW> oq;
     constexpr int kLoads = decltype(op)::kLoads + decltype(oq)::kLoads;
     op.init_frag(lane, wp * 32 * IP);
     oq.init_frag(lane, wq * 32 * IQ);

@@ -68,13 +68,13 @@ template <int R, int NW, int S = 32> struct F32Direct : RowsDirect<R, NW, 64> {
     int part;
 };
 
-// [k][row] operand of R rows: LDS [BK k][R], see TransOperand64
-template <int R, int NW, int BK = 64> struct RowsTrans {
-    static constexpr int kLoads = R * BK / (512 * NW);
+// [k][row] operand of R rows: LDS [64 k][R], see TransOperand64
+template <int R, int NW> struct RowsTrans {
+    static constexpr int kLoads = R / (8 * NW);
     static constexpr int kChunks = R / 8;          // 16-byte chunks of a k-row
     static constexpr int kPeriod = R == 384 ? 3 : R == 256 ? 2 : 1;   // loads until (k-row mod 4, chunk) repeat
     static constexpr int kPeriodRows = kPeriod * 64 / kChunks;        // k-rows they cover
-    static_assert(kLoads * 512 * NW == R * BK && kLoads % kPeriod == 0, "rows divide over the waves");
+    static_assert(kLoads * 8 * NW == R && kLoads % kPeriod == 0, "rows divide over the waves");
     static_assert(R >= 128, "the permutation moves a chunk by up to 12");
     static __device__ __forceinline__ int perm(int kr) { return (kr & 3) << 2; }
     i32x4 rsrc;
