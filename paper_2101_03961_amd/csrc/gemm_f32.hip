@@ -218,7 +218,7 @@ __global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32A
             for (int r = 0; r < kAcc; ++r) acc[i][j][r] = total[i][j][r] = 0.f;
 
     constexpr int kLoads = decltype(op)::kLoads + decltype(oq)::kLoads;
-    auto issue = [&](int kt) {   // k past the end: zeros
+    auto issue = [&](int kt) {   // (steps past the end: never read)
         const uint32_t at = lds0 + (uint32_t)(kt % STAGES * kStage);
 #pragma unroll
         for (int i = 0; i < decltype(op)::kLoads; ++i) op.issue_one(at, kt * 32, wave, i);
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32A
                     for (int j = 0; j < IQ; ++j) acc[i][j] = mfma_f32(fp[i][m], fq[j][m], acc[i][j]);
         }
     }
-    rows_wait_vmcnt<0>();   // the trailing (zero) loads
+    rows_wait_vmcnt<0>();   // the trailing loads
     if (!live) return;
     // a lane holds, for row q = lane % S of each tile, columns 256 / S g + 4 (lane / S) .. + 3
     float *Cout = a.Cout + (size_t)e * a.c_batch;
@@ -305,7 +305,8 @@ __global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32A
                 }
                 *(float4 *)(Cout + at) = make_float4(v[0], v[1], v[2], v[3]);
                 if (EPI == F32_COMBINE)
-                    *(float4 *)(a.y + (size_t)tok * a.ldc + p) = make_float4(v[0] * gate, v[1] * gate, v[2] * gate, v[3] * gate);
+                    *(float4 *)(a.y + (size_t)tok * a.ldc + p) =
+                        make_float4(v[0] * gate, v[1] * gate, v[2] * gate, v[3] * gate);
             }
     }
 }

@@ -1,4 +1,5 @@
-// Grouped expert GEMMs with one tile per block (bf16 MFMA, fp32 accumulation).
+// Grouped expert GEMMs with one tile per block (bf16 MFMA, fp32 accumulation): the products whose rows are tokens,
+// and the weight gradients of layers with few or small tiles (the others: gemm_wgrad.hip, gemm_bf16.hip).
 //
 // The same products as gemm_bf16.hip's,
 //     C_e[q][p] = sum_k Q_e(q, k) P_e(p, k),
@@ -6,7 +7,9 @@
 // computes one tile and ends, so the hardware deals the tiles to the CUs as they become free.
 // (Persistent blocks with the next tile's loads under way during the epilogue, fragments read
 // one sub-step ahead, or half of the waves loading and the other half storing, measured the same or
-// slower with these tiles: experts hold different numbers of rows, and the deal evens that out.)
+// slower for the products whose rows are tokens, before their loads were spread over the step: experts
+// hold different numbers of rows, and the deal evens that out.  The weight gradients, whose tiles are all alike,
+// gain by persistent blocks: gemm_wgrad.hip.)
 //
 // What bounds it.  With few rows per expert: streaming the weights from HBM.  So a tile is as tall
 // as the capacity asks for, every weight line is read once, and rows that do not exist cost no
@@ -101,7 +104,7 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    auto issue_load = [&](uint32_t at, int kt, int i) {   // load i of a step; k past the end: zeros
+    auto issue_load = [&](uint32_t at, int kt, int i) {   // load i of a step (past the end: never read)
         if (i < kLoadsP) op.issue_one(at, kt * BK, wave, i);
         else oq.issue_one(at + kPBytes, kt * BK, wave, i - kLoadsP);
     };
@@ -148,7 +151,7 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
         st = st == STAGES - 1 ? 0 : st + 1;
         fill = fill == STAGES - 1 ? 0 : fill + 1;
     }
-    rows_wait_vmcnt<0>();   // the trailing (zero) loads
+    rows_wait_vmcnt<0>();   // the trailing loads
     __syncthreads();
 
     // Epilogue: 32 rows at a time through LDS of the wave's own, so that rows leave in segments
@@ -403,8 +406,11 @@ static hipError_t rows_launch(RowsArgs a, int E, hipStream_t s) {
 // ---- which tile ---------------------------------------------------------------------
 // Per tile shape: CU time of one 64-k step and of a tile's start and epilogue (microseconds, all
 // CUs busy), and the rate at which the shape streams weights when they are what it waits for
-// (GB/s).  Measured on 128 experts of 768 x 3072 with 16 .. 512 rows each; the estimate made from
-// them picks the fastest or one within 5 % of it over that range and at 64 experts of 4096 x 10240.
+// (GB/s).  Measured on 128 experts of 768 x 3072 with 16 .. 512 rows each, when a tile cost the same however
+// many rows it held; the estimate made from them picked the fastest or one within 5 % of it over that range
+// and at 64 experts of 4096 x 10240.  Since then tiles of eight waves with few rows run with fewer row blocks,
+// which only 256 x 384's line below knows of: between 64 and 200 rows per expert, and where 256 x 256
+// wins by a few per cent, the choice may be off by more.
 struct RowsModel {
     int tile, qb, pb;
     double step, once, gbs;

@@ -119,7 +119,7 @@ __global__ __launch_bounds__(64 * (RouterBlock<XT, ET, WT, TT>::NW), 2) void rou
     ow.init(W_r, d, E, lane, et);
     constexpr int kLX = decltype(ox)::kLoads, kLoads = kLX + decltype(ow)::kLoads;
     const int nk = (d + BK - 1) / BK;
-    auto issue = [&](int kt) {   // k past the end: zeros
+    auto issue = [&](int kt) {   // (steps past the end: never read)
         const uint32_t st = lds0 + (uint32_t)((kt % STAGES) * R::kStage);
 #pragma unroll
         for (int i = 0; i < kLX; ++i) ox.issue_one(st, kt * BK, wave % NX, i);
