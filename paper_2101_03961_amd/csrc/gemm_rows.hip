@@ -64,7 +64,7 @@ enum { ROWS_PLAIN = 0, ROWS_RELU = 1, ROWS_MASK = 2, ROWS_COMBINE = 3 };
 // Mask bits: one byte per 16-byte piece of the output (bits 0..3: low halves of its four words, 4..7:
 // high halves), [tile][wave][32-row round][pass][lane] in the order the epilogue handles them.
 template <int IP, int WP, int IQ, int IQ_MAX, int WQ, int STAGES, bool P_TRANS, int EPI, bool DROP,
-          bool WGRAD>
+          bool WGRAD, bool GUARD = false>
 __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, int e, int q0, int p0, int qlim,
                                           int klim, int lane, int wave) {
     constexpr int NW = WP * WQ, PB = 32 * IP * WP, QB = 32 * IQ_MAX * WQ;
@@ -162,7 +162,10 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
     const int wrow = lane & 31;
     auto swz = [](int row) { return IP == 1 ? (row >> 2) & 3 : IP == 2 ? (row >> 1) & 7 : 0; };
     // Stores through a descriptor: rows past the last one and columns past the matrix get an offset outside it
-    // and store nothing, without a branch per store.
+    // and store nothing, without a branch per store.  GUARD: with one, which spaces the stores; large weight gradients of
+    // rows that share lines gain by it (see rows_part_lines; us of both gradients, with / without, five tokens per
+    // expert, 208 experts of 1080 x 2408 456 / 486, 34 of 2160 x 8520 569 / 588; smaller ones and whole lines lose, 69 of
+    // 616 x 1944 73 / 68, 110 of 768 x 3072 193 / 185).
     const auto crsrc = __builtin_amdgcn_make_buffer_rsrc(a.Cout + (size_t)e * a.c_batch, 0,
                                                          (int)((uint32_t)qlim * (uint32_t)a.ldc * 2u), 0x00020000);
     const uint32_t c_step = 64u * (uint32_t)a.ldc;   // bytes of 32 rows
@@ -241,7 +244,7 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
                 for (int w = 0; w < 4; ++w) val[w] &= ((byte >> w) & 0x10001u) * 0xffffu;
             }
             const uint32_t off = 32 * j < left[x] ? cvoff[x] + (uint32_t)j * c_step : kOobOffset;
-            __builtin_amdgcn_raw_buffer_store_b128(val, crsrc, (int)off, 0, 0);
+            if (!GUARD || off != kOobOffset) __builtin_amdgcn_raw_buffer_store_b128(val, crsrc, (int)off, 0, 0);
             if (EPI == ROWS_COMBINE && tok[x] >= 0) {   // of the rounded values, as the combine pass
                 u32x4 out;
 #pragma unroll
@@ -264,7 +267,7 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
 // with as few blocks as hold them, so with fewer products, fragment reads and loads (128 experts of 768 x 3072, 64
 // rows in tiles of 256: masked gradient 152 -> 140 us, first forward 186 -> 176; 64 of 4096 x 10240, 256 rows in
 // tiles of 320: 1530 -> 1480).
-template <int IP, int WP, int IQ, int WQ, int STAGES, bool P_TRANS, int EPI, bool DROP, bool WGRAD>
+template <int IP, int WP, int IQ, int WQ, int STAGES, bool P_TRANS, int EPI, bool DROP, bool WGRAD, bool GUARD = false>
 __device__ __forceinline__ void rows_block(const RowsArgs &a, char *lds, int L) {
     constexpr int PB = 32 * IP * WP, QB = 32 * IQ * WQ;
     const int lane = threadIdx.x & 63;
@@ -327,8 +330,8 @@ __device__ __forceinline__ void rows_block(const RowsArgs &a, char *lds, int L) 
     const int q0 = qt * QB, p0 = pt * PB;
     if (q0 >= qlim) return;
 #define SW_ROWS(N) \
-    rows_tile<IP, WP, (N) < IQ ? (N) : IQ, IQ, WQ, STAGES, P_TRANS, EPI, DROP, WGRAD>(a, lds, L, e, q0, p0, qlim, \
-                                                                                          klim, lane, wave)
+    rows_tile<IP, WP, (N) < IQ ? (N) : IQ, IQ, WQ, STAGES, P_TRANS, EPI, DROP, WGRAD, GUARD>(a, lds, L, e, q0, p0, \
+                                                                                                 qlim, klim, lane, wave)
     if constexpr (WP * WQ == 8 && !WGRAD) {
         const int blocks = (qlim - q0 + 32 * WQ - 1) / (32 * WQ);
         if (blocks <= 1) SW_ROWS(1);
@@ -343,10 +346,10 @@ __device__ __forceinline__ void rows_block(const RowsArgs &a, char *lds, int L) 
 }
 
 template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, bool P_TRANS, int EPI, bool DROP,
-          bool WGRAD>
+          bool WGRAD, bool GUARD>
 __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    rows_block<IP, WP, IQ, WQ, STAGES, P_TRANS, EPI, DROP, WGRAD>(a, lds, blockIdx.y * a.grid_x + blockIdx.x);
+    rows_block<IP, WP, IQ, WQ, STAGES, P_TRANS, EPI, DROP, WGRAD, GUARD>(a, lds, blockIdx.y * a.grid_x + blockIdx.x);
 }
 
 // Three products in one launch: the first layer's data gradient and both weight gradients, which do not depend on
@@ -385,9 +388,9 @@ static int64_t rows_plan(RowsArgs &a, int E, int QB, int PB, bool wgrad) {
 }
 
 template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, bool P_TRANS, int EPI, bool DROP,
-          bool WGRAD>
+          bool WGRAD, bool GUARD = false>
 static hipError_t rows_launch(RowsArgs a, int E, hipStream_t s) {
-    auto kern = gemm_rows_kernel<IP, WP, IQ, WQ, STAGES, WPE, P_TRANS, EPI, DROP, WGRAD>;
+    auto kern = gemm_rows_kernel<IP, WP, IQ, WQ, STAGES, WPE, P_TRANS, EPI, DROP, WGRAD, GUARD>;
     constexpr int PB = 32 * IP * WP, QB = 32 * IQ * WQ;
     constexpr int lds = rows_lds(IP, WP, IQ, WQ, STAGES);
     static PerDeviceOnce once;
@@ -492,13 +495,25 @@ static const WgradModel kWgradModels[] = {
     {ROWS_384x256, 384, 256, 2.05, 6.0, true},
 };
 
+// A weight gradient whose rows begin inside a 128-byte line and that is more than twice the memory-side cache: two waves
+// write each row's shared lines, and parts of a line that do not meet in L2 go to HBM one by one.
+static bool rows_part_lines(const Workspace &w, int64_t Qdim, int64_t Pdim) {
+    return Pdim % 64 != 0 && (double)w.E * (double)Qdim * (double)Pdim * 2. > 512e6;
+}
+
 // Tile of a weight gradient of Qdim x Pdim; ROWS_NONE: the persistent kernel of gemm_bf16.hip.
 int rows_wgrad_tile(const Workspace &w, int64_t Qdim, int64_t Pdim) {
     const double cap = (double)w.C, mean = fmin((double)w.T / (double)w.E, cap);
     // Fewer than eight tokens per expert: little but the store, where two small blocks per CU do as well or better
     // (169 experts of 272 x 2064, 186 tokens: 31 us, 384 x 256 36; 236 of 2000 x 856, 205 tokens: 191, 256 x 384 200;
     // 147 of 296 x 2464, 96 tokens: 43, 128 x 128 48).
-    if (mean < 8.) return w.E * ceil_div(Qdim, 256) * ceil_div(Pdim, 256) < 256 ? ROWS_128x128 : ROWS_256x128;
+    // Large gradients with shared lines: fewer than 32 where the column tiles, which share them, follow each other (us of
+    // the second gradient, 256 x 128 / persistent; 208 experts of 1080 x 2408, 12, 24 and 40 tokens each 237 / 271,
+    // 255 / 275, 284 / 261; 34 of 2160 x 8520 282 / 336, 288 / 329, 301 / 311; the other way, 32 of 3000 x 6008 with 12
+    // tokens each, 406 / 298).
+    const bool in_turn = ceil_div(Qdim, 256) > ceil_div(Pdim, 128);
+    if (mean < (in_turn && rows_part_lines(w, Qdim, Pdim) ? 32. : 8.))
+        return w.E * ceil_div(Qdim, 256) * ceil_div(Pdim, 256) < 256 ? ROWS_128x128 : ROWS_256x128;
     const double steps = rows_tiles(mean, cap, 64);
     int best = ROWS_128x128;
     double best_us = 1e30;
@@ -603,7 +618,10 @@ hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const v
         ProfScope ps(two ? "gemm2_wgrad" : "gemm1_wgrad", s);
         switch (tile) {
         case ROWS_128x128: return rows_launch<2, 2, 2, 2, 2, 2, true, ROWS_PLAIN, false, true>(a, E, s);
-        case ROWS_256x128: return rows_launch<2, 2, 4, 2, 1, 2, true, ROWS_PLAIN, false, true>(a, E, s);
+        case ROWS_256x128:
+            if (rows_part_lines(w, a.Qdim, a.Pdim))
+                return rows_launch<2, 2, 4, 2, 1, 2, true, ROWS_PLAIN, false, true, true>(a, E, s);
+            return rows_launch<2, 2, 4, 2, 1, 2, true, ROWS_PLAIN, false, true>(a, E, s);
         }
         return hipErrorInvalidValue;
     }

@@ -112,6 +112,14 @@ def test_weight_gradients_of_persistent_blocks(T, d, f, E, cf, likes):
         assert not empty[0 if likes == "first" else -1]
 
 
+@pytest.mark.parametrize("T,cf,bias", [(500, 4.0, False), (2400, 1.25, False), (2400, 4.0, True)])
+def test_large_weight_gradients_with_shared_lines(T, cf, bias):
+    """Rows that share 128-byte lines, more than 512 MB: both gradients or the second one with guarded stores."""
+    from parity import compare_sampled
+    s = SwitchShape("t", T, 1080, 2408, 100, cf, dtype="bf16", zipf_bias=bias, seed_index=53)
+    _report("shared lines %s" % ((T, cf, bias),), compare_sampled(s, make_inputs(s, _dev()), n_experts=3))
+
+
 def test_bf16_without_slots():
     """Capacity 0 in a layer of many experts: zero outputs and zero weight gradients."""
     from parity import compare_full

@@ -107,6 +107,13 @@ def test_tile_follows_the_rows_of_an_expert(recorder, T, d, f, E, cf, first, sec
     (9000, 264, 760, 80, 0.007, "rows 2,2,4,2", "rows 2,2,4,2"),        # no slots
     (32768, 512, 1024, 32, 1.0, "bf16", "bf16"),
     (512, 768, 3072, 128, 4.0, "rows 2,2,4,2", "rows 2,2,4,2"),
+    # rows that share lines, more than 512 MB: guarded stores, up to 32 tokens per expert if column tiles are neighbours
+    (500, 1080, 2408, 100, 4.0, "rows 2,2,4,2 guarded", "rows 2,2,4,2 guarded"),
+    (2400, 1080, 2408, 100, 1.25, "wgrad 4,2,3,4", "rows 2,2,4,2 guarded"),
+    (3200, 1080, 2408, 100, 1.25, "wgrad 4,2,3,4", "wgrad 3,4,4,2"),
+    (384, 3000, 6008, 32, 1.25, "wgrad 4,2,3,4", "wgrad 3,4,4,2"),
+    (490, 1080, 2408, 98, 4.0, "rows 2,2,4,2", "rows 2,2,4,2"),         # less than 512 MB
+    (500, 1088, 2432, 100, 4.0, "rows 2,2,4,2", "rows 2,2,4,2"),        # whole lines
 ])
 def test_kernel_of_the_weight_gradients(recorder, T, d, f, E, cf, first, second):
     (status, _, _, launches), = recorder(call("backward", T, d, f, E, cf))
@@ -114,8 +121,10 @@ def test_kernel_of_the_weight_gradients(recorder, T, d, f, E, cf, first, second)
     got = []
     for name, *_ in launches:
         m = re.search(r"gemm_(rows|wgrad|bf16)_kernelI((?:L[ib]\d+E)*)", name)
-        if m and (m[1] == "wgrad" or m[1] == "rows" and m[2].endswith("Lb1E") or m[1] == "bf16" and m[2].startswith("Lb1ELb1E")):
-            got.append(m[1] + ("" if m[1] == "bf16" else " " + ",".join(re.findall(r"Li(\d+)E", m[2])[:4])))
+        flags = re.findall(r"Lb([01])E", m[2]) if m else []
+        if m and (m[1] == "wgrad" or m[1] == "rows" and flags[-2] == "1" or m[1] == "bf16" and flags[:2] == ["1", "1"]):
+            got.append(m[1] + ("" if m[1] == "bf16" else " " + ",".join(re.findall(r"Li(\d+)E", m[2])[:4])) +
+                       (" guarded" if m[1] == "rows" and flags[-1] == "1" else ""))
     assert got[:2] == [first, second]
 
 
