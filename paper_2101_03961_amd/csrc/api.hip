@@ -177,10 +177,13 @@ Workspace layout_workspace(const switch_config *cfg) {
     }
     w.relu_bits = take(bits);
     // The combine costs a launch; in the epilogues of small tiles, the fp32 ones among them, it costs nearly nothing.
-    // (256-row tiles: their second set of stores takes two thirds of the pass it saves.)
+    // (256-row tiles: their second set of stores takes two thirds of the pass it saves.  Behind re-routing stages a pass
+    // that clears rows would take the combine's place: 45 tokens of 80 x 176, 29 experts, one stage, 65 us with the
+    // combine and 66 in the epilogue.)
     const int second = w.gemm_tile[GEMM_FWD2];
-    w.combine_in_gemm = w.C > 0 && !w.fused && (cfg->act_dtype == SW_BF16 ? second >= ROWS_32x128 && second <= ROWS_128x128
-                                                                          : gemm_f32_on_mfma(w, w.C, w.d));
+    w.combine_in_gemm = w.C > 0 && !w.fused && cfg->ntlb_rounds == 0 &&
+                        (cfg->act_dtype == SW_BF16 ? second >= ROWS_32x128 && second <= ROWS_128x128
+                                                   : gemm_f32_on_mfma(w, w.C, w.d));
     w.ntlb_rounds = cfg->ntlb_rounds;
     if (w.ntlb_rounds > 0) {
         const size_t nE = (size_t)w.n * E * 4;
@@ -338,7 +341,7 @@ static int forward_on(const switch_config *cfg, const Workspace &w, const void *
     const TokenMajor tm{x, nullptr, y};
     // combine in the second GEMM: rows of tokens without a slot are +0 (cleared above, or here once the
     // re-routing stages have run), all others are written by its epilogue
-    if ((w.fused || w.combine_in_gemm) && !zero_rows_with_positions(w) &&
+    if (w.fused && !zero_rows_with_positions(w) &&
         (st = status_of(launch_zero_dropped(w, ws, y, s))))
         return st;
     if ((st = status_of(gemm(GEMM_FWD1, w, ws, W_in, W_out, nullptr, nullptr, tm, s)))) return st;

@@ -139,8 +139,8 @@ struct Workspace {
     size_t kept;                // i32 [E]      kept tokens per expert: sum over groups of min(count, Cg)
     int fused;                  // bf16: dispatch and combine run inside the GEMMs (x, dy gathered by
                                 //   the slot -> token table, y written by the second GEMM)
-    bool combine_in_gemm;       // the second GEMM's epilogue writes y too (small tiles, fp32); rows without a slot are
-                                //   cleared where the slots are assigned
+    bool combine_in_gemm;       // the second GEMM's epilogue writes y too (small tiles, fp32; not behind re-routing
+                                //   stages); rows without a slot are cleared where the slots are assigned
     int gemm_tile[6];           // RowsTile of each GemmKind; ROWS_NONE: the persistent kernel (bf16)
     size_t slot_token;          // i32 [E][C] + 128  token held by each slot (valid for slot < kept[e])
     size_t slot_gate;           // f32 [E][C]   gate of that token (the probability that scales its output)

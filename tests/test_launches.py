@@ -144,6 +144,20 @@ def test_small_layers_take_three_products_in_one_launch(recorder, T, d, f, E, cf
     assert sum("gemm_rows" in k[0] or "gemm_wgrad" in k[0] for k in launches) == (2 if data else 4)
 
 
+# The combine: in the second GEMM's epilogue (small tiles, fp32), which saves a launch unless re-routing stages follow the
+# assignment of the slots; else a pass of its own.
+@pytest.mark.parametrize("T,d,f,E,cf,dtype,rounds,own", [
+    (45, 80, 176, 29, 2.6, "bf16", 0, False), (45, 80, 176, 29, 2.6, "bf16", 1, True),
+    (256, 64, 256, 4, 1.25, "f32", 0, False), (256, 64, 256, 4, 1.25, "f32", 3, True),
+    (65536, 768, 3072, 128, 1.0, "bf16", 0, True),
+])
+def test_combine_in_the_epilogue_or_as_a_pass(recorder, T, d, f, E, cf, dtype, rounds, own):
+    (status, _, _, launches), = recorder(call("forward", T, d, f, E, cf, dtype=dtype, ntlb=rounds))
+    assert status == 0
+    assert sum("combine_kernel" in k[0] for k in launches) == (1 if own else 0)
+    assert not any("zero_dropped" in k[0] for k in launches)
+
+
 # fp32 products: matrix cores while an expert's matrices fit a buffer descriptor, else the FMA kernel
 @pytest.mark.parametrize("T,d,f,E,cf,kernel", [(256, 64, 256, 4, 1.25, "gemm_f32_mfma_kernel"),
                                                (101, 12, 516, 2, 20800.0, "gemm_f32_kernel"),
