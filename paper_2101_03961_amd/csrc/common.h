@@ -133,7 +133,7 @@ struct Workspace {
     size_t counts_g;            // i32 [n][E]   ... per group
     size_t psum_g;              // f32 [n][E]   sum of router probabilities per group and expert
     size_t loss_part;           // f64 [8]      parts of sum (counts / Tg) (psum / Tg), one per scan block
-    size_t hit;                 // i32          experts with a kept token, before re-routing stages
+    size_t hit;                 // i32          experts with a kept token, before re-routing stages (rows_count_hit)
     size_t grp_off;             // i32 [n][E]   first slot of group g inside expert e's slots:
                                 //              sum of min(counts_g, Cg) over earlier groups
     size_t kept;                // i32 [E]      kept tokens per expert: sum over groups of min(count, Cg)
@@ -313,6 +313,9 @@ enum RowsTile {
 // gradients), and the bytes of ReLU bits it takes
 int rows_tile_for(const Workspace &w, int64_t Pdim, int64_t Kdim, int64_t bits_limit);
 int rows_wgrad_tile(const Workspace &w, int64_t Qdim, int64_t Pdim);
+// a product of the layer looks at the number of experts with kept tokens (half a microsecond of the kernel that assigns
+// the slots)
+bool rows_count_hit(const Workspace &w);
 int64_t rows_bits_bytes(int tile, int64_t E, int64_t C, int64_t f);
 hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const void *W_in, const void *W_out,
                             void *dW_in, void *dW_out, void *y, int tile, hipStream_t s);

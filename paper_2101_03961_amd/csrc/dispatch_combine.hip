@@ -72,7 +72,8 @@ __device__ __forceinline__ uint32_t wave_token() {
 struct AssignArgs {
     const int32_t *idx, *local_rank, *block_counts, *block_off;
     const float *block_psum, *gate;
-    int32_t *grp_off, *counts, *kept, *counts_g, *hit;
+    int32_t *grp_off, *counts, *kept, *counts_g;
+    int32_t *hit;               // (null: not counted)
     int32_t *pos_out, *counts_out;
     uint8_t *dropped_out;
     int32_t *slot_token;
@@ -165,9 +166,9 @@ __global__ __launch_bounds__(256) void assign_kernel(AssignArgs a) {
                 a.counts_out[e0 + tid] = total;
                 a.kept[e0 + tid] = kept;
             }
-            hit += __syncthreads_count(kept > 0);
+            if (a.hit) hit += __syncthreads_count(kept > 0);
         }
-        if (tid == 0) *a.hit = hit;
+        if (a.hit && tid == 0) *a.hit = hit;
         red[tid] = loss;
         __syncthreads();
         for (int s = 128; s >= 1; s >>= 1) {
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(256) void assign_kernel(AssignArgs a) {
             for (int i = 0; i < a.loss_parts; ++i) sum += a.loss_part[i];
             a.aux_out[0] = (float)(a.loss_scale * sum);
         }
-        if (blockIdx.x == 0) {
+        if (a.hit && blockIdx.x == 0) {
             int hit = 0;
             for (int e0 = 0; e0 < E; e0 += 256) hit += __syncthreads_count(e0 + tid < E && a.kept[e0 + tid] > 0);
             if (tid == 0) *a.hit = hit;
@@ -432,7 +433,7 @@ hipError_t launch_dispatch(const Workspace &w, int dtype, float alpha, const voi
         a.counts = (int32_t *)(ws + w.counts);
         a.kept = (int32_t *)(ws + w.kept);
         a.counts_g = (int32_t *)(ws + w.counts_g);
-        a.hit = (int32_t *)(ws + w.hit);
+        a.hit = rows_count_hit(w) ? (int32_t *)(ws + w.hit) : nullptr;
         a.pos_out = position_in_expert;
         a.counts_out = expert_counts;
         a.dropped_out = dropped;

@@ -439,6 +439,12 @@ static double rows_tiles(double mean, double cap, int qb) {
     return sum / 5.;
 }
 
+bool rows_count_hit(const Workspace &w) {
+    for (GemmKind k : {GEMM_FWD1, GEMM_FWD2, GEMM_DGRAD2, GEMM_DGRAD1})   // (tiles of eight waves: rows_block)
+        if (w.gemm_tile[k] == ROWS_64x256 || w.gemm_tile[k] >= ROWS_256x256) return w.E <= 64 * kFewExperts;
+    return false;
+}
+
 int64_t rows_bits_bytes(int tile, int64_t E, int64_t C, int64_t f) {
     for (const RowsModel &m : kRowsModels)
         if (m.tile == tile) return E * ceil_div(C, m.qb) * ceil_div(f, m.pb) * (m.qb * m.pb / 8);
