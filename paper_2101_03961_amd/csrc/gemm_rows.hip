@@ -19,8 +19,10 @@
 // allow: eight waves with 3 x 4 or 2 x 5 MFMA tiles of 32 x 32 each hold 256 x 384 or 320 x 256
 // accumulators, 20 % fewer operand bytes per product than 256 x 256.
 //
-// A block has WP x WQ waves, each with IP x IQ MFMA 32x32x16 tiles (P is the MFMA "A" side).  k
-// advances 64 (BK) at a time through STAGES LDS stages filled by direct loads; one barrier per step.
+// A block has WP x WQ waves, each with 2 IP x 2 IQ MFMA 16x16x32 tiles (P is the MFMA "A" side).  (Of 32x32x16 tiles half
+// as many instructions do the same products with the same reads, but they draw more power: with random operands
+// and nothing else the chip holds 1750 TFLOP/s with them and 2060 with 16x16x32; here 2.0 and 2.2 GHz.)  k advances 64 (BK)
+// at a time through STAGES LDS stages filled by direct loads.
 #include <math.h>
 
 #include "common.h"
@@ -74,8 +76,8 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
 
     typename std::conditional<P_TRANS, RowsTrans<PB, NW>, RowsDirect<PB, NW>>::type op;
     typename std::conditional<WGRAD, RowsTrans<QB, NW>, RowsDirect<QB, NW>>::type oq;
-    op.init_frag(lane, wp * 32 * IP);
-    oq.init_frag(lane, wq * 32 * IQ);
+    op.init_frag16(lane, wp * 32 * IP);
+    oq.init_frag16(lane, wq * 32 * IQ);
     op.init(a.P + (size_t)e * a.p_batch, a.ldp, p0, a.Pdim, klim, lane, wave);
     oq.init(a.Q + (size_t)e * a.q_batch, a.ldq, q0, qlim, klim, lane, wave);
     constexpr int kLoadsP = decltype(op)::kLoads;
@@ -96,13 +98,11 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
         }
     }
 
-    f32x16 acc[IP][IQ];
+    f32x4 acc[2 * IP][2 * IQ];
 #pragma unroll
-    for (int i = 0; i < IP; ++i)
+    for (int i = 0; i < 2 * IP; ++i)
 #pragma unroll
-        for (int j = 0; j < IQ; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int j = 0; j < 2 * IQ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     auto issue_load = [&](uint32_t at, int kt, int i) {   // load i of a step (past the end: never read)
         if (i < kLoadsP) op.issue_one(at, kt * BK, wave, i);
@@ -112,44 +112,94 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
 #pragma unroll
         for (int i = 0; i < kLoads; ++i) issue_load(lds0 + (uint32_t)(st * kStage), kt, i);
     };
-    // Eight waves issue a step's loads in parts behind the fragment reads of its first sub-steps: in one
-    // burst ahead of them, the address unit's queue held up the reads and with them the products (start
-    // of a step 1300 cycles without an MFMA; over 3 of the 4 sub-steps / before the reads: masked gradient of
-    // 128 experts x 512 x 768 x 3072 310 / 332 us, 64 x 256 x 4096 x 10240 1360-1530 / 1380-1580).  Four waves
-    // issue few, and their steps are short: first.
-    constexpr int kSpread = NW < 8 ? 0 : 3;
+    // Eight waves, two stages.  The P fragments of a half step (32 k) are held in registers, the Q fragments pass by, one
+    // ahead.  So P's stage is free once the fragments of its second half are read, in the middle of the step, and is filled
+    // with the step after the next from there on, Q's stage at the end: every load has between half a step and one
+    // and a half to land.  us, loads of the next step only and a barrier per step / here: 128 experts x 512 x 768 x 3072 first
+    // forward 314 / 295, second 280 / 253, masked gradient 312 / 296, first data gradient 283 / 257; 64 x 256 x 4096 x 10240
+    // 1346 / 1240, 1327 / 1170, 1470 / 1382, 1434 / 1300.  (The next P fragments read between the products that use the
+    // present ones last: registers spill.)
+    if constexpr (NW == 8 && STAGES == 2) {
+        constexpr int kLoadsQ = kLoads - kLoadsP, kGroups = 2 * IQ;   // groups of products per half step
+        auto issue_p = [&](int kt, int i) { issue_load(lds0 + (uint32_t)((kt & 1) * kStage), kt, i); };
+        auto issue_q = [&](int kt, int i) { issue_load(lds0 + (uint32_t)((kt & 1) * kStage), kt, kLoadsP + i); };
 #pragma unroll
-    for (int s = 0; s < STAGES - 1; ++s) issue(s, s);
-    int st = 0, fill = STAGES - 1;
-    for (int kt = 0; kt < nk; ++kt) {
-        if (STAGES == 1) {   // a single stage: other blocks of the CU cover the wait
-            if (kt) __syncthreads();
-            issue(kt, 0);
+        for (int i = 0; i < kLoads; ++i) issue_load(lds0, 0, i);
+#pragma unroll
+        for (int i = 0; i < kLoadsP; ++i) issue_p(1, i);
+        rows_wait_vmcnt<kLoadsP>();
+        __syncthreads();
+        bf16x8 held[2 * IP], next = oq.frag16(lds + kPBytes, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 2 * IP; ++i) held[i] = op.frag16(lds, i, 0);
+#pragma nounroll
+        for (int kt = 0; kt < nk; ++kt) {
+            const char *sp = lds + (kt & 1) * kStage, *sq = sp + kPBytes;
+            const char *np = lds + (~kt & 1) * kStage, *nq = np + kPBytes;
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                op.reload_frag();
+                oq.reload_frag();
+#pragma unroll
+                for (int j = 0; j < kGroups; ++j) {
+                    const bool last = j == kGroups - 1;
+                    const bf16x8 fq = next;
+                    if (ks == 0)
+#pragma unroll
+                        for (int i = 0; i < kLoadsQ; ++i)
+                            if (i == j) issue_q(kt + 1, i);
+                    if (ks == 1)
+#pragma unroll
+                        for (int i = 0; i < kLoadsP; ++i)
+                            if (1 + i * (kGroups - 1) / kLoadsP == j) issue_p(kt + 2, i);
+                    if (ks == 1 && last) {
+                        rows_wait_vmcnt<kLoadsP>();   // step kt + 1 has landed
+                        __syncthreads();              // ... for all waves, and Q's stage is read
+                        next = oq.frag16(nq, 0, 0);
+                    } else {
+                        next = last ? oq.frag16(sq, 0, 1) : oq.frag16(sq, j + 1, ks);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int i = 0; i < 2 * IP; ++i)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(held[i], fq, acc[i][j], 0, 0, 0);
+                    if (last)
+#pragma unroll
+                        for (int i = 0; i < 2 * IP; ++i) held[i] = ks == 0 ? op.frag16(sp, i, 1) : op.frag16(np, i, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (ks == 1 && j == 0) __syncthreads();   // all waves have read P's stage
+                }
+            }
         }
-        rows_wait_vmcnt<(STAGES > 2 ? STAGES - 2 : 0) * kLoads>();   // step kt has landed
-        __syncthreads();                                             // ... for all waves; step kt - 1 is read
-        const uint32_t fill_at = lds0 + (uint32_t)(fill * kStage);
-        if (STAGES > 1 && kSpread == 0) issue(kt + STAGES - 1, fill);
-        const char *sp = lds + st * kStage, *sq = sp + kPBytes;
+    } else {
 #pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
-            bf16x8 fp[IP], fq[IQ];
+        for (int s = 0; s < STAGES - 1; ++s) issue(s, s);
+        int st = 0, fill = STAGES - 1;
+        for (int kt = 0; kt < nk; ++kt) {
+            if (STAGES == 1) {   // a single stage: other blocks of the CU cover the wait
+                if (kt) __syncthreads();
+                issue(kt, 0);
+            }
+            rows_wait_vmcnt<(STAGES > 2 ? STAGES - 2 : 0) * kLoads>();   // step kt has landed
+            __syncthreads();                                             // ... for all waves; step kt - 1 is read
+            if (STAGES > 1) issue(kt + STAGES - 1, fill);
+            const char *sp = lds + st * kStage, *sq = sp + kPBytes;
 #pragma unroll
-            for (int i = 0; i < IP; ++i) fp[i] = op.frag(sp, i, ks);
+            for (int ks = 0; ks < BK / 32; ++ks) {
+                bf16x8 fp[2 * IP], fq[2 * IQ];
 #pragma unroll
-            for (int j = 0; j < IQ; ++j) fq[j] = oq.frag(sq, j, ks);
-            if (STAGES > 1 && kSpread > 0)
+                for (int i = 0; i < 2 * IP; ++i) fp[i] = op.frag16(sp, i, ks);
 #pragma unroll
-                for (int i = 0; i < kLoads; ++i)
-                    if (i * kSpread / kLoads == ks) issue_load(fill_at, kt + STAGES - 1, i);
+                for (int j = 0; j < 2 * IQ; ++j) fq[j] = oq.frag16(sq, j, ks);
 #pragma unroll
-            for (int i = 0; i < IP; ++i)
+                for (int j = 0; j < 2 * IQ; ++j)
 #pragma unroll
-                for (int j = 0; j < IQ; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fp[i], fq[j], acc[i][j], 0, 0, 0);
+                    for (int i = 0; i < 2 * IP; ++i)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp[i], fq[j], acc[i][j], 0, 0, 0);
+            }
+            st = st == STAGES - 1 ? 0 : st + 1;
+            fill = fill == STAGES - 1 ? 0 : fill + 1;
         }
-        st = st == STAGES - 1 ? 0 : st + 1;
-        fill = fill == STAGES - 1 ? 0 : fill + 1;
     }
     rows_wait_vmcnt<0>();   // the trailing loads
     __syncthreads();
@@ -159,7 +209,6 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
     constexpr int kPitch = rows_turn_pitch(IP), kChunks = 4 * IP, kPasses = 2 * IP;
     char *ep = lds + wave * 32 * kPitch;
     const int pw = p0 + wp * 32 * IP;
-    const int wrow = lane & 31;
     auto swz = [](int row) { return IP == 1 ? (row >> 2) & 3 : IP == 2 ? (row >> 1) & 7 : 0; };
     // Stores through a descriptor: rows past the last one and columns past the matrix get an offset outside it
     // and store nothing, without a branch per store.  GUARD: with one, which spaces the stores; large weight gradients of
@@ -181,27 +230,28 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
     for (int j = 0; j < IQ; ++j) {
         const int qw = q0 + (wq * IQ + j) * 32;
         if (qw >= qlim) break;
-        // expert dropout: the draw of hidden unit p of token t is element t * d_ff + p
-        uint32_t drop_row = 0;
-        if (DROP && EPI == ROWS_RELU) {
-            const int q = qw + wrow;
-            const int tok = q < qlim ? a.slot_token[(size_t)e * a.slots + q] : 0;
-            drop_row = (uint32_t)tok * (uint32_t)a.Pdim + (uint32_t)(pw + ((lane >> 5) << 2));
-        }
 #pragma unroll
-        for (int i = 0; i < IP; ++i)
+        for (int h = 0; h < 2; ++h) {   // rows 16 h .. + 15
+            const int wrow = 16 * h + (lane & 15);
+            // expert dropout: the draw of hidden unit p of token t is element t * d_ff + p
+            uint32_t drop_row = 0;
+            if (DROP && EPI == ROWS_RELU) {
+                const int q = qw + wrow;
+                const int tok = q < qlim ? a.slot_token[(size_t)e * a.slots + q] : 0;
+                drop_row = (uint32_t)tok * (uint32_t)a.Pdim + (uint32_t)(pw + ((lane >> 4) << 2));
+            }
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
+            for (int i = 0; i < 2 * IP; ++i) {
                 float v[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = acc[i][j][4 * g + r];
+                for (int r = 0; r < 4; ++r) v[r] = acc[i][2 * j + h][r];
                 if (DROP && EPI == ROWS_RELU) {
-                    const uint32_t first = drop_row + (uint32_t)(i * 32 + g * 8);
+                    const uint32_t first = drop_row + (uint32_t)(i * 16);
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const uint32_t z = dropout_pair_bits(a.nz, (first >> 1) + (uint32_t)h);
-                        v[2 * h] = dropout_keeps_even(a.nz, z) ? v[2 * h] * a.nz.drop_scale : 0.f;
-                        v[2 * h + 1] = dropout_keeps_odd(a.nz, z) ? v[2 * h + 1] * a.nz.drop_scale : 0.f;
+                    for (int m = 0; m < 2; ++m) {
+                        const uint32_t z = dropout_pair_bits(a.nz, (first >> 1) + (uint32_t)m);
+                        v[2 * m] = dropout_keeps_even(a.nz, z) ? v[2 * m] * a.nz.drop_scale : 0.f;
+                        v[2 * m + 1] = dropout_keeps_odd(a.nz, z) ? v[2 * m + 1] * a.nz.drop_scale : 0.f;
                     }
                 }
                 if (DROP && EPI == ROWS_MASK)
@@ -212,9 +262,10 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
                     o.x = pk_max_i16(o.x, 0u);
                     o.y = pk_max_i16(o.y, 0u);
                 }
-                const int ch = i * 4 + g;
-                *(uint2 *)(ep + wrow * kPitch + ((ch ^ swz(wrow)) << 4) + ((lane >> 5) << 3)) = o;
+                const int ch = i * 2 + (lane >> 5);
+                *(uint2 *)(ep + wrow * kPitch + ((ch ^ swz(wrow)) << 4) + ((lane >> 4 & 1) << 3)) = o;
             }
+        }
         uint32_t nb[2] = {0u, 0u};
         int tok[kPasses];
         float gate[kPasses];
