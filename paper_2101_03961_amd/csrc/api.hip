@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "common.h"
+#include "router_wgrad.h"
 
 namespace sw {
 
@@ -194,6 +195,11 @@ Workspace layout_workspace(const switch_config *cfg) {
         w.ntlb_free = take(nE);
         w.ntlb_base = take(nE);
     }
+    // (a layer near the static scratch's limit does without)
+    w.rw_nsplit = router_wgrad_splits(w);
+    const size_t rw_bytes = (size_t)w.rw_nsplit * (d + 1) * E * 4;
+    if (off <= SW_STATIC_SCRATCH_BYTES && off + rw_bytes > SW_STATIC_SCRATCH_BYTES / 4 * 3) w.rw_nsplit = 0;
+    w.rw_part = take(w.rw_nsplit ? rw_bytes : 0);
     w.total = off;
     return w;
 }
@@ -453,25 +459,28 @@ int switch_backward(const switch_config *cfg, const void *dy, float d_aux, const
     auto gemm = dt == SW_BF16 ? launch_gemm_bf16 : launch_gemm_f32;
 
     const TokenMajor tm{x, dy, nullptr};
+    const RouterWgradArgs parts = router_wgrad_args(w, cfg->alpha, d_aux, x, ws, db_r != nullptr);
     // fused: only the gate gradient is left of the combine's backward pass (dy is read by the
     // GEMMs through the slot -> token table)
     if (w.fused)
         st = status_of(launch_gate_grad(w, dy, ws, s));
     else
-        st = status_of(launch_combine_bwd(w, dt, dy, ws, s));
+        st = status_of(launch_combine_bwd(w, dt, dy, ws, parts, s));
     if (st) return st;
     if ((st = status_of(gemm(GEMM_DGRAD2, w, ws, W_in, W_out, dW_in, dW_out, tm, s)))) return st;
     if (w.geglu && (st = status_of(launch_geglu_bwd(w, dt, ws, s)))) return st;
     // dH is consumed right after it is produced (the first-layer data gradient walks the
     // experts backwards, see launch_gemm_bf16), then the two weight gradients
     if (dt == SW_BF16 && rows_backward_supported(w)) {
-        if ((st = status_of(launch_rows_backward(w, ws, W_in, W_out, dW_in, dW_out, s)))) return st;
+        if ((st = status_of(launch_rows_backward(w, ws, W_in, W_out, dW_in, dW_out, parts, s)))) return st;
     } else {
         if ((st = status_of(gemm(GEMM_DGRAD1, w, ws, W_in, W_out, dW_in, dW_out, tm, s)))) return st;
-        if ((st = status_of(gemm(GEMM_WGRAD1, w, ws, W_in, W_out, dW_in, dW_out, tm, s)))) return st;
+        st = status_of(parts.blocks ? launch_gemm_f32_wgrad1(w, ws, dW_in, parts, s)
+                                    : gemm(GEMM_WGRAD1, w, ws, W_in, W_out, dW_in, dW_out, tm, s));
+        if (st) return st;
         if ((st = status_of(gemm(GEMM_WGRAD2, w, ws, W_in, W_out, dW_in, dW_out, tm, s)))) return st;
     }
-    if ((st = status_of(launch_router_bwd(w, dt, cfg->alpha, d_aux, x, W_r, ws, dx, dW_r, db_r, s))))
+    if ((st = status_of(launch_router_bwd(w, dt, cfg->alpha, d_aux, x, W_r, ws, dx, dW_r, db_r, parts, s))))
         return st;
     return SW_OK;
 }

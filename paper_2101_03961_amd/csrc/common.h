@@ -177,6 +177,8 @@ struct Workspace {
     size_t relu_bits;           // u8  one bit per element of A, A > 0, in the order the epilogue of the
                                 //     first forward GEMM (and of the masked gradient) visits its tiles
     int64_t nsplit;
+    int64_t rw_nsplit;          // parts of the router's weight gradient beside the experts' (router_wgrad.h), 0: none
+    size_t rw_part;             // f32 [rw_nsplit][d + 1][E]
     // No-Token-Left-Behind (only laid out when ntlb_rounds > 0)
     int ntlb_rounds;
     size_t ntlb_logits;         // f32 [T][E]   logits, when the caller asks for none
@@ -219,6 +221,8 @@ struct ProfScope {
     ~ProfScope() { prof_end(s); }
 };
 
+struct RouterWgradArgs;   // router_wgrad.h
+
 // ---- kernel launchers (each returns hipSuccess or the launch error) ----------
 // Router forward: logits, softmax, arg max, gate, in-block rank, per-block
 // expert histogram and probability sums.
@@ -259,14 +263,20 @@ hipError_t launch_ntlb(const Workspace &w, char *ws, const float *logits, int32_
 hipError_t launch_geglu_fwd(const Workspace &w, int dtype, char *ws, hipStream_t s);
 hipError_t launch_geglu_bwd(const Workspace &w, int dtype, char *ws, hipStream_t s);
 hipError_t launch_combine(const Workspace &w, int dtype, char *ws, void *y, hipStream_t s);
-hipError_t launch_combine_bwd(const Workspace &w, int dtype, const void *dy, char *ws,
+// (parts: also each token's sum of p dp, for router_wgrad_block)
+hipError_t launch_combine_bwd(const Workspace &w, int dtype, const void *dy, char *ws, const RouterWgradArgs &parts,
                               hipStream_t s);
+// dx, dW_r, db_r (parts: those of dW_r and db_r are there)
 hipError_t launch_router_bwd(const Workspace &w, int dtype, float alpha, float d_aux,
                              const void *x, const float *W_r, char *ws, void *dx, float *dW_r,
-                             float *db_r, hipStream_t s);
-// dlogits and dx in one kernel (router_bwd.hip); bias: also the per-block sums for db_r
+                             float *db_r, const RouterWgradArgs &parts, hipStream_t s);
+// The router's weight gradient beside the experts' (router_wgrad.h), or no blocks where it has launches of its own.
+int64_t router_wgrad_splits(const Workspace &w);
+RouterWgradArgs router_wgrad_args(const Workspace &w, float alpha, float d_aux, const void *x, char *ws, bool bias);
+// dlogits and dx in one kernel (router_bwd.hip); bias: also the per-block sums for db_r; parts: instead of both, the
+// sums over the parts of dW_r and db_r
 hipError_t launch_router_dx_block(const Workspace &w, int dtype, float aux_scale, const float *W_r, char *ws,
-                                  void *dx, bool bias, hipStream_t s);
+                                  void *dx, float *dW_r, float *db_r, const RouterWgradArgs &parts, hipStream_t s);
 // MFMA pieces of the router backward (bf16), in gemm_bf16.hip
 hipError_t launch_router_split_bwd(const Workspace &w, const float *W_r, char *ws, hipStream_t s);
 hipError_t launch_router_dx_mfma(const Workspace &w, char *ws, void *dx, hipStream_t s);
@@ -322,13 +332,15 @@ hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const v
 // First layer's data gradient and both weight gradients in one launch, where that pays.
 bool rows_backward_supported(const Workspace &w);
 hipError_t launch_rows_backward(const Workspace &w, char *ws, const void *W_in, const void *W_out, void *dW_in,
-                                void *dW_out, hipStream_t s);
+                                void *dW_out, const RouterWgradArgs &parts, hipStream_t s);
 // Weight gradients with persistent blocks (gemm_wgrad.hip), tile ROWS_256x384 or ROWS_384x256.
 hipError_t launch_gemm_wgrad(GemmKind kind, const Workspace &w, char *ws, void *dW_in, void *dW_out, int tile,
                              hipStream_t s);
 hipError_t launch_gemm_f32(GemmKind kind, const Workspace &w, char *ws, const void *W_in,
                            const void *W_out, void *dW_in, void *dW_out, const TokenMajor &tm,
                            hipStream_t s);
+// The first weight gradient, and the parts of the router's in blocks behind it.
+hipError_t launch_gemm_f32_wgrad1(const Workspace &w, char *ws, void *dW_in, const RouterWgradArgs &parts, hipStream_t s);
 // fp32: a product of Qdim x Pdim runs on the matrix cores
 bool gemm_f32_on_mfma(const Workspace &w, int64_t Qdim, int64_t Pdim);
 // Combine inside the second GEMM: the rows of y of tokens without a slot are cleared by

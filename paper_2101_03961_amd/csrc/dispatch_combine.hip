@@ -2,6 +2,7 @@
 // All of these stream rows through HBM once; they are laid out so that a wave
 // moves whole 16-byte chunks of a row with every lane busy.
 #include "common.h"
+#include "router_wgrad.h"
 
 namespace sw {
 
@@ -308,38 +309,57 @@ __global__ __launch_bounds__(256) void combine_kernel(const Chunk16 *__restrict_
 // Combine backward: for kept tokens dO[slot_t][:] = gate[t] * dy[t][:] and
 // dgate[t] = <dy[t], O[slot_t]>; dropped tokens get dgate = 0.  One wave per token.
 // -----------------------------------------------------------------------------
-template <typename XT>
+template <typename XT, bool SUM>
 __global__ __launch_bounds__(256) void combine_bwd_kernel(
     const Chunk16 *__restrict__ dy, const Chunk16 *__restrict__ O, Chunk16 *__restrict__ dO,
     const int32_t *__restrict__ tok_slot, const float *__restrict__ gate,
-    float *__restrict__ dgate, int T, int cpr) {
+    float *__restrict__ dgate, int T, int cpr, RouterWgradArgs r, float *__restrict__ rowsum) {
     const int lane = threadIdx.x % kWave;
     const uint32_t t = wave_token();
     if (t >= (uint32_t)T) return;
+    // SUM (up to 256 experts): the token's s = sum_i p[i] dp[i], without the gate's gradient at first
+    float s = 0.f, p_me = 0.f;
+    if (SUM) {
+        const float mean_count = (float)r.Tg / (float)r.E;
+        const int32_t *counts = r.counts_g + (size_t)((int)t / r.Tg) * r.E;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int e = lane + j * kWave;
+            if (e < r.E) s += r.probs[(size_t)t * r.E + e] * (r.aux_scale * ((float)counts[e] - mean_count));
+        }
+        p_me = r.probs[(size_t)t * r.E + r.idx[t]];
+    }
     const int slot_or_none = tok_slot[t];
-    if (slot_or_none < 0) {
+    float dot = 0.f;
+    if (slot_or_none >= 0) {
+        const size_t slot = (size_t)slot_or_none;
+        const float g = gate[t];
+        for (int col = lane; col < cpr; col += kWave) {
+            const Chunk16 a = dy[(size_t)t * cpr + col];
+            const Chunk16 b = O[slot * cpr + col];
+            float av[Vec<XT>::N], bv[Vec<XT>::N];
+            unpack<XT>(a, av);
+            unpack<XT>(b, bv);
+#pragma unroll
+            for (int i = 0; i < Vec<XT>::N; ++i) {
+                dot = fmaf(av[i], bv[i], dot);
+                av[i] *= g;
+            }
+            dO[slot * cpr + col] = pack<XT>(av);
+        }
+    } else if (!SUM) {
         if (lane == 0) dgate[t] = 0.f;
         return;
     }
-    const size_t slot = (size_t)slot_or_none;
-    const float g = gate[t];
-    float dot = 0.f;
-    for (int col = lane; col < cpr; col += kWave) {
-        const Chunk16 a = dy[(size_t)t * cpr + col];
-        const Chunk16 b = O[slot * cpr + col];
-        float av[Vec<XT>::N], bv[Vec<XT>::N];
-        unpack<XT>(a, av);
-        unpack<XT>(b, bv);
 #pragma unroll
-        for (int i = 0; i < Vec<XT>::N; ++i) {
-            dot = fmaf(av[i], bv[i], dot);
-            av[i] *= g;
-        }
-        dO[slot * cpr + col] = pack<XT>(av);
+    for (int m = 32; m >= 1; m >>= 1) {
+        dot += __shfl_xor(dot, m, kWave);
+        if (SUM) s += __shfl_xor(s, m, kWave);
     }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) dot += __shfl_xor(dot, m, kWave);
-    if (lane == 0) dgate[t] = dot;
+    if (lane == 0) {
+        dgate[t] = dot;
+        if (SUM) rowsum[t] = fmaf(p_me, dot, s);
+    }
 }
 
 // -----------------------------------------------------------------------------
@@ -492,22 +512,21 @@ hipError_t launch_combine(const Workspace &w, int dtype, char *ws, void *y, hipS
     return hipGetLastError();
 }
 
-hipError_t launch_combine_bwd(const Workspace &w, int dtype, const void *dy, char *ws,
+hipError_t launch_combine_bwd(const Workspace &w, int dtype, const void *dy, char *ws, const RouterWgradArgs &parts,
                               hipStream_t s) {
     ProfScope ps("combine_bwd", s);
-    const int vec = dtype == SW_BF16 ? 8 : 4;
-    const int cpr = (int)(w.d / vec);
-    const dim3 grid = row_grid(w.T);
-    if (dtype == SW_BF16)
-        hipLaunchKernelGGL(combine_bwd_kernel<bf16>, grid, dim3(256), 0, s, (const Chunk16 *)dy,
-                           (const Chunk16 *)(ws + w.O), (Chunk16 *)(ws + w.dO),
-                           (const int32_t *)(ws + w.tok_slot), (const float *)(ws + w.gate),
-                           (float *)(ws + w.dgate), (int)w.T, cpr);
-    else
-        hipLaunchKernelGGL(combine_bwd_kernel<float>, grid, dim3(256), 0, s, (const Chunk16 *)dy,
-                           (const Chunk16 *)(ws + w.O), (Chunk16 *)(ws + w.dO),
-                           (const int32_t *)(ws + w.tok_slot), (const float *)(ws + w.gate),
-                           (float *)(ws + w.dgate), (int)w.T, cpr);
+    auto launch = [&](auto kern, int vec) {
+        hipLaunchKernelGGL(kern, row_grid(w.T), dim3(256), 0, s, (const Chunk16 *)dy, (const Chunk16 *)(ws + w.O),
+                           (Chunk16 *)(ws + w.dO), (const int32_t *)(ws + w.tok_slot), (const float *)(ws + w.gate),
+                           (float *)(ws + w.dgate), (int)w.T, (int)(w.d / vec), parts, (float *)(ws + w.local_rank));
+    };
+    if (dtype == SW_BF16) {
+        if (parts.blocks) launch(combine_bwd_kernel<bf16, true>, 8);
+        else launch(combine_bwd_kernel<bf16, false>, 8);
+    } else {
+        if (parts.blocks) launch(combine_bwd_kernel<float, true>, 4);
+        else launch(combine_bwd_kernel<float, false>, 4);
+    }
     return hipGetLastError();
 }
 

@@ -5,6 +5,7 @@
 
 #include "common.h"
 #include "lds_operands.h"
+#include "router_wgrad.h"
 #include "rows_operands.h"
 
 namespace sw {
@@ -27,6 +28,7 @@ struct GemmF32Args {
     float *y;
     long slots;
     Noise nz;
+    RouterWgradArgs router;      // first weight gradient: parts of the router's, in blocks behind it
 };
 
 constexpr int kF32Tile = 64;
@@ -188,6 +190,11 @@ __global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32A
     static_assert(S == 32 || IP * IQ == 1, "fragments lie 32 rows apart");
     __shared__ __attribute__((aligned(16))) char lds[STAGES * kStage];
     const int per_e = tiles_q * tiles_p;
+    if constexpr (Q_TRANS) {   // (a weight gradient)
+        static_assert(STAGES * kStage >= kRwLds && NW == 4, "room for the router's blocks");
+        const int beyond = (int)blockIdx.x - ((int)gridDim.x - a.router.blocks);
+        if (beyond >= 0) return router_wgrad_block<float>(a.router, beyond, lds);
+    }
     const int e = blockIdx.x / per_e, rem = blockIdx.x - e * per_e;
     const int pt = rem / tiles_q, qt = rem - pt * tiles_q;
     const int lim = a.kept[e];
@@ -319,7 +326,7 @@ template <int S, int IP, int WP, int IQ, int WQ, int STAGES, bool Q_TRANS, bool 
 static hipError_t f32_launch(const GemmF32Args &a, int E, hipStream_t s) {
     const int tq = (int)ceil_div(a.Qdim, S * IQ * WQ), tp = (int)ceil_div(a.Pdim, S * IP * WP);
     hipLaunchKernelGGL((gemm_f32_mfma_kernel<S, IP, WP, IQ, WQ, STAGES, Q_TRANS, P_TRANS, EPI>),
-                       dim3((unsigned)(tq * tp * E)), dim3(64 * WP * WQ), 0, s, a, tq, tp);
+                       dim3((unsigned)(tq * tp * E + a.router.blocks)), dim3(64 * WP * WQ), 0, s, a, tq, tp);
     return hipGetLastError();
 }
 
@@ -349,16 +356,16 @@ bool gemm_f32_on_mfma(const Workspace &w, int64_t Qdim, int64_t Pdim) {
     return most < 2147483647. && w.E * ceil_div(Qdim, 64) * ceil_div(Pdim, 128) * 256 <= kMaxGridThreads;
 }
 
-hipError_t launch_gemm_f32(GemmKind kind, const Workspace &w, char *ws, const void *W_in,
-                           const void *W_out, void *dW_in, void *dW_out, const TokenMajor &tm,
-                           hipStream_t s) {
+static hipError_t gemm_f32(GemmKind kind, const Workspace &w, char *ws, const void *W_in, const void *W_out,
+                           void *dW_in, void *dW_out, void *y, const RouterWgradArgs &parts, hipStream_t s) {
     const long d = w.d, f = w.f, f1 = w.f1, C = w.C;
     GemmF32Args a{};
     a.kept = (const int32_t *)(ws + w.kept);
     a.slot_token = (const int32_t *)(ws + w.slot_token);
     a.slots = C;
     a.slot_gate = (const float *)(ws + w.slot_gate);
-    a.y = (float *)tm.y;
+    a.y = (float *)y;
+    a.router = parts;
     a.nz = w.noise;
     const float *Xd = (const float *)(ws + w.Xd);
     float *A = (float *)(ws + w.A);
@@ -431,6 +438,16 @@ hipError_t launch_gemm_f32(GemmKind kind, const Workspace &w, char *ws, const vo
               (unsigned)w.E);
     hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, s, a);
     return hipGetLastError();
+}
+
+hipError_t launch_gemm_f32(GemmKind kind, const Workspace &w, char *ws, const void *W_in,
+                           const void *W_out, void *dW_in, void *dW_out, const TokenMajor &tm,
+                           hipStream_t s) {
+    return gemm_f32(kind, w, ws, W_in, W_out, dW_in, dW_out, tm.y, RouterWgradArgs{}, s);
+}
+
+hipError_t launch_gemm_f32_wgrad1(const Workspace &w, char *ws, void *dW_in, const RouterWgradArgs &parts, hipStream_t s) {
+    return gemm_f32(GEMM_WGRAD1, w, ws, nullptr, nullptr, dW_in, nullptr, nullptr, parts, s);
 }
 
 }  // namespace sw

@@ -27,6 +27,7 @@
 
 #include "common.h"
 #include "lds_operands.h"
+#include "router_wgrad.h"
 #include "rows_operands.h"
 
 namespace sw {
@@ -407,7 +408,8 @@ __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a
 // each other.  Tiles of four waves.
 struct RowsArgs3 {
     RowsArgs data, first, second;
-    int end[2];   // blocks of the data gradient, and of it and the first weight gradient (multiples of eight)
+    int end[3];   // blocks up to the end of the data gradient and of each weight gradient (multiples of eight)
+    RouterWgradArgs router;   // parts of the router's weight gradient, in blocks behind them
 };
 template <int IP, int WP, int IQ, int WQ, int STAGES, int GP, int GWP, int GQ, int GWQ, int GSTAGES>
 __global__ __launch_bounds__(256, 2) void gemm_rows_backward_kernel(RowsArgs3 a) {
@@ -417,8 +419,10 @@ __global__ __launch_bounds__(256, 2) void gemm_rows_backward_kernel(RowsArgs3 a)
     if (L < a.end[0]) rows_block<IP, WP, IQ, WQ, STAGES, false, ROWS_PLAIN, false, false>(a.data, lds, L);
     else if (L < a.end[1])
         rows_block<GP, GWP, GQ, GWQ, GSTAGES, true, ROWS_PLAIN, false, true>(a.first, lds, L - a.end[0]);
-    else
+    else if (L < a.end[2])
         rows_block<GP, GWP, GQ, GWQ, GSTAGES, true, ROWS_PLAIN, false, true>(a.second, lds, L - a.end[1]);
+    else
+        router_wgrad_block<bf16>(a.router, L - a.end[2], lds);
 }
 
 constexpr int rows_lds(int IP, int WP, int IQ, int WQ, int STAGES) {
@@ -691,6 +695,7 @@ static hipError_t rows_backward_launch(RowsArgs3 a, int E, hipStream_t s) {
     auto kern = gemm_rows_backward_kernel<IP, WP, IQ, WQ, STAGES, GP, GWP, GQ, GWQ, GSTAGES>;
     constexpr int l0 = rows_lds(IP, WP, IQ, WQ, STAGES), l1 = rows_lds(GP, GWP, GQ, GWQ, GSTAGES);
     constexpr int lds = l0 > l1 ? l0 : l1;
+    static_assert(lds >= kRwLds, "room for the router's blocks");
     static PerDeviceOnce once;
     hipError_t err = once_per_device(once, [&] {
         return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -701,7 +706,8 @@ static hipError_t rows_backward_launch(RowsArgs3 a, int E, hipStream_t s) {
     const int64_t n2 = rows_plan(a.second, E, 32 * GQ * GWQ, 32 * GP * GWP, true);
     a.end[0] = (int)n0;
     a.end[1] = (int)(n0 + n1);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(n0 + n1 + n2)), dim3(256), lds, s, a);
+    a.end[2] = (int)(n0 + n1 + n2);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.end[2] + a.router.blocks)), dim3(256), lds, s, a);
     return hipGetLastError();
 }
 
@@ -718,9 +724,10 @@ bool rows_backward_supported(const Workspace &w) {
 }
 
 hipError_t launch_rows_backward(const Workspace &w, char *ws, const void *W_in, const void *W_out, void *dW_in,
-                                void *dW_out, hipStream_t s) {
+                                void *dW_out, const RouterWgradArgs &parts, hipStream_t s) {
     ProfScope ps("gemm_backward", s);
     RowsArgs3 a{};
+    a.router = parts;
     a.data = rows_args(GEMM_DGRAD1, w, ws, W_in, W_out, dW_in, dW_out);
     a.first = rows_args(GEMM_WGRAD1, w, ws, W_in, W_out, dW_in, dW_out);
     a.second = rows_args(GEMM_WGRAD2, w, ws, W_in, W_out, dW_in, dW_out);

@@ -4,6 +4,7 @@
 // The router is computed in fp32 whatever the activation dtype is (Sec. 2.4,
 // selective precision): x is widened to fp32 before the contraction.
 #include "common.h"
+#include "router_wgrad.h"
 
 namespace sw {
 
@@ -429,30 +430,6 @@ __global__ __launch_bounds__(256) void router_dlogits_kernel(
     }
 }
 
-// db_r[e] = sum over parts of part[q][e], in blocks behind those of a dW_r reduction: kDbrExperts
-// experts per block, eight interleaved chains per expert, added in order.
-constexpr int kDbrExperts = 32;
-struct DbrArgs {
-    const float *part;   // [nparts][E]
-    float *out;          // nullptr: no bias
-    int E, nparts;
-};
-__device__ static void reduce_dbr(const DbrArgs &a, int block) {
-    __shared__ float sums[8][kDbrExperts];
-    const int j = threadIdx.x % kDbrExperts, chain = threadIdx.x / kDbrExperts;
-    const int e = block * kDbrExperts + j;
-    float s = 0.f;
-    if (e < a.E) {
-#pragma unroll 8
-        for (int q = chain; q < a.nparts; q += 8) s += a.part[(size_t)q * a.E + e];
-    }
-    sums[chain][j] = s;
-    __syncthreads();
-    if (chain != 0 || e >= a.E) return;
-    for (int c = 1; c < 8; ++c) s += sums[c][j];
-    a.out[e] = s;
-}
-
 // dW_r[k][j] = sum over splits of (part[s][k][j] + part[s][k][128 + j]), fixed order.
 // rows = rows of one split's part; second > 0: the operand had a second plane (input jitter:
 // x * m as hi + mid), whose rows start at `second` and are added in.
@@ -692,14 +669,7 @@ __global__ __launch_bounds__(256) void router_dbr_kernel(const float *__restrict
 __global__ __launch_bounds__(256) void reduce_partials_kernel(const float *__restrict__ part,
                                                               float *__restrict__ out, size_t n,
                                                               int nsplit, DbrArgs db) {
-    const size_t blocks = (n + 255) / 256;
-    if (blockIdx.x >= blocks) return reduce_dbr(db, (int)(blockIdx.x - blocks));
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float s = 0.f;
-#pragma unroll 8
-    for (int q = 0; q < nsplit; ++q) s += part[(size_t)q * n + i];
-    out[i] = s;
+    reduce_partials(part, out, n, nsplit, db, blockIdx.x);
 }
 
 // -----------------------------------------------------------------------------
@@ -782,10 +752,50 @@ hipError_t launch_route_scan(const Workspace &w, char *ws, int32_t *expert_count
     return hipGetLastError();
 }
 
+static float aux_scale_of(const Workspace &w, float alpha, float d_aux) {
+    return (float)((double)d_aux * (double)alpha * (double)w.E / ((double)w.n * (double)w.Tg * (double)w.Tg));
+}
+
+// dW_r's parts beside the experts' weight gradients: where those leave the chip room (fp32: in blocks of the first one's
+// launch; bf16: of the launch that computes three products of a small layer) and the one kernel computes dx, whose
+// launch then adds up the parts.  That saves two launches of the chain (us per forward + backward pass, without /
+// with: fp32 256 x 64 x 256, 4 experts 56.8 / 51.0; bf16 5003 x 392 x 1000, 10 experts 115.0 / 106.3; large fp32 layers the
+// same).  At most 64 parts of at least 32 tokens and 16 MB in all: more would be read for longer than they are summed.
+int64_t router_wgrad_splits(const Workspace &w) {
+    if (!w.router_bwd_block || w.fused || w.C == 0) return 0;
+    if (w.elt == 2 ? !rows_backward_supported(w) : !gemm_f32_on_mfma(w, w.d, w.f1)) return 0;
+    const int64_t most = ((int64_t)16 << 20) / (4 * (w.d + 1) * w.E);   // 16 MB of parts
+    int64_t n = ceil_div(w.T, kRwTokens);
+    if (n > 64) n = 64;
+    return n < most ? n : most;
+}
+
+RouterWgradArgs router_wgrad_args(const Workspace &w, float alpha, float d_aux, const void *x, char *ws, bool bias) {
+    RouterWgradArgs a{};
+    if (w.rw_nsplit == 0) return a;
+    a.x = x;
+    a.probs = (const float *)(ws + w.probs);
+    a.dgate = (const float *)(ws + w.dgate);
+    a.rowsum = (const float *)(ws + w.local_rank);   // (the ranks: the forward pass's)
+    a.idx = (const int32_t *)(ws + w.idx);
+    a.counts_g = (const int32_t *)(ws + w.counts_g);
+    a.T = (int)w.T; a.Tg = (int)w.Tg; a.d = (int)w.d; a.E = (int)w.E;
+    a.tokens_per_split = (int)(ceil_div(ceil_div(w.T, w.rw_nsplit), kRwTokens) * kRwTokens);
+    a.nsplit = (int)ceil_div(w.T, a.tokens_per_split);
+    a.part = (float *)(ws + w.rw_part);
+    a.dbr_part = bias ? a.part + (size_t)a.nsplit * a.d * a.E : nullptr;
+    const int experts = router_wgrad_experts(w.E);
+    a.tiles_k = (int)ceil_div(w.d, kRwElements / experts);
+    a.blocks = (int)(a.tiles_k * ceil_div(w.E, experts) * a.nsplit);
+    a.aux_scale = aux_scale_of(w, alpha, d_aux);
+    a.nz = w.noise;
+    return a;
+}
+
 template <typename XT>
 static hipError_t router_bwd_typed(const Workspace &w, float alpha, float d_aux, const XT *x,
                                    const float *W_r, char *ws, XT *dx, float *dW_r, float *db_r,
-                                   hipStream_t s) {
+                                   const RouterWgradArgs &parts, hipStream_t s) {
     hipError_t err = hipSuccess;
     float *dlogits = (float *)(ws + w.dlogits);
     // bf16 tokens and a multiple of 4 experts: the two contractions run on the bf16 matrix cores (dl
@@ -795,11 +805,10 @@ static hipError_t router_bwd_typed(const Workspace &w, float alpha, float d_aux,
     bf16 *dl_split = mfma ? (bf16 *)(ws + w.dl_split) : nullptr;
     // the fp32 copy is read only by the vector-ALU contractions and by the bias gradient
     float *dlogits_out = (mfma && !db_r) ? nullptr : dlogits;
-    const float aux_scale =
-        (float)((double)d_aux * (double)alpha * (double)w.E / ((double)w.n * (double)w.Tg * (double)w.Tg));
+    const float aux_scale = aux_scale_of(w, alpha, d_aux);
     if (w.router_bwd_block) {
-        err = launch_router_dx_block(w, sizeof(XT) == 2 ? SW_BF16 : SW_F32, aux_scale, W_r, ws, dx, db_r != nullptr, s);
-        if (err != hipSuccess) return err;
+        err = launch_router_dx_block(w, sizeof(XT) == 2 ? SW_BF16 : SW_F32, aux_scale, W_r, ws, dx, dW_r, db_r, parts, s);
+        if (err != hipSuccess || parts.blocks) return err;
     } else {
         ProfScope ps("router_dlogits", s);
 #define CALL(N)                                                                                  \
@@ -871,12 +880,12 @@ static hipError_t router_bwd_typed(const Workspace &w, float alpha, float d_aux,
 
 hipError_t launch_router_bwd(const Workspace &w, int dtype, float alpha, float d_aux,
                              const void *x, const float *W_r, char *ws, void *dx, float *dW_r,
-                             float *db_r, hipStream_t s) {
+                             float *db_r, const RouterWgradArgs &parts, hipStream_t s) {
     if (dtype == SW_BF16)
         return router_bwd_typed<bf16>(w, alpha, d_aux, (const bf16 *)x, W_r, ws, (bf16 *)dx, dW_r,
-                                      db_r, s);
+                                      db_r, parts, s);
     return router_bwd_typed<float>(w, alpha, d_aux, (const float *)x, W_r, ws, (float *)dx, dW_r,
-                                   db_r, s);
+                                   db_r, parts, s);
 }
 
 }  // namespace sw

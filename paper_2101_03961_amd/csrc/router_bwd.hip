@@ -20,6 +20,7 @@
 // 65536 with jitter: 110 (160); fp32 256 x 64, E 4: 6 (25), 8192 x 768, E 32: 17 (54).
 #include "common.h"
 #include "lds_operands.h"
+#include "router_wgrad.h"
 #include "rows_operands.h"
 
 namespace sw {
@@ -35,6 +36,11 @@ struct RouterBwdArgs {
     int T, Tg, d, E, groups_per_block;
     float aux_scale;
     Noise nz;
+    int token_blocks;  // blocks behind them add up the parts of dW_r and db_r
+    const float *dWr_part;
+    float *dW_r;
+    int nsplit;
+    DbrArgs db;
 };
 
 // EK: 16 experts each.  WIDE: E is a multiple of 4 (rows of E floats are read 16 bytes at a time).
@@ -49,6 +55,11 @@ __global__ __launch_bounds__(256, EK > 8 ? 1 : 2) void router_dx_block_kernel(Ro
     typedef XT piece_t __attribute__((ext_vector_type(kCPL)));
     __shared__ __attribute__((aligned(16))) char wlds[NT * EK * 2048];
     __shared__ __attribute__((aligned(16))) float turn_all[4][32 * kPitch];
+    if ((int)blockIdx.x >= a.token_blocks) {
+        if (blockIdx.y == 0)
+            reduce_partials(a.dWr_part, a.dW_r, (size_t)a.d * a.E, a.nsplit, a.db, blockIdx.x - a.token_blocks);
+        return;
+    }
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int half = lane >> 5;
@@ -141,7 +152,7 @@ __global__ __launch_bounds__(256, EK > 8 ? 1 : 2) void router_dx_block_kernel(Ro
             for (int r = 0; r < 8; ++r) dl[ks][r] *= dp[r] - s;   // p is 0 past E and past T
         }
     }
-    const bool writer = blockIdx.y == 0;
+    const bool writer = blockIdx.y == 0 && a.nsplit == 0;   // (with parts of dW_r nothing reads dl)
     if (writer && a.dbr_part) {   // column sums over the block's 128 tokens, 16 experts at a time
         __shared__ float dbs[4][EK * 16];
 #pragma unroll
@@ -290,11 +301,14 @@ __global__ __launch_bounds__(256, EK > 8 ? 1 : 2) void router_dx_block_kernel(Ro
 template <typename XT, int EK, bool WIDE>
 static void dx_block_launch(RouterBwdArgs a, hipStream_t s) {
     const int groups = (int)ceil_div(a.d, EK > 8 ? 32 : 64), token_blocks = (int)ceil_div(a.T, 128);
+    a.token_blocks = token_blocks;
+    const int64_t sums = a.nsplit ? ceil_div((int64_t)a.d * a.E, 256) + (a.db.out ? ceil_div(a.E, kDbrExperts) : 0) : 0;
     // two blocks per CU want 512 blocks
     const int splits = token_blocks >= 512 ? 1 : (int)ceil_div(512, token_blocks);
     a.groups_per_block = (int)ceil_div(groups, splits < groups ? splits : groups);
     hipLaunchKernelGGL((router_dx_block_kernel<XT, EK, WIDE>),
-                       dim3((unsigned)token_blocks, (unsigned)ceil_div(groups, a.groups_per_block)), dim3(256), 0, s, a);
+                       dim3((unsigned)(token_blocks + sums), (unsigned)ceil_div(groups, a.groups_per_block)), dim3(256), 0,
+                       s, a);
 }
 
 template <typename XT, int EK> static void dx_block_wide(const RouterBwdArgs &a, hipStream_t s) {
@@ -312,7 +326,7 @@ template <typename XT> static void dx_block_typed(const RouterBwdArgs &a, hipStr
 }
 
 hipError_t launch_router_dx_block(const Workspace &w, int dtype, float aux_scale, const float *W_r, char *ws,
-                                  void *dx, bool bias, hipStream_t s) {
+                                  void *dx, float *dW_r, float *db_r, const RouterWgradArgs &parts, hipStream_t s) {
     ProfScope ps("router_dx", s);
     RouterBwdArgs a{};
     a.probs = (const float *)(ws + w.probs);
@@ -325,7 +339,13 @@ hipError_t launch_router_dx_block(const Workspace &w, int dtype, float aux_scale
     a.dx = dx;
     a.dlogits = (float *)(ws + w.dlogits);
     a.dl_split = (bf16 *)(ws + w.dl_split);
-    a.dbr_part = bias ? (float *)(ws + w.dbr_part) : nullptr;
+    a.dbr_part = db_r && !parts.blocks ? (float *)(ws + w.dbr_part) : nullptr;
+    if (parts.blocks) {
+        a.dWr_part = parts.part;
+        a.dW_r = dW_r;
+        a.nsplit = parts.nsplit;
+        a.db = DbrArgs{parts.dbr_part, db_r, (int)w.E, parts.nsplit};
+    }
     a.T = (int)w.T; a.Tg = (int)w.Tg; a.d = (int)w.d; a.E = (int)w.E;
     a.aux_scale = aux_scale;
     a.nz = w.noise;

@@ -141,6 +141,28 @@ def test_three_backward_products_in_one_launch(T, d, f, E, cf, ffn, bias):
     _report("three products %s" % ((T, d, f, E, cf, ffn, bias),), errs)
 
 
+@pytest.mark.parametrize("dtype,T,d,f,E,cf,n,jit,bias", [
+    ("bf16", 1, 8, 8, 1, 4.0, 1, 0.0, True), ("bf16", 65, 72, 136, 65, 8.0, 1, 0.0, True),   # edges of 64 x 64 x 32
+    ("bf16", 4160, 136, 264, 130, 1.25, 2, 0.0, True), ("f32", 97, 68, 132, 3, 1.0, 1, 0.0, True),
+    ("f32", 4100, 132, 68, 64, 1.25, 4, 0.1, False), ("f32", 2100, 20, 36, 256, 2.0, 1, 0.0, True)])
+def test_router_weight_gradient_beside_the_experts(dtype, T, d, f, E, cf, n, jit, bias):
+    """Its parts in blocks of the experts' launches, twice over on one forward pass."""
+    from parity import compare_full
+    s = SwitchShape("t", T, d, f, E, cf, dtype=dtype, zipf_bias=bias, seed_index=67, n_groups=n, jitter_eps=jit,
+                    noise_seed=3)
+    inp = make_inputs(s, _dev())
+    errs, gpu, _, _ = compare_full(s, inp, d_aux=1.0)
+    _report("router weight gradient %s" % ((dtype, T, d, f, E, cf, n, jit),), errs)
+    from paper_2101_03961_amd.layer import SwitchLayer
+    layer = SwitchLayer(T, d, f, E, cf, s.alpha, dtype, _dev(), n_groups=n, jitter_eps=jit, seed=3)
+    args = (inp["x"], inp["W_r"], inp["W_in"], inp["W_out"], inp["b_r"])
+    layer.forward(*args)
+    layer.alloc_grads(with_bias=inp["b_r"] is not None)
+    first = {k: v.clone() for k, v in layer.backward(inp["dy"], *args).items() if v is not None}
+    again = layer.backward(inp["dy"], *args)
+    assert all(torch.equal(first[k], again[k]) for k in first)
+
+
 @pytest.mark.parametrize("T,d,f,E,cf,n,rate,ffn,rounds", [
     (12000, 264, 1544, 64, 1.0, 1, 0.0, "relu", 0),     # 256 x 384, one row tile per expert, ragged both ways
     (16000, 264, 1544, 60, 1.25, 2, 0.1, "relu", 0),    # 320 x 256, two row tiles, groups, dropout
