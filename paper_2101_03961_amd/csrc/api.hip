@@ -120,14 +120,14 @@ Workspace layout_workspace(const switch_config *cfg) {
     nz.drop_thr = (uint32_t)floor((double)cfg->expert_dropout * 65536.0);
     nz.drop_scale = (float)(65536.0 / (65536.0 - (double)nz.drop_thr));
     nz.jitter_eps = cfg->jitter_eps;
-    const bool jit_mfma = nz.jitter && cfg->act_dtype == SW_BF16;
+    const bool jit_mfma = nz.jitter && cfg->act_dtype == SW_BF16 && !w.router_block;
     w.dpad_r = jit_mfma ? 3 * w.dpad : w.dpad;
     w.etiles = ceil_div(w.E, 128);
     const bool mfma = router_bwd_mfma_supported(w, cfg->act_dtype);
-    // With fp32 products (fp32 tokens, or an expert count that is no multiple of 4) the one kernel serves
-    // all that the one-kernel forward does.  With bf16 terms it holds too much in registers for two blocks
+    // With fp32 products (fp32 tokens, and behind the one-kernel forward an expert count that is no multiple of 4, or
+    // input jitter) the one kernel serves all that the one-kernel forward does.  With bf16 terms it holds too much in registers for two blocks
     // per CU beyond 128 experts: 222 us against 46 + 145 for the two it replaces; 65536 x 768, 256 experts.
-    const bool f32_products = cfg->act_dtype == SW_F32 || (w.router_block && w.E % 4 != 0);
+    const bool f32_products = cfg->act_dtype == SW_F32 || (w.router_block && (w.E % 4 != 0 || nz.jitter));
     w.router_bwd_block = f32_products ? w.E <= 256 : mfma && w.E <= 128;
     w.wsplit = take(w.router_block ? 0 : (size_t)w.etiles * 3 * 128 * w.dpad_r * 2);
     w.has_wsplit_b = mfma && !w.router_bwd_block;
@@ -475,7 +475,7 @@ int switch_backward(const switch_config *cfg, const void *dy, float d_aux, const
         if ((st = status_of(launch_rows_backward(w, ws, W_in, W_out, dW_in, dW_out, parts, s)))) return st;
     } else {
         if ((st = status_of(gemm(GEMM_DGRAD1, w, ws, W_in, W_out, dW_in, dW_out, tm, s)))) return st;
-        st = status_of(parts.blocks ? launch_gemm_f32_wgrad1(w, ws, dW_in, parts, s)
+        st = status_of(parts.blocks && !parts.own_launch ? launch_gemm_f32_wgrad1(w, ws, dW_in, parts, s)
                                     : gemm(GEMM_WGRAD1, w, ws, W_in, W_out, dW_in, dW_out, tm, s));
         if (st) return st;
         if ((st = status_of(gemm(GEMM_WGRAD2, w, ws, W_in, W_out, dW_in, dW_out, tm, s)))) return st;

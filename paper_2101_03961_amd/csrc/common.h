@@ -270,7 +270,7 @@ hipError_t launch_combine_bwd(const Workspace &w, int dtype, const void *dy, cha
 hipError_t launch_router_bwd(const Workspace &w, int dtype, float alpha, float d_aux,
                              const void *x, const float *W_r, char *ws, void *dx, float *dW_r,
                              float *db_r, const RouterWgradArgs &parts, hipStream_t s);
-// The router's weight gradient beside the experts' (router_wgrad.h), or no blocks where it has launches of its own.
+// The router's weight gradient from fp32 operands in parts (router_wgrad.h), or no blocks where it takes another form.
 int64_t router_wgrad_splits(const Workspace &w);
 RouterWgradArgs router_wgrad_args(const Workspace &w, float alpha, float d_aux, const void *x, char *ws, bool bias);
 // dlogits and dx in one kernel (router_bwd.hip); bias: also the per-block sums for db_r; parts: instead of both, the

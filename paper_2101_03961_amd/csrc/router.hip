@@ -646,6 +646,11 @@ __global__ __launch_bounds__(256) void router_dWr_kernel(const XT *__restrict__ 
     }
 }
 
+template <typename XT> __global__ __launch_bounds__(256) void router_wgrad_kernel(RouterWgradArgs a) {
+    __shared__ __attribute__((aligned(16))) char lds[kRwLds];
+    router_wgrad_block<XT>(a, blockIdx.x, lds);
+}
+
 // db_r partials: part[split][j] = sum over the split's tokens of dl[t][j]
 __global__ __launch_bounds__(256) void router_dbr_kernel(const float *__restrict__ dlogits,
                                                          float *__restrict__ part, int T, int E) {
@@ -760,10 +765,18 @@ static float aux_scale_of(const Workspace &w, float alpha, float d_aux) {
 // launch; bf16: of the launch that computes three products of a small layer) and the one kernel computes dx, whose
 // launch then adds up the parts.  That saves two launches of the chain (us per forward + backward pass, without /
 // with: fp32 256 x 64 x 256, 4 experts 56.8 / 51.0; bf16 5003 x 392 x 1000, 10 experts 115.0 / 106.3; large fp32 layers the
-// same).  At most 64 parts of at least 32 tokens and 16 MB in all: more would be read for longer than they are summed.
+// same).  The parts of other layers have a launch of their own, behind the experts': where the router gradients take fp32
+// operands, and up to 5e8 products, where the matrix cores' kernel is slower (us of a pass, that kernel / here: 768 x
+// 1536, 128 experts, 512 tokens 462 / 453, 2048 475 / 469, 4096 516 / 505, 8192 555 / 570).  At
+// most 64 parts of at least 32 tokens and 16 MB in all: more would be read for longer than they are summed.
+static bool router_wgrad_hosted(const Workspace &w) {
+    return w.elt == 2 ? rows_backward_supported(w) : gemm_f32_on_mfma(w, w.d, w.f1);
+}
 int64_t router_wgrad_splits(const Workspace &w) {
     if (!w.router_bwd_block || w.fused || w.C == 0) return 0;
-    if (w.elt == 2 ? !rows_backward_supported(w) : !gemm_f32_on_mfma(w, w.d, w.f1)) return 0;
+    if (router_bwd_mfma_supported(w, w.elt == 2 ? SW_BF16 : SW_F32) && !router_wgrad_hosted(w) &&
+        (double)w.T * (double)w.d * (double)w.E > 5e8)
+        return 0;
     const int64_t most = ((int64_t)16 << 20) / (4 * (w.d + 1) * w.E);   // 16 MB of parts
     int64_t n = ceil_div(w.T, kRwTokens);
     if (n > 64) n = 64;
@@ -787,6 +800,7 @@ RouterWgradArgs router_wgrad_args(const Workspace &w, float alpha, float d_aux, 
     const int experts = router_wgrad_experts(w.E);
     a.tiles_k = (int)ceil_div(w.d, kRwElements / experts);
     a.blocks = (int)(a.tiles_k * ceil_div(w.E, experts) * a.nsplit);
+    a.own_launch = !router_wgrad_hosted(w);
     a.aux_scale = aux_scale_of(w, alpha, d_aux);
     a.nz = w.noise;
     return a;
@@ -806,6 +820,11 @@ static hipError_t router_bwd_typed(const Workspace &w, float alpha, float d_aux,
     // the fp32 copy is read only by the vector-ALU contractions and by the bias gradient
     float *dlogits_out = (mfma && !db_r) ? nullptr : dlogits;
     const float aux_scale = aux_scale_of(w, alpha, d_aux);
+    if (parts.own_launch) {
+        ProfScope ps("router_dWr", s);
+        hipLaunchKernelGGL(router_wgrad_kernel<XT>, dim3((unsigned)parts.blocks), dim3(256), 0, s, parts);
+        if ((err = hipGetLastError()) != hipSuccess) return err;
+    }
     if (w.router_bwd_block) {
         err = launch_router_dx_block(w, sizeof(XT) == 2 ? SW_BF16 : SW_F32, aux_scale, W_r, ws, dx, dW_r, db_r, parts, s);
         if (err != hipSuccess || parts.blocks) return err;

@@ -5,7 +5,8 @@
 // contraction runs on the bf16 matrix cores: a fp32 weight is split, where its fragment is read,
 // into three bf16 terms hi + mid + lo (8 + 8 + 8 mantissa bits, the split is exact), so every
 // product x * term is exact in fp32 and the MFMA accumulates in fp32.  With fp32 tokens it runs on
-// the fp32 MFMA (input jitter applied to the token fragments).  Every sum runs over all of d in one
+// the fp32 MFMA (input jitter applied to the token fragments), and so with bf16 tokens and input jitter, whose x * m is no
+// bf16 value (F32P).  Every sum runs over all of d in one
 // wave, in order, so a token's logits, and its expert, do not depend on the batch it comes in.
 //
 // A wave owns one tile of 32 experts and TT / WT MFMA tiles of 32 tokens ("A" = weights, "B" =
@@ -76,9 +77,9 @@ template <int EP, int BK, int NW, int SH, bool WIDE> struct RouterWeights {
 };
 
 // ET expert tiles times WT shares of the TT token tiles.
-template <typename XT, int ET, int WT, int TT> struct RouterBlock {
+template <typename XT, int ET, int WT, int TT, bool F32P> struct RouterBlock {
     static constexpr int kTok = 32 * TT;
-    static constexpr bool kBf16 = sizeof(XT) == 2;
+    static constexpr bool kBf16 = sizeof(XT) == 2 && !F32P;   // products
     static constexpr int NW = ET * WT;
     static constexpr int EP = 32 * ET;
     static constexpr int BK = kBf16 && ET <= 2 ? 64 : 32;
@@ -92,14 +93,14 @@ template <typename XT, int ET, int WT, int TT> struct RouterBlock {
     static_assert(kLds <= 160 * 1024, "the block fits a CU");
 };
 
-template <typename XT, int ET, int WT, int TT, bool WIDE>
-__global__ __launch_bounds__(64 * (RouterBlock<XT, ET, WT, TT>::NW), 2) void router_block_kernel(
+template <typename XT, int ET, int WT, int TT, bool WIDE, bool F32P>
+__global__ __launch_bounds__(64 * (RouterBlock<XT, ET, WT, TT, F32P>::NW), 2) void router_block_kernel(
     const XT *__restrict__ x, const float *__restrict__ W_r, const float *__restrict__ b_r,
     float *__restrict__ probs, float *__restrict__ logits_out, int32_t *__restrict__ idx_out,
     float *__restrict__ gate_out, int32_t *__restrict__ idx_ws, float *__restrict__ gate_ws,
     int32_t *__restrict__ local_rank, int32_t *__restrict__ block_counts,
     float *__restrict__ block_psum, int nbg, int Tg, int d, int E, Noise nz) {
-    typedef RouterBlock<XT, ET, WT, TT> R;
+    typedef RouterBlock<XT, ET, WT, TT, F32P> R;
     constexpr bool BF = R::kBf16;
     constexpr int NW = R::NW, EP = R::EP, BK = R::BK, STAGES = R::STAGES, TOK = R::kTok;
     constexpr int TW = TT / WT, NX = NW < 4 ? NW : 4;   // token tiles per wave, waves that load tokens
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(64 * (RouterBlock<XT, ET, WT, TT>::NW), 2) void rou
     int t0, tend;   // the block's tokens, inside one routing group
     block_token_range(b, nbg, Tg, TOK, t0, tend);
 
-    typename std::conditional<BF, RowsDirect<TOK, NX, BK>, F32Direct<TOK, NX>>::type ox;
+    typename std::conditional<sizeof(XT) == 2, RowsDirect<TOK, NX, BK>, F32Direct<TOK, NX>>::type ox;
     RouterWeights<EP, BK, NW, BF ? 3 : 0, WIDE> ow;
     ox.init(x, d, t0, tend, d, lane, wave % NX);   // (waves past the fourth repeat the loads of the first four)
     ox.init_frag(lane, wt * TW * 32);
@@ -173,7 +174,14 @@ __global__ __launch_bounds__(64 * (RouterBlock<XT, ET, WT, TT>::NW), 2) void rou
                 f32x4 fx[TW];
 #pragma unroll
                 for (int tt = 0; tt < TW; ++tt) {
-                    fx[tt] = ox.frag4(sx, tt, u);
+                    if constexpr (F32P) {   // the lane's four (every other) of the token's eight bf16 values
+                        const u32x4 v = *(const u32x4 *)(sx + ((ox.frag0 ^ (uint32_t)((lane >> 5) << 4) ^ (uint32_t)(u << 4)) +
+                                                               (uint32_t)(tt * 32 * 2 * BK)));
+#pragma unroll
+                        for (int m = 0; m < 4; ++m) fx[tt][m] = __uint_as_float(lane >> 5 ? v[m] & 0xffff0000u : v[m] << 16);
+                    } else {
+                        fx[tt] = ox.frag4(sx, tt, u);
+                    }
                     if (nz.jitter) {   // input jitter (App. C): the router sees x * m
                         const uint32_t t = (uint32_t)(t0 + (wt * TW + tt) * 32 + (lane & 31));
                         const uint32_t at = t * (uint32_t)d + (uint32_t)(kt * BK + u * 8 + (lane >> 5));
@@ -308,27 +316,31 @@ __global__ __launch_bounds__(64 * (RouterBlock<XT, ET, WT, TT>::NW), 2) void rou
     }
 }
 
-// Up to 256 experts whose weights and tokens fit a buffer descriptor each; input jitter on bf16
-// tokens goes through planes of x * m (router_mfma.hip) or the vector ALUs (router.hip).
+// Up to 256 experts whose weights and tokens fit a buffer descriptor each.  Input jitter on bf16 tokens, for large layers
+// with a multiple of 4 experts: planes of x * m (router_mfma.hip), whose products are cheaper, but which take three launches
+// and long chains of few blocks.  (us of the forward router / of a pass, planes or vector ALUs -> here: 512 tokens of 768, 128
+// experts 109 -> 65 / 528 -> 500, 8192 116 -> 66; 32768 of 1024, 8 experts 208 -> 74 / 1232 -> 1051; 32 of 2400, 10 experts
+// 799 -> 98 / 1223 -> 518; 65536 of 768, 128 experts 217 -> 275, which keeps its planes.)
 // Tokens per block: 128 halves what the weights cost (traffic and splits) once there are blocks
 // for two per CU.
 int router_block_tokens(const switch_config *cfg) {
-    return cfg->act_dtype == SW_BF16 && cfg->E <= 128 && cfg->T >= 32768 ? 128 : 64;
+    return cfg->act_dtype == SW_BF16 && cfg->jitter_eps == 0.f && cfg->E <= 128 && cfg->T >= 32768 ? 128 : 64;
 }
 
 bool router_block_supported(const switch_config *cfg) {
     const double elt = cfg->act_dtype == SW_BF16 ? 2. : 4.;
     return cfg->E <= 256 && (double)cfg->d_model * (double)cfg->E * 4. < 2147483647. &&
            (double)cfg->T * (double)cfg->d_model * elt < 2147483647. &&
-           !(cfg->act_dtype == SW_BF16 && cfg->jitter_eps > 0.f);
+           !(cfg->act_dtype == SW_BF16 && cfg->jitter_eps > 0.f && cfg->E % 4 == 0 &&
+             (double)cfg->T * (double)cfg->d_model * (double)cfg->E > 8e8);
 }
 
-template <typename XT, int ET, int WT, int TT, bool WIDE>
+template <typename XT, int ET, int WT, int TT, bool WIDE, bool F32P>
 static hipError_t router_block_launch(const Workspace &w, const void *x, const float *W_r, const float *b_r,
                                       char *ws, int32_t *expert_index, float *gate, float *router_logits,
                                       hipStream_t s) {
-    auto kern = router_block_kernel<XT, ET, WT, TT, WIDE>;
-    typedef RouterBlock<XT, ET, WT, TT> R;
+    auto kern = router_block_kernel<XT, ET, WT, TT, WIDE, F32P>;
+    typedef RouterBlock<XT, ET, WT, TT, F32P> R;
     static PerDeviceOnce once;
     hipError_t err = once_per_device(once, [&] {
         return hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, R::kLds);
@@ -342,13 +354,13 @@ static hipError_t router_block_launch(const Workspace &w, const void *x, const f
     return hipGetLastError();
 }
 
-template <typename XT>
+template <typename XT, bool F32P>
 static hipError_t router_block_typed(const Workspace &w, const void *x, const float *W_r, const float *b_r,
                                      char *ws, int32_t *expert_index, float *gate, float *logits, hipStream_t s) {
 #define SW_RB(ET, WT, TT)                                                                                          \
-    (w.E % 4 == 0 ? router_block_launch<XT, ET, WT, TT, true>(w, x, W_r, b_r, ws, expert_index, gate, logits, s)   \
-                  : router_block_launch<XT, ET, WT, TT, false>(w, x, W_r, b_r, ws, expert_index, gate, logits, s))
-    if constexpr (sizeof(XT) == 2)
+    (w.E % 4 == 0 ? router_block_launch<XT, ET, WT, TT, true, F32P>(w, x, W_r, b_r, ws, expert_index, gate, logits, s) \
+                  : router_block_launch<XT, ET, WT, TT, false, F32P>(w, x, W_r, b_r, ws, expert_index, gate, logits, s))
+    if constexpr (sizeof(XT) == 2 && !F32P)
         if (w.tb == 128) return w.E <= 32 ? SW_RB(1, 4, 4) : w.E <= 64 ? SW_RB(2, 2, 4) : SW_RB(4, 1, 4);
     if (w.E <= 32) return SW_RB(1, 2, 2);
     if (w.E <= 64) return SW_RB(2, 2, 2);
@@ -360,9 +372,10 @@ hipError_t launch_router_block(const Workspace &w, int dtype, const void *x, con
                                const float *b_r, char *ws, int32_t *expert_index, float *gate,
                                float *router_logits, hipStream_t s) {
     ProfScope ps("router_fwd", s);
-    return dtype == SW_BF16
-               ? router_block_typed<bf16>(w, x, W_r, b_r, ws, expert_index, gate, router_logits, s)
-               : router_block_typed<float>(w, x, W_r, b_r, ws, expert_index, gate, router_logits, s);
+    if (dtype != SW_BF16)
+        return router_block_typed<float, false>(w, x, W_r, b_r, ws, expert_index, gate, router_logits, s);
+    return w.noise.jitter ? router_block_typed<bf16, true>(w, x, W_r, b_r, ws, expert_index, gate, router_logits, s)
+                          : router_block_typed<bf16, false>(w, x, W_r, b_r, ws, expert_index, gate, router_logits, s);
 }
 
 }  // namespace sw

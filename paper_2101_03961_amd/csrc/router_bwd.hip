@@ -30,8 +30,8 @@ struct RouterBwdArgs {
     const int32_t *idx, *counts_g, *tok_slot;
     const void *dXd;
     void *dx;
-    float *dlogits;    // fp32 products: [T][E]
-    bf16 *dl_split;    // bf16 terms: [T][hi 128 | lo 128]
+    float *dlogits;    // dl for dW_r, as that takes it: fp32 [T][E],
+    bf16 *dl_split;    // or bf16 terms [T][hi 128 | lo 128], or null
     float *dbr_part;   // [ceil(T / 128)][E] sums of dl, or nullptr
     int T, Tg, d, E, groups_per_block;
     float aux_scale;
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(256, EK > 8 ? 1 : 2) void router_dx_block_kernel(Ro
             }
     }
     if (writer && live) {
-        if (kSplit) {
+        if (kSplit && a.dl_split) {
 #pragma unroll
             for (int ks = 0; ks < 8; ++ks) {   // all 128 columns of each half
                 bf16 *row = a.dl_split + (size_t)t * 256 + ks * 16 + half * 8;
@@ -338,7 +338,7 @@ hipError_t launch_router_dx_block(const Workspace &w, int dtype, float aux_scale
     a.dXd = ws + w.dXd;
     a.dx = dx;
     a.dlogits = (float *)(ws + w.dlogits);
-    a.dl_split = (bf16 *)(ws + w.dl_split);
+    a.dl_split = router_bwd_mfma_supported(w, dtype) ? (bf16 *)(ws + w.dl_split) : nullptr;   // else dl in fp32
     a.dbr_part = db_r && !parts.blocks ? (float *)(ws + w.dbr_part) : nullptr;
     if (parts.blocks) {
         a.dWr_part = parts.part;

@@ -360,7 +360,9 @@ hipError_t launch_router_split_bwd(const Workspace &w, const float *W_r, char *w
 // They address all expert tiles' planes of dl and of W_r through one
 // buffer descriptor each; with input jitter they read the planes of x * m that the forward pass left.
 bool router_bwd_mfma_supported(const Workspace &w, int dtype) {
-    return dtype == SW_BF16 && w.E % 4 == 0 && (w.router_block || router_fwd_mfma_supported(w, dtype)) &&
+    // (the one-kernel forward leaves no planes of x * m: fp32 operands then)
+    return dtype == SW_BF16 && w.E % 4 == 0 && !(w.router_block && w.noise.jitter) &&
+           (w.router_block || router_fwd_mfma_supported(w, dtype)) &&
            (uint64_t)w.etiles * (uint64_t)w.T * 512u < 0x7fffffffu &&
            (uint64_t)w.etiles * (uint64_t)w.d * 512u < 0x7fffffffu;
 }

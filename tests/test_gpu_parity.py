@@ -163,6 +163,17 @@ def test_router_weight_gradient_beside_the_experts(dtype, T, d, f, E, cf, n, jit
     assert all(torch.equal(first[k], again[k]) for k in first)
 
 
+@pytest.mark.parametrize("T,d,E,n", [(1, 8, 3, 1), (65, 72, 32, 1), (130, 40, 33, 1), (1000, 264, 64, 2), (700, 136, 128, 1),
+                                     (515, 72, 130, 1), (300, 264, 256, 4)])
+def test_bf16_tokens_with_jitter_in_the_one_kernel_router(T, d, E, n):
+    """fp32 products of x * m, forward and backward; the logits to fp32 rounding."""
+    from parity import compare_full
+    s = SwitchShape("t", T // n * n, d, 72, E, 1.25, dtype="bf16", zipf_bias=E % 4 != 0, seed_index=73, n_groups=n,
+                    jitter_eps=0.1, noise_seed=11)
+    errs, _, _, _ = compare_full(s, make_inputs(s, _dev()), d_aux=1.0)
+    _report("jitter %s" % ((T, d, E, n),), errs)
+
+
 @pytest.mark.parametrize("T,d,f,E,cf,n,rate,ffn,rounds", [
     (12000, 264, 1544, 64, 1.0, 1, 0.0, "relu", 0),     # 256 x 384, one row tile per expert, ragged both ways
     (16000, 264, 1544, 60, 1.25, 2, 0.1, "relu", 0),    # 320 x 256, two row tiles, groups, dropout
