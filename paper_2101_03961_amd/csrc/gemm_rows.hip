@@ -67,7 +67,7 @@ enum { ROWS_PLAIN = 0, ROWS_RELU = 1, ROWS_MASK = 2, ROWS_COMBINE = 3 };
 // Mask bits: one byte per 16-byte piece of the output (bits 0..3: low halves of its four words, 4..7:
 // high halves), [tile][wave][32-row round][pass][lane] in the order the epilogue handles them.
 template <int IP, int WP, int IQ, int IQ_MAX, int WQ, int STAGES, bool P_TRANS, int EPI, bool DROP,
-          bool WGRAD, bool GUARD = false>
+          bool WGRAD, bool GUARD = false, bool ONCE = false>
 __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, int e, int q0, int p0, int qlim,
                                           int klim, int lane, int wave) {
     constexpr int NW = WP * WQ, PB = 32 * IP * WP, QB = 32 * IQ_MAX * WQ;
@@ -75,7 +75,7 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
     const int wp = wave % WP, wq = wave / WP;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
 
-    typename std::conditional<P_TRANS, RowsTrans<PB, NW>, RowsDirect<PB, NW>>::type op;
+    typename std::conditional<P_TRANS, RowsTrans<PB, NW, BK, ONCE>, RowsDirect<PB, NW, BK, ONCE>>::type op;
     typename std::conditional<WGRAD, RowsTrans<QB, NW>, RowsDirect<QB, NW>>::type oq;
     op.init_frag16(lane, wp * 32 * IP);
     oq.init_frag16(lane, wq * 32 * IQ);
@@ -319,7 +319,8 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
 // with as few blocks as hold them, so with fewer products, fragment reads and loads (128 experts of 768 x 3072, 64
 // rows in tiles of 256: masked gradient 152 -> 140 us, first forward 186 -> 176; 64 of 4096 x 10240, 256 rows in
 // tiles of 320: 1530 -> 1480).
-template <int IP, int WP, int IQ, int WQ, int STAGES, bool P_TRANS, int EPI, bool DROP, bool WGRAD, bool GUARD = false>
+template <int IP, int WP, int IQ, int WQ, int STAGES, bool P_TRANS, int EPI, bool DROP, bool WGRAD, bool GUARD = false,
+          bool ONCE = false>
 __device__ __forceinline__ void rows_block(const RowsArgs &a, char *lds, int L) {
     constexpr int PB = 32 * IP * WP, QB = 32 * IQ * WQ;
     const int lane = threadIdx.x & 63;
@@ -382,8 +383,8 @@ __device__ __forceinline__ void rows_block(const RowsArgs &a, char *lds, int L) 
     const int q0 = qt * QB, p0 = pt * PB;
     if (q0 >= qlim) return;
 #define SW_ROWS(N) \
-    rows_tile<IP, WP, (N) < IQ ? (N) : IQ, IQ, WQ, STAGES, P_TRANS, EPI, DROP, WGRAD, GUARD>(a, lds, L, e, q0, p0, \
-                                                                                                 qlim, klim, lane, wave)
+    rows_tile<IP, WP, (N) < IQ ? (N) : IQ, IQ, WQ, STAGES, P_TRANS, EPI, DROP, WGRAD, GUARD, ONCE>( \
+        a, lds, L, e, q0, p0, qlim, klim, lane, wave)
     if constexpr (WP * WQ == 8 && !WGRAD) {
         const int blocks = (qlim - q0 + 32 * WQ - 1) / (32 * WQ);
         if (blocks <= 1) SW_ROWS(1);
@@ -398,10 +399,11 @@ __device__ __forceinline__ void rows_block(const RowsArgs &a, char *lds, int L) 
 }
 
 template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, bool P_TRANS, int EPI, bool DROP,
-          bool WGRAD, bool GUARD>
+          bool ONCE, bool WGRAD, bool GUARD>
 __global__ __launch_bounds__(64 * WP * WQ, WPE) void gemm_rows_kernel(RowsArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    rows_block<IP, WP, IQ, WQ, STAGES, P_TRANS, EPI, DROP, WGRAD, GUARD>(a, lds, blockIdx.y * a.grid_x + blockIdx.x);
+    rows_block<IP, WP, IQ, WQ, STAGES, P_TRANS, EPI, DROP, WGRAD, GUARD, ONCE>(a, lds,
+                                                                               blockIdx.y * a.grid_x + blockIdx.x);
 }
 
 // Three products in one launch: the first layer's data gradient and both weight gradients, which do not depend on
@@ -443,9 +445,9 @@ static int64_t rows_plan(RowsArgs &a, int E, int QB, int PB, bool wgrad) {
 }
 
 template <int IP, int WP, int IQ, int WQ, int STAGES, int WPE, bool P_TRANS, int EPI, bool DROP,
-          bool WGRAD, bool GUARD = false>
+          bool ONCE, bool WGRAD, bool GUARD = false>
 static hipError_t rows_launch(RowsArgs a, int E, hipStream_t s) {
-    auto kern = gemm_rows_kernel<IP, WP, IQ, WQ, STAGES, WPE, P_TRANS, EPI, DROP, WGRAD, GUARD>;
+    auto kern = gemm_rows_kernel<IP, WP, IQ, WQ, STAGES, WPE, P_TRANS, EPI, DROP, ONCE, WGRAD, GUARD>;
     constexpr int PB = 32 * IP * WP, QB = 32 * IQ * WQ;
     constexpr int lds = rows_lds(IP, WP, IQ, WQ, STAGES);
     static PerDeviceOnce once;
@@ -592,18 +594,36 @@ int rows_wgrad_tile(const Workspace &w, int64_t Qdim, int64_t Pdim) {
     return best;
 }
 
+// Weights that no other block reads (one row tile per expert, whole lines) of a layer beyond the memory-side cache
+// bypass L2 (nt): they stream faster, and what the cache holds from before, the last gradients written among it, is not
+// pushed out to HBM meanwhile.  us of a pass, without / with: 64 tokens, 128 experts of 768 x 3072 forward 118.5 / 107.5,
+// 2048 267 / 252, 16384 349 / 322, forward + backward 8192 914 / 875; 32 experts (302 MB), 512 tokens forward
+// 84 / 81, both 265 / 241; but 16 experts, which the cache holds, 50 / 61 and 122 / 135; lines shared by tiles, 104
+// experts of 2000 x 8032 4570 / 5118; two row tiles, Switch-Base 2008 / 2055.  (320 x 256, 64 experts of 4096 x 10240:
+// 9580 / 9575.)
+static bool rows_read_once(const Workspace &w, const RowsArgs &a, int QB) {
+    return a.Qdim <= QB && a.ldp % 64 == 0 && (double)w.E * (double)w.d * (double)(w.f1 + w.f) * 2. > 256e6;
+}
+
+template <int IP, int WP, int IQ, int WQ, int STAGES, bool P_TRANS, int EPI, bool DROP>
+static hipError_t rows_stream(const Workspace &w, const RowsArgs &a, hipStream_t s) {
+    if (rows_read_once(w, a, 32 * IQ * WQ))
+        return rows_launch<IP, WP, IQ, WQ, STAGES, 2, P_TRANS, EPI, DROP, true, false>(a, (int)w.E, s);
+    return rows_launch<IP, WP, IQ, WQ, STAGES, 2, P_TRANS, EPI, DROP, false, false>(a, (int)w.E, s);
+}
+
 template <bool P_TRANS, int EPI, bool DROP>
-static hipError_t rows_by_tile(const RowsArgs &a, int E, int tile, hipStream_t s) {
+static hipError_t rows_by_tile(const Workspace &w, const RowsArgs &a, int tile, hipStream_t s) {
     switch (tile) {
-    case ROWS_32x128: return rows_launch<1, 4, 1, 1, 3, 2, P_TRANS, EPI, DROP, false>(a, E, s);
-    case ROWS_64x256: return rows_launch<2, 4, 2, 1, 2, 2, P_TRANS, EPI, DROP, false>(a, E, s);
-    case ROWS_96x128: return rows_launch<1, 4, 3, 1, 2, 2, P_TRANS, EPI, DROP, false>(a, E, s);
-    case ROWS_128x128: return rows_launch<2, 2, 2, 2, 2, 2, P_TRANS, EPI, DROP, false>(a, E, s);
+    case ROWS_32x128: return rows_stream<1, 4, 1, 1, 3, P_TRANS, EPI, DROP>(w, a, s);
+    case ROWS_64x256: return rows_stream<2, 4, 2, 1, 2, P_TRANS, EPI, DROP>(w, a, s);
+    case ROWS_96x128: return rows_stream<1, 4, 3, 1, 2, P_TRANS, EPI, DROP>(w, a, s);
+    case ROWS_128x128: return rows_stream<2, 2, 2, 2, 2, P_TRANS, EPI, DROP>(w, a, s);
     }
     if constexpr (EPI != ROWS_COMBINE) switch (tile) {
-    case ROWS_256x256: return rows_launch<2, 4, 4, 2, 2, 2, P_TRANS, EPI, DROP, false>(a, E, s);
-    case ROWS_320x256: return rows_launch<2, 4, 5, 2, 2, 2, P_TRANS, EPI, DROP, false>(a, E, s);
-    case ROWS_256x384: return rows_launch<3, 4, 4, 2, 2, 2, P_TRANS, EPI, DROP, false>(a, E, s);
+    case ROWS_256x256: return rows_launch<2, 4, 4, 2, 2, 2, P_TRANS, EPI, DROP, false, false>(a, (int)w.E, s);
+    case ROWS_320x256: return rows_launch<2, 4, 5, 2, 2, 2, P_TRANS, EPI, DROP, false, false>(a, (int)w.E, s);
+    case ROWS_256x384: return rows_stream<3, 4, 4, 2, 2, P_TRANS, EPI, DROP>(w, a, s);
     }
     return hipErrorInvalidValue;
 }
@@ -653,24 +673,24 @@ hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const v
     switch (kind) {
     case GEMM_FWD1: {
         ProfScope ps(w.geglu ? "gemm1_fwd" : "gemm1_fwd_relu", s);
-        if (w.geglu) return rows_by_tile<true, ROWS_PLAIN, false>(a, E, tile, s);
-        if (drop) return rows_by_tile<true, ROWS_RELU, true>(a, E, tile, s);
-        return rows_by_tile<true, ROWS_RELU, false>(a, E, tile, s);
+        if (w.geglu) return rows_by_tile<true, ROWS_PLAIN, false>(w, a, tile, s);
+        if (drop) return rows_by_tile<true, ROWS_RELU, true>(w, a, tile, s);
+        return rows_by_tile<true, ROWS_RELU, false>(w, a, tile, s);
     }
     case GEMM_FWD2: {
         ProfScope ps("gemm2_fwd", s);
-        if (w.combine_in_gemm) return rows_by_tile<true, ROWS_COMBINE, false>(a, E, tile, s);
-        return rows_by_tile<true, ROWS_PLAIN, false>(a, E, tile, s);
+        if (w.combine_in_gemm) return rows_by_tile<true, ROWS_COMBINE, false>(w, a, tile, s);
+        return rows_by_tile<true, ROWS_PLAIN, false>(w, a, tile, s);
     }
     case GEMM_DGRAD2: {
         ProfScope ps(w.geglu ? "gemm2_dgrad" : "gemm2_dgrad_relumask", s);
-        if (w.geglu) return rows_by_tile<false, ROWS_PLAIN, false>(a, E, tile, s);
-        if (drop) return rows_by_tile<false, ROWS_MASK, true>(a, E, tile, s);
-        return rows_by_tile<false, ROWS_MASK, false>(a, E, tile, s);
+        if (w.geglu) return rows_by_tile<false, ROWS_PLAIN, false>(w, a, tile, s);
+        if (drop) return rows_by_tile<false, ROWS_MASK, true>(w, a, tile, s);
+        return rows_by_tile<false, ROWS_MASK, false>(w, a, tile, s);
     }
     case GEMM_DGRAD1: {
         ProfScope ps("gemm1_dgrad", s);
-        return rows_by_tile<false, ROWS_PLAIN, false>(a, E, tile, s);
+        return rows_by_tile<false, ROWS_PLAIN, false>(w, a, tile, s);
     }
     case GEMM_WGRAD2:
     case GEMM_WGRAD1: {
@@ -678,11 +698,11 @@ hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const v
         const bool two = kind == GEMM_WGRAD2;
         ProfScope ps(two ? "gemm2_wgrad" : "gemm1_wgrad", s);
         switch (tile) {
-        case ROWS_128x128: return rows_launch<2, 2, 2, 2, 2, 2, true, ROWS_PLAIN, false, true>(a, E, s);
+        case ROWS_128x128: return rows_launch<2, 2, 2, 2, 2, 2, true, ROWS_PLAIN, false, false, true>(a, E, s);
         case ROWS_256x128:
             if (rows_part_lines(w, a.Qdim, a.Pdim))
-                return rows_launch<2, 2, 4, 2, 1, 2, true, ROWS_PLAIN, false, true, true>(a, E, s);
-            return rows_launch<2, 2, 4, 2, 1, 2, true, ROWS_PLAIN, false, true>(a, E, s);
+                return rows_launch<2, 2, 4, 2, 1, 2, true, ROWS_PLAIN, false, false, true, true>(a, E, s);
+            return rows_launch<2, 2, 4, 2, 1, 2, true, ROWS_PLAIN, false, false, true>(a, E, s);
         }
         return hipErrorInvalidValue;
     }

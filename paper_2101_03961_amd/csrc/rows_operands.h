@@ -9,7 +9,7 @@ namespace sw {
 
 // [row][k] operand of R rows, BK (64 or 32) k per step: LDS [R][BK k]; the 16-byte chunks of a
 // row are permuted as in DirectOperand64 / DirectOperand.
-template <int R, int NW, int BK = 64> struct RowsDirect {
+template <int R, int NW, int BK = 64, bool ONCE = false> struct RowsDirect {
     static constexpr int kRowsPerLoad = 512 / BK;            // rows of one wave-wide load
     static constexpr int kLoads = R / (kRowsPerLoad * NW);   // per wave and step
     static constexpr int kPitch = BK * 2;                    // bytes of an LDS row
@@ -36,7 +36,7 @@ template <int R, int NW, int BK = 64> struct RowsDirect {
     __device__ __forceinline__ void issue_one(uint32_t st, int k0, int wave, int i) const {
         // (chunks past the last k: the sign of the difference, which is kOobOffset)
         const uint32_t vo = voff | ((uint32_t)(klim - k0 - 1 - c8) & kOobOffset);
-        dma16(rsrc, vo, (uint32_t)i * row_step + (uint32_t)k0 * 2u,
+        dma16<ONCE>(rsrc, vo, (uint32_t)i * row_step + (uint32_t)k0 * 2u,
               st + (uint32_t)((i * NW + wave) * 1024));
     }
     __device__ __forceinline__ bf16x8 frag(const char *st, int x, int ks) const {
@@ -89,7 +89,7 @@ template <int R, int NW, int S = 32> struct F32Direct : RowsDirect<R, NW, 64> {
 // of 16; group g covers k 8 g .. + 8; inside a group lane j supplies the 8 bytes at k-row j/4, rows 4 (j%4) .. +4, and
 // receives k-rows 0..3 of row j.
 // (Rows of 384 bytes: 128 from the parity of the k-row, the rest from the permutation of eight chunks.)
-template <int R, int NW, int BK = 64> struct RowsTrans {
+template <int R, int NW, int BK = 64, bool ONCE = false> struct RowsTrans {
     static constexpr int kLoads = R * BK / (512 * NW);
     static constexpr int kChunks = R / 8;          // 16-byte chunks of a k-row
     static constexpr int kRun = BK / NW < 8 ? BK / NW : 8;   // k-rows that a wave loads at a time, all with k and 8 alike
@@ -139,12 +139,12 @@ template <int R, int NW, int BK = 64> struct RowsTrans {
     __device__ __forceinline__ void issue_one(uint32_t st, int k0, int wave, int i) const {
         if (R == 256) {
             const int row = first_row(wave, i) - first_row(wave, 0);
-            dma16(rsrc, voff[0], (uint32_t)(k0 + row) * k_step, st + (uint32_t)(first_row(wave, i) * (R * 2)));
+            dma16<ONCE>(rsrc, voff[0], (uint32_t)(k0 + row) * k_step, st + (uint32_t)(first_row(wave, i) * (R * 2)));
             return;
         }
         // load i: k-rows kRun NW (i / kGroup) + kRun wave + ..
         const int in = i % kGroup, at = i / kGroup * kRun * NW;
-        dma16(rsrc, voff[in % kPeriod], (uint32_t)(k0 + at + in / kPeriod * kPeriodRows) * k_step,
+        dma16<ONCE>(rsrc, voff[in % kPeriod], (uint32_t)(k0 + at + in / kPeriod * kPeriodRows) * k_step,
               st + (uint32_t)(at * (R * 2) + (wave * kGroup + in) * 1024));
     }
     __device__ __forceinline__ bf16x8 frag16(const char *st, int x, int ks) const {
