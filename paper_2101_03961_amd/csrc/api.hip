@@ -153,10 +153,9 @@ Workspace layout_workspace(const switch_config *cfg) {
     w.dbr_part = take_dead((size_t)ceil_div(w.T, 128) * E * 4);
     w.xj = take(jit_mfma ? T * (size_t)w.dpad_r * 2 : 0);
     w.no_slot = take(jit_mfma && !w.router_bwd_block ? T * 4 : 0);
-    w.tps_m = ceil_div(ceil_div(w.T, 85), 64) * 64;
-    if (w.tps_m < 64) w.tps_m = 64;   // empty batch
+    w.tps_m = router_dwr_tokens(w);
     w.nsplit_m = ceil_div(w.T, w.tps_m);
-    w.dWr_part_m = take_dead((size_t)w.etiles * w.nsplit_m * (jit_mfma ? 2 * (size_t)w.dpad : d) * 256 * 4);
+    w.dWr_part_m = take_dead(mfma ? (size_t)w.etiles * w.nsplit_m * d * 128 * 4 : 0);
     size_t bits = 0;
     for (int &t : w.gemm_tile) t = ROWS_NONE;
     if (cfg->act_dtype == SW_BF16) {

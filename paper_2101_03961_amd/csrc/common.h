@@ -171,8 +171,7 @@ struct Workspace {
     size_t wsplit_b;            // bf16 [etiles][d][256]   W_r rows as hi | lo halves (MFMA router backward)
     bool has_wsplit_b;          // it is laid out: only where the backward pass reads it
     size_t dl_split;            // bf16 [etiles][T][256]   dlogits rows as hi | lo halves
-    size_t dWr_part_m;          // f32 [etiles][nsplit_m][d][256]  partial sums of x^T [dl_hi | dl_lo]
-                                //     (with jitter: [nsplit_m][2 dpad][256], hi and mid plane of x * m)
+    size_t dWr_part_m;          // f32 [etiles][nsplit_m][d][128]  partial sums of x^T dl
     int64_t tps_m, nsplit_m;    // tokens per split (multiple of 32), number of splits
     size_t relu_bits;           // u8  one bit per element of A, A > 0, in the order the epilogue of the
                                 //     first forward GEMM (and of the masked gradient) visits its tiles
@@ -280,7 +279,9 @@ hipError_t launch_router_dx_block(const Workspace &w, int dtype, float aux_scale
 // MFMA pieces of the router backward (bf16), in gemm_bf16.hip
 hipError_t launch_router_split_bwd(const Workspace &w, const float *W_r, char *ws, hipStream_t s);
 hipError_t launch_router_dx_mfma(const Workspace &w, char *ws, void *dx, hipStream_t s);
+// Partial sums of dW_r (router_dwr.hip), and how many tokens each takes
 hipError_t launch_router_dWr_mfma(const Workspace &w, const void *x, char *ws, hipStream_t s);
+int64_t router_dwr_tokens(const Workspace &w);
 
 // Grouped GEMMs over experts.  Each computes, for every expert e,
 //   C_e[q][p] = sum_k Q_e(q,k) * P_e(p,k)

@@ -114,8 +114,6 @@ struct GemmArgs {
     const int32_t *tok_slot;            // ROUTER_DX: row of the addend for each token, -1: none
     int router_tiles;                   // ROUTER_DX: tiles of 128 experts; operands are planes
     int q_plane, p_plane;               //   [tile][row][256], plane sizes in elements
-    float *Cf;                          // ROUTER_DWR: fp32 partial sums [split][q][p]
-    int T_total, tps;                   // ROUTER_DWR: tokens, tokens per split
     // dispatch / combine inside the GEMM (see GATHER, EPI_SCALE, EPI_SCATTER)
     uint32_t gather_bytes;              // bytes of a token-major matrix (gathered operand, Cscatter)
     const uint32_t *slot_off;           // byte offset of each slot's token row in the token-major tensors
@@ -128,9 +126,7 @@ struct GemmArgs {
 //   ROUTER_DX   dx = dl W_r^T + gathered dXd: one batch; k runs over three blocks of
 //               128 experts pairing the bf16 halves of dl (hi|lo per row, 256 wide)
 //               with those of W_r^T (hi|lo per row): hi*hi, hi*lo, lo*hi.
-//   ROUTER_DWR  partial sums of x^T [dl_hi | dl_lo] over token ranges: batch = token
-//               range, k = tokens of the range, fp32 output.
-enum GemmMode { MODE_EXPERTS = 0, MODE_ROUTER_DX = 1, MODE_ROUTER_DWR = 2 };
+enum GemmMode { MODE_EXPERTS = 0, MODE_ROUTER_DX = 1 };
 
 template <bool TRANS, bool GATHER> struct OperandOf { typedef DirectOperand64 type; };
 template <> struct OperandOf<true, false> { typedef TransOperand64 type; };
@@ -178,7 +174,6 @@ __device__ __forceinline__ bool next_tile(const GemmArgs &a, int &L, int L_end, 
         }
         int kept = 0;
         if (MODE == MODE_EXPERTS) kept = a.kept[e];
-        if (MODE == MODE_ROUTER_DWR) kept = min(a.tps, a.T_total - e * a.tps);
         t.e = e;
         t.p0 = pt * kBP;
         t.q0 = qt * kBQ;
@@ -614,25 +609,7 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_bf16_kernel(GemmArgs a) {
         // here, per tile, instead of being kept in registers across the k loop.
         int ln = lane;
         asm volatile("" : "+v"(ln));
-        if (MODE == MODE_ROUTER_DWR) {
-            // fp32 partial sums straight from the accumulators: four consecutive p per lane
-            float *Cf = a.Cf + (size_t)cur.e * a.c_batch;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int q = cur.q0 + wq * 128 + j * 32 + (ln & 31);
-                if (q >= cur.qlim) continue;
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int p = cur.p0 + wp * 128 + i * 32 + g * 8 + ((ln >> 5) << 2);
-                        if (p < a.Pdim)
-                            *(float4 *)(Cf + (size_t)q * a.ldc + p) =
-                                make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1],
-                                            acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
-                    }
-            }
-        } else {
+        {
             char *ep = lds + turn_stage * kOpBytes64 + wave * kTurnBytes;
             bf16 *Cout = a.Cout + (size_t)cur.e * a.c_batch;
             const int c = ln & 15;
@@ -1030,34 +1007,6 @@ hipError_t launch_router_dx_mfma(const Workspace &w, char *ws, void *dx, hipStre
     a.total_tiles = a.tiles_q * a.tiles_p;
     ProfScope ps("router_dx_mfma", s);
     return gemm_launch<false, false, EPI_NONE, false, false, MODE_ROUTER_DX>(a, s);
-}
-
-// Partial sums over token ranges of x^T [dl_hi | dl_lo]  ->  part[split][d][256] (fp32).
-// With input jitter x is replaced by the hi and mid planes of x * m, taken as one operand of
-// 2 dpad rows: part[split][2 dpad][256], row k from the hi plane, row dpad + k from the mid plane.
-hipError_t launch_router_dWr_mfma(const Workspace &w, const void *x, char *ws, hipStream_t s) {
-    const bool jitter = w.noise.jitter;
-    const int ldx = jitter ? (int)w.dpad_r : (int)w.d;
-    const int rows = jitter ? 2 * (int)w.dpad : (int)w.d;
-    ProfScope ps("router_dWr_mfma", s);
-    // one launch per tile of 128 experts: part[tile][split][rows][256]
-    for (int tile = 0; tile < (int)w.etiles; ++tile) {
-        GemmArgs a{};
-        a.Q = jitter ? (const bf16 *)(ws + w.xj) : (const bf16 *)x;                  // [k = token][q]
-        a.q_batch = (size_t)w.tps_m * ldx; a.ldq = ldx;
-        a.P = (const bf16 *)(ws + w.dl_split) + (size_t)tile * w.T * 256;           // [k = token][p]
-        a.p_batch = (size_t)w.tps_m * 256; a.ldp = 256;
-        a.Cf = (float *)(ws + w.dWr_part_m) + (size_t)tile * w.nsplit_m * rows * 256;
-        a.c_batch = (size_t)rows * 256; a.ldc = 256;
-        a.T_total = (int)w.T; a.tps = (int)w.tps_m;
-        a.Qdim = rows; a.Pdim = 256; a.Kdim = (int)w.tps_m;
-        a.tiles_q = (int)ceil_div(a.Qdim, kBQ);
-        a.tiles_p = 1;
-        a.total_tiles = a.tiles_q * a.tiles_p * (int)w.nsplit_m;
-        hipError_t err = gemm_launch<true, true, EPI_NONE, false, true, MODE_ROUTER_DWR>(a, s);
-        if (err != hipSuccess) return err;
-    }
-    return hipSuccess;
 }
 
 }  // namespace sw

@@ -430,35 +430,19 @@ __global__ __launch_bounds__(256) void router_dlogits_kernel(
     }
 }
 
-// dW_r[k][j] = sum over splits of (part[s][k][j] + part[s][k][128 + j]), fixed order.
-// rows = rows of one split's part; second > 0: the operand had a second plane (input jitter:
-// x * m as hi + mid), whose rows start at `second` and are added in.
+// dW_r[k][j] = sum over splits of part[j / 128][s][k][j % 128], fixed order.
 __global__ __launch_bounds__(256) void reduce_dWr_split_kernel(const float *__restrict__ part,
                                                                float *__restrict__ dW_r, int d,
-                                                               int E, int nsplit, int rows,
-                                                               int second, DbrArgs db) {
+                                                               int E, int nsplit, DbrArgs db) {
     const int blocks = (d * E + 255) / 256;
     if ((int)blockIdx.x >= blocks) return reduce_dbr(db, (int)blockIdx.x - blocks);
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= d * E) return;
     const int k = i / E, j = i - k * E;
-    // the parts of expert j's tile of 128 experts: [tile][split][rows][hi 128 | lo 128]
-    const float *tile_part = part + (size_t)(j >> 7) * nsplit * rows * 256 + (j & 127);
+    const float *row = part + ((size_t)(j >> 7) * nsplit * d + k) * 128 + (j & 127);
     float s = 0.f;
 #pragma unroll 8
-    for (int q = 0; q < nsplit; ++q) {   // unrolled: eight splits' loads in flight, same order of sums
-        const float *row = tile_part + ((size_t)q * rows + k) * 256;
-        s += row[0] + row[128];
-    }
-    if (second > 0) {
-        float s2 = 0.f;
-#pragma unroll 8
-        for (int q = 0; q < nsplit; ++q) {
-            const float *row = tile_part + ((size_t)q * rows + second + k) * 256;
-            s2 += row[0] + row[128];
-        }
-        s += s2;
-    }
+    for (int q = 0; q < nsplit; ++q) s += row[(size_t)q * d * 128];   // unrolled: eight splits' loads in flight
     dW_r[i] = s;
 }
 
@@ -766,8 +750,9 @@ static float aux_scale_of(const Workspace &w, float alpha, float d_aux) {
 // launch then adds up the parts.  That saves two launches of the chain (us per forward + backward pass, without /
 // with: fp32 256 x 64 x 256, 4 experts 56.8 / 51.0; bf16 5003 x 392 x 1000, 10 experts 115.0 / 106.3; large fp32 layers the
 // same).  The parts of other layers have a launch of their own, behind the experts': where the router gradients take fp32
-// operands, and up to 5e8 products, where the matrix cores' kernel is slower (us of a pass, that kernel / here: 768 x
-// 1536, 128 experts, 512 tokens 462 / 453, 2048 475 / 469, 4096 516 / 505, 8192 555 / 570).  At
+// operands, and up to 2.5e8 products, where the matrix cores' two kernels are slower (us of a pass, a slower form of those /
+// here: 768 x 1536, 128 experts, 512 tokens 462 / 453, 2048 475 / 469, 4096 516 / 505, 8192 555 / 570; since then they take
+// 10 less from 4096 on).  At
 // most 64 parts of at least 32 tokens and 16 MB in all: more would be read for longer than they are summed.
 static bool router_wgrad_hosted(const Workspace &w) {
     return w.elt == 2 ? rows_backward_supported(w) : gemm_f32_on_mfma(w, w.d, w.f1);
@@ -775,7 +760,7 @@ static bool router_wgrad_hosted(const Workspace &w) {
 int64_t router_wgrad_splits(const Workspace &w) {
     if (!w.router_bwd_block || w.fused || w.C == 0) return 0;
     if (router_bwd_mfma_supported(w, w.elt == 2 ? SW_BF16 : SW_F32) && !router_wgrad_hosted(w) &&
-        (double)w.T * (double)w.d * (double)w.E > 5e8)
+        (double)w.T * (double)w.d * (double)w.E > 2.5e8)
         return 0;
     const int64_t most = ((int64_t)16 << 20) / (4 * (w.d + 1) * w.E);   // 16 MB of parts
     int64_t n = ceil_div(w.T, kRwTokens);
@@ -881,8 +866,7 @@ static hipError_t router_bwd_typed(const Workspace &w, float alpha, float d_aux,
         ProfScope ps("router_dWr_reduce", s);
         hipLaunchKernelGGL(reduce_dWr_split_kernel, dim3((unsigned)ceil_div(w.d * w.E, 256) + db_blocks),
                            dim3(256), 0, s, (const float *)(ws + w.dWr_part_m), dW_r, (int)w.d,
-                           (int)w.E, (int)w.nsplit_m, jitter ? 2 * (int)w.dpad : (int)w.d,
-                           jitter ? (int)w.dpad : 0, db);
+                           (int)w.E, (int)w.nsplit_m, db);
         return hipGetLastError();
     }
     ProfScope ps("router_dWr", s);

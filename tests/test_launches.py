@@ -148,14 +148,14 @@ def test_small_layers_take_three_products_in_one_launch(recorder, T, d, f, E, cf
 # the workspace near the static scratch's limit; a launch less for the parts and one less for their sums.
 @pytest.mark.parametrize("T,d,f,E,cf,kw,own", [
     (5003, 392, 1000, 10, 1.25, dict(bias=True), False), (256, 64, 256, 4, 1.25, dict(dtype="f32"), False),
-    (8192, 768, 3072, 32, 1.25, dict(dtype="f32", bias=True), False), (900, 512, 2048, 16, 2.0, dict(), True),   # 29 MB
+    (8192, 768, 3072, 32, 1.25, dict(dtype="f32", bias=True), False), (1050, 512, 2048, 16, 2.0, dict(), True),   # 25 MB
     (8192, 768, 3072, 128, 1.25, dict(), True), (500, 64, 256, 300, 4.0, dict(dtype="f32"), True),
     (5003, 392, 1000, 10, 1.25, dict(fused=True), True),
 ])
 def test_router_weight_gradient_beside_the_experts(recorder, T, d, f, E, cf, kw, own):
     (status, base, size, launches), = recorder(call("backward", T, d, f, E, cf, **kw))
     assert status == 0
-    assert any("dWr" in k[0] or "gemm_bf16_kernelILb1ELb1ELi0ELb0" in k[0] for k in launches) == own
+    assert any("dWr" in k[0] for k in launches) == own
     assert any("reduce" in k[0] for k in launches) == own
 
 
