@@ -16,8 +16,8 @@
 // What bounds it: HBM (probabilities, dXd and dx once each: about 50 us at 65536 tokens x 768, 128
 // experts) and what two blocks per CU, the most that LDS and registers leave room for, do not
 // overlap of products and loads.  Measured (us, before: dlogits + weight split + product kernels):
-// 65536 x 768, E 128: 97 (138); 8192: 30 (49); 5003 x 392, E 10 (fp32 products) with the bias sums: 11 (56);
-// 65536 with jitter: 110 (160); fp32 256 x 64, E 4: 6 (25), 8192 x 768, E 32: 17 (54).
+// 65536 x 768, E 128: 82 (138); 8192: 23 (49); 5003 x 392, E 10 (fp32 products) with the bias sums: 11 (56);
+// 65536 with jitter: 97 (160); fp32 256 x 64, E 4: 6 (25), 8192 x 768, E 32: 17 (54).
 #include "common.h"
 #include "lds_operands.h"
 #include "router_wgrad.h"
@@ -93,6 +93,10 @@ __global__ __launch_bounds__(256, EK > 8 ? 1 : 2) void router_dx_block_kernel(Ro
     load_w(g_first);
 
     // ---- dl of the lane's token: experts 16 ks + 8 half .. + 7 ----
+    // Loads from places that are there, without a branch around each, so that all are in flight at once; what
+    // lies past E or T is replaced by 0 afterwards.  (us with branches / without: 65536 tokens x 768, 128 experts 90 / 82,
+    // 8192 29 / 23.  Whole row segments turned in LDS, or eight waves per block that split the next group's weights beside
+    // the products: the same.)
     float dl[EK][8];
     const int slot_mine = live ? a.tok_slot[t] : -1;
     {
@@ -101,56 +105,49 @@ __global__ __launch_bounds__(256, EK > 8 ? 1 : 2) void router_dx_block_kernel(Ro
         const float dg = live ? a.dgate[t] : 0.f;
         const float *prow = a.probs + (size_t)(live ? t : 0) * E;
         const int32_t *counts = a.counts_g + (size_t)(live ? t / a.Tg : 0) * E;
-        auto dp_of = [&](int e0, float (&dp)[8]) {   // 0 past E
-            int c[8];
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-                if (WIDE) {
-                    if (e0 + 4 * q < E) *(int4 *)&c[4 * q] = *(const int4 *)(counts + e0 + 4 * q);
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (e0 + 4 * q + r < E) c[4 * q + r] = counts[e0 + 4 * q + r];
-                }
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                // counts centred on their mean: see router_dlogits_kernel
-                dp[r] = e0 + r < E ? a.aux_scale * ((float)c[r] - mean_count) : 0.f;
-                if (e0 + r == me) dp[r] += dg;
-            }
-        };
+        float dp[EK][8];
 #pragma unroll
         for (int ks = 0; ks < EK; ++ks)
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const int e0 = ks * 16 + half * 8 + 4 * q;
-                f32x4 v = {0.f, 0.f, 0.f, 0.f};
                 if (WIDE) {
-                    if (live && e0 < E) v = *(const f32x4 *)(prow + e0);
+                    const int at = min(e0, E - 4);
+                    const f32x4 v = *(const f32x4 *)(prow + at);
+                    const int4 c = *(const int4 *)(counts + at);
+                    const int ci[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        dl[ks][4 * q + r] = v[r];
+                        dp[ks][4 * q + r] = (float)ci[r];
+                    }
                 } else {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (live && e0 + r < E) v[r] = prow[e0 + r];
+                    for (int r = 0; r < 4; ++r) {
+                        const int at = min(e0 + r, E - 1);
+                        dl[ks][4 * q + r] = prow[at];
+                        dp[ks][4 * q + r] = (float)counts[at];
+                    }
                 }
-#pragma unroll
-                for (int r = 0; r < 4; ++r) dl[ks][4 * q + r] = v[r];
             }
         float s = 0.f;
 #pragma unroll
-        for (int ks = 0; ks < EK; ++ks) {
-            float dp[8];
-            dp_of(ks * 16 + half * 8, dp);
+        for (int ks = 0; ks < EK; ++ks)
 #pragma unroll
-            for (int r = 0; r < 8; ++r) s += dl[ks][r] * dp[r];
-        }
+            for (int r = 0; r < 8; ++r) {
+                const int e = ks * 16 + half * 8 + r;
+                // counts centred on their mean: see router_dlogits_kernel
+                float v = a.aux_scale * (dp[ks][r] - mean_count);
+                if (e == me) v += dg;
+                if (!(live && e < E)) dl[ks][r] = 0.f;
+                dp[ks][r] = v;
+                s += dl[ks][r] * v;
+            }
         s += __shfl_xor(s, 32);
 #pragma unroll
-        for (int ks = 0; ks < EK; ++ks) {
-            float dp[8];
-            dp_of(ks * 16 + half * 8, dp);
+        for (int ks = 0; ks < EK; ++ks)
 #pragma unroll
-            for (int r = 0; r < 8; ++r) dl[ks][r] *= dp[r] - s;   // p is 0 past E and past T
-        }
+            for (int r = 0; r < 8; ++r) dl[ks][r] *= dp[ks][r] - s;   // p is 0 past E and past T
     }
     const bool writer = blockIdx.y == 0 && a.nsplit == 0;   // (with parts of dW_r nothing reads dl)
     if (writer && a.dbr_part) {   // column sums over the block's 128 tokens, 16 experts at a time
