@@ -187,6 +187,9 @@ __device__ __forceinline__ void rows_tile(const RowsArgs &a, char *lds, int L, i
             const char *sp = lds + st * kStage, *sq = sp + kPBytes;
 #pragma unroll
             for (int ks = 0; ks < BK / 32; ++ks) {
+                // a half step past an expert's last slot: zeros (us, second gradient with / without these products: 25
+                // slots, 104 experts of 2000 x 8032 771 / 720; 4 slots, 128 of 768 x 1536 61 / 57)
+                if (WGRAD && kt * BK + ks * 32 >= klim) break;
                 bf16x8 fp[2 * IP], fq[2 * IQ];
 #pragma unroll
                 for (int i = 0; i < 2 * IP; ++i) fp[i] = op.frag16(sp, i, ks);

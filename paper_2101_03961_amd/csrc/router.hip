@@ -755,7 +755,10 @@ static float aux_scale_of(const Workspace &w, float alpha, float d_aux) {
 // 10 less from 4096 on).  At
 // most 64 parts of at least 32 tokens and 16 MB in all: more would be read for longer than they are summed.
 static bool router_wgrad_hosted(const Workspace &w) {
-    return w.elt == 2 ? rows_backward_supported(w) : gemm_f32_on_mfma(w, w.d, w.f1);
+    // (fp32: far enough inside one dimension of the grid)
+    return w.elt == 2 ? rows_backward_supported(w)
+                      : gemm_f32_on_mfma(w, w.d, w.f1) &&
+                            w.E * ceil_div(w.d, 64) * ceil_div(w.f1, 64) * 256 <= kMaxGridThreads / 2;
 }
 int64_t router_wgrad_splits(const Workspace &w) {
     if (!w.router_bwd_block || w.fused || w.C == 0) return 0;
