@@ -191,6 +191,13 @@ def test_static_scratch_variant_keeps_what_fits():
     assert fitted > 10000
 
 
+def test_static_scratch_variant_takes_no_more_than_it_did():
+    """Smaller buffers of the router's backward pass do not change which layers fit."""
+    big = sw.SwitchConfig(262, 2584, 10248, 6, 2.0, 0.01, sw.SW_BF16)
+    assert sw.switch_workspace_size(big) > sw.SW_STATIC_SCRATCH_BYTES
+    assert sw.switch_forward_static(big, *([None] * 13), check=False) == -9
+
+
 def test_status_strings():
     assert sw.switch_status_string(0) == "ok"
     seen = {sw.switch_status_string(s) for s in range(-9, 1)}
