@@ -36,7 +36,8 @@ struct RouterBwdArgs {
     int T, Tg, d, E, groups_per_block;
     float aux_scale;
     Noise nz;
-    int token_blocks;  // blocks behind them add up the parts of dW_r and db_r
+    int token_blocks;  // of 128 tokens, each once per range of columns, one range after the other;
+    int dx_blocks;     // blocks behind these add up the parts of dW_r and db_r
     const float *dWr_part;
     float *dW_r;
     int nsplit;
@@ -55,20 +56,18 @@ __global__ __launch_bounds__(256, EK > 8 ? 1 : 2) void router_dx_block_kernel(Ro
     typedef XT piece_t __attribute__((ext_vector_type(kCPL)));
     __shared__ __attribute__((aligned(16))) char wlds[NT * EK * 2048];
     __shared__ __attribute__((aligned(16))) float turn_all[4][32 * kPitch];
-    if ((int)blockIdx.x >= a.token_blocks) {
-        if (blockIdx.y == 0)
-            reduce_partials(a.dWr_part, a.dW_r, (size_t)a.d * a.E, a.nsplit, a.db, blockIdx.x - a.token_blocks);
-        return;
-    }
+    if ((int)blockIdx.x >= a.dx_blocks)
+        return reduce_partials(a.dWr_part, a.dW_r, (size_t)a.d * a.E, a.nsplit, a.db, blockIdx.x - a.dx_blocks);
+    const int range = (int)blockIdx.x / a.token_blocks, tb = (int)blockIdx.x - range * a.token_blocks;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int half = lane >> 5;
     float *turn = turn_all[wave];
-    const int t0 = (int)blockIdx.x * 128 + wave * 32;
+    const int t0 = tb * 128 + wave * 32;
     const int t = t0 + (lane & 31);
     const bool live = t < a.T;
     const int E = a.E;
-    const int g_first = (int)blockIdx.y * a.groups_per_block;
+    const int g_first = range * a.groups_per_block;
     const int g_last = min(g_first + a.groups_per_block, (a.d + COLS - 1) / COLS);
 
     // ---- the group's weights, one group ahead in registers ----
@@ -149,7 +148,7 @@ __global__ __launch_bounds__(256, EK > 8 ? 1 : 2) void router_dx_block_kernel(Ro
 #pragma unroll
             for (int r = 0; r < 8; ++r) dl[ks][r] *= dp[ks][r] - s;   // p is 0 past E and past T
     }
-    const bool writer = blockIdx.y == 0 && a.nsplit == 0;   // (with parts of dW_r nothing reads dl)
+    const bool writer = range == 0 && a.nsplit == 0;   // (with parts of dW_r nothing reads dl)
     if (writer && a.dbr_part) {   // column sums over the block's 128 tokens, 16 experts at a time
         __shared__ float dbs[4][EK * 16];
 #pragma unroll
@@ -166,7 +165,7 @@ __global__ __launch_bounds__(256, EK > 8 ? 1 : 2) void router_dx_block_kernel(Ro
         }
         __syncthreads();
         for (int e = threadIdx.x; e < E; e += 256)
-            a.dbr_part[(size_t)blockIdx.x * E + e] = (dbs[0][e] + dbs[1][e]) + (dbs[2][e] + dbs[3][e]);
+            a.dbr_part[(size_t)tb * E + e] = (dbs[0][e] + dbs[1][e]) + (dbs[2][e] + dbs[3][e]);
     }
     bf16x8 hi[EK], lo[EK];
     if (kSplit) {
@@ -298,14 +297,15 @@ __global__ __launch_bounds__(256, EK > 8 ? 1 : 2) void router_dx_block_kernel(Ro
 template <typename XT, int EK, bool WIDE>
 static void dx_block_launch(RouterBwdArgs a, hipStream_t s) {
     const int groups = (int)ceil_div(a.d, EK > 8 ? 32 : 64), token_blocks = (int)ceil_div(a.T, 128);
-    a.token_blocks = token_blocks;
-    const int64_t sums = a.nsplit ? ceil_div((int64_t)a.d * a.E, 256) + (a.db.out ? ceil_div(a.E, kDbrExperts) : 0) : 0;
     // two blocks per CU want 512 blocks
     const int splits = token_blocks >= 512 ? 1 : (int)ceil_div(512, token_blocks);
     a.groups_per_block = (int)ceil_div(groups, splits < groups ? splits : groups);
-    hipLaunchKernelGGL((router_dx_block_kernel<XT, EK, WIDE>),
-                       dim3((unsigned)(token_blocks + sums), (unsigned)ceil_div(groups, a.groups_per_block)), dim3(256), 0,
-                       s, a);
+    a.token_blocks = token_blocks;
+    // (One dimension: the sums' blocks once, not once per range of columns to return at once, two or three per CU at a time for
+    // their LDS.  us of a pass, so / here: 64 tokens x 4096, 128 experts 808 / 781, 300 x 8192, 256 fp32 3810 / 3368.)
+    a.dx_blocks = token_blocks * (int)ceil_div(groups, a.groups_per_block);
+    const int64_t sums = a.nsplit ? ceil_div((int64_t)a.d * a.E, 256) + (a.db.out ? ceil_div(a.E, kDbrExperts) : 0) : 0;
+    hipLaunchKernelGGL((router_dx_block_kernel<XT, EK, WIDE>), dim3((unsigned)(a.dx_blocks + sums)), dim3(256), 0, s, a);
 }
 
 template <typename XT, int EK> static void dx_block_wide(const RouterBwdArgs &a, hipStream_t s) {

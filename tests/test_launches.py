@@ -159,6 +159,20 @@ def test_router_weight_gradient_beside_the_experts(recorder, T, d, f, E, cf, kw,
     assert any("reduce" in k[0] for k in launches) == own
 
 
+# The sums over its parts: blocks of the launch that computes dx, each once (256 sums each, and db_r's), behind those of 128
+# tokens by a range of columns.
+@pytest.mark.parametrize("T,d,f,E,cf,kw,dx_blocks", [
+    (64, 4096, 256, 128, 4.0, dict(), 64), (300, 4096, 1024, 100, 4.0, dict(bias=True), 3 * 64),
+    (1000, 2048, 256, 256, 2.0, dict(dtype="f32", bias=True), 8 * 64), (256, 64, 256, 4, 1.25, dict(dtype="f32"), 2),
+    (60000, 128, 512, 16, 1.0, dict(bias=True), 469 * 2),
+])
+def test_sums_of_the_router_weight_gradient_are_launched_once(recorder, T, d, f, E, cf, kw, dx_blocks):
+    (status, _, _, launches), = recorder(call("backward", T, d, f, E, cf, **kw))
+    assert status == 0
+    (grid,) = [k[1] for k in launches if "router_dx" in k[0]]
+    assert grid == (dx_blocks + -(-d * E // 256) + (-(-E // 32) if kw.get("bias") else 0), 1, 1)
+
+
 # The combine: in the second GEMM's epilogue (small tiles, fp32), which saves a launch unless re-routing stages follow the
 # assignment of the slots; else a pass of its own.
 @pytest.mark.parametrize("T,d,f,E,cf,dtype,rounds,own", [
