@@ -48,9 +48,7 @@ int64_t capacity_of(const switch_config *cfg) {
     return (int64_t)floor((double)(cfg->T / n) / (double)cfg->E * cfg->capacity_factor);
 }
 
-// former: what decides which layers the static scratch takes (see layout_workspace): planes for every bf16 layer with
-// input jitter, and parts of the router's weight gradient with a column for each bf16 term.
-static Workspace layout(const switch_config *cfg, bool former) {
+Workspace layout_workspace(const switch_config *cfg) {
     Workspace w{};
     w.T = cfg->T; w.d = cfg->d_model; w.f = cfg->d_ff; w.E = cfg->E;
     w.geglu = cfg->ffn_kind == SW_FFN_GEGLU;
@@ -59,7 +57,7 @@ static Workspace layout(const switch_config *cfg, bool former) {
     w.Tg = w.T / w.n;
     w.Cg = capacity_of(cfg);
     w.C = w.n * w.Cg;
-    w.router_block = router_block_supported(cfg) && !(former && cfg->act_dtype == SW_BF16 && cfg->jitter_eps > 0.f);
+    w.router_block = router_block_supported(cfg);
     w.tb = w.router_block ? router_block_tokens(cfg) : kRouteTB;
     w.nbg = ceil_div(w.Tg, w.tb);
     w.nb = w.n * w.nbg;
@@ -155,11 +153,9 @@ static Workspace layout(const switch_config *cfg, bool former) {
     w.dbr_part = take_dead((size_t)ceil_div(w.T, 128) * E * 4);
     w.xj = take(jit_mfma ? T * (size_t)w.dpad_r * 2 : 0);
     w.no_slot = take(jit_mfma && !w.router_bwd_block ? T * 4 : 0);
-    w.tps_m = former ? ceil_div(ceil_div(w.T, 85), 64) * 64 : router_dwr_tokens(w);
-    if (w.tps_m < 64) w.tps_m = 64;   // empty batch
+    w.tps_m = router_dwr_tokens(w);
     w.nsplit_m = ceil_div(w.T, w.tps_m);
-    w.dWr_part_m = take_dead(former ? (size_t)w.etiles * w.nsplit_m * (jit_mfma ? 2 * (size_t)w.dpad : d) * 256 * 4
-                                    : mfma ? (size_t)w.etiles * w.nsplit_m * d * 128 * 4 : 0);
+    w.dWr_part_m = take_dead(mfma ? (size_t)w.etiles * w.nsplit_m * d * 128 * 4 : 0);
     size_t bits = 0;
     for (int &t : w.gemm_tile) t = ROWS_NONE;
     if (cfg->act_dtype == SW_BF16) {
@@ -199,26 +195,12 @@ static Workspace layout(const switch_config *cfg, bool former) {
         w.ntlb_base = take(nE);
     }
     // (a layer near the static scratch's limit does without)
-    w.rw_nsplit = former ? 0 : router_wgrad_splits(w);
+    w.rw_nsplit = router_wgrad_splits(w);
     const size_t rw_bytes = (size_t)w.rw_nsplit * (d + 1) * E * 4;
     if (off <= SW_STATIC_SCRATCH_BYTES && off + rw_bytes > SW_STATIC_SCRATCH_BYTES / 4 * 3) w.rw_nsplit = 0;
     w.rw_part = take(w.rw_nsplit ? rw_bytes : 0);
     w.total = off;
     return w;
-}
-
-// The static scratch takes the layers that it took when the router had the buffers of the former layout, no more and no
-// fewer: one that would not fit without them keeps them, and one that would fit only without them reports their size.
-Workspace layout_workspace(const switch_config *cfg) {
-    const Workspace w = layout(cfg, false);
-    if (w.total <= SW_STATIC_SCRATCH_BYTES || cfg->act_dtype != SW_BF16) return w;
-    const Workspace f = layout(cfg, true);
-    return f.total <= SW_STATIC_SCRATCH_BYTES ? f : w;
-}
-static size_t reported_bytes(const switch_config *cfg, const Workspace &w) {
-    if (w.total > SW_STATIC_SCRATCH_BYTES) return w.total;
-    const size_t f = layout(cfg, true).total;
-    return f > SW_STATIC_SCRATCH_BYTES ? f : w.total;
 }
 
 // ---- event-based kernel timing -------------------------------------------------
@@ -317,7 +299,7 @@ int switch_workspace_size(const switch_config *cfg, size_t *bytes_out) {
     if (!cfg || !bytes_out) return SW_ERR_NULL;
     int st = check_config(cfg);
     if (st != SW_OK) return st;
-    *bytes_out = reported_bytes(cfg, layout_workspace(cfg));
+    *bytes_out = layout_workspace(cfg).total;
     return SW_OK;
 }
 
@@ -422,7 +404,7 @@ int switch_forward_static(const switch_config *cfg, const void *x, const float *
     if (st != SW_OK) return st;
     // the size limit comes first: it depends on the configuration alone
     const Workspace w = layout_workspace(cfg);
-    if (reported_bytes(cfg, w) > (size_t)SW_STATIC_SCRATCH_BYTES) return SW_ERR_STATIC_LIMIT;
+    if (w.total > (size_t)SW_STATIC_SCRATCH_BYTES) return SW_ERR_STATIC_LIMIT;
     hipStream_t s = (hipStream_t)hip_stream;
     if (cfg->T == 0) {
         if (!expert_counts || !aux_loss) return SW_ERR_NULL;

@@ -191,11 +191,18 @@ def test_static_scratch_variant_keeps_what_fits():
     assert fitted > 10000
 
 
-def test_static_scratch_variant_takes_no_more_than_it_did():
-    """Smaller buffers of the router's backward pass do not change which layers fit."""
-    big = sw.SwitchConfig(262, 2584, 10248, 6, 2.0, 0.01, sw.SW_BF16)
-    assert sw.switch_workspace_size(big) > sw.SW_STATIC_SCRATCH_BYTES
-    assert sw.switch_forward_static(big, *([None] * 13), check=False) == -9
+@pytest.mark.parametrize("T,d,f,E,cf,dtype,jitter", [
+    (262, 2584, 10248, 6, 2.0, "bf16", 0.0), (1050, 512, 1856, 16, 2.0, "bf16", 0.0), (1050, 512, 2304, 16, 2.0, "bf16", 0.0),
+    (1024, 512, 2048, 16, 2.0, "bf16", 0.01), (700, 768, 3072, 16, 1.25, "bf16", 0.01), (1050, 512, 1024, 16, 2.0, "f32", 0.0),
+    (65536, 768, 3072, 128, 1.0, "bf16", 0.0), (256, 64, 256, 4, 1.25, "f32", 0.0)])
+def test_workspace_size_is_what_the_passes_ask_for(T, d, f, E, cf, dtype, jitter):
+    """Not a byte more: one less is refused, by both passes, and the static scratch takes a layer if and only if it fits."""
+    cfg = sw.SwitchConfig(T, d, f, E, cf, 0.01, sw.SW_BF16 if dtype == "bf16" else sw.SW_F32, 0, 1, 0.0, jitter)
+    need, ok = sw.switch_workspace_size(cfg), 0x1000   # (pointers are not followed: the checks come first)
+    assert sw.switch_forward(cfg, *([ok] * 13), ok, need - 1, check=False) == -5
+    assert sw.switch_backward(cfg, ok, 1.0, *([ok] * 10), ok, need - 1, check=False) == -5
+    fits = need <= sw.SW_STATIC_SCRATCH_BYTES
+    assert sw.switch_forward_static(cfg, None, *([ok] * 12), check=False) == (-1 if fits else -9)
 
 
 def test_status_strings():
