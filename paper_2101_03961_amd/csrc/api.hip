@@ -97,16 +97,6 @@ Workspace layout_workspace(const switch_config *cfg) {
     w.dA = take(w.geglu ? E * C * f * w.elt : 0);
     w.dH = take(E * C * f1 * w.elt);
     w.dXd = take(E * C * d * w.elt);
-    // What only the router's backward pass writes, after the last kernel that reads dH: in dH's
-    // memory while it fits.
-    size_t dead = 0;
-    const size_t dead_room = E * C * f1 * w.elt;
-    auto take_dead = [&](size_t bytes) {
-        if (dead + bytes > dead_room) return take(bytes);
-        const size_t o = w.dH + dead;
-        dead = align_up(dead + bytes, 256);
-        return o;
-    };
     w.dgate = take(T * 4);
     w.dpad = ceil_div(w.d, 32) * 32;
     // noise parameters first: the router's layout depends on the jitter
@@ -132,30 +122,8 @@ Workspace layout_workspace(const switch_config *cfg) {
     w.wsplit = take(w.router_block ? 0 : (size_t)w.etiles * 3 * 128 * w.dpad_r * 2);
     w.has_wsplit_b = mfma && !w.router_bwd_block;
     w.wsplit_b = take(w.has_wsplit_b ? (size_t)w.etiles * d * 256 * 2 : 0);
-    w.dl_split = take_dead(mfma ? (size_t)w.etiles * T * 256 * 2 : 0);
-    const size_t dlogits_bytes = w.router_bwd_block && mfma ? 0 : T * E * 4;
-    const bool dlogits_own = dead + dlogits_bytes > dead_room;   // ... in memory of its own
-    w.dlogits = take_dead(dlogits_bytes);
-    // The routing tables of the token blocks: nothing reads them once the forward pass has assigned the
-    // slots, so they share the memory of dlogits if that has its own.
-    const size_t table = align_up(nb * E * 4, 256);
-    w.block_counts = dlogits_own && 3 * table <= dlogits_bytes ? w.dlogits : take(3 * table);
-    w.block_psum = w.block_counts + table;
-    w.block_off = w.block_psum + table;
-    // Vector-ALU dW_r: a split of 64 tokens is two short chains of loads; the parts lie in the
-    // gradient of the expert outputs, which the second weight gradient has read by then.
-    w.nsplit = w.T < 64 * 64 ? ceil_div(w.T, 64) : 64;
-    w.dWr_part = w.dO;
-    if ((size_t)w.nsplit * 4 > C * w.elt) {
-        if (w.nsplit > w.nb_r) w.nsplit = w.nb_r;
-        w.dWr_part = take(mfma ? 0 : (size_t)w.nsplit * d * E * 4);
-    }
-    w.dbr_part = take_dead((size_t)ceil_div(w.T, 128) * E * 4);
     w.xj = take(jit_mfma ? T * (size_t)w.dpad_r * 2 : 0);
     w.no_slot = take(jit_mfma && !w.router_bwd_block ? T * 4 : 0);
-    w.tps_m = router_dwr_tokens(w);
-    w.nsplit_m = ceil_div(w.T, w.tps_m);
-    w.dWr_part_m = take_dead(mfma ? (size_t)w.etiles * w.nsplit_m * d * 128 * 4 : 0);
     size_t bits = 0;
     for (int &t : w.gemm_tile) t = ROWS_NONE;
     if (cfg->act_dtype == SW_BF16) {
@@ -194,11 +162,58 @@ Workspace layout_workspace(const switch_config *cfg) {
         w.ntlb_free = take(nE);
         w.ntlb_base = take(nE);
     }
-    // (a layer near the static scratch's limit does without)
+    // What only the router's backward pass writes, after the last kernel that reads dH: in dH's
+    // memory while it fits.
+    size_t dead = 0;
+    const size_t dead_room = E * C * f1 * w.elt;
+    auto take_dead = [&](size_t bytes) {
+        if (dead + bytes > dead_room) return take(bytes);
+        const size_t o = w.dH + dead;
+        dead = align_up(dead + bytes, 256);
+        return o;
+    };
+    const size_t table = align_up(nb * E * 4, 256);
+    // The parts of its weight gradient: in memory of their own if a launch of the experts' computes them.  Where that would
+    // take the layer out of the static scratch: in a launch behind those, in dH's memory, or with fewer parts, or not in
+    // parts.
+    const size_t part = (d + 1) * E * 4, room = off + 3 * table <= SW_STATIC_SCRATCH_BYTES
+                                                    ? SW_STATIC_SCRATCH_BYTES - off - 3 * table : SIZE_MAX;
+    w.rw_hosted = router_wgrad_hosted(w);
     w.rw_nsplit = router_wgrad_splits(w);
-    const size_t rw_bytes = (size_t)w.rw_nsplit * (d + 1) * E * 4;
-    if (off <= SW_STATIC_SCRATCH_BYTES && off + rw_bytes > SW_STATIC_SCRATCH_BYTES / 4 * 3) w.rw_nsplit = 0;
-    w.rw_part = take(w.rw_nsplit ? rw_bytes : 0);
+    if (w.rw_hosted && w.rw_nsplit * part > room) {
+        w.rw_hosted = false;
+        w.rw_nsplit = router_wgrad_splits(w);
+    }
+    if (!w.rw_hosted && w.rw_nsplit * part > dead_room && w.rw_nsplit * part > room) {
+        const int64_t most = (dead_room > room ? dead_room : room) / part;
+        w.rw_nsplit = 4 * most < w.rw_nsplit ? 0 : most;
+    }
+    if (w.rw_nsplit) {
+        w.block_counts = take(3 * table);
+        w.rw_part = w.rw_hosted ? take(w.rw_nsplit * part) : take_dead(w.rw_nsplit * part);
+    } else {
+        w.dl_split = take_dead(mfma ? (size_t)w.etiles * T * 256 * 2 : 0);
+        const size_t dlogits_bytes = w.router_bwd_block && mfma ? 0 : T * E * 4;
+        const bool dlogits_own = dead + dlogits_bytes > dead_room;   // ... in memory of its own
+        w.dlogits = take_dead(dlogits_bytes);
+        // The routing tables of the token blocks: nothing reads them once the forward pass has assigned the
+        // slots, so they share the memory of dlogits if that has its own.
+        w.block_counts = dlogits_own && 3 * table <= dlogits_bytes ? w.dlogits : take(3 * table);
+        // Vector-ALU dW_r: a split of 64 tokens is two short chains of loads; the parts lie in the
+        // gradient of the expert outputs, which the second weight gradient has read by then.
+        w.nsplit = w.T < 64 * 64 ? ceil_div(w.T, 64) : 64;
+        w.dWr_part = w.dO;
+        if ((size_t)w.nsplit * 4 > C * w.elt) {
+            if (w.nsplit > w.nb_r) w.nsplit = w.nb_r;
+            w.dWr_part = take(mfma ? 0 : (size_t)w.nsplit * d * E * 4);
+        }
+        w.dbr_part = take_dead((size_t)ceil_div(w.T, 128) * E * 4);
+        w.tps_m = router_dwr_tokens(w);
+        w.nsplit_m = ceil_div(w.T, w.tps_m);
+        w.dWr_part_m = take_dead(mfma ? (size_t)w.etiles * w.nsplit_m * d * 128 * 4 : 0);
+    }
+    w.block_psum = w.block_counts + table;
+    w.block_off = w.block_psum + table;
     w.total = off;
     return w;
 }
@@ -459,6 +474,7 @@ int switch_backward(const switch_config *cfg, const void *dy, float d_aux, const
 
     const TokenMajor tm{x, dy, nullptr};
     const RouterWgradArgs parts = router_wgrad_args(w, cfg->alpha, d_aux, x, ws, db_r != nullptr);
+    const RouterWgradArgs beside = w.rw_hosted ? parts : RouterWgradArgs{};
     // fused: only the gate gradient is left of the combine's backward pass (dy is read by the
     // GEMMs through the slot -> token table)
     if (w.fused)
@@ -471,10 +487,10 @@ int switch_backward(const switch_config *cfg, const void *dy, float d_aux, const
     // dH is consumed right after it is produced (the first-layer data gradient walks the
     // experts backwards, see launch_gemm_bf16), then the two weight gradients
     if (dt == SW_BF16 && rows_backward_supported(w)) {
-        if ((st = status_of(launch_rows_backward(w, ws, W_in, W_out, dW_in, dW_out, parts, s)))) return st;
+        if ((st = status_of(launch_rows_backward(w, ws, W_in, W_out, dW_in, dW_out, beside, s)))) return st;
     } else {
         if ((st = status_of(gemm(GEMM_DGRAD1, w, ws, W_in, W_out, dW_in, dW_out, tm, s)))) return st;
-        st = status_of(parts.blocks && !parts.own_launch ? launch_gemm_f32_wgrad1(w, ws, dW_in, parts, s)
+        st = status_of(beside.blocks ? launch_gemm_f32_wgrad1(w, ws, dW_in, beside, s)
                                     : gemm(GEMM_WGRAD1, w, ws, W_in, W_out, dW_in, dW_out, tm, s));
         if (st) return st;
         if ((st = status_of(gemm(GEMM_WGRAD2, w, ws, W_in, W_out, dW_in, dW_out, tm, s)))) return st;

@@ -176,7 +176,8 @@ struct Workspace {
     size_t relu_bits;           // u8  one bit per element of A, A > 0, in the order the epilogue of the
                                 //     first forward GEMM (and of the masked gradient) visits its tiles
     int64_t nsplit;
-    int64_t rw_nsplit;          // parts of the router's weight gradient beside the experts' (router_wgrad.h), 0: none
+    bool rw_hosted;             // a launch of the experts' weight gradients computes the router's too (router_wgrad.h)
+    int64_t rw_nsplit;          // parts of the router's weight gradient there or in a launch of their own, 0: none
     size_t rw_part;             // f32 [rw_nsplit][d + 1][E]
     // No-Token-Left-Behind (only laid out when ntlb_rounds > 0)
     int ntlb_rounds;
@@ -270,6 +271,7 @@ hipError_t launch_router_bwd(const Workspace &w, int dtype, float alpha, float d
                              const void *x, const float *W_r, char *ws, void *dx, float *dW_r,
                              float *db_r, const RouterWgradArgs &parts, hipStream_t s);
 // The router's weight gradient from fp32 operands in parts (router_wgrad.h), or no blocks where it takes another form.
+bool router_wgrad_hosted(const Workspace &w);
 int64_t router_wgrad_splits(const Workspace &w);
 RouterWgradArgs router_wgrad_args(const Workspace &w, float alpha, float d_aux, const void *x, char *ws, bool bias);
 // dlogits and dx in one kernel (router_bwd.hip); bias: also the per-block sums for db_r; parts: instead of both, the

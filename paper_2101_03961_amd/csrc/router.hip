@@ -754,7 +754,7 @@ static float aux_scale_of(const Workspace &w, float alpha, float d_aux) {
 // here: 768 x 1536, 128 experts, 512 tokens 462 / 453, 2048 475 / 469, 4096 516 / 505, 8192 555 / 570; since then they take
 // 10 less from 4096 on).  At
 // most 64 parts of at least 32 tokens and 16 MB in all: more would be read for longer than they are summed.
-static bool router_wgrad_hosted(const Workspace &w) {
+bool router_wgrad_hosted(const Workspace &w) {
     // (fp32: far enough inside one dimension of the grid)
     return w.elt == 2 ? rows_backward_supported(w)
                       : gemm_f32_on_mfma(w, w.d, w.f1) &&
@@ -762,7 +762,7 @@ static bool router_wgrad_hosted(const Workspace &w) {
 }
 int64_t router_wgrad_splits(const Workspace &w) {
     if (!w.router_bwd_block || w.fused || w.C == 0) return 0;
-    if (router_bwd_mfma_supported(w, w.elt == 2 ? SW_BF16 : SW_F32) && !router_wgrad_hosted(w) &&
+    if (router_bwd_mfma_supported(w, w.elt == 2 ? SW_BF16 : SW_F32) && !w.rw_hosted &&
         (double)w.T * (double)w.d * (double)w.E > 2.5e8)
         return 0;
     const int64_t most = ((int64_t)16 << 20) / (4 * (w.d + 1) * w.E);   // 16 MB of parts
@@ -788,7 +788,6 @@ RouterWgradArgs router_wgrad_args(const Workspace &w, float alpha, float d_aux, 
     const int experts = router_wgrad_experts(w.E);
     a.tiles_k = (int)ceil_div(w.d, kRwElements / experts);
     a.blocks = (int)(a.tiles_k * ceil_div(w.E, experts) * a.nsplit);
-    a.own_launch = !router_wgrad_hosted(w);
     a.aux_scale = aux_scale_of(w, alpha, d_aux);
     a.nz = w.noise;
     return a;
@@ -808,7 +807,7 @@ static hipError_t router_bwd_typed(const Workspace &w, float alpha, float d_aux,
     // the fp32 copy is read only by the vector-ALU contractions and by the bias gradient
     float *dlogits_out = (mfma && !db_r) ? nullptr : dlogits;
     const float aux_scale = aux_scale_of(w, alpha, d_aux);
-    if (parts.own_launch) {
+    if (parts.blocks && !w.rw_hosted) {
         ProfScope ps("router_dWr", s);
         hipLaunchKernelGGL(router_wgrad_kernel<XT>, dim3((unsigned)parts.blocks), dim3(256), 0, s, parts);
         if ((err = hipGetLastError()) != hipSuccess) return err;

@@ -51,7 +51,6 @@ __device__ __forceinline__ void reduce_partials(const float *part, float *out, s
 
 struct RouterWgradArgs {
     int blocks;              // 0: none
-    int own_launch;          // no launch of the experts' takes them
     const void *x;
     const float *probs, *dgate, *rowsum;
     const int32_t *idx, *counts_g;

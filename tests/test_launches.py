@@ -144,19 +144,25 @@ def test_small_layers_take_three_products_in_one_launch(recorder, T, d, f, E, cf
     assert sum("gemm_rows" in k[0] or "gemm_wgrad" in k[0] for k in launches) == (2 if data else 4)
 
 
-# The router's weight gradient: its parts beside the experts' where those are small, or fp32, unless the parts would bring
-# the workspace near the static scratch's limit; a launch less for the parts and one less for their sums.
-@pytest.mark.parametrize("T,d,f,E,cf,kw,own", [
-    (5003, 392, 1000, 10, 1.25, dict(bias=True), False), (256, 64, 256, 4, 1.25, dict(dtype="f32"), False),
-    (8192, 768, 3072, 32, 1.25, dict(dtype="f32", bias=True), False), (1050, 512, 2048, 16, 2.0, dict(), True),   # 25 MB
-    (8192, 768, 3072, 128, 1.25, dict(), True), (500, 64, 256, 300, 4.0, dict(dtype="f32"), True),
-    (5003, 392, 1000, 10, 1.25, dict(fused=True), True),
+# The router's weight gradient: its parts beside the experts' where those are small, or fp32 ("beside"), which saves a launch
+# for the parts and one for their sums; in a launch of their own ("parts"); on the matrix cores, or the vector ALUs.  Whether a
+# layer fits the static scratch, whose calls have no backward pass, only moves the parts (1050 x 512 x 2600).
+@pytest.mark.parametrize("T,d,f,E,cf,kw,form", [
+    (5003, 392, 1000, 10, 1.25, dict(bias=True), "beside"), (256, 64, 256, 4, 1.25, dict(dtype="f32"), "beside"),
+    (8192, 768, 3072, 32, 1.25, dict(dtype="f32", bias=True), "beside"), (1050, 512, 2048, 16, 2.0, dict(), "beside"),
+    (1050, 512, 2048, 16, 2.0, dict(jitter=0.01), "beside"), (1050, 512, 2600, 16, 2.0, dict(), "parts"),
+    (1050, 512, 2600, 16, 2.0, dict(jitter=0.01), "parts"), (1050, 512, 2720, 16, 2.0, dict(), "parts"),
+    (512, 768, 3072, 128, 1.25, dict(), "parts"),
+    (8192, 768, 3072, 128, 1.25, dict(), "mfma"), (500, 64, 256, 300, 4.0, dict(dtype="f32"), "vector"),
+    (5003, 392, 1000, 10, 1.25, dict(fused=True), "vector"),
 ])
-def test_router_weight_gradient_beside_the_experts(recorder, T, d, f, E, cf, kw, own):
+def test_router_weight_gradient_beside_the_experts(recorder, T, d, f, E, cf, kw, form):
     (status, base, size, launches), = recorder(call("backward", T, d, f, E, cf, **kw))
     assert status == 0
-    assert any("dWr" in k[0] for k in launches) == own
-    assert any("reduce" in k[0] for k in launches) == own
+    kernels = {"parts": "router_wgrad_kernel", "mfma": "router_dWr_mfma_kernel", "vector": "router_dWr_kernel"}
+    got = [k for k, name in kernels.items() if any(name in launch[0] for launch in launches)]
+    assert got == ([] if form == "beside" else [form])
+    assert any("reduce" in k[0] for k in launches) == (form in ("mfma", "vector"))
 
 
 # The sums over its parts: blocks of the launch that computes dx, each once (256 sums each, and db_r's), behind those of 128
