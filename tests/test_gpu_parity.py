@@ -184,10 +184,10 @@ def router_gradient_error(SwitchLayer, T, d, E, dtype="f32", **kw):
 
 def test_router_weight_gradient_sums_in_short_chains():
     """Few parts of many tokens (their memory is limited).  With terms of random sign a chain of n fp32 sums is off by
-    2^-24 sqrt(n / 6) of its result: 2.8e-7 for 128 tokens, 2.2e-7 for the sum of the 78 chains of a part; one chain of
-    10016 would be off by 2.4e-6."""
+    2^-24 sqrt(n / 6) of its result: 2.8e-7 for 128 tokens, 1.0e-7 for the sum of the 16 chains of a part; one chain of
+    2016 would be off by 1.1e-6."""
     from paper_2101_03961_amd.layer import SwitchLayer
-    error = router_gradient_error(SwitchLayer, 30000, 4096, 256)
+    error = router_gradient_error(SwitchLayer, 30000, 8192, 32)
     _report("router weight gradient in chains", {"dW_r": error})
     assert error <= 4e-7
 

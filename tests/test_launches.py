@@ -155,6 +155,11 @@ def test_small_layers_take_three_products_in_one_launch(recorder, T, d, f, E, cf
     (512, 768, 3072, 128, 1.25, dict(), "parts"),
     (8192, 768, 3072, 128, 1.25, dict(), "mfma"), (500, 64, 256, 300, 4.0, dict(dtype="f32"), "vector"),
     (5003, 392, 1000, 10, 1.25, dict(fused=True), "vector"),
+    # memory for few parts: of many experts, from 1e9 products on
+    (6050, 5000, 64, 33, 1.25, dict(), "parts"), (6072, 5000, 64, 33, 1.25, dict(), "vector"),
+    (2850, 5000, 64, 70, 1.25, dict(dtype="f32"), "beside"), (2870, 5000, 64, 70, 1.25, dict(dtype="f32"), "vector"),
+    (6072, 5000, 64, 64, 1.25, dict(dtype="f32"), "beside"), (12000, 5000, 64, 30, 1.25, dict(), "parts"),
+    (20000, 768, 64, 140, 1.25, dict(dtype="f32"), "vector"), (20000, 768, 64, 133, 1.25, dict(), "parts"),
 ])
 def test_router_weight_gradient_beside_the_experts(recorder, T, d, f, E, cf, kw, form):
     (status, base, size, launches), = recorder(call("backward", T, d, f, E, cf, **kw))
