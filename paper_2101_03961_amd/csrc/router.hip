@@ -753,7 +753,9 @@ static float aux_scale_of(const Workspace &w, float alpha, float d_aux) {
 // operands, and up to 2.5e8 products, where the matrix cores' two kernels are slower (us of a pass, a slower form of those /
 // here: 768 x 1536, 128 experts, 512 tokens 462 / 453, 2048 475 / 469, 4096 516 / 505, 8192 555 / 570; since then they take
 // 10 less from 4096 on).  At
-// most 64 parts of at least 32 tokens and 16 MB in all: more would be read for longer than they are summed.  Where 16 MB
+// most 64 parts of at least 32 tokens, or 256 of at least 256, and 16 MB in all: more would be read for longer than they
+// are summed, and fewer are too few blocks (us of a pass with d_ff 512, 64 parts / here: 65536 x 384, 16 experts with jitter
+// 634 / 523; 40000 x 128, 62 experts 220 / 192; 200000 x 128, 62 experts 1032 / 818, fp32, 8 experts 2148 / 2001).  Where 16 MB
 // leaves fewer than 40 to a large layer of many experts, the vector-ALU kernel: its 64 parts are blocks for the whole
 // chip, the others are few long ones (us of a pass, that / parts: fp32 65536 x 2048, 256 experts 7050 / 7700, 60000 x 1024,
 // 256 2220 / 2380, 8192 x 768, 256 609 / 625, 4096 x 4096, 64 995 / 973; bf16 65536 x 2048, 62 experts 1704 / 1843, 20000 x
@@ -771,7 +773,8 @@ int64_t router_wgrad_splits(const Workspace &w) {
         return 0;
     const int64_t most = ((int64_t)16 << 20) / (4 * (w.d + 1) * w.E);   // 16 MB of parts
     int64_t n = ceil_div(w.T, kRwTokens);
-    if (n > 64) n = 64;
+    const int64_t enough = w.T >= 65536 ? 256 : w.T > 64 * 256 ? w.T / 256 : 64;
+    if (n > enough) n = enough;
     if (n > most) n = most;
     return w.E > (w.rw_hosted ? 64 : 32) && n < 40 && (double)w.T * (double)w.d * (double)w.E > 1e9 ? 0 : n;
 }

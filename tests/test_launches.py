@@ -170,6 +170,17 @@ def test_router_weight_gradient_beside_the_experts(recorder, T, d, f, E, cf, kw,
     assert any("reduce" in k[0] for k in launches) == (form in ("mfma", "vector"))
 
 
+# How many parts it comes in, in tiles of 4096 elements: one per 32 tokens up to 64, one per 256 up to 256, up to 16 MB; each a
+# multiple of 32 tokens.
+@pytest.mark.parametrize("T,d,E,parts", [(1, 512, 30, 1), (33, 512, 30, 2), (2048, 512, 30, 64), (16640, 512, 30, 65),
+                                         (40000, 512, 30, 139), (65536, 512, 30, 256), (200000, 512, 30, 250), (40000, 4096, 30, 34)])
+def test_parts_of_the_router_weight_gradient(recorder, T, d, E, parts):
+    (status, _, _, launches), = recorder(call("backward", T, d, 8192, E, max(1.25, 4 * E / T)))
+    assert status == 0
+    (grid,) = [k[1] for k in launches if "router_wgrad_kernel" in k[0]]
+    assert grid == (-(-d // 128) * parts, 1, 1)
+
+
 # The sums over its parts: blocks of the launch that computes dx, each once (256 sums each, and db_r's), behind those of 128
 # tokens by a range of columns.
 @pytest.mark.parametrize("T,d,f,E,cf,kw,dx_blocks", [
