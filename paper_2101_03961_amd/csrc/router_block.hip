@@ -318,21 +318,32 @@ __global__ __launch_bounds__(64 * (RouterBlock<XT, ET, WT, TT, F32P>::NW), 2) vo
 
 // Up to 256 experts whose weights and tokens fit a buffer descriptor each.  Input jitter on bf16 tokens, for large layers
 // with a multiple of 4 experts: planes of x * m (router_mfma.hip), whose products are cheaper, but which take three launches
-// and long chains of few blocks.  (us of the forward router / of a pass, planes or vector ALUs -> here: 512 tokens of 768, 128
-// experts 109 -> 65 / 528 -> 500, 8192 116 -> 66; 32768 of 1024, 8 experts 208 -> 74 / 1232 -> 1051; 32 of 2400, 10 experts
-// 799 -> 98 / 1223 -> 518; 65536 of 768, 128 experts 217 -> 275, which keeps its planes.)
+// and long chains of few blocks.  us of a pass (d_ff 256 unless said), planes or vector ALUs / here:
+//   experts without 4 as a divisor: 32 x 2400, 10 experts 1223 / 518
+//   up to 64: 8192 x 2048, 32 experts 510 / 353, 32768 x 1024 x 2048, 32 experts 1156 / 1067, 65536 x 768 x 512, 64 experts 846 / 818
+//   up to 128, up to 16384 tokens (a block per CU) and 1e9 products: 512 x 768 x 1024, 128 experts 528 / 500, 10000 x 768 x 3072,
+//     128 experts 984 / 968; 16384 x 768 x 3072, 128 experts 1099 / 1104, 17000 x 128, 128 experts 154 / 171, 65536 x 768 x 3072,
+//     128 experts 2426 / 2753
+//   up to 256, short rows and few products: 4000 x 256, 256 experts 186 / 162; 2048 x 768, 256 experts 336 / 343, 8000 x 256, 256
+//     experts 198 / 208, 64 x 2048, 256 experts 475 / 497 (a block reads and splits all of W_r, however few its tokens)
 // Tokens per block: 128 halves what the weights cost (traffic and splits) once there are blocks
 // for two per CU.
 int router_block_tokens(const switch_config *cfg) {
     return cfg->act_dtype == SW_BF16 && cfg->jitter_eps == 0.f && cfg->E <= 128 && cfg->T >= 32768 ? 128 : 64;
 }
 
+static bool jitter_takes_planes(const switch_config *cfg) {
+    const double products = (double)cfg->T * (double)cfg->d_model * (double)cfg->E;
+    if (cfg->act_dtype != SW_BF16 || !(cfg->jitter_eps > 0.f) || cfg->E % 4 != 0) return false;
+    if (cfg->E <= 64) return false;
+    if (cfg->E <= 128) return products > 1e9 || cfg->T > 16384;
+    return products > 3e8 || cfg->d_model > 1024;
+}
+
 bool router_block_supported(const switch_config *cfg) {
     const double elt = cfg->act_dtype == SW_BF16 ? 2. : 4.;
     return cfg->E <= 256 && (double)cfg->d_model * (double)cfg->E * 4. < 2147483647. &&
-           (double)cfg->T * (double)cfg->d_model * elt < 2147483647. &&
-           !(cfg->act_dtype == SW_BF16 && cfg->jitter_eps > 0.f && cfg->E % 4 == 0 &&
-             (double)cfg->T * (double)cfg->d_model * (double)cfg->E > 8e8);
+           (double)cfg->T * (double)cfg->d_model * elt < 2147483647. && !jitter_takes_planes(cfg);
 }
 
 template <typename XT, int ET, int WT, int TT, bool WIDE, bool F32P>

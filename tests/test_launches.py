@@ -49,7 +49,7 @@ def call(what, T, d, f, E, cf, dtype="bf16", ffn="relu", n=1, dropout=0.0, jitte
     (dict(T=524288, d=512, f=1536, E=1024, cf=1.0, ffn="geglu"), False),
     (dict(T=1 << 22, d=64, f=64, E=128, cf=1.0, jitter=0.01), False),
     (dict(T=8192, d=768, f=3072, E=2048, cf=1.0, ffn="geglu"), True),
-    (dict(T=8192, d=768, f=3072, E=128, cf=1.0, jitter=0.01), False),      # the one-kernel backward reads W_r
+    (dict(T=32768, d=768, f=3072, E=128, cf=1.0, jitter=0.01), False),     # the one-kernel backward reads W_r
 ])
 def test_split_router_weights_stay_in_the_workspace(recorder, kw, backward_reads):
     (status, base, size, launches), = recorder(call("forward", **kw))
@@ -142,6 +142,19 @@ def test_small_layers_take_three_products_in_one_launch(recorder, T, d, f, E, cf
     assert [(",".join(g[:5]), ",".join(g[5:])) for g in got] == ([(data, weights)] if data else [])
     # the masked gradient, and the three others once
     assert sum("gemm_rows" in k[0] or "gemm_wgrad" in k[0] for k in launches) == (2 if data else 4)
+
+
+# Input jitter on bf16 tokens: in the one-kernel router, or planes of x * m for large layers of many experts.
+@pytest.mark.parametrize("T,d,E,planes", [
+    (16384, 128, 128, False), (16385, 128, 128, True), (10000, 768, 128, False), (10200, 768, 128, True), (65536, 768, 64, False),
+    (65536, 768, 68, True), (65536, 768, 127, False), (2280, 512, 256, False), (2300, 512, 256, True), (64, 1024, 132, False),
+    (64, 1032, 132, True), (64, 1032, 128, False), (512, 64, 260, True)])
+@pytest.mark.parametrize("fused", [False, True])
+def test_route_of_input_jitter(recorder, T, d, E, planes, fused):
+    (status, _, _, launches), = recorder(call("forward", T, d, 512, E, 4.0, jitter=0.01, fused=fused))
+    assert status == 0
+    assert any("jitter_split" in k[0] for k in launches) == planes
+    assert any("router_block_kernel" in k[0] for k in launches) != planes
 
 
 # The router's weight gradient: its parts beside the experts' where those are small, or fp32 ("beside"), which saves a launch
