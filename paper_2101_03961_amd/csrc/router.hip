@@ -200,6 +200,7 @@ __global__ __launch_bounds__(WAVES * kWave) void router_softmax_kernel(
                 pacc[j] += p;   // padded experts add 0
             }
             if (lane == 0) {
+                if (besti[u] >= E) besti[u] = 0;   // (no logit above -inf, not even one that is no NaN: the lowest index)
                 idx_s[tl] = besti[u];
                 idx_out[t] = besti[u];
                 idx_ws[t] = besti[u];

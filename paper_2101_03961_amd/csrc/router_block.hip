@@ -275,6 +275,7 @@ __global__ __launch_bounds__(64 * (RouterBlock<XT, ET, WT, TT, F32P>::NW), 2) vo
         if (t < tend) put(probs + (size_t)t * E, e, p);
     }
     if (l == 0) {
+        if (besti >= E) besti = 0;   // (no logit above -inf, not even one that is no NaN: the lowest index)
         idx_s[row] = t < tend ? besti : -1;
         if (t < tend) {
             idx_out[t] = besti;

@@ -271,6 +271,7 @@ __global__ __launch_bounds__(256) void router_fwd_mfma_kernel(
                                 acc[tt][et][4 * g + 2] * rz, acc[tt][et][4 * g + 3] * rz);
             }
         if (lane < 32) {
+            if (besti >= E) besti = 0;   // (no logit above -inf, not even one that is no NaN: the lowest index)
             if (t < tend) {
                 const float gt = rz;
                 idx_s[tl] = besti;

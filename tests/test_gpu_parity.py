@@ -957,3 +957,25 @@ def test_router_gradients_keep_fp32_operands(dtype, E):
     err = float((grads["dx"].cpu().double() - want).norm() / want.norm())
     # one rounding to the tokens' type: at most half a unit, 2^-9 of the value in bf16
     assert err < (2.0 ** -9 if dtype == "bf16" else 2.0 ** -20)
+
+
+@pytest.mark.parametrize("dtype,T,d,E,jitter", [("f32", 70, 72, 8, 0.0), ("bf16", 70, 72, 8, 0.0), ("bf16", 70, 72, 300, 0.0),
+                                                ("bf16", 70, 1032, 132, 0.1), ("bf16", 16400, 64, 128, 0.1)])
+def test_token_without_a_largest_logit(dtype, T, d, E, jitter):
+    """Not a number in a token: it goes to expert 0, like equal logits, and no other token's results change."""
+    from paper_2101_03961_amd.layer import SwitchLayer
+    gen = torch.Generator(device=_dev()).manual_seed(89)
+    act = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rand = lambda *size: torch.randn(size, generator=gen, device=_dev())
+    x, dy, W_r = rand(T, d).to(act), rand(T, d).to(act), rand(d, E)
+    W_in, W_out = (rand(E, d, 16) * 0.1).to(act), (rand(E, 16, d) * 0.1).to(act)
+    others = torch.arange(T, device=_dev()) != 37
+    outs = []
+    for value in (0.0, float("nan")):
+        x[37] = value
+        layer = SwitchLayer(T, d, 16, E, 4.0, 0.01, dtype, _dev(), jitter_eps=jitter, seed=5)
+        fwd = {k: v.clone() for k, v in layer.forward(x, W_r, W_in, W_out).items() if v is not None}
+        dx = layer.backward(dy, x, W_r, W_in, W_out)["dx"].clone()
+        assert fwd["expert_index"][37] == 0
+        outs.append([fwd["expert_index"], fwd["expert_counts"], fwd["y"][others], dx[others]])
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
