@@ -478,7 +478,7 @@ int switch_backward(const switch_config *cfg, const void *dy, float d_aux, const
     // fused: only the gate gradient is left of the combine's backward pass (dy is read by the
     // GEMMs through the slot -> token table)
     if (w.fused)
-        st = status_of(launch_gate_grad(w, dy, ws, s));
+        st = status_of(launch_gate_grad(w, dy, ws, parts, s));
     else
         st = status_of(launch_combine_bwd(w, dt, dy, ws, parts, s));
     if (st) return st;

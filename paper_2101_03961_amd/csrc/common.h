@@ -354,6 +354,6 @@ inline bool zero_rows_with_positions(const Workspace &w) {
 }
 // +0 rows of y for the tokens without a slot; fused path: gate gradient from the saved outputs
 hipError_t launch_zero_dropped(const Workspace &w, char *ws, void *y, hipStream_t s);
-hipError_t launch_gate_grad(const Workspace &w, const void *dy, char *ws, hipStream_t s);
+hipError_t launch_gate_grad(const Workspace &w, const void *dy, char *ws, const RouterWgradArgs &parts, hipStream_t s);
 
 }  // namespace sw

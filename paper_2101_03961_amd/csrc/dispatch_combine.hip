@@ -309,6 +309,21 @@ __global__ __launch_bounds__(256) void combine_kernel(const Chunk16 *__restrict_
 // Combine backward: for kept tokens dO[slot_t][:] = gate[t] * dy[t][:] and
 // dgate[t] = <dy[t], O[slot_t]>; dropped tokens get dgate = 0.  One wave per token.
 // -----------------------------------------------------------------------------
+// The lane's share (up to 256 experts) of the token's s = sum_i p[i] dp[i] for router_wgrad_block, without the gate's gradient,
+// which enters times p_me.
+__device__ __forceinline__ float lane_row_sum(const RouterWgradArgs &r, uint32_t t, int lane, float &p_me) {
+    const float mean_count = (float)r.Tg / (float)r.E;
+    const int32_t *counts = r.counts_g + (size_t)((int)t / r.Tg) * r.E;
+    float s = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int e = lane + j * kWave;
+        if (e < r.E) s += r.probs[(size_t)t * r.E + e] * (r.aux_scale * ((float)counts[e] - mean_count));
+    }
+    p_me = r.probs[(size_t)t * r.E + r.idx[t]];
+    return s;
+}
+
 template <typename XT, bool SUM>
 __global__ __launch_bounds__(256) void combine_bwd_kernel(
     const Chunk16 *__restrict__ dy, const Chunk16 *__restrict__ O, Chunk16 *__restrict__ dO,
@@ -317,18 +332,8 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(
     const int lane = threadIdx.x % kWave;
     const uint32_t t = wave_token();
     if (t >= (uint32_t)T) return;
-    // SUM (up to 256 experts): the token's s = sum_i p[i] dp[i], without the gate's gradient at first
     float s = 0.f, p_me = 0.f;
-    if (SUM) {
-        const float mean_count = (float)r.Tg / (float)r.E;
-        const int32_t *counts = r.counts_g + (size_t)((int)t / r.Tg) * r.E;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int e = lane + j * kWave;
-            if (e < r.E) s += r.probs[(size_t)t * r.E + e] * (r.aux_scale * ((float)counts[e] - mean_count));
-        }
-        p_me = r.probs[(size_t)t * r.E + r.idx[t]];
-    }
+    if (SUM) s = lane_row_sum(r, t, lane, p_me);
     const int slot_or_none = tok_slot[t];
     float dot = 0.f;
     if (slot_or_none >= 0) {
@@ -381,34 +386,42 @@ __global__ __launch_bounds__(256) void zero_dropped_kernel(Chunk16 *__restrict__
     for (int col = lane; col < cpr; col += kWave) y[(size_t)t * cpr + col] = zero;
 }
 
-template <typename XT>
+template <typename XT, bool SUM>
 __global__ __launch_bounds__(256) void gate_grad_kernel(const Chunk16 *__restrict__ dy,
                                                         const Chunk16 *__restrict__ Y,
                                                         const int32_t *__restrict__ tok_slot,
                                                         const float *__restrict__ gate,
-                                                        float *__restrict__ dgate, int T, int cpr) {
+                                                        float *__restrict__ dgate, int T, int cpr,
+                                                        RouterWgradArgs r, float *__restrict__ rowsum) {
     const int lane = threadIdx.x % kWave;
     const uint32_t t = wave_token();
     if (t >= (uint32_t)T) return;
+    float s = 0.f, p_me = 0.f;
+    if (SUM) s = lane_row_sum(r, t, lane, p_me);
     const int slot_or_none = tok_slot[t];
-    if (slot_or_none < 0) {
+    float dot = 0.f;
+    if (slot_or_none >= 0) {
+        const size_t slot = (size_t)slot_or_none;
+        for (int col = lane; col < cpr; col += kWave) {
+            float av[Vec<XT>::N], bv[Vec<XT>::N];
+            unpack<XT>(dy[(size_t)t * cpr + col], av);
+            unpack<XT>(Y[slot * cpr + col], bv);
+#pragma unroll
+            for (int i = 0; i < Vec<XT>::N; ++i) dot = fmaf(av[i], bv[i], dot);
+        }
+    } else if (!SUM) {
         if (lane == 0) dgate[t] = 0.f;
         return;
     }
-    const size_t slot = (size_t)slot_or_none;
-    float dot = 0.f;
-    for (int col = lane; col < cpr; col += kWave) {
-        float av[Vec<XT>::N], bv[Vec<XT>::N];
-        unpack<XT>(dy[(size_t)t * cpr + col], av);
-        unpack<XT>(Y[slot * cpr + col], bv);
 #pragma unroll
-        for (int i = 0; i < Vec<XT>::N; ++i) dot = fmaf(av[i], bv[i], dot);
+    for (int m = 32; m >= 1; m >>= 1) {
+        dot += __shfl_xor(dot, m, kWave);
+        if (SUM) s += __shfl_xor(s, m, kWave);
     }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) dot += __shfl_xor(dot, m, kWave);
     if (lane == 0) {
-        const float g = gate[t];
-        dgate[t] = g > 0.f ? dot / g : 0.f;
+        const float g = gate[t], dg = slot_or_none >= 0 && g > 0.f ? dot / g : 0.f;
+        dgate[t] = dg;
+        if (SUM) rowsum[t] = fmaf(p_me, dg, s);
     }
 }
 
@@ -423,12 +436,12 @@ hipError_t launch_zero_dropped(const Workspace &w, char *ws, void *y, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_gate_grad(const Workspace &w, const void *dy, char *ws, hipStream_t s) {
+hipError_t launch_gate_grad(const Workspace &w, const void *dy, char *ws, const RouterWgradArgs &parts, hipStream_t s) {
     ProfScope ps("gate_grad", s);
-    hipLaunchKernelGGL(gate_grad_kernel<bf16>, row_grid(w.T), dim3(256),
+    hipLaunchKernelGGL((parts.blocks ? gate_grad_kernel<bf16, true> : gate_grad_kernel<bf16, false>), row_grid(w.T), dim3(256),
                        0, s, (const Chunk16 *)dy, (const Chunk16 *)(ws + w.O),
                        (const int32_t *)(ws + w.tok_slot), (const float *)(ws + w.gate),
-                       (float *)(ws + w.dgate), (int)w.T, (int)(w.d / 8));
+                       (float *)(ws + w.dgate), (int)w.T, (int)(w.d / 8), parts, (float *)(ws + w.local_rank));
     return hipGetLastError();
 }
 

@@ -768,7 +768,9 @@ bool router_wgrad_hosted(const Workspace &w) {
                             w.E * ceil_div(w.d, 64) * ceil_div(w.f1, 64) * 256 <= kMaxGridThreads / 2;
 }
 int64_t router_wgrad_splits(const Workspace &w) {
-    if (!w.router_bwd_block || w.fused || w.C == 0) return 0;
+    // (dispatch inside the GEMMs: where the fp32 operands of input jitter rule out the matrix cores.  us of dW_r on the vector
+    // ALUs / in parts, with the sums of each: 512 x 768, 128 experts 40 / 12, 30000 x 1024, 24 experts 100 / 60)
+    if (!w.router_bwd_block || (w.fused && !w.noise.jitter) || w.C == 0) return 0;
     if (router_bwd_mfma_supported(w, w.elt == 2 ? SW_BF16 : SW_F32) && !w.rw_hosted &&
         (double)w.T * (double)w.d * (double)w.E > 2.5e8)
         return 0;

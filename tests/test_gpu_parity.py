@@ -195,13 +195,14 @@ def test_router_weight_gradient_sums_in_short_chains():
 @pytest.mark.parametrize("T,d,E,n", [(1, 8, 3, 1), (65, 72, 32, 1), (130, 40, 33, 1), (1000, 264, 64, 2), (700, 136, 128, 1),
                                      (515, 72, 130, 1), (300, 264, 256, 4),
                                      (70, 1032, 132, 1), (333, 1160, 256, 1)])   # planes of x * m
-def test_bf16_tokens_with_jitter_in_the_one_kernel_router(T, d, E, n):
+@pytest.mark.parametrize("fused", [False, True])
+def test_bf16_tokens_with_jitter_in_the_one_kernel_router(T, d, E, n, fused):
     """fp32 products of x * m, forward and backward, beside the other route; the logits to fp32 rounding."""
     from parity import compare_full
     s = SwitchShape("t", T // n * n, d, 72, E, 1.25, dtype="bf16", zipf_bias=E % 4 != 0, seed_index=73, n_groups=n,
-                    jitter_eps=0.1, noise_seed=11)
+                    jitter_eps=0.1, noise_seed=11, fused_dispatch=fused)
     errs, _, _, _ = compare_full(s, make_inputs(s, _dev()), d_aux=1.0)
-    _report("jitter %s" % ((T, d, E, n),), errs)
+    _report("jitter %s" % ((T, d, E, n, fused),), errs)
 
 
 @pytest.mark.parametrize("T,d,f,E,cf,n,rate,ffn,rounds", [

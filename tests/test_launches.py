@@ -167,7 +167,10 @@ def test_route_of_input_jitter(recorder, T, d, E, planes, fused):
     (1050, 512, 2600, 16, 2.0, dict(jitter=0.01), "parts"), (1050, 512, 2720, 16, 2.0, dict(), "parts"),
     (512, 768, 3072, 128, 1.25, dict(), "parts"),
     (8192, 768, 3072, 128, 1.25, dict(), "mfma"), (500, 64, 256, 300, 4.0, dict(dtype="f32"), "vector"),
-    (5003, 392, 1000, 10, 1.25, dict(fused=True), "vector"),
+    (5003, 392, 1000, 10, 1.25, dict(fused=True), "vector"), (2000, 512, 2048, 16, 1.25, dict(fused=True), "mfma"),
+    (2000, 512, 2048, 16, 1.25, dict(fused=True, jitter=0.01), "parts"),
+    (4096, 768, 3072, 128, 1.25, dict(fused=True, jitter=0.01, bias=True), "parts"),
+    (65536, 768, 3072, 128, 1.25, dict(fused=True, jitter=0.01), "mfma"),
     # memory for few parts: of many experts, from 1e9 products on
     (6050, 5000, 64, 33, 1.25, dict(), "parts"), (6072, 5000, 64, 33, 1.25, dict(), "vector"),
     (2850, 5000, 64, 70, 1.25, dict(dtype="f32"), "beside"), (2870, 5000, 64, 70, 1.25, dict(dtype="f32"), "vector"),
