@@ -162,36 +162,25 @@ Workspace layout_workspace(const switch_config *cfg) {
         w.ntlb_free = take(nE);
         w.ntlb_base = take(nE);
     }
-    // What only the router's backward pass writes, after the last kernel that reads dH: in dH's
-    // memory while it fits.
-    size_t dead = 0;
-    const size_t dead_room = E * C * f1 * w.elt;
-    auto take_dead = [&](size_t bytes) {
-        if (dead + bytes > dead_room) return take(bytes);
-        const size_t o = w.dH + dead;
-        dead = align_up(dead + bytes, 256);
-        return o;
-    };
-    const size_t table = align_up(nb * E * 4, 256);
-    // The parts of its weight gradient: in memory of their own if a launch of the experts' computes them.  Where that would
-    // take the layer out of the static scratch: in a launch behind those, in dH's memory, or with fewer parts, or not in
-    // parts.
-    const size_t part = (d + 1) * E * 4, room = off + 3 * table <= SW_STATIC_SCRATCH_BYTES
-                                                    ? SW_STATIC_SCRATCH_BYTES - off - 3 * table : SIZE_MAX;
-    w.rw_hosted = router_wgrad_hosted(w);
-    w.rw_nsplit = router_wgrad_splits(w);
-    if (w.rw_hosted && w.rw_nsplit * part > room) {
-        w.rw_hosted = false;
-        w.rw_nsplit = router_wgrad_splits(w);
-    }
-    if (!w.rw_hosted && w.rw_nsplit * part > dead_room && w.rw_nsplit * part > room) {
-        const int64_t most = (dead_room > room ? dead_room : room) / part;
-        w.rw_nsplit = 4 * most < w.rw_nsplit ? 0 : most;
-    }
-    if (w.rw_nsplit) {
-        w.block_counts = take(3 * table);
-        w.rw_part = w.rw_hosted ? take(w.rw_nsplit * part) : take_dead(w.rw_nsplit * part);
-    } else {
+    const size_t dead_room = E * C * f1 * w.elt, table = align_up(nb * E * 4, 256), part = (d + 1) * E * 4, before = off;
+    auto router_backward = [&](bool hosted, int64_t nsplit) {   // the rest of the workspace, with so many parts of dW_r
+        off = before;
+        w.rw_hosted = hosted;
+        w.rw_nsplit = nsplit;
+        // What only the router's backward pass writes, after the last kernel that reads dH: in dH's
+        // memory while it fits.
+        size_t dead = 0;
+        auto take_dead = [&](size_t bytes) {
+            if (dead + bytes > dead_room) return take(bytes);
+            const size_t o = w.dH + dead;
+            dead = align_up(dead + bytes, 256);
+            return o;
+        };
+        if (nsplit) {   // (a launch of the experts' reads dH while it computes them)
+            w.block_counts = take(3 * table);
+            w.rw_part = hosted ? take(nsplit * part) : take_dead(nsplit * part);
+            return;
+        }
         w.dl_split = take_dead(mfma ? (size_t)w.etiles * T * 256 * 2 : 0);
         const size_t dlogits_bytes = w.router_bwd_block && mfma ? 0 : T * E * 4;
         const bool dlogits_own = dead + dlogits_bytes > dead_room;   // ... in memory of its own
@@ -211,6 +200,19 @@ Workspace layout_workspace(const switch_config *cfg) {
         w.tps_m = router_dwr_tokens(w);
         w.nsplit_m = ceil_div(w.T, w.tps_m);
         w.dWr_part_m = take_dead(mfma ? (size_t)w.etiles * w.nsplit_m * d * 128 * 4 : 0);
+    };
+    const bool hosted = router_wgrad_hosted(w);
+    const int64_t beside = router_wgrad_splits(w, hosted), alone = hosted ? router_wgrad_splits(w, false) : beside;
+    router_backward(false, 0);
+    const bool fits = off <= SW_STATIC_SCRATCH_BYTES;
+    if (beside) router_backward(hosted, beside);
+    // A layer that fits the static scratch without parts fits it: with those in a launch behind the experts', in dH's memory,
+    // or with fewer of them, or without.
+    if (fits && off > SW_STATIC_SCRATCH_BYTES && hosted) router_backward(false, alone);
+    if (fits && off > SW_STATIC_SCRATCH_BYTES) {
+        const size_t room = SW_STATIC_SCRATCH_BYTES - before - 3 * table;
+        const int64_t most = (dead_room > room ? dead_room : room) / part;
+        router_backward(false, 4 * most < alone ? 0 : most);
     }
     w.block_psum = w.block_counts + table;
     w.block_off = w.block_psum + table;

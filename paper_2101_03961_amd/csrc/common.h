@@ -272,7 +272,7 @@ hipError_t launch_router_bwd(const Workspace &w, int dtype, float alpha, float d
                              float *db_r, const RouterWgradArgs &parts, hipStream_t s);
 // The router's weight gradient from fp32 operands in parts (router_wgrad.h), or no blocks where it takes another form.
 bool router_wgrad_hosted(const Workspace &w);
-int64_t router_wgrad_splits(const Workspace &w);
+int64_t router_wgrad_splits(const Workspace &w, bool hosted);
 RouterWgradArgs router_wgrad_args(const Workspace &w, float alpha, float d_aux, const void *x, char *ws, bool bias);
 // dlogits and dx in one kernel (router_bwd.hip); bias: also the per-block sums for db_r; parts: instead of both, the
 // sums over the parts of dW_r and db_r

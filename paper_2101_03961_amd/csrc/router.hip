@@ -767,11 +767,11 @@ bool router_wgrad_hosted(const Workspace &w) {
                       : gemm_f32_on_mfma(w, w.d, w.f1) &&
                             w.E * ceil_div(w.d, 64) * ceil_div(w.f1, 64) * 256 <= kMaxGridThreads / 2;
 }
-int64_t router_wgrad_splits(const Workspace &w) {
+int64_t router_wgrad_splits(const Workspace &w, bool hosted) {
     // (dispatch inside the GEMMs: where the fp32 operands of input jitter rule out the matrix cores.  us of dW_r on the vector
     // ALUs / in parts, with the sums of each: 512 x 768, 128 experts 40 / 12, 30000 x 1024, 24 experts 100 / 60)
     if (!w.router_bwd_block || (w.fused && !w.noise.jitter) || w.C == 0) return 0;
-    if (router_bwd_mfma_supported(w, w.elt == 2 ? SW_BF16 : SW_F32) && !w.rw_hosted &&
+    if (router_bwd_mfma_supported(w, w.elt == 2 ? SW_BF16 : SW_F32) && !hosted &&
         (double)w.T * (double)w.d * (double)w.E > 2.5e8)
         return 0;
     const int64_t most = ((int64_t)16 << 20) / (4 * (w.d + 1) * w.E);   // 16 MB of parts
@@ -779,7 +779,7 @@ int64_t router_wgrad_splits(const Workspace &w) {
     const int64_t enough = w.T >= 65536 ? 256 : w.T > 64 * 256 ? w.T / 256 : 64;
     if (n > enough) n = enough;
     if (n > most) n = most;
-    return w.E > (w.rw_hosted ? 64 : 32) && n < 40 && (double)w.T * (double)w.d * (double)w.E > 1e9 ? 0 : n;
+    return w.E > (hosted ? 64 : 32) && n < 40 && (double)w.T * (double)w.d * (double)w.E > 1e9 ? 0 : n;
 }
 
 RouterWgradArgs router_wgrad_args(const Workspace &w, float alpha, float d_aux, const void *x, char *ws, bool bias) {

@@ -171,6 +171,8 @@ def test_route_of_input_jitter(recorder, T, d, E, planes, fused):
     (2000, 512, 2048, 16, 1.25, dict(fused=True, jitter=0.01), "parts"),
     (4096, 768, 3072, 128, 1.25, dict(fused=True, jitter=0.01, bias=True), "parts"),
     (65536, 768, 3072, 128, 1.25, dict(fused=True, jitter=0.01), "mfma"),
+    # near the static scratch's limit, but beyond it without parts too: nothing moves
+    (8484, 296, 208, 64, 1.0, dict(n=4, dropout=0.1), "beside"), (2470, 768, 48, 64, 1.0, dict(dtype="f32"), "beside"),
     # memory for few parts: of many experts, from 1e9 products on
     (6050, 5000, 64, 33, 1.25, dict(), "parts"), (6072, 5000, 64, 33, 1.25, dict(), "vector"),
     (2850, 5000, 64, 70, 1.25, dict(dtype="f32"), "beside"), (2870, 5000, 64, 70, 1.25, dict(dtype="f32"), "vector"),
