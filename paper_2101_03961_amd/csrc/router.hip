@@ -750,36 +750,47 @@ static float aux_scale_of(const Workspace &w, float alpha, float d_aux) {
 // launch; bf16: of the launch that computes three products of a small layer) and the one kernel computes dx, whose
 // launch then adds up the parts.  That saves two launches of the chain (us per forward + backward pass, without /
 // with: fp32 256 x 64 x 256, 4 experts 56.8 / 51.0; bf16 5003 x 392 x 1000, 10 experts 115.0 / 106.3; large fp32 layers the
-// same).  The parts of other layers have a launch of their own, behind the experts': where the router gradients take fp32
-// operands, and up to 2.5e8 products, where the matrix cores' two kernels are slower (us of a pass, a slower form of those /
-// here: 768 x 1536, 128 experts, 512 tokens 462 / 453, 2048 475 / 469, 4096 516 / 505, 8192 555 / 570; since then they take
-// 10 less from 4096 on).  At
-// most 64 parts of at least 32 tokens, or 256 of at least 256, and 16 MB in all: more would be read for longer than they
-// are summed, and fewer are too few blocks (us of a pass with d_ff 512, 64 parts / here: 65536 x 384, 16 experts with jitter
-// 634 / 523; 40000 x 128, 62 experts 220 / 192; 200000 x 128, 62 experts 1032 / 818, fp32, 8 experts 2148 / 2001).  Where 16 MB
-// leaves fewer than 40 to a large layer of many experts, the vector-ALU kernel: its 64 parts are blocks for the whole
-// chip, the others are few long ones (us of a pass, that / parts: fp32 65536 x 2048, 256 experts 7050 / 7700, 60000 x 1024,
-// 256 2220 / 2380, 8192 x 768, 256 609 / 625, 4096 x 4096, 64 995 / 973; bf16 65536 x 2048, 62 experts 1704 / 1843, 20000 x
-// 8192, 130 4382 / 4990, and 30 1959 / 1857; with more parts, 65536 x 768, 62 experts 767 / 736).
+// same).  The parts of other layers have a launch of their own, behind the experts', where the router gradients take fp32
+// operands.
+// Where they may take bf16 terms, the matrix cores' two kernels cost 15 us at least, but little more with many tokens: them
+// for more than 32 experts and 8192 tokens or 1.5e8 products (us of a pass, parts in the launch of three products / here:
+// 41878 x 232 x 88, 112 experts 230 / 178, 20000 x 208 x 104, 128 experts 144 / 119, 8192 x 384 x 64, 128 experts 107 / 94;
+// 4096 x 256 x 64, 32 experts 53 / 56), and instead of a launch of the parts' own for more than 4096 tokens or 4e7 products
+// (2048 x 1024 x 3072, 8 experts 199 / 204, 512 x 512 x 3072, 32 experts 170 / 172, 8192 x 512 x 64, 8 experts 87 / 83, 4096 x
+// 512 x 64, 92 experts 84 / 80, 736 x 1536 x 112, 92 experts 133 / 127, 20000 x 64 x 64, 128 experts 111 / 85).
 bool router_wgrad_hosted(const Workspace &w) {
-    // (fp32: far enough inside one dimension of the grid)
-    return w.elt == 2 ? rows_backward_supported(w)
-                      : gemm_f32_on_mfma(w, w.d, w.f1) &&
-                            w.E * ceil_div(w.d, 64) * ceil_div(w.f1, 64) * 256 <= kMaxGridThreads / 2;
+    const double products = (double)w.T * (double)w.d * (double)w.E;
+    if (w.elt == 2)
+        return rows_backward_supported(w) &&
+               !(w.E > 32 && (w.T > 8192 || products > 1.5e8) && router_bwd_mfma_supported(w, SW_BF16));
+    // (far enough inside one dimension of the grid)
+    return gemm_f32_on_mfma(w, w.d, w.f1) && w.E * ceil_div(w.d, 64) * ceil_div(w.f1, 64) * 256 <= kMaxGridThreads / 2;
 }
+// How many: one per 32 tokens up to 64, and for longer batches one per 128 up to 256, but no more blocks than run at a
+// time (two per CU beside the experts'), or whole rounds of those with about 512 tokens per part (us of a pass, 64 parts /
+// here: 16000 x 512 x 256, 8 experts with jitter 152 / 134, 65536 x 384 x 256, 16 experts with jitter 568 / 458, 40000 x 64 x
+// 256, 62 experts 179 / 136, fp32 16000 x 64 x 256, 16 experts 137 / 126); 16 MB in all.
+// Where 16 MB leaves fewer than 40 to a large layer of many experts, the vector-ALU kernel: its 64 parts are blocks for
+// the whole chip, the others are few long ones (us of a pass, that / parts: fp32 65536 x 2048, 256 experts 7050 / 7700,
+// 60000 x 1024, 256 2220 / 2380, 8192 x 768, 256 609 / 625, 4096 x 4096, 64 995 / 973; bf16 65536 x 2048, 62 experts 1704 /
+// 1843, 20000 x 8192, 130 4382 / 4990, and 30 1959 / 1857; with more parts, 65536 x 768, 62 experts 767 / 736).
 int64_t router_wgrad_splits(const Workspace &w, bool hosted) {
+    const double products = (double)w.T * (double)w.d * (double)w.E;
     // (dispatch inside the GEMMs: where the fp32 operands of input jitter rule out the matrix cores.  us of dW_r on the vector
     // ALUs / in parts, with the sums of each: 512 x 768, 128 experts 40 / 12, 30000 x 1024, 24 experts 100 / 60)
     if (!w.router_bwd_block || (w.fused && !w.noise.jitter) || w.C == 0) return 0;
-    if (router_bwd_mfma_supported(w, w.elt == 2 ? SW_BF16 : SW_F32) && !hosted &&
-        (double)w.T * (double)w.d * (double)w.E > 2.5e8)
-        return 0;
-    const int64_t most = ((int64_t)16 << 20) / (4 * (w.d + 1) * w.E);   // 16 MB of parts
-    int64_t n = ceil_div(w.T, kRwTokens);
-    const int64_t enough = w.T >= 65536 ? 256 : w.T > 64 * 256 ? w.T / 256 : 64;
-    if (n > enough) n = enough;
+    if (!hosted && (w.T > 4096 || products > 4e7) && router_bwd_mfma_supported(w, w.elt == 2 ? SW_BF16 : SW_F32)) return 0;
+    const int experts = router_wgrad_experts(w.E);
+    const int64_t tiles = ceil_div(w.d, kRwElements / experts) * ceil_div(w.E, experts);
+    const int64_t round = tiles < 512 ? 512 / tiles : 1;
+    int64_t n = w.T / 128 < round ? w.T / 128 : round;
+    if (w.T / 512 > n) n = (w.T / 512 + round / 2) / round * round;
+    if (n < 64) n = 64;
+    if (n > 256) n = 256;
+    if (n > ceil_div(w.T, kRwTokens)) n = ceil_div(w.T, kRwTokens);
+    const int64_t most = ((int64_t)16 << 20) / (4 * (w.d + 1) * w.E);
     if (n > most) n = most;
-    return w.E > (hosted ? 64 : 32) && n < 40 && (double)w.T * (double)w.d * (double)w.E > 1e9 ? 0 : n;
+    return w.E > (hosted ? 64 : 32) && n < 40 && products > 1e9 ? 0 : n;
 }
 
 RouterWgradArgs router_wgrad_args(const Workspace &w, float alpha, float d_aux, const void *x, char *ws, bool bias) {

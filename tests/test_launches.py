@@ -165,14 +165,19 @@ def test_route_of_input_jitter(recorder, T, d, E, planes, fused):
     (8192, 768, 3072, 32, 1.25, dict(dtype="f32", bias=True), "beside"), (1050, 512, 2048, 16, 2.0, dict(), "beside"),
     (1050, 512, 2048, 16, 2.0, dict(jitter=0.01), "beside"), (1050, 512, 2600, 16, 2.0, dict(), "parts"),
     (1050, 512, 2600, 16, 2.0, dict(jitter=0.01), "parts"), (1050, 512, 2720, 16, 2.0, dict(), "parts"),
-    (512, 768, 3072, 128, 1.25, dict(), "parts"),
+    (512, 512, 3072, 128, 1.25, dict(), "parts"), (736, 1536, 112, 92, 1.25, dict(), "mfma"),
+    (1513, 1312, 48, 16, 2.0, dict(jitter=0.01), "vector"),   # room for a quarter of the parts
     (8192, 768, 3072, 128, 1.25, dict(), "mfma"), (500, 64, 256, 300, 4.0, dict(dtype="f32"), "vector"),
     (5003, 392, 1000, 10, 1.25, dict(fused=True), "vector"), (2000, 512, 2048, 16, 1.25, dict(fused=True), "mfma"),
     (2000, 512, 2048, 16, 1.25, dict(fused=True, jitter=0.01), "parts"),
     (4096, 768, 3072, 128, 1.25, dict(fused=True, jitter=0.01, bias=True), "parts"),
     (65536, 768, 3072, 128, 1.25, dict(fused=True, jitter=0.01), "mfma"),
     # near the static scratch's limit, but beyond it without parts too: nothing moves
-    (8484, 296, 208, 64, 1.0, dict(n=4, dropout=0.1), "beside"), (2470, 768, 48, 64, 1.0, dict(dtype="f32"), "beside"),
+    (7900, 296, 208, 64, 1.0, dict(n=4, dropout=0.1), "beside"), (2470, 768, 48, 64, 1.0, dict(dtype="f32"), "beside"),
+    # many tokens to many experts: on the matrix cores where those take its operands
+    (8192, 256, 64, 64, 1.25, dict(), "beside"), (8193, 256, 64, 64, 1.25, dict(), "mfma"), (8193, 256, 64, 32, 1.25, dict(), "beside"),
+    (8193, 256, 64, 62, 1.25, dict(), "beside"), (4096, 384, 64, 96, 1.25, dict(), "mfma"),
+    (4096, 512, 8192, 16, 1.25, dict(), "parts"), (4100, 512, 8192, 16, 1.25, dict(), "mfma"),
     # memory for few parts: of many experts, from 1e9 products on
     (6050, 5000, 64, 33, 1.25, dict(), "parts"), (6072, 5000, 64, 33, 1.25, dict(), "vector"),
     (2850, 5000, 64, 70, 1.25, dict(dtype="f32"), "beside"), (2870, 5000, 64, 70, 1.25, dict(dtype="f32"), "vector"),
@@ -188,10 +193,10 @@ def test_router_weight_gradient_beside_the_experts(recorder, T, d, f, E, cf, kw,
     assert any("reduce" in k[0] for k in launches) == (form in ("mfma", "vector"))
 
 
-# How many parts it comes in, in tiles of 4096 elements: one per 32 tokens up to 64, one per 256 up to 256, up to 16 MB; each a
-# multiple of 32 tokens.
-@pytest.mark.parametrize("T,d,E,parts", [(1, 512, 30, 1), (33, 512, 30, 2), (2048, 512, 30, 64), (16640, 512, 30, 65),
-                                         (40000, 512, 30, 139), (65536, 512, 30, 256), (200000, 512, 30, 250), (40000, 4096, 30, 34)])
+# How many parts it comes in, in tiles of 4096 elements: one per 32 tokens up to 64, one per 128 while the blocks run at a time
+# (512), one per 512; up to 256, and 16 MB; each a multiple of 32 tokens.
+@pytest.mark.parametrize("T,d,E,parts", [(1, 512, 30, 1), (33, 512, 30, 2), (2048, 512, 30, 64), (12000, 512, 30, 75),
+                                         (40000, 512, 30, 125), (100000, 512, 30, 241), (200000, 512, 30, 250), (40000, 4096, 30, 34)])
 def test_parts_of_the_router_weight_gradient(recorder, T, d, E, parts):
     (status, _, _, launches), = recorder(call("backward", T, d, 8192, E, max(1.25, 4 * E / T)))
     assert status == 0
@@ -202,7 +207,7 @@ def test_parts_of_the_router_weight_gradient(recorder, T, d, E, parts):
 # The sums over its parts: blocks of the launch that computes dx, each once (256 sums each, and db_r's), behind those of 128
 # tokens by a range of columns.
 @pytest.mark.parametrize("T,d,f,E,cf,kw,dx_blocks", [
-    (64, 4096, 256, 128, 4.0, dict(), 64), (300, 4096, 1024, 100, 4.0, dict(bias=True), 3 * 64),
+    (64, 4096, 256, 128, 4.0, dict(), 64), (300, 4096, 1024, 98, 4.0, dict(bias=True), 3 * 64),
     (1000, 2048, 256, 256, 2.0, dict(dtype="f32", bias=True), 8 * 64), (256, 64, 256, 4, 1.25, dict(dtype="f32"), 2),
     (60000, 128, 512, 16, 1.0, dict(bias=True), 469 * 2),
 ])
