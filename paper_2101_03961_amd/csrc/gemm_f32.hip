@@ -28,7 +28,6 @@ struct GemmF32Args {
     float *y;
     long slots;
     Noise nz;
-    RouterWgradArgs router;      // first weight gradient: parts of the router's, in blocks behind it
 };
 
 constexpr int kF32Tile = 64;
@@ -181,8 +180,13 @@ __device__ __forceinline__ f32x4 mfma_f32(float p, float q, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(p, q, c, 0, 0, 0);
 }
 
-template <int S, int IP, int WP, int IQ, int WQ, int STAGES, bool Q_TRANS, bool P_TRANS, int EPI>
-__global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32Args a, int tiles_q, int tiles_p) {
+// R: RouterWgradArgs, parts of the router's weight gradient in blocks behind those of a weight gradient of the experts', or
+// nothing.  Two kernels, for those blocks take twice the registers (one kernel / two, us of a pass: 826 x 1824 x 1280, 128
+// experts 2156 / 2075, 2088 x 496 x 5040, 128 experts 2131 / 2012).
+struct NoRouterWgrad {};
+
+template <int S, int IP, int WP, int IQ, int WQ, int STAGES, bool Q_TRANS, bool P_TRANS, int EPI, typename R>
+__global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32Args a, int tiles_q, int tiles_p, R router) {
     constexpr int NW = WP * WQ, PB = S * IP * WP, QB = S * IQ * WQ;
     constexpr int kPBytes = PB * 128, kStage = (PB + QB) * 128;
     constexpr int kAcc = S * S / 64;   // accumulators per lane and MFMA tile
@@ -190,10 +194,10 @@ __global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32A
     static_assert(S == 32 || IP * IQ == 1, "fragments lie 32 rows apart");
     __shared__ __attribute__((aligned(16))) char lds[STAGES * kStage];
     const int per_e = tiles_q * tiles_p;
-    if constexpr (Q_TRANS) {   // (a weight gradient)
+    if constexpr (std::is_same<R, RouterWgradArgs>::value) {
         static_assert(STAGES * kStage >= kRwLds && NW == 4, "room for the router's blocks");
-        const int beyond = (int)blockIdx.x - ((int)gridDim.x - a.router.blocks);
-        if (beyond >= 0) return router_wgrad_block<float>(a.router, beyond, lds);
+        const int beyond = (int)blockIdx.x - ((int)gridDim.x - router.blocks);
+        if (beyond >= 0) return router_wgrad_block<float>(router, beyond, lds);
     }
     const int e = blockIdx.x / per_e, rem = blockIdx.x - e * per_e;
     const int pt = rem / tiles_q, qt = rem - pt * tiles_q;
@@ -323,19 +327,24 @@ __global__ __launch_bounds__(64 * WP * WQ, 2) void gemm_f32_mfma_kernel(GemmF32A
 }
 
 template <int S, int IP, int WP, int IQ, int WQ, int STAGES, bool Q_TRANS, bool P_TRANS, int EPI>
-static hipError_t f32_launch(const GemmF32Args &a, int E, hipStream_t s) {
+static hipError_t f32_launch(const GemmF32Args &a, int E, const RouterWgradArgs &parts, hipStream_t s) {
     const int tq = (int)ceil_div(a.Qdim, S * IQ * WQ), tp = (int)ceil_div(a.Pdim, S * IP * WP);
-    hipLaunchKernelGGL((gemm_f32_mfma_kernel<S, IP, WP, IQ, WQ, STAGES, Q_TRANS, P_TRANS, EPI>),
-                       dim3((unsigned)(tq * tp * E + a.router.blocks)), dim3(64 * WP * WQ), 0, s, a, tq, tp);
-    return hipGetLastError();
+    auto launch = [&](auto kern, auto router) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)(tq * tp * E + parts.blocks)), dim3(64 * WP * WQ), 0, s, a, tq, tp, router);
+        return hipGetLastError();
+    };
+    if constexpr (Q_TRANS)
+        if (parts.blocks)
+            return launch(gemm_f32_mfma_kernel<S, IP, WP, IQ, WQ, STAGES, Q_TRANS, P_TRANS, EPI, RouterWgradArgs>, parts);
+    return launch(gemm_f32_mfma_kernel<S, IP, WP, IQ, WQ, STAGES, Q_TRANS, P_TRANS, EPI, NoRouterWgrad>, NoRouterWgrad{});
 }
 
 template <bool Q_TRANS, bool P_TRANS, int EPI>
-static hipError_t f32_mfma(const GemmF32Args &a, int E, hipStream_t s) {
+static hipError_t f32_mfma(const GemmF32Args &a, int E, hipStream_t s, const RouterWgradArgs &parts = {}) {
     // 64 x 64 keeps the chip even (a 128 x 128 tile takes 573 instead of 364 us in the second GEMM of
     // 32 experts x 256 tokens x 768 x 3072); twice as wide is 2-8 % faster where there are many tiles.
     if (E * ceil_div(a.Qdim, 64) * ceil_div(a.Pdim, 128) >= 1024)
-        return f32_launch<32, 2, 2, 1, 2, 2, Q_TRANS, P_TRANS, EPI>(a, E, s);
+        return f32_launch<32, 2, 2, 1, 2, 2, Q_TRANS, P_TRANS, EPI>(a, E, parts, s);
     // Few tiles: a 64 x 64 tile keeps one CU's matrix cores busy for 1024 cycles per 32 k, whatever the others do.
     // Tiles of 32 x 32, a quarter of 16 x 16 per wave, spread over four times as many (us per forward + backward
     // pass, 64 x 64 / 32 x 32: 256 x 64 x 256, 4 experts 71 / 56; 1000 x 512 x 1536, 8 experts 244 / 219; 512 x 768 x
@@ -345,8 +354,8 @@ static hipError_t f32_mfma(const GemmF32Args &a, int E, hipStream_t s) {
     // (Four waves that take a quarter of the k each of one 32 x 32: 2-8 % less per pass, but other sums than the
     // larger tiles'.)
     if (E * ceil_div(a.Qdim, 64) * ceil_div(a.Pdim, 64) <= 384)
-        return f32_launch<16, 1, 2, 1, 2, 4, Q_TRANS, P_TRANS, EPI>(a, E, s);
-    return f32_launch<32, 1, 2, 1, 2, 2, Q_TRANS, P_TRANS, EPI>(a, E, s);
+        return f32_launch<16, 1, 2, 1, 2, 4, Q_TRANS, P_TRANS, EPI>(a, E, parts, s);
+    return f32_launch<32, 1, 2, 1, 2, 2, Q_TRANS, P_TRANS, EPI>(a, E, parts, s);
 }
 
 // The matrix-core kernel addresses one expert's matrices through 32-bit buffer descriptors, and all of a
@@ -365,7 +374,6 @@ static hipError_t gemm_f32(GemmKind kind, const Workspace &w, char *ws, const vo
     a.slots = C;
     a.slot_gate = (const float *)(ws + w.slot_gate);
     a.y = (float *)y;
-    a.router = parts;
     a.nz = w.noise;
     const float *Xd = (const float *)(ws + w.Xd);
     float *A = (float *)(ws + w.A);
@@ -431,7 +439,7 @@ static hipError_t gemm_f32(GemmKind kind, const Workspace &w, char *ws, const vo
             return w.geglu ? f32_mfma<false, false, F32_PLAIN>(a, E, s) : f32_mfma<false, false, F32_MASK>(a, E, s);
         case GEMM_DGRAD1: return f32_mfma<false, false, F32_PLAIN>(a, E, s);
         case GEMM_WGRAD2:
-        case GEMM_WGRAD1: return f32_mfma<true, true, F32_PLAIN>(a, E, s);
+        case GEMM_WGRAD1: return f32_mfma<true, true, F32_PLAIN>(a, E, s, parts);
         }
     }
     dim3 grid((unsigned)ceil_div(a.Pdim, kF32Tile), (unsigned)ceil_div(a.Qdim, kF32Tile),
