@@ -43,9 +43,19 @@ __device__ __forceinline__ void reduce_partials(const float *part, float *out, s
     if (block >= blocks) return reduce_dbr(db, (int)(block - blocks));
     const size_t i = block * 256 + threadIdx.x;
     if (i >= n) return;
+    // (32 loads in flight, then eight: a small matrix is one block with a chain of up to 256 parts.  us of the launch that
+    // computes dx, eight / here: 36737 tokens of 40, 5 experts, 250 parts 16 / 10)
     float s = 0.f;
+    int q = 0;
+    for (; q + 32 <= nsplit; q += 32) {
+        float v[32];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) v[u] = part[(size_t)(q + u) * n + i];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) s += v[u];
+    }
 #pragma unroll 8
-    for (int q = 0; q < nsplit; ++q) s += part[(size_t)q * n + i];
+    for (; q < nsplit; ++q) s += part[(size_t)q * n + i];
     out[i] = s;
 }
 
