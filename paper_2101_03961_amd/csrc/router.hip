@@ -631,7 +631,9 @@ __global__ __launch_bounds__(256) void router_dWr_kernel(const XT *__restrict__ 
     }
 }
 
-template <typename XT> __global__ __launch_bounds__(256) void router_wgrad_kernel(RouterWgradArgs a) {
+// (bf16: 96 registers, five blocks per CU; us of this launch with 100 and four / here: 29802 x 1256, 33 experts 120 / 98.  fp32
+// spills there.)
+template <typename XT> __global__ __launch_bounds__(256, sizeof(XT) == 2 ? 5 : 4) void router_wgrad_kernel(RouterWgradArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[kRwLds];
     router_wgrad_block<XT>(a, blockIdx.x, lds);
 }
