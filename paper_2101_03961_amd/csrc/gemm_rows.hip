@@ -704,9 +704,9 @@ hipError_t launch_gemm_rows(GemmKind kind, const Workspace &w, char *ws, const v
         case ROWS_128x128: return rows_launch<2, 2, 2, 2, 2, 2, true, ROWS_PLAIN, false, false, true>(a, E, s);
         case ROWS_256x128: {
             // Three blocks per CU, which 168 registers allow, cover the waits of a single stage where an expert has more than
-            // one step of slots; with one step the stores bound it and 174 registers are better (us of a pass, two / three: 39584
-            // x 752 x 2696, 8 experts 1550 / 1284, 65536 x 512 x 2048, 4 experts 1326 / 1219; 512 x 1080 x 2408, 208 experts 1346 /
-            // 1388, 64 x 4096 x 1024, 128 experts 780 / 790).
+            // one step of slots; with one step the stores bound it and 174 registers are better (us of both gradients, two /
+            // three: 39584 x 752 x 2696, 8 experts 592 / 375; of a pass: 512 x 1080 x 2408, 208 experts 1346 / 1388, 64 x 4096 x
+            // 1024, 128 experts 780 / 790).
             const bool part = rows_part_lines(w, a.Qdim, a.Pdim);
             if (w.C > BK && w.T > w.E * BK)
                 return part ? rows_launch<2, 2, 4, 2, 1, 3, true, ROWS_PLAIN, false, false, true, true>(a, E, s)
