@@ -39,8 +39,10 @@
  *     tokens and E a multiple of 4 beyond; otherwise on the vector ALUs, several
  *     times slower.  Logits: fp32 products (bf16 tokens times fp32 weights as exact
  *     sums of three bf16 terms).  Backward: with bf16 tokens and E a multiple of 4
- *     the logits' gradient and the weights enter as two bf16 terms each (16
- *     mantissa bits), otherwise as fp32; sums are fp32.
+ *     the logits' gradient and, for dx, the weights enter as two bf16 terms (16
+ *     mantissa bits), otherwise as fp32; dW_r and db_r of smaller layers, and both
+ *     contractions of most layers with input jitter up to 256 experts, take fp32
+ *     operands too.  Sums are fp32.
  */
 #ifndef SWITCHFFN_H
 #define SWITCHFFN_H
@@ -136,8 +138,9 @@ typedef struct {
  *           i = t * d_ff + j; it takes 16 bits of the z drawn for idx = i / 2 -- z & 0xFFFF if
  *           i is even, z >> 16 if odd -- and is zeroed iff they are < thr = floor(rate * 2^16);
  *           survivors are scaled by 2^16 / (2^16 - thr)
- * With jitter_eps > 0 and bf16 tokens the workspace also holds x * m as three bf16 planes
- * (6 * T * d_model bytes, d_model rounded up to a multiple of 32).
+ * With jitter_eps > 0, bf16 tokens and E a multiple of 4 the workspace of a large layer of more
+ * than 64 experts also holds x * m as three bf16 planes (6 * T * d_model bytes, d_model rounded up
+ * to a multiple of 32); the others draw m where they read x.
  */
 
 /* Expert capacity, Eq. 3, rounded down:
