@@ -66,8 +66,9 @@ def kernel_work(shape, kept, elt):
     else:
         block = 128 if shape.dtype == "bf16" and E <= 128 and T >= 32768 else 64
     dpad = -(-d // 32) * 32
-    # parts of dW_r: a block of 256 columns x 128 experts per CU, 128 parts at most
+    # parts of dW_r: a block of 256 columns x 128 experts per CU, 128 parts at most, whole 32s of at least 64 tokens
     dwr_splits = min(128, max(1, 256 // (-(-d // 256) * -(-E // 128))))
+    dwr_splits = -(-T // max(64, -(-(-(-T // dwr_splits)) // 32) * 32))
     x_router = T * 3 * dpad * 2 if jit else T * d * elt     # bytes of the router's input operand
     return {**{
         "router_jitter_split": (0.0, T * d * elt + T * 3 * dpad * 2, "hbm"),
@@ -104,7 +105,7 @@ def kernel_work(shape, kept, elt):
         "router_dlogits": (0.0, T * E * 4 + T * 512 + T * 8, "hbm"),
         "router_dx_mfma": (6.0 * T * d * E, T * 512 + kept * d * elt + T * d * elt, "hbm"),
         "router_dWr_mfma": (4.0 * T * d * E, (T * 2 * dpad * 2 if jit else T * d * elt) + T * 512, "hbm"),
-        "router_dWr_reduce": (0.0, dwr_splits * d * 128 * 4.0 + d * E * 4.0, "hbm"),
+        "router_dWr_reduce": (0.0, -(-E // 128) * dwr_splits * d * 128 * 4.0 + d * E * 4.0, "hbm"),
         "router_dx": ((6.0 if bf16_block else 2.0) * T * d * E,
                       T * E * 4 + T * (512 if bf16_block else 4 * E) + kept * d * elt + T * d * elt,
                       "hbm"),
