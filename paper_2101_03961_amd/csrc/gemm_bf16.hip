@@ -609,200 +609,198 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_bf16_kernel(GemmArgs a) {
         // here, per tile, instead of being kept in registers across the k loop.
         int ln = lane;
         asm volatile("" : "+v"(ln));
-        {
-            char *ep = lds + turn_stage * kOpBytes64 + wave * kTurnBytes;
-            bf16 *Cout = a.Cout + (size_t)cur.e * a.c_batch;
-            const int c = ln & 15;
-            uint32_t *bits = EPI_BASE == EPI_NONE ? nullptr : bits_of(ln);
-            const int p = cur.p0 + wp * 128 + c * 8;
-            // ASYNC_STORES: the tile's rows that exist as a buffer of their own, so that rows
-            // past them (and, by their offset, columns past the matrix) store nothing
-            i32x4 c_rsrc = {0, 0, 0, 0}, s_rsrc = {0, 0, 0, 0};
-            uint32_t c_voff = 0;
-            const uint32_t row_bytes = (uint32_t)a.ldc * 2u;
-            if (ASYNC_STORES) {
-                const int rows = cur.qlim - cur.q0 < kBQ ? cur.qlim - cur.q0 : kBQ;
-                c_rsrc = make_rsrc(Cout + (size_t)cur.q0 * a.ldc, (uint32_t)rows * row_bytes);
-                if (SCATTER) s_rsrc = make_rsrc(a.Cscatter, a.gather_bytes);
-                c_voff = (p < a.Pdim ? (uint32_t)p * 2u : kOobOffset) +
-                         (uint32_t)(wq * 128 + (ln >> 4)) * row_bytes;
+        char *ep = lds + turn_stage * kOpBytes64 + wave * kTurnBytes;
+        bf16 *Cout = a.Cout + (size_t)cur.e * a.c_batch;
+        const int c = ln & 15;
+        uint32_t *bits = EPI_BASE == EPI_NONE ? nullptr : bits_of(ln);
+        const int p = cur.p0 + wp * 128 + c * 8;
+        // ASYNC_STORES: the tile's rows that exist as a buffer of their own, so that rows
+        // past them (and, by their offset, columns past the matrix) store nothing
+        i32x4 c_rsrc = {0, 0, 0, 0}, s_rsrc = {0, 0, 0, 0};
+        uint32_t c_voff = 0;
+        const uint32_t row_bytes = (uint32_t)a.ldc * 2u;
+        if (ASYNC_STORES) {
+            const int rows = cur.qlim - cur.q0 < kBQ ? cur.qlim - cur.q0 : kBQ;
+            c_rsrc = make_rsrc(Cout + (size_t)cur.q0 * a.ldc, (uint32_t)rows * row_bytes);
+            if (SCATTER) s_rsrc = make_rsrc(a.Cscatter, a.gather_bytes);
+            c_voff = (p < a.Pdim ? (uint32_t)p * 2u : kOobOffset) +
+                     (uint32_t)(wq * 128 + (ln >> 4)) * row_bytes;
+        }
+        // ReLU mask: byte j * 8 + i8 of a lane's 32 bytes says which of the eight
+        // elements of the 16-byte piece the lane handles in round j, iteration i8 are
+        // > 0.  EPI_RELU (the first forward GEMM) writes the bits, EPI_MASK (the gradient
+        // w.r.t. the hidden activations, same tiling and same lane-to-element map)
+        // applies them: 32 bytes per lane instead of a second read of the activations.
+        uint32_t new_bits[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};   // EPI_RELU: the lane's bits of this tile
+        const int wrow = ln & 31;
+        // ROUTER_DX: the round's eight addend pieces, asked for before the round is turned
+        // around so that their latency overlaps it
+        u32x4 addend[8];
+        bool has_addend[8];
+        auto ask_addend = [&](int j) {
+#pragma unroll
+            for (int i8 = 0; i8 < 8; ++i8) {
+                const int row = j * 32 + i8 * 4 + (ln >> 4);
+                const int slot = __shfl(j < 2 ? tv.slot_lo : tv.slot_hi, row & 63);
+                has_addend[i8] = slot >= 0 && p < a.Pdim;
+                addend[i8] = u32x4{0u, 0u, 0u, 0u};
+                if (has_addend[i8]) addend[i8] = *(const u32x4 *)(a.mask + (size_t)slot * a.ldc + p);
             }
-            // ReLU mask: byte j * 8 + i8 of a lane's 32 bytes says which of the eight
-            // elements of the 16-byte piece the lane handles in round j, iteration i8 are
-            // > 0.  EPI_RELU (the first forward GEMM) writes the bits, EPI_MASK (the gradient
-            // w.r.t. the hidden activations, same tiling and same lane-to-element map)
-            // applies them: 32 bytes per lane instead of a second read of the activations.
-            uint32_t new_bits[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};   // EPI_RELU: the lane's bits of this tile
-            const int wrow = ln & 31;
-            // ROUTER_DX: the round's eight addend pieces, asked for before the round is turned
-            // around so that their latency overlaps it
-            u32x4 addend[8];
-            bool has_addend[8];
-            auto ask_addend = [&](int j) {
+        };
+        // round j, first half: the lane's accumulators of rows 32 j .. of the wave's sub-tile,
+        // converted, into the turn-around buffer
+        auto turn_in = [&](int j) {
+            // expert dropout: the draw of hidden unit p of token t is element t * d_ff + p of
+            // the dropout stream; the lane's accumulators of this round belong to one slot
+            uint32_t drop_row = 0;
+            if (DROP && EPI_BASE == EPI_RELU) {
+                const int tok = __shfl(j < 2 ? tv.tok_lo : tv.tok_hi, (j & 1) * 32 + wrow, kWave);
+                drop_row = (uint32_t)tok * (uint32_t)a.Pdim +
+                           (uint32_t)(cur.p0 + wp * 128 + ((ln >> 5) << 2));
+            }
+            // the gate of the slot whose accumulators the lane holds in this round
+            float row_gate = 1.f;
+            if (SCALE)
+                row_gate = __uint_as_float(
+                    (uint32_t)__shfl((int)(j < 2 ? tv.ep_lo : tv.ep_hi), (j & 1) * 32 + wrow, kWave));
 #pragma unroll
-                for (int i8 = 0; i8 < 8; ++i8) {
-                    const int row = j * 32 + i8 * 4 + (ln >> 4);
-                    const int slot = __shfl(j < 2 ? tv.slot_lo : tv.slot_hi, row & 63);
-                    has_addend[i8] = slot >= 0 && p < a.Pdim;
-                    addend[i8] = u32x4{0u, 0u, 0u, 0u};
-                    if (has_addend[i8]) addend[i8] = *(const u32x4 *)(a.mask + (size_t)slot * a.ldc + p);
-                }
-            };
-            // round j, first half: the lane's accumulators of rows 32 j .. of the wave's sub-tile,
-            // converted, into the turn-around buffer
-            auto turn_in = [&](int j) {
-                // expert dropout: the draw of hidden unit p of token t is element t * d_ff + p of
-                // the dropout stream; the lane's accumulators of this round belong to one slot
-                uint32_t drop_row = 0;
-                if (DROP && EPI_BASE == EPI_RELU) {
-                    const int tok = __shfl(j < 2 ? tv.tok_lo : tv.tok_hi, (j & 1) * 32 + wrow, kWave);
-                    drop_row = (uint32_t)tok * (uint32_t)a.Pdim +
-                               (uint32_t)(cur.p0 + wp * 128 + ((ln >> 5) << 2));
-                }
-                // the gate of the slot whose accumulators the lane holds in this round
-                float row_gate = 1.f;
-                if (SCALE)
-                    row_gate = __uint_as_float(
-                        (uint32_t)__shfl((int)(j < 2 ? tv.ep_lo : tv.ep_hi), (j & 1) * 32 + wrow, kWave));
+            for (int i = 0; i < 4; ++i) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
+                for (int g = 0; g < 4; ++g) {
+                    float v[4];
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        float v[4];
+                    for (int r = 0; r < 4; ++r) v[r] = acc[i][j][g * 4 + r];
+                    if (EPI_BASE == EPI_RELU) {
+                        // (the ReLU itself is taken on the rounded values below: every
+                        // factor applied in between is positive or zero)
+                        if (DROP) {   // the lane's four units are two aligned pairs
+                            const uint32_t first = drop_row + (uint32_t)(i * 32 + g * 8);
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) v[r] = acc[i][j][g * 4 + r];
-                        if (EPI_BASE == EPI_RELU) {
-                            // (the ReLU itself is taken on the rounded values below: every
-                            // factor applied in between is positive or zero)
-                            if (DROP) {   // the lane's four units are two aligned pairs
-                                const uint32_t first = drop_row + (uint32_t)(i * 32 + g * 8);
-#pragma unroll
-                                for (int h = 0; h < 2; ++h) {
-                                    const uint32_t z = dropout_pair_bits(a.nz, (first >> 1) + (uint32_t)h);
-                                    v[2 * h] = dropout_keeps_even(a.nz, z) ? v[2 * h] * a.nz.drop_scale : 0.f;
-                                    v[2 * h + 1] =
-                                        dropout_keeps_odd(a.nz, z) ? v[2 * h + 1] * a.nz.drop_scale : 0.f;
-                                }
+                            for (int h = 0; h < 2; ++h) {
+                                const uint32_t z = dropout_pair_bits(a.nz, (first >> 1) + (uint32_t)h);
+                                v[2 * h] = dropout_keeps_even(a.nz, z) ? v[2 * h] * a.nz.drop_scale : 0.f;
+                                v[2 * h + 1] =
+                                    dropout_keeps_odd(a.nz, z) ? v[2 * h + 1] * a.nz.drop_scale : 0.f;
                             }
                         }
-                        if (DROP && EPI_BASE == EPI_MASK) {
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) v[r] *= a.nz.drop_scale;
-                        }
-                        if (SCALE) {
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) v[r] *= row_gate;
-                        }
-                        uint2 o = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
-                        if (EPI_BASE == EPI_RELU) {
-                            // ReLU on the bf16 values, two per instruction: read as 16-bit
-                            // integers the negative ones (and -0) are < 0, the others unchanged
-                            o.x = pk_max_i16(o.x, 0u);
-                            o.y = pk_max_i16(o.y, 0u);
-                        }
-                        const int ch = i * 4 + g;
-                        *(uint2 *)(ep + wrow * 256 + ((ch ^ (wrow & 15)) << 4) + ((ln >> 5) << 3)) = o;
                     }
-                }
-            };
-            // second half: the round's rows read back as 16-byte pieces of 256-byte segments.  All
-            // eight are read before the first is stored (the stores are fences to the compiler,
-            // which would otherwise read, wait and store in turn).
-            u32x4 vals[8];
-            auto turn_out = [&]() {
+                    if (DROP && EPI_BASE == EPI_MASK) {
 #pragma unroll
-                for (int i8 = 0; i8 < 8; ++i8) {
-                    const int rrow = i8 * 4 + (ln >> 4);
-                    vals[i8] = *(const u32x4 *)(ep + rrow * 256 + ((c ^ (rrow & 15)) << 4));
-                }
-            };
-            // third: what is left to do on the pieces, and their stores
-            auto store_round = [&](int j) {
-                uint32_t m_lo = 0u, m_hi = 0u;
-                if (EPI_BASE == EPI_MASK) { m_lo = tv.mb[2 * j]; m_hi = tv.mb[2 * j + 1]; }
+                        for (int r = 0; r < 4; ++r) v[r] *= a.nz.drop_scale;
+                    }
+                    if (SCALE) {
 #pragma unroll
-                for (int i8 = 0; i8 < 8; ++i8) {
-                    const int rrow = i8 * 4 + (ln >> 4);       // row within the round
-                    const int row = j * 32 + rrow;               // row within the wave's sub-tile
-                    const int q = cur.q0 + row_of(wq, j, rrow);
-                    u32x4 val = vals[i8];
-                    uint32_t row_off = 0;   // SCATTER: the row's place (asked of the lane that holds it, by all lanes)
-                    if (SCATTER) row_off = (uint32_t)__shfl((int)(j < 2 ? tv.ep_lo : tv.ep_hi), row & 63, kWave);
+                        for (int r = 0; r < 4; ++r) v[r] *= row_gate;
+                    }
+                    uint2 o = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
                     if (EPI_BASE == EPI_RELU) {
-                        // After ReLU every half word is a non-negative bf16: read as an unsigned
-                        // integer it is > 0 exactly when min(., 1) is 1.  Bits 0..3 of the
-                        // byte: low halves of the four words, bits 4..7: high halves.
-                        uint32_t u = 0;
-#pragma unroll
-                        for (int w = 0; w < 4; ++w) u |= pk_min_u16(val[w], 0x00010001u) << w;
-                        const uint32_t byte = (u & 0xfu) | ((u >> 12) & 0xf0u);
-                        if (i8 < 4) m_lo |= byte << (8 * i8);
-                        else m_hi |= byte << (8 * (i8 - 4));
+                        // ReLU on the bf16 values, two per instruction: read as 16-bit
+                        // integers the negative ones (and -0) are < 0, the others unchanged
+                        o.x = pk_max_i16(o.x, 0u);
+                        o.y = pk_max_i16(o.y, 0u);
                     }
-                    if (EPI_BASE == EPI_MASK) {
-                        uint32_t byte = (i8 < 4 ? m_lo >> (8 * i8) : m_hi >> (8 * (i8 - 4))) & 0xffu;
-                        byte |= byte << 12;   // bit w -> bit w, bit 4+w -> bit 16+w
-#pragma unroll
-                        for (int w = 0; w < 4; ++w) val[w] &= ((byte >> w) & 0x10001u) * 0xffffu;
-                    }
-                    if (ASYNC_STORES) {
-                        store16(c_rsrc, c_voff + (uint32_t)(j * 32 + i8 * 4) * row_bytes, val);
-                        // the same row, at its token's place in the token-major output
-                        if (SCATTER)
-                            store16(s_rsrc, p < a.Pdim ? row_off + (uint32_t)p * 2u : kOobOffset, val);
-                    } else if (q < cur.qlim && p < a.Pdim) {
-                        const size_t off = (size_t)q * a.ldc + p;
-                        if (MODE == MODE_ROUTER_DX && has_addend[i8]) {
-                            // add the token's row of the expert-side gradient (to the product, which is
-                            // rounded already: fp32 add, a second rounding)
-                            const bf16x8 va = __builtin_bit_cast(bf16x8, val);
-                            const bf16x8 vb = __builtin_bit_cast(bf16x8, addend[i8]);
-                            bf16x8 vo;
-#pragma unroll
-                            for (int w = 0; w < 8; ++w) vo[w] = (bf16)((float)va[w] + (float)vb[w]);
-                            val = __builtin_bit_cast(u32x4, vo);
-                        }
-                        *(u32x4 *)(Cout + off) = val;
-                    }
+                    const int ch = i * 4 + g;
+                    *(uint2 *)(ep + wrow * 256 + ((ch ^ (wrow & 15)) << 4) + ((ln >> 5) << 3)) = o;
                 }
+            }
+        };
+        // second half: the round's rows read back as 16-byte pieces of 256-byte segments.  All
+        // eight are read before the first is stored (the stores are fences to the compiler,
+        // which would otherwise read, wait and store in turn).
+        u32x4 vals[8];
+        auto turn_out = [&]() {
+#pragma unroll
+            for (int i8 = 0; i8 < 8; ++i8) {
+                const int rrow = i8 * 4 + (ln >> 4);
+                vals[i8] = *(const u32x4 *)(ep + rrow * 256 + ((c ^ (rrow & 15)) << 4));
+            }
+        };
+        // third: what is left to do on the pieces, and their stores
+        auto store_round = [&](int j) {
+            uint32_t m_lo = 0u, m_hi = 0u;
+            if (EPI_BASE == EPI_MASK) { m_lo = tv.mb[2 * j]; m_hi = tv.mb[2 * j + 1]; }
+#pragma unroll
+            for (int i8 = 0; i8 < 8; ++i8) {
+                const int rrow = i8 * 4 + (ln >> 4);       // row within the round
+                const int row = j * 32 + rrow;               // row within the wave's sub-tile
+                const int q = cur.q0 + row_of(wq, j, rrow);
+                u32x4 val = vals[i8];
+                uint32_t row_off = 0;   // SCATTER: the row's place (asked of the lane that holds it, by all lanes)
+                if (SCATTER) row_off = (uint32_t)__shfl((int)(j < 2 ? tv.ep_lo : tv.ep_hi), row & 63, kWave);
                 if (EPI_BASE == EPI_RELU) {
-                    new_bits[2 * j] = m_lo;
-                    new_bits[2 * j + 1] = m_hi;
-                }
-            };
-            if (MODE == MODE_ROUTER_DX) {
+                    // After ReLU every half word is a non-negative bf16: read as an unsigned
+                    // integer it is > 0 exactly when min(., 1) is 1.  Bits 0..3 of the
+                    // byte: low halves of the four words, bits 4..7: high halves.
+                    uint32_t u = 0;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    ask_addend(j);
-                    turn_in(j);
-                    turn_out();
-                    store_round(j);
+                    for (int w = 0; w < 4; ++w) u |= pk_min_u16(val[w], 0x00010001u) << w;
+                    const uint32_t byte = (u & 0xfu) | ((u >> 12) & 0xf0u);
+                    if (i8 < 4) m_lo |= byte << (8 * i8);
+                    else m_hi |= byte << (8 * (i8 - 4));
                 }
-            } else {
-                // The rounds overlap: round j + 1 is converted and written into the buffer (behind
-                // round j's reads, which the LDS executes in order) before round j's pieces are
-                // waited for and stored, so that the conversions cover the reads' latency.
-                turn_in(0);
-                turn_out();
+                if (EPI_BASE == EPI_MASK) {
+                    uint32_t byte = (i8 < 4 ? m_lo >> (8 * i8) : m_hi >> (8 * (i8 - 4))) & 0xffu;
+                    byte |= byte << 12;   // bit w -> bit w, bit 4+w -> bit 16+w
 #pragma unroll
-                for (int j = 1; j < 4; ++j) {
-                    turn_in(j);
-                    store_round(j - 1);
-                    turn_out();
+                    for (int w = 0; w < 4; ++w) val[w] &= ((byte >> w) & 0x10001u) * 0xffffu;
                 }
-                store_round(3);
+                if (ASYNC_STORES) {
+                    store16(c_rsrc, c_voff + (uint32_t)(j * 32 + i8 * 4) * row_bytes, val);
+                    // the same row, at its token's place in the token-major output
+                    if (SCATTER)
+                        store16(s_rsrc, p < a.Pdim ? row_off + (uint32_t)p * 2u : kOobOffset, val);
+                } else if (q < cur.qlim && p < a.Pdim) {
+                    const size_t off = (size_t)q * a.ldc + p;
+                    if (MODE == MODE_ROUTER_DX && has_addend[i8]) {
+                        // add the token's row of the expert-side gradient (to the product, which is
+                        // rounded already: fp32 add, a second rounding)
+                        const bf16x8 va = __builtin_bit_cast(bf16x8, val);
+                        const bf16x8 vb = __builtin_bit_cast(bf16x8, addend[i8]);
+                        bf16x8 vo;
+#pragma unroll
+                        for (int w = 0; w < 8; ++w) vo[w] = (bf16)((float)va[w] + (float)vb[w]);
+                        val = __builtin_bit_cast(u32x4, vo);
+                    }
+                    *(u32x4 *)(Cout + off) = val;
+                }
             }
             if (EPI_BASE == EPI_RELU) {
-                if (ASYNC_STORES) {
-                    const i32x4 b_rsrc =
-                        make_rsrc(a.relu_bits + (size_t)cur.index * kReluBitsPerTile, kReluBitsPerTile);
-                    const uint32_t at = (uint32_t)(wave * 64 + ln) * 32u;
-                    store16(b_rsrc, at, u32x4{new_bits[0], new_bits[1], new_bits[2], new_bits[3]});
-                    store16(b_rsrc, at + 16u, u32x4{new_bits[4], new_bits[5], new_bits[6], new_bits[7]});
-                } else {
-                    *(u32x4 *)bits = u32x4{new_bits[0], new_bits[1], new_bits[2], new_bits[3]};
-                    *(u32x4 *)(bits + 4) = u32x4{new_bits[4], new_bits[5], new_bits[6], new_bits[7]};
-                }
+                new_bits[2 * j] = m_lo;
+                new_bits[2 * j + 1] = m_hi;
+            }
+        };
+        if (MODE == MODE_ROUTER_DX) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                ask_addend(j);
+                turn_in(j);
+                turn_out();
+                store_round(j);
+            }
+        } else {
+            // The rounds overlap: round j + 1 is converted and written into the buffer (behind
+            // round j's reads, which the LDS executes in order) before round j's pieces are
+            // waited for and stored, so that the conversions cover the reads' latency.
+            turn_in(0);
+            turn_out();
+#pragma unroll
+            for (int j = 1; j < 4; ++j) {
+                turn_in(j);
+                store_round(j - 1);
+                turn_out();
+            }
+            store_round(3);
+        }
+        if (EPI_BASE == EPI_RELU) {
+            if (ASYNC_STORES) {
+                const i32x4 b_rsrc =
+                    make_rsrc(a.relu_bits + (size_t)cur.index * kReluBitsPerTile, kReluBitsPerTile);
+                const uint32_t at = (uint32_t)(wave * 64 + ln) * 32u;
+                store16(b_rsrc, at, u32x4{new_bits[0], new_bits[1], new_bits[2], new_bits[3]});
+                store16(b_rsrc, at + 16u, u32x4{new_bits[4], new_bits[5], new_bits[6], new_bits[7]});
+            } else {
+                *(u32x4 *)bits = u32x4{new_bits[0], new_bits[1], new_bits[2], new_bits[3]};
+                *(u32x4 *)(bits + 4) = u32x4{new_bits[4], new_bits[5], new_bits[6], new_bits[7]};
             }
         }
         if (!have_next) break;

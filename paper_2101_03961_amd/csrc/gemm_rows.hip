@@ -472,8 +472,9 @@ static hipError_t rows_launch(RowsArgs a, int E, hipStream_t s) {
 // (GB/s).  Measured on 128 experts of 768 x 3072 with 16 .. 512 rows each, when a tile cost the same however
 // many rows it held; the estimate made from them picked the fastest or one within 5 % of it over that range
 // and at 64 experts of 4096 x 10240.  Since then tiles of eight waves with few rows run with fewer row blocks,
-// which only 256 x 384's line below knows of: between 64 and 200 rows per expert, and where 256 x 256
-// wins by a few per cent, the choice may be off by more.
+// which only 256 x 384's line below knows of, and have their loads further ahead (6-12 % less per step, not measured
+// again here): between 64 and 200 rows per expert, and where 256 x 256 wins by a few per cent, the choice may be off
+// by more.
 struct RowsModel {
     int tile, qb, pb;
     double step, once, gbs;
@@ -501,7 +502,7 @@ static double rows_tiles(double mean, double cap, int qb) {
 
 bool rows_count_hit(const Workspace &w) {
     for (GemmKind k : {GEMM_FWD1, GEMM_FWD2, GEMM_DGRAD2, GEMM_DGRAD1})   // (tiles of eight waves: rows_block)
-        if (w.gemm_tile[k] == ROWS_64x256 || w.gemm_tile[k] >= ROWS_256x256) return w.E <= 64 * kFewExperts;
+        if (w.gemm_tile[k] >= ROWS_256x256) return w.E <= 64 * kFewExperts;
     return false;
 }
 

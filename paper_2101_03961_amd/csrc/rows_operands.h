@@ -88,21 +88,20 @@ template <int R, int NW, int S = 32> struct F32Direct : RowsDirect<R, NW, 64> {
 // further; the chunks are permuted so that the eight use the eight parts of the 256-byte bank window.  Lanes form groups
 // of 16; group g covers k 8 g .. + 8; inside a group lane j supplies the 8 bytes at k-row j/4, rows 4 (j%4) .. +4, and
 // receives k-rows 0..3 of row j.
-// (Rows of 384 bytes: 128 from the parity of the k-row, the rest from the permutation of eight chunks.)
 template <int R, int NW, int BK = 64, bool ONCE = false> struct RowsTrans {
     static constexpr int kLoads = R * BK / (512 * NW);
     static constexpr int kChunks = R / 8;          // 16-byte chunks of a k-row
     static constexpr int kRun = BK / NW < 8 ? BK / NW : 8;   // k-rows that a wave loads at a time, all with k and 8 alike
     static constexpr int kGroup = R * kRun / 512;  // ... in so many loads
-    static constexpr int kWindow = R % 128 ? 8 : 16;   // chunks that trade places
+    static constexpr int kWindow = 16;             // chunks that trade places
     // R = 256: a load is two k-rows, those of a wave 4 apart, so that the permutation is the same in all of its loads
-    static constexpr int kPeriod = R % 128 || R == 384 ? 3 : 1;   // loads until (permutation, chunk) repeat
+    static constexpr int kPeriod = R == 384 ? 3 : 1;   // loads until (permutation, chunk) repeat
     static constexpr int kPeriodRows = kPeriod * 64 / kChunks;    // k-rows they cover
     static_assert(kLoads * 512 * NW == R * BK && kLoads % kGroup == 0 && kGroup % kPeriod == 0 && kRun * NW % 16 == 0,
                   "the rows divide over the waves");
     static_assert(kChunks % kWindow == 0, "the permutation stays inside a window");
     static __device__ __forceinline__ int perm(int kr) {
-        return (kWindow == 16 ? (kr & 3) | (kr >> 1 & 4) : (kr >> 1 & 1) | (kr >> 2 & 2)) << 1;
+        return ((kr & 3) | (kr >> 1 & 4)) << 1;
     }
     static __device__ __forceinline__ int first_row(int wave, int i) {   // R = 256
         return (wave & 1) * 2 + (wave >> 1) * 8 + (i & 1) * 4 + (i >> 1) * (4 * NW);
