@@ -105,7 +105,7 @@ def kernel_work(shape, kept, elt):
         "router_dlogits": (0.0, T * E * 4 + T * 512 + T * 8, "hbm"),
         "router_dx_mfma": (6.0 * T * d * E, T * 512 + kept * d * elt + T * d * elt, "hbm"),
         "router_dWr_mfma": (4.0 * T * d * E, (T * 2 * dpad * 2 if jit else T * d * elt) + T * 512, "hbm"),
-        "router_dWr_reduce": (0.0, -(-E // 128) * dwr_splits * d * 128 * 4.0 + d * E * 4.0, "hbm"),
+        "router_dWr_reduce": (0.0, (dwr_splits + 1) * d * E * 4.0, "hbm"),
         "router_dx": ((6.0 if bf16_block else 2.0) * T * d * E,
                       T * E * 4 + T * (512 if bf16_block else 4 * E) + kept * d * elt + T * d * elt,
                       "hbm"),
