@@ -21,7 +21,7 @@
 //
 // A block has WP x WQ waves, each with 2 IP x 2 IQ MFMA 16x16x32 tiles (P is the MFMA "A" side).  (Of 32x32x16 tiles half
 // as many instructions do the same products with the same reads, but they draw more power: with random operands
-// and nothing else the chip holds 1750 TFLOP/s with them and 2060 with 16x16x32; here 2.0 and 2.2 GHz.)  k advances 64 (BK)
+// and nothing else the chip holds 1750 TFLOP/s with them and 2060 with 16x16x32; beside the loads both run at 2.0-2.2 GHz.)  k advances 64 (BK)
 // at a time through STAGES LDS stages filled by direct loads.
 #include <math.h>
 
